@@ -268,13 +268,14 @@ approx_lstm_status approx_lstm_run_schedule(approx_lstm_model* m, const float* x
  *                      (ignored when online != 0: the plan of an anytime or
  *                      scheduled run sized for the whole rank)
  *   num_cu             compute units to plan for (0 = the model's device)
- *   out                host [10]: workgroups, all-timestep P_x resident in LDS
+ *   out                host [10]: workgroups (of a pair-kernel run: of one
+ *                      group, widest level), all-timestep P_x resident in LDS
  *                      (1/0), all (level, sequence) pairs in one phase-B pass
  *                      (1/0), h-part entries per lane in registers, U entries
  *                      per thread in registers, output rows per thread, bulk
  *                      h exchange (1/0), LDS bytes per workgroup (above
  *                      163840: the run returns UNSUPPORTED), 1 when the run
- *                      takes the one-pair recurrence kernel (see
+ *                      takes the pair recurrence kernel (see
  *                      approx_lstm_set_recurrence), else 0, and the K tile of
  *                      a phase B that reads each U entry once per timestep
  *                      for every sequence (0: one pass per sequence)
@@ -338,17 +339,26 @@ approx_lstm_status approx_lstm_set_launch(approx_lstm_model* m, int32_t blocks, 
 
 /*
  * approx_lstm_set_recurrence -- recurrence kernel of an fp32 model's fixed-
- * budget runs, from the next run on.  kernel = 0 (the default): a run of one
- * level over one sequence (approx_lstm_run with n_levels = 1 and B = 1, and
- * the runs approx_lstm_run_deadline and approx_lstm_run_stack make of that
- * form) takes the one-pair kernel where its launch plan fits (every owned
- * h-part entry and U entry in registers: at most 2048 terms per
- * sequence in use, K <= 1024, and the entries per lane it needs), every other
- * run the general persistent kernel; kernel = 1: the general kernel always.
- * Both compute every sum in the same order: the outputs are bitwise equal.
- * Errors: null model, kernel not 0 or 1.
+ * budget runs, from the next run on.  kernel = 0 (the default): a run whose
+ * launch plan fits takes the pair kernel, where every (level, sequence) pair
+ * is a recurrence of its own on a group of workgroups (every owned h-part
+ * entry and U entry in registers; P_x of every timestep in LDS; several pairs
+ * only on the automatic launch width and a whole device, and with timing
+ * enabled at most 8), every other run the general persistent kernel; kernel =
+ * 1: the general kernel always.  Both compute every sum in the same order:
+ * the outputs are bitwise equal.  Errors: null model, kernel not 0 or 1.
  */
 approx_lstm_status approx_lstm_set_recurrence(approx_lstm_model* m, int32_t kernel);
+
+/*
+ * approx_lstm_set_start_wait -- how long, in microseconds, the workgroups of a
+ * pair-kernel group wait at the start of a run for each other to be resident,
+ * from the next run on (default 2000).  When the wait runs out (another
+ * stream's kernels hold the compute units) one workgroup computes the group's
+ * pairs alone, slowly and with the same bits, and the others leave; 0 does so
+ * unless all are there at once.  Errors: null model, wait_us not in [0, 1e7].
+ */
+approx_lstm_status approx_lstm_set_start_wait(approx_lstm_model* m, double wait_us);
 
 /*
  * approx_lstm_set_batched_path -- kernels of a bf16 model's recurrence (Eq. (1)

@@ -70,6 +70,7 @@ _sigs = {
     "approx_lstm_set_launch": [_vp, _i32, _i32],
     "approx_lstm_set_batched_path": [_vp, _i32],
     "approx_lstm_set_recurrence": [_vp, _i32],
+    "approx_lstm_set_start_wait": [_vp, ctypes.c_double],
     "approx_lstm_model_info": [_vp, ctypes.POINTER(Info)],
     "approx_lstm_set_timing": [_vp, _i32],
     "approx_lstm_get_timing": [_vp, _vp, _vp, _i32],
@@ -266,6 +267,10 @@ def approx_lstm_set_launch(model, blocks, cooperative=0):
 
 def approx_lstm_set_recurrence(model, kernel):
     return _check(lib.approx_lstm_set_recurrence(model.handle, int(kernel)))
+
+
+def approx_lstm_set_start_wait(model, wait_us):
+    return _check(lib.approx_lstm_set_start_wait(model.handle, float(wait_us)))
 
 
 def approx_lstm_set_batched_path(model, persistent):

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -114,6 +115,10 @@ struct approx_lstm_model {
   unsigned* d_hflag = nullptr;       // bulk h exchange flags, one per workgroup
   size_t hflag_cap = 0;
   unsigned* d_err = nullptr;
+  float* d_pex = nullptr;                // pair kernel's exchange slots
+  size_t pex_cap = 0;                    // floats
+  unsigned long long* d_ctl = nullptr;   // start words of the pair kernel's groups, zero between runs
+  unsigned start_wait_ticks = 200000;    // wall ticks (10 ns) a group waits for all its workgroups
   unsigned long long* d_stamps = nullptr;
   size_t stamps_cap = 0;             // words
   int timing = 0;                    // record per-timestep stamps
@@ -133,7 +138,7 @@ struct approx_lstm_model {
   size_t kt_cap = 0;
   int launch_blocks = 0;             // 0 = automatic
   int cooperative = 0;               // 1: cooperative launch API
-  int recurrence = 0;                // 0: one-pair kernel where it applies, 1: general kernel only
+  int recurrence = 0;                // 0: pair kernel where it applies, 1: general kernel only
   // persistent batched recurrence (bf16 models): cohort exchange buffers
   int batched_persistent = 1;        // 0: per-timestep kernel pairs only; 1: persistent where it
                                      // fits; 2, 3: persistent with z always tagged / always flagged
@@ -148,7 +153,7 @@ struct approx_lstm_model {
 
   ~approx_lstm_model() {
     if (!has_dev && !d_px && !d_zx && !d_hx && !d_hbx && !d_hflag && !d_err && !d_stamps && !d_stack && !d_bz &&
-        !d_bh && !d_bc && !d_kt && !d_pzx && !d_phx && !d_pflag && !d_ppart)
+        !d_bh && !d_bc && !d_kt && !d_ctl && !d_pex && !d_pzx && !d_phx && !d_pflag && !d_ppart)
       return;
     DeviceScope ds(device);
     dfree(d_pzx);
@@ -173,6 +178,8 @@ struct approx_lstm_model {
     dfree(d_hbx);
     dfree(d_hflag);
     dfree(d_err);
+    dfree(d_ctl);
+    dfree(d_pex);
     dfree(d_stamps);
     dfree(d_kt);
     dfree(d_stack);
@@ -474,6 +481,7 @@ struct CallerScratch {
   unsigned char* base;
   size_t bytes;
   unsigned* seq;
+  unsigned long long* ctl;   // start words of the pair kernel's groups (zero between runs)
 };
 
 // Launch tag sequence of the next run: the model's own counter, or the
@@ -519,39 +527,60 @@ approx_lstm_status ensure_stamps(approx_lstm_model* m, int T, hipStream_t stream
   return APPROX_LSTM_OK;
 }
 
-// Plan of a one-pair run (one level, one sequence, K >= 1): P > 0 when the
-// one-pair kernel takes it.
-int plan_pair_run(const approx_lstm_model* m, alstm::PairArgs& pa, int T, int K, int num_cu, size_t* lds) {
-  pa = alstm::PairArgs{};
-  pa.D = m->D; pa.H = m->H; pa.G = m->G; pa.N = m->N; pa.NZ = m->NZ; pa.T = T;
-  pa.K = K; pa.GK = m->G * K;
-  pa.hcap = m->hpre[pa.GK - 1];
-  return alstm::plan_pair(pa, num_cu, m->launch_blocks, lds);
+// Whether a fixed-budget run may take the pair kernel: a width given by the
+// caller keeps a run of several pairs on the general kernel, and timed runs
+// of more pairs than there are XCDs too (their pairs would take turns, so
+// that no single stamp covered a timestep of all).
+bool pair_allowed(const approx_lstm_model* m, int pairs, int kmax) {
+  return kmax > 0 && m->recurrence == 0 && !m->cooperative && (pairs == 1 || m->launch_blocks == 0) &&
+         !(m->timing && pairs > alstm::kXcds);
 }
 
-// One (level, sequence) pair on the one-pair kernel (P workgroups from
-// plan_pair_run): input projection, then the recurrence.
-approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, const float* x, int32_t T,
-                            const float* h0, const float* c0, float* h_out, float* c_out, hipStream_t stream,
-                            const CallerScratch* ws) {
-  const size_t px_floats = (size_t)pa.GK * T, zx_words = (size_t)P * pa.OM, hx_words = round_up(m->H, 4);
+// Plan of a pair run: P > 0 when the pair kernel takes it.
+int plan_pair_run(const approx_lstm_model* m, alstm::PairArgs& pa, int T, int B, const int32_t* levels, int n_levels,
+                  int num_cu, size_t* lds) {
+  pa = alstm::PairArgs{};
+  pa.D = m->D; pa.H = m->H; pa.G = m->G; pa.N = m->N; pa.NZ = m->NZ; pa.T = T; pa.B = B; pa.L = n_levels;
+  int hcap[alstm::kMaxLevels];
+  for (int l = 0; l < n_levels; ++l) {
+    pa.lv[l].K = levels[l];
+    hcap[l] = levels[l] > 0 ? m->hpre[(size_t)m->G * levels[l] - 1] : 0;
+  }
+  return alstm::plan_pair(pa, hcap, num_cu, m->launch_blocks, lds);
+}
+
+// XCD of the first group of the next pair run: in turn, so that runs on
+// several streams tend to sit on different XCDs (a group whose XCD is taken
+// waits, or runs on one workgroup; see group_start).
+std::atomic<unsigned> g_next_xcd{0};
+
+// The pair kernel (P workgroups per group from plan_pair_run): input
+// projection, then the recurrences.  *taken = false (nothing launched): the
+// caller's workspace is too small for it.
+approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, const float* x, const float* h0,
+                            const float* c0, int kmax, float* h_out, float* c_out, hipStream_t stream,
+                            const CallerScratch* ws, bool* taken) {
+  const size_t pairs = (size_t)pa.L * pa.B, GK = (size_t)m->G * kmax;
+  const size_t px_floats = GK * pa.T * pa.B, ex_floats = pairs * 2 * ((size_t)pa.zslots + pa.hpad);
   size_t exch_off = 0;
   float* pxw = nullptr;   // x-part projections: written by the input projection, read by the recurrence
+  *taken = true;
   if (ws) {
-    const ScratchLayout sl = scratch_layout(px_floats, zx_words, hx_words, 0, 0);
-    if (sl.total > ws->bytes)
-      return fail(APPROX_LSTM_ERR_UNSUPPORTED,
-                  "run needs %zu bytes of workspace, above the %zu-byte static scratch of the allocation-free entry "
-                  "point (T=%d, B=1, G*K=%d)",
-                  sl.total, ws->bytes, T, pa.GK);
-    pa.zx = reinterpret_cast<unsigned long long*>(ws->base + sl.zx);
-    pa.hx = reinterpret_cast<unsigned long long*>(ws->base + sl.hx);
+    const ScratchLayout sl = scratch_layout(px_floats, (ex_floats + 1) / 2, 0, 0, 0);
+    if (sl.total > ws->bytes) {
+      *taken = false;
+      return APPROX_LSTM_OK;
+    }
+    pa.ex = reinterpret_cast<float*>(ws->base + sl.zx);
+    pa.ctl = ws->ctl;
     pxw = reinterpret_cast<float*>(ws->base + sl.px);
     exch_off = sl.zx;
   } else {
-    approx_lstm_status st = ensure_workspace(m, px_floats, zx_words, hx_words, stream);
+    approx_lstm_status st = ensure_workspace(m, px_floats, 0, 0, stream);
+    if (st == APPROX_LSTM_OK) st = grow(m->d_pex, m->pex_cap, ex_floats, stream, "hipMalloc(pair exchange)");
     if (st != APPROX_LSTM_OK) return st;
-    pa.zx = m->d_zx; pa.hx = m->d_hx; pxw = m->d_px;
+    pa.ex = m->d_pex; pxw = m->d_px;
+    pa.ctl = m->d_ctl;
   }
   pa.px = pxw;
   unsigned tag_seq = 0;
@@ -560,15 +589,17 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
   pa.tag_base = tag_seq << 16;
   pa.stamps = nullptr;
   if (m->timing && !ws) {
-    st = ensure_stamps(m, T, stream);
+    st = ensure_stamps(m, pa.T, stream);
     if (st != APPROX_LSTM_OK) return st;
     pa.stamps = m->d_stamps;
   }
+  if (pa.groups > 1) pa.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)pairs, std::memory_order_relaxed) % alstm::kXcds);
+  pa.wait_ticks = m->start_wait_ticks;
   pa.h0 = h0; pa.c0 = c0; pa.h_out = h_out; pa.c_out = c_out;
   pa.sigma = m->d_sigma; pa.Ut = m->d_Ut; pa.vidx = m->d_vidx; pa.vval = m->d_vval; pa.nx = m->d_nx;
   pa.bias = m->d_bias; pa.err = m->d_err;
   alstm::RunArgs proj{};
-  proj.x = x; proj.D = m->D; proj.NZ = m->NZ; proj.T = T; proj.B = 1; proj.GK = pa.GK;
+  proj.x = x; proj.D = m->D; proj.NZ = m->NZ; proj.T = pa.T; proj.B = pa.B; proj.GK = (int)GK;
   proj.vidx = m->d_vidx; proj.vval = m->d_vval; proj.nx = m->d_nx; proj.px = pxw;
   proj.xvec = (m->D % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   proj.num_cu = m->num_cu;
@@ -585,11 +616,15 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
                                    float* c_out, hipStream_t stream, const OnlineCfg* on,
                                    const CallerScratch* ws = nullptr) {
   if (on && ws) return fail(APPROX_LSTM_ERR_UNSUPPORTED, "online runs need the model's own workspace");
-  if (!on && n_levels == 1 && B == 1 && kmax > 0 && m->recurrence == 0 && !m->cooperative) {
+  if (!on && pair_allowed(m, n_levels * B, kmax)) {
     alstm::PairArgs pa{};
     size_t plds = 0;
-    const int Pp = plan_pair_run(m, pa, T, kmax, m->num_cu, &plds);
-    if (Pp > 0) return run_pair(m, pa, Pp, x, T, h0, c0, h_out, c_out, stream, ws);
+    const int Pp = plan_pair_run(m, pa, T, B, levels, n_levels, m->num_cu, &plds);
+    if (Pp > 0) {
+      bool taken = false;
+      const approx_lstm_status st = run_pair(m, pa, Pp, x, h0, c0, kmax, h_out, c_out, stream, ws, &taken);
+      if (taken || st != APPROX_LSTM_OK) return st;
+    }
   }
   alstm::RunArgs a{};
   int P = 1;
@@ -671,7 +706,8 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
 // address is used (kernel arguments, fills).  Every call on a device shares
 // its array, which keeps the last call's contents.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kCtlBytes = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;   // behind the workspace
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kCtlBytes];
 
 namespace {
 
@@ -882,6 +918,11 @@ approx_lstm_status approx_lstm_prepare(const float* w_ih, const float* w_hh, con
     // that may not allocate) only set it, approx_lstm_check reads and clears it
     if (st == APPROX_LSTM_OK) step(hipMalloc(&m->d_err, 64), "hipMalloc(err)");
     if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_err, 0, 64, stream), "clear(err)");
+    if (!bf && st == APPROX_LSTM_OK) {
+      const size_t ctl = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;
+      step(hipMalloc(&m->d_ctl, ctl), "hipMalloc(ctl)");
+      if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_ctl, 0, ctl, stream), "clear(ctl)");
+    }
     if (st == APPROX_LSTM_OK) step(hipStreamSynchronize(stream), "hipStreamSynchronize");
     if (st != APPROX_LSTM_OK) {
       delete m;
@@ -916,6 +957,10 @@ approx_lstm_status approx_lstm_reserve(approx_lstm_model* m, int32_t T_max, int3
   st = ensure_workspace(m, GK * T_max * B_max, LB * (GK + P_max), 2 * hhalf, nullptr);
   if (st == APPROX_LSTM_OK && alstm::use_bulk_h(L_max, B_max, m->H))
     st = ensure_bulk(m, 2 * hhalf, nullptr);
+  // pair kernel: two halves of z slots (G * N, at most 4 * 16 more per group) and h per pair
+  if (st == APPROX_LSTM_OK)
+    st = grow(m->d_pex, m->pex_cap, LB * 2 * (GK + 64 * (size_t)m->G + round_up(m->H, 4)), nullptr,
+              "hipMalloc(pair exchange)");
   if (st != APPROX_LSTM_OK) return st;
   HIP_TRY(hipDeviceSynchronize(), "hipDeviceSynchronize");
   return APPROX_LSTM_OK;
@@ -984,7 +1029,8 @@ approx_lstm_status approx_lstm_run_noalloc(approx_lstm_model* m, const float* x,
     if (!p) return fail(APPROX_LSTM_ERR_DEVICE, "hipGetSymbolAddress(scratch) returned null");
     slot.ptr = static_cast<unsigned char*>(p);
   }
-  const CallerScratch ws{slot.ptr, kScratchBytes, &slot.seq};
+  const CallerScratch ws{slot.ptr, kScratchBytes, &slot.seq,
+                         reinterpret_cast<unsigned long long*>(slot.ptr + kScratchBytes)};
   return run_progressive(m, x, T, B, h0, c0, levels, n_levels, kmax, h_out, c_out, (hipStream_t)hip_stream,
                          nullptr, &ws);
 }
@@ -1084,6 +1130,14 @@ approx_lstm_status approx_lstm_set_recurrence(approx_lstm_model* m, int32_t kern
   if (!m) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null model");
   if (kernel < 0 || kernel > 1) return fail(APPROX_LSTM_ERR_INVALID_ARG, "kernel must be 0 or 1");
   m->recurrence = kernel;
+  return APPROX_LSTM_OK;
+}
+
+approx_lstm_status approx_lstm_set_start_wait(approx_lstm_model* m, double wait_us) {
+  g_last_error.clear();
+  if (!m) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null model");
+  if (!(wait_us >= 0.0 && wait_us <= 1e7)) return fail(APPROX_LSTM_ERR_INVALID_ARG, "wait must be in [0, 1e7] us");
+  m->start_wait_ticks = (unsigned)(wait_us * 100.0);   // the device's 100 MHz wall clock
   return APPROX_LSTM_OK;
 }
 
@@ -1337,13 +1391,14 @@ approx_lstm_status approx_lstm_plan(const approx_lstm_model* m, int32_t T, int32
   }
   const int ncu = num_cu > 0 ? num_cu : m->num_cu;
   for (int i = 0; i < 10; ++i) out[i] = 0;
-  if (!online && lv.size() == 1 && B == 1 && kmax > 0 && m->recurrence == 0 && !m->cooperative) {
+  if (!online && pair_allowed(m, (int)lv.size() * B, kmax)) {
     alstm::PairArgs pa{};
     size_t plds = 0;
-    const int Pp = plan_pair_run(m, pa, T, kmax, ncu, &plds);
+    const int Pp = plan_pair_run(m, pa, T, B, lv.data(), (int)lv.size(), ncu, &plds);
     if (Pp > 0) {
       out[0] = Pp;
-      out[1] = pa.px_lds;
+      out[1] = 1;
+      out[2] = lv.size() * B > 1 ? 1 : 0;
       out[3] = pa.hpl;
       out[4] = pa.upt;
       out[5] = pa.opt;

@@ -137,15 +137,38 @@ size_t plan_progressive(RunArgs& a, int P);
 // Uses a.x, a.T, a.B, a.D, a.NZ, a.GK, a.vidx, a.vval, a.nx, a.px, a.xvec.
 hipError_t launch_input_proj(const RunArgs& a, hipStream_t stream);
 
-// One (level, sequence) pair: the recurrence of one budget K over one
-// sequence, with every owned slice in registers (pair_lstm_kernel).  The
+// Every (level, sequence) pair of a run as its own recurrence, each on a group
+// of workgroups with every owned slice in registers (pair_lstm_kernel).  The
 // summation order of every quantity is that of progressive_lstm_kernel (16
 // lanes per term in phase A, lanes_for_level(K) lanes per U row in phase B),
-// so both kernels give bitwise the same outputs.  Device pointers:
-//   px     [GK][T]              x-part projections (input_proj_kernel, B = 1)
-//   zx     [P*OM] u64           tagged z words, slot j*OM + i carries term j + i*P
-//   hx     [H] u64              tagged h words
-//   h_out  [T][H]               this level's outputs; c_out [H] or null
+// so both kernels give bitwise the same outputs.
+constexpr int kXcds = 8;          // XCDs of the device, to which consecutive blocks go in turn
+constexpr int kXcdCus = 32;       // compute units per XCD
+constexpr int kNearWidth = 64;    // most workgroups of a group on one XCD (two per compute unit)
+constexpr int kTwoHmax = 16;      // h-part entries per lane up to which two workgroups share a compute unit
+constexpr int kCtlWords = kNearWidth + 8;   // start words of a group: one per workgroup, then its decision
+constexpr int kSpreadWords = 512;           // start words of a single group over the whole device, then its decision
+static_assert(kSpreadWords < kXcds * kCtlWords, "the spread group's decision lies within the start words");
+
+// One level of a pair run: its budget and launch shape.
+struct PairLevel {
+  int K;         // terms per group
+  int P;         // workgroups of a group
+  int S, lgS;    // lanes per U row (lanes_for_level(K)) and its log2
+  int kpl;       // exchange slots of a lane: ceil(K / S) rounded up to 4
+  int slots;     // exchange slots in all: G * S * kpl
+  int OM;        // slots owned per workgroup (at most 32 * apass)
+  int RU;        // hidden units owned per workgroup
+  int kst;       // LDS floats between the terms of consecutive lanes of a row
+  int zst;       // LDS floats per group of z
+};
+
+// Device pointers:
+//   px     [GK][T*B]            x-part projections (input_proj_kernel)
+//   ex     [L*B][2*(zslots + hpad)] float   exchange of every pair: z [2][zslots], h [2][hpad]
+//   ctl    [kXcds][kCtlWords]   start words of the groups (or of one spread over the
+//                               device: kSpreadWords of them), all zero between runs
+//   h_out  [L][T][B][H]; c_out [L][B][H] or null
 struct PairArgs {
   const float* h0;
   const float* c0;
@@ -158,38 +181,37 @@ struct PairArgs {
   const uint16_t* nx;
   const float* bias;
   const float* px;
-  unsigned long long* zx;
-  unsigned long long* hx;
+  float* ex;
+  unsigned long long* ctl;
   unsigned* err;
-  unsigned long long* stamps;   // as RunArgs::stamps (workgroup 0), or null
-  int D, H, G, N, NZ, T;
-  int K;         // budget (terms per group), >= 1
-  int GK;        // G * K
-  int hcap;      // largest h-part entry count of the terms in use
+  unsigned long long* stamps;   // as RunArgs::stamps (pair 0, workgroup 0), or null
+  int D, H, G, N, NZ, T, B, L;
+  PairLevel lv[kMaxLevels];
   // launch plan (plan_pair)
-  int OM;        // terms owned per workgroup (at most 32 * apass)
-  int RU;        // hidden units owned per workgroup
+  int groups;    // groups the blocks are dealt to (kXcds, or 1)
+  int first_xcd; // XCD of group 0
+  int OMmax;     // largest OM
+  int zslots;    // largest slots
+  int zfloats;   // LDS floats of z
+  int hpad;      // LDS floats of h (H rounded up to 4)
   int apass;     // phase-A passes of 32 terms (1 or 2)
   int hpl;       // h-part entries per lane held (register bucket: 4, 8, 12, 16, 24, 32)
-  int S, lgS;    // lanes per U row (lanes_for_level(K)) and its log2
-  int upt;       // U entries per row and lane in use: ceil(K / S)
+  int upt;       // U entries per row and lane in use
   int umax;      // U entries per row and lane held (register bucket: 8, 16, 32)
   int opt;       // output rows per thread (1, 2, 4)
-  int kstride;   // LDS floats between the terms of consecutive lanes of a row
-  int zstride;   // LDS floats per group of z
-  int hpad;      // LDS floats of h (H rounded up to 4)
-  int px_lds;    // 1: P_x of every timestep staged in LDS (required)
   unsigned tag_base;
+  unsigned wait_ticks;   // wall ticks a workgroup waits for its group to be present
 };
 
-// Launch shape of a pair run: fills the plan fields and returns the
-// workgroup count P (0: the shape does not fit this kernel) for `num_cu`
-// compute units, or checks a requested width (`want` > 0).  *lds receives
-// the LDS bytes per workgroup.
-int plan_pair(PairArgs& a, int num_cu, int want, size_t* lds);
+// Launch shape of a pair run (D .. L and every level's K given; hcap[l]
+// the largest h-part entry count of level l's terms): fills the plan fields
+// and returns the workgroups per group (0: the shape does not fit this
+// kernel) for `num_cu` compute units, or checks a requested width (`want` > 0,
+// one pair).  *lds receives the LDS bytes per workgroup.
+int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds);
 
 // Launches, on `stream`, the input projection (as launch_progressive) and the
-// one-pair recurrence with P workgroups.
+// pair recurrences with P workgroups per group.
 hipError_t launch_pair(const RunArgs& proj, const PairArgs& a, int P, hipStream_t stream);
 
 // Launches, on `stream`, the input projection over the whole device and then

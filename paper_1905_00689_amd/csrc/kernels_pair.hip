@@ -1,30 +1,59 @@
-// gfx950 recurrence for one (level, sequence) pair of the progressive
-// approximate LSTM (arXiv 1905.00689: Sec. III Eq. (1) per gate, then the
-// Sec. II cell update): the batch-1, single-budget run.
+// gfx950 recurrence of the progressive approximate LSTM (arXiv 1905.00689:
+// Sec. III Eq. (1) per gate, then the Sec. II cell update) with every factor
+// slice in registers: each (level, sequence) pair of a run is its own
+// recurrence, computed by a group of P workgroups of 512 threads.
 //
-// P workgroups of 512 threads, all resident.  Workgroup j owns the terms
-// tau = j + i*P (i < OM, round-robin over the refinement order, so every
-// budget prefix is spread over all workgroups) and the hidden units
-// [j*RU, j*RU + RU).  Every slice it needs stays in registers for the whole
-// sequence: the h-part entries of its terms (16 lanes per term, hpl entries
-// per lane, one or two passes) and the U entries of its 4*RU gate rows
-// (S lanes per row, upt entries per lane, one, two or four rows per thread).
-// P_x of every timestep (input_proj_kernel) is staged in LDS up front.
-// Per timestep:
+// Workgroup j of a group owns OM consecutive slots of the z exchange (a slot
+// is one term; the slots go lane by lane of a U row, see slot_tau) and the
+// hidden units [j*RU, j*RU + RU): the h-part entries of its terms (16 lanes
+// per term, one or two passes) and the U entries of its 4*RU gate rows (S
+// lanes per row, one, two or four rows per thread) stay in registers for the
+// whole sequence, P_x of every timestep (input_proj_kernel) in LDS.  Per
+// timestep:
 //   phase A  each term's lane group sums its h-part entries against h_{t-1}
-//            (LDS), reduces over its 16 lanes and forms z = sigma * (P_x + s);
-//   z        the last wave (the publisher) stores the workgroup's z as
-//            tagged words; waves 0-6 poll every workgroup's words into LDS;
+//            (LDS), reduces over its 16 lanes, forms z = sigma * (P_x + s)
+//            and stores it into its exchange slot;
+//   z        every thread polls its share of the slots into LDS, four values
+//            to a load;
 //   phase B  each row's lanes sum u * z over their terms and reduce; the four
-//            gate rows of a unit lie in one wave (rows gate-minor), so the
-//            unit's lane gathers them by lane shuffles and applies the gate
-//            nonlinearities and the c/h update with c held in a register;
-//   h        the publisher writes h to h_out and stores it as tagged words;
-//            waves 0-6 poll every unit's h into LDS.
-// The publisher only stores and the pollers only load: a wave's loads and
-// stores retire through one in-order counter, so a wave that polled after
-// storing would wait for its own stores' acknowledgements every round.
+//            gate rows of a unit lie in one wave (rows gate-minor), whose
+//            lanes apply the gate nonlinearities and the c/h update and store
+//            h into its exchange slot and to h_out;
+//   h        every thread polls its share of the units' h into LDS.
 // With one workgroup (P = 1) nothing is exchanged: z and h go through LDS.
+//
+// What bounds a timestep is the latency of its two exchanges.  Two things
+// make them short:
+// * Near groups.  Between workgroups of one XCD a word stored with a plain
+//   store is in the L2 they share, and an agent-scope load (which passes the
+//   L1 by) finds it there: 0.7-0.85 us for a probe's all-to-all round of 32
+//   workgroups (2 to 16 64-bit words each) on MI355X, against 1.3-1.7 us with
+//   agent-scope stores between XCDs.  So a group of up to kNearWidth
+//   workgroups is placed on one XCD: consecutive blocks go to the XCDs in
+//   turn, so group g is the blocks b with b % kXcds == g, and up to kXcds
+//   pairs run side by side, one XCD each.  The placement is not assumed:
+//   every workgroup tells the others its XCD id once at the start, and a
+//   group found on several XCDs uses agent-scope stores.
+// * Slots that tell by themselves whether their value has arrived (kEmpty), so
+//   that a 16-byte load polls four values: half the bytes of (value, tag)
+//   words and a quarter of the loads.
+// Driving shape (D = 2048, H = 512, 75% pruning, T = 16, one sequence), whole
+// run, us, with tagged words across XCDs / near groups with tagged words /
+// near groups with slots: K = 32 75.2 / 60.3 / 40.8, K = 128 76.9 / 63.2 /
+// 45.5, K = 512 87.5 / 92.3 / 70.1; phases at K = 64 (A, z, B, h) 0.25, 1.31,
+// 0.70, 1.69 -> 0.33, 0.51, 0.49, 0.47 us.  Several pairs, against the general
+// kernel's one launch for all of them: eight sequences at K = 128 389 -> 60,
+// levels 16, 64, 128, 192 201 -> 53; H = 2048, K = 64, T = 64, eight sequences
+// 1499 -> 173.
+//
+// Residency.  A group's workgroups wait for each other, so all of them must
+// be resident.  When another stream's kernels hold part of an XCD that may
+// take time, and two such launches holding parts of one XCD would wait for
+// each other.  The start of a group is therefore a bounded decision: once all
+// have arrived they go ahead (one compare-and-swap on the group's decision
+// word); a workgroup whose wait runs out first decides otherwise, takes the
+// group's pairs alone (every slice read from memory, nothing exchanged) and
+// the rest of the group leaves.  Both ways compute every sum in one order.
 //
 // The order of every sum is that of progressive_lstm_kernel (phase A: entry
 // sla + 16k of the term's h part at lane sla, k ascending, then the 16-lane
@@ -40,429 +69,693 @@ namespace alstm {
 
 namespace {
 
-// Poll tagged words src[si[k]] (si[k] < 0: none) until each carries `tag`;
-// the value goes to dst[di[k]] (LDS).  One generation of loads per round:
-// every word of the thread is loaded, all are awaited, the arrived ones are
-// kept and the rest loaded again.  Nothing is left in flight when it returns,
-// so no later instruction waits on a stray poll (a second generation in
-// flight would halve the detection delay, but its loads outlive the poll and
-// the compiler's wait counts across the loop then stall every round anyway).
-// Bounded: past the spin limit, or once another wait has failed, the
-// failure is recorded and the missing values read 0.
-template <int NW>
-__device__ __forceinline__ void poll_words(float* dst, const unsigned long long* src, const int* si, const int* di,
-                                           int nw, unsigned tag, unsigned* err) {
-  unsigned pending = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k)
-    if (k < nw && si[k] >= 0) pending |= 1u << k;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// 16-byte units polled per thread and exchange (up to 4096 values).
+constexpr int kMaxUnits = 2;
+
+// An exchange slot holds this pattern (a NaN no computation here stores) until
+// its value is there, so that every 4-byte value tells by itself whether it
+// has arrived and a poll takes four of them with one load.  Each slot exists
+// twice, for odd and even timesteps: its owner empties the half of timestep
+// t-1 while timestep t is under way, when everyone is past reading it.
+constexpr unsigned kEmpty = 0xFFFFFFFFu;
+
+// Stores of the exchange: plain (the L2 of the group's XCD) when the whole
+// group sits on one XCD, agent scope otherwise.
+__device__ __forceinline__ void store_slot(float* p, unsigned bits, bool near) {
+  unsigned* q = reinterpret_cast<unsigned*>(p);
+  if (near) __hip_atomic_store(q, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(q, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_slot(float* p, float v, bool near) {
+  const unsigned bits = __float_as_uint(v);
+  store_slot(p, bits == kEmpty ? 0x7FC00000u : bits, near);
+}
+
+// Poll the 16-byte units tid + 512 r of src (uniform; `bytes` long) whose bit
+// r is set in `pending` until none of their slots is empty; unit r goes to
+// dst + map[r] (LDS, 16-byte aligned).  Agent-scope loads pass the L1 by.
+// Bounded: past the spin limit, or once another wait has failed, the failure
+// is recorded and the missing values read 0.
+__device__ __forceinline__ void poll_units(float* dst, const float* src, int bytes, const int* map, unsigned pending,
+                                           unsigned* err) {
+  const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(addr >> 32));
+  void* base = reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo);
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(base, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  const int tid = threadIdx.x;
   unsigned spins = 0;
   while (pending) {
-    unsigned long long w[NW];
-    // words k < nw (uniform): every one loaded, unused ones at src[0]
+    u32x4 w[kMaxUnits];
 #pragma unroll
-    for (int k = 0; k < NW; ++k)
-      if (k < nw) w[k] = load_tagged(src + max(si[k], 0));
+    for (int r = 0; r < kMaxUnits; ++r)
+      if ((pending >> r) & 1u) w[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + kThreads * r) * 16, 0, 16 /* sc1 */);
+    asm volatile("" ::: "memory");   // the loads of the next round are new ones
 #pragma unroll
-    for (int k = 0; k < NW; ++k)
-      if (((pending >> k) & 1u) && (unsigned)(w[k] >> 32) == tag) {
-        dst[di[k]] = __uint_as_float((unsigned)w[k]);
-        pending &= ~(1u << k);
+    for (int r = 0; r < kMaxUnits; ++r)
+      if (((pending >> r) & 1u) && w[r][0] != kEmpty && w[r][1] != kEmpty && w[r][2] != kEmpty && w[r][3] != kEmpty) {
+        *reinterpret_cast<u32x4*>(dst + map[r]) = w[r];
+        pending &= ~(1u << r);
       }
     if ((++spins & 255u) == 0u && pending &&
         (spins >= kSpinLimit || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
       __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-      for (int k = 0; k < NW; ++k)
-        if ((pending >> k) & 1u) dst[di[k]] = 0.0f;
+      for (int r = 0; r < kMaxUnits; ++r)
+        if ((pending >> r) & 1u) *reinterpret_cast<u32x4*>(dst + map[r]) = u32x4{0u, 0u, 0u, 0u};
       break;
     }
   }
 }
 
-// The last wave publishes (z, h and h_out: every global store of the
-// recurrence); the other waves poll.  A wave's stores and loads share one
-// in-order completion counter, so a wave that polled after storing would
-// wait for its own stores to be acknowledged at every poll round.
-constexpr int kPollThreads = kThreads - 64;
-// Words polled per thread and exchange (up to 8 * 448 = 3584 slots).
-constexpr int kMaxWords = 8;
+// this wave's loads and stores have completed
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Timestep stamps of workgroup 0 are kept in LDS (written out at the end) up
-// to this many timesteps; beyond, they go straight to memory.
+// Timestep stamps are kept in LDS (written out at the end) up to this many
+// timesteps; beyond, they go straight to memory.
 constexpr int kLdsStamps = 255;
-
-// LDS carve-up (floats): stamps [2 * (4 + 4 * kLdsStamps)] (8-byte aligned
-// at offset 0), P_x [T][OM], then h [hpad], z [G][zstride], z of the owned
-// terms [OM], h of the owned units [RU], and per wave the gate
-// pre-activations of its rows [opt][64 / S] (16-byte aligned).
 constexpr int kStampFloats = 2 * (4 + 4 * kLdsStamps);
+
+// LDS carve-up (floats): with stamps their block first (8-byte aligned), the
+// group's start mode [4], P_x [T][OM], h [hpad], z [G][zst], c [H] (of a
+// workgroup that runs its pairs alone) and per wave the gate pre-activations
+// of its rows [opt][64 / S] (16-byte aligned).
 struct PairLayout {
-  size_t px, hs, zs, zown, hown, ys, total;
+  int mode, px, hs, zs, cs, ys, total;
 };
 __host__ __device__ inline PairLayout pair_layout(const PairArgs& a) {
   PairLayout l;
-  l.px = kStampFloats;
-  l.hs = l.px + (((size_t)a.T * a.OM + 3) & ~(size_t)3);
+  l.mode = a.stamps ? kStampFloats : 0;
+  l.px = l.mode + 4;
+  l.hs = l.px + ((a.T * a.OMmax + 3) & ~3);
   l.zs = l.hs + a.hpad;
-  l.zown = l.zs + (size_t)a.G * a.zstride;
-  l.hown = l.zown + a.OM;
-  l.ys = (l.hown + a.RU + 3) & ~(size_t)3;   // 16-byte aligned
-  l.total = l.ys + (size_t)kWaves * a.opt * (64 / a.S);
+  l.cs = l.zs + a.zfloats;
+  l.ys = l.cs + a.hpad;
+  l.total = l.ys + kThreads * a.opt;   // [8 waves][opt][64 / S], S >= 1
   return l;
 }
-__host__ __device__ inline size_t pair_lds_floats(const PairArgs& a) { return pair_layout(a).total; }
+
+// How a group starts: all present (on one XCD, or not), one workgroup alone,
+// or nothing left to do here.
+enum StartMode { kNear = 0, kFar = 1, kAlone = 2, kLeave = 3 };
+
+// The start of a group, run by one wave of each of its P workgroups:
+// workgroup j's word gets (tag, XCD id), the lanes wait for everyone's words.
+// decide[0]: 0 open, 1 everyone goes, 2 one workgroup alone; decide[1] counts
+// the workgroups that left, the last of which reopens the group's words.
+__device__ int group_start(unsigned long long* hand, unsigned* decide, int j, int P, unsigned tag,
+                           unsigned wait_ticks) {
+  const int lane = threadIdx.x & 63;
+  unsigned xcc;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+  xcc &= 15u;
+  if (lane == 0)
+    __hip_atomic_store(hand + j, ((unsigned long long)tag << 32) | xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long t0 = wall_clock64();
+  bool same = true, late = false;
+  int next = lane;   // words lane, lane + 64, ... of the group, in turn
+  while (true) {
+    if (next < P) {
+      const unsigned long long w = load_tagged(hand + next);
+      if ((unsigned)(w >> 32) == tag) {
+        same = same && (unsigned)w == xcc;
+        next += 64;
+      }
+    }
+    if (__all(next >= P)) break;
+    if (!late && (wall_clock64() - t0 >= (unsigned long long)wait_ticks ||
+                  __hip_atomic_load(decide, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u)) {
+      // one outcome for the whole group: whoever swaps first decides
+      late = true;
+      unsigned seen = 0u;
+      if (lane == 0)
+        __hip_atomic_compare_exchange_strong(decide, &seen, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+      seen = __builtin_amdgcn_readfirstlane(seen);
+      if (seen != 1u) return seen == 0u ? kAlone : kLeave;
+      // someone saw everyone: all are resident, their words are coming
+    }
+  }
+  if (!late) {
+    unsigned seen = 0u;
+    if (lane == 0)
+      __hip_atomic_compare_exchange_strong(decide, &seen, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(seen) == 2u) return kLeave;
+  }
+  return __all(same) ? kNear : kFar;
+}
+
+// A workgroup of a group that does not go: the last of its P to come through
+// here (the one that ran alone among them) reopens the group's words.
+__device__ void group_leave(unsigned long long* hand, unsigned* decide, int P) {
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(decide + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(P - 1)) {
+    for (int i = 0; i < P; ++i)
+      __hip_atomic_store(hand + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(decide + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// One pair by one workgroup, every slice read from memory: the sums of the
+// register path in the same order.  z at its LDS place, c and h in LDS.
+__device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* zs, float* cs, float* ys) {
+  const PairLevel& v = a.lv[lev];
+  const int tid = threadIdx.x, H = a.H, G = a.G, T = a.T, TB = a.T * a.B, K = v.K, S = v.S, lgS = v.lgS;
+  for (int i = tid; i < H; i += kThreads) {
+    hs[i] = a.h0 ? a.h0[(size_t)b * H + i] : 0.0f;
+    cs[i] = a.c0 ? a.c0[(size_t)b * H + i] : 0.0f;
+  }
+  __syncthreads();
+  const int sub = tid >> 4, sla = tid & 15;
+  const int rs = tid >> lgS, sl = tid & (S - 1), q = rs & 3;
+  const int units = kThreads >> (lgS + 2);              // units per pass, their four rows gate-minor
+  const int wv = tid >> 6, lane = tid & 63, rpw = 64 >> lgS;
+  float* ysw = ys + wv * rpw;
+  float* hout = a.h_out + ((size_t)lev * T * a.B + b) * H;
+  for (int t = 0; t < T; ++t) {
+    for (int base = 0; base < G * K; base += kThreads / 16) {
+      const int tau = base + sub;
+      float acc = 0.0f;
+      if (tau < G * K) {
+        const size_t src = (size_t)tau * a.NZ;
+        for (int e = a.nx[tau] + sla; e < a.NZ; e += 16) acc += a.vval[src + e] * hs[(int)a.vidx[src + e] - a.D];
+      }
+      acc = group_sum<16>(acc);
+      if (sla == 0 && tau < G * K) {
+        const int g = tau % G, n = tau / G;
+        zs[g * v.zst + (n & (S - 1)) * v.kst + (n >> lgS)] =
+            a.sigma[tau] * (a.px[(size_t)tau * TB + t * a.B + b] + acc);
+      }
+    }
+    __syncthreads();
+    for (int u0 = 0; u0 < H; u0 += units) {
+      const int u = u0 + (rs >> 2);
+      float acc = 0.0f, bias = 0.0f;
+      if (u < H) {
+        const size_t row = (size_t)q * H + u;
+        const float* urow = a.Ut + row * a.N;
+        const float* z = zs + (G == 4 ? q : 0) * v.zst + sl * v.kst;
+        for (int n = sl; n < K; n += S) acc += urow[n] * z[n >> lgS];
+        bias = a.bias[row];
+      }
+      acc = group_sum_rt(acc, S) + bias;
+      if (sl == 0) ysw[lane >> lgS] = acc;
+      __syncthreads();
+      if (lane < (rpw >> 2)) {
+        const int uc = u0 + wv * (rpw >> 2) + lane;
+        if (uc < H) {
+          float c = cs[uc], h2;
+          cell_update(ysw[4 * lane], ysw[4 * lane + 1], ysw[4 * lane + 2], ysw[4 * lane + 3], c, h2);
+          cs[uc] = c;
+          hs[uc] = h2;
+          hout[(size_t)t * a.B * H + uc] = h2;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (a.c_out)
+    for (int i = tid; i < H; i += kThreads) a.c_out[((size_t)lev * a.B + b) * H + i] = cs[i];
+  __syncthreads();
+}
 
 // OPT output rows per thread with UMAX U entries each in registers, APASS
 // phase-A passes with HMAX h-part entries per lane each.  Every loop runs to
 // its compile-time bound: entries past a lane's share are zeros (a U entry
 // past the budget, an h-part slot past the term's count), whose products add
 // nothing, so the sums equal those over the live entries in the same order.
-template <int OPT, int UMAX, int APASS, int HMAX>
-__global__ void __launch_bounds__(kThreads) pair_lstm_kernel(PairArgs a) {
+// TWO: the instance keeps to 128 registers, so that two workgroups share a
+// compute unit (near groups of more than 32 workgroups).
+template <int OPT, int UMAX, int APASS, int HMAX, bool TWO>
+__global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr int kChunk = 16;   // LDS reads in flight per batch
-  constexpr int NWMAX = kMaxWords;
-  const int P = gridDim.x, j = blockIdx.x;
+  // group of this workgroup and its place in it
+  const int ng = a.groups;
+  const int g = ng > 1 ? (int)((blockIdx.x + ng - a.first_xcd) % ng) : 0, j = blockIdx.x / ng;
+  if (g >= a.L * a.B) return;
   const int tid = threadIdx.x, lane = tid & 63;
-  const bool publisher = tid >= kPollThreads;
-  const int D = a.D, H = a.H, G = a.G, N = a.N, NZ = a.NZ, T = a.T, K = a.K, GK = a.GK;
-  const int OM = a.OM, RU = a.RU, zst = a.zstride, kst = a.kstride;
-  const bool local = P == 1;
+  const int D = a.D, H = a.H, G = a.G, N = a.N, NZ = a.NZ, T = a.T, B = a.B;
   const PairLayout lay = pair_layout(a);
   float* ldsf = reinterpret_cast<float*>(lds_raw);
   unsigned long long* lstamp = reinterpret_cast<unsigned long long*>(lds_raw);
+  int* modes = reinterpret_cast<int*>(ldsf + lay.mode);
   float* pxs = ldsf + lay.px;      // P_x [T][OM]
   float* hs = ldsf + lay.hs;       // h_{t-1} [H]
   float* zs = ldsf + lay.zs;       // z of this timestep [G][zst]
-  float* zown = ldsf + lay.zown;   // z of the owned terms [OM]
-  float* hown = ldsf + lay.hown;   // h of the owned units [RU]
-  const int r0 = j * RU, rc = max(0, min(RU, H - r0));
-  const int n_owned = GK > j ? (GK - j + P - 1) / P : 0;
-  // uniform plan values, kept in scalar registers
-  const int S = __builtin_amdgcn_readfirstlane(a.S), lgS = __builtin_amdgcn_readfirstlane(a.lgS);
-  // z of term (n, g) sits at zs[g*zst + (n % S)*kst + n / S]: lane sl of a row
-  // reads its terms sl + S*k at consecutive addresses (immediate offsets)
-  auto zpos = [&](int tau) { const int g = tau % G, n = tau / G; return g * zst + (n & (S - 1)) * kst + (n >> lgS); };
+  const int wv = tid >> 6;
 
-  // Prologue loads, ordered so that every independent load is in flight
-  // before the first wait: the first share of P_x and h0, sigma and the
-  // h/x split of the owned terms, the U entries, bias and c0; then the
-  // h-part entries (their addresses need the split).
-  const int npx = T * n_owned;
-  float px0 = 0.0f, h00 = 0.0f;
-  if (tid < npx) {
-    const int t0 = tid / n_owned, io0 = tid - t0 * n_owned;
-    px0 = a.px[(size_t)(j + io0 * P) * T + t0];
+  // The group starts once, for the widest of its pairs: the last wave decides
+  // while the others load the first pair's slices.
+  int pg = 1;
+  for (int lb = g; lb < a.L * B; lb += ng) {
+    const PairLevel& v = a.lv[lb / B];
+    if (v.K > 0) pg = max(pg, v.P);
   }
-  if (tid < H && a.h0) h00 = a.h0[tid];
-
-  // ---- phase-A roles: lane group sub (16 lanes) takes owned terms sub + 32p
-  const int sub = tid >> 4, sla = tid & 15;
-  float hv[APASS][HMAX];
-  int hi[APASS][HMAX];
-  float sg[APASS];
-  int slot[APASS], zdst[APASS], e0v[APASS];
-#pragma unroll
-  for (int p = 0; p < APASS; ++p) {
-    const int ia = sub + 32 * p;
-    const bool own = ia < n_owned;
-    const int tau = j + ia * P;
-    sg[p] = own ? a.sigma[tau] : 0.0f;
-    slot[p] = own ? j * OM + ia : -1;
-    zdst[p] = own ? zpos(tau) : 0;
-    e0v[p] = own ? (int)a.nx[tau] : NZ;
-  }
-
-  // ---- phase-B roles: row slot rs = tid / S, rows rs + o * (512 / S); row ol
-  // is gate q = ol & 3 of owned unit ol >> 2 (gate-minor: a unit's four rows
-  // are four adjacent lane groups of one wave)
-  const int rs = tid >> lgS, sl = tid & (S - 1);
-  const int nslots = kThreads >> lgS;
-  float uv[OPT][UMAX];
-  float bq[OPT];
-  // every row of a thread has gate q = rs & 3 (row slots per pass are a
-  // multiple of 4): one z base for all of them
-  const int zb = (G == 4 ? (rs & 3) : 0) * zst + sl * kst;
-  // ---- cell roles: a wave holds the rows of 16 * OPT / S units (row slots
-  // [w * 64/S, (w+1) * 64/S) in each of the OPT passes); its lane cl takes
-  // unit cl, pass co = cl / (16/S), row slots 4 ck .. 4 ck + 3 (ck = cl %
-  // (16/S)), and keeps that unit's c in a register.  The rows' sums reach
-  // it through the wave's LDS block ysw[o][64/S] (no cross-wave traffic).
-  const int wv = tid >> 6, rpw = 64 >> lgS, upw = (16 * OPT) >> lgS;
-  const int co = lane / (16 >> lgS), ck = lane % (16 >> lgS);
-  const int cunit = (wv * rpw + 4 * ck + co * nslots) >> 2;
-  const bool cell_ok = lane < upw && cunit < rc;
-  float cst = (cell_ok && a.c0) ? a.c0[r0 + cunit] : 0.0f;
-  float* ysw = ldsf + lay.ys + (size_t)wv * OPT * rpw;
-#pragma unroll
-  for (int o = 0; o < OPT; ++o) {
-    const int ol = rs + o * nslots, ul = ol >> 2, q = ol & 3;
-    const bool rowv = ul < rc;
-    const size_t row = (size_t)q * H + r0 + ul;
-    bq[o] = rowv ? a.bias[row] : 0.0f;
-    const float* urow = a.Ut + (rowv ? row : 0) * N;
-#pragma unroll
-    for (int k = 0; k < UMAX; ++k) uv[o][k] = urow[min(sl + S * k, K - 1)];
-#pragma unroll
-    for (int k = 0; k < UMAX; ++k) uv[o][k] = (rowv && sl + S * k < K) ? uv[o][k] : 0.0f;
-  }
-
-#pragma unroll
-  for (int p = 0; p < APASS; ++p) {
-    const int ia = sub + 32 * p;
-    const int tau = ia < n_owned ? j + ia * P : 0;
-    const int e0 = e0v[p], cnt = NZ - e0;
-    const size_t src = (size_t)tau * NZ;
-    // every load issued (index clamped into the term's entries), then masked
-#pragma unroll
-    for (int k = 0; k < HMAX; ++k) {
-      const int e = min(e0 + sla + 16 * k, NZ - 1);
-      hv[p][k] = a.vval[src + e];
-      hi[p][k] = (int)a.vidx[src + e];
+  const bool started = pg > 1 && j < pg;
+  unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
+  unsigned* decide = reinterpret_cast<unsigned*>(ng > 1 ? hand + kNearWidth : a.ctl + kSpreadWords);
+  const size_t exf = 2 * ((size_t)a.zslots + a.hpad);   // floats of a pair's exchange: z [2][zslots], h [2][hpad]
+  if (wv == kWaves - 1) {
+    int mode = kFar;
+    if (started) {
+      // own slots of both halves empty (the padding of h holds zeros) before
+      // the group's other workgroups hear of this one
+      for (int lb = g; lb < a.L * B; lb += ng) {
+        const PairLevel& v = a.lv[lb / B];
+        float* zx = a.ex + lb * exf;
+        float* hx = zx + 2 * a.zslots;
+        for (int half = 0; half < 2; ++half) {
+          for (int i = j * v.OM + lane; i < min((j + 1) * v.OM, v.slots); i += 64)
+            store_slot(zx + half * a.zslots + i, kEmpty, false);
+          for (int i = j * v.RU + lane; i < min((j + 1) * v.RU, H); i += 64)
+            store_slot(hx + half * a.hpad + i, kEmpty, false);
+          if (j == 0 && H + lane < a.hpad) store_slot(hx + half * a.hpad + H + lane, 0u, false);
+        }
+      }
+      wait_memory();
     }
-#pragma unroll
-    for (int k = 0; k < HMAX; ++k) {
-      const bool live = sla + 16 * k < cnt;
-      hv[p][k] = live ? hv[p][k] : 0.0f;
-      hi[p][k] = 4 * (int)lay.hs + (live ? 4 * (hi[p][k] - D) : 0);   // byte offset of h[k - D] in LDS
+    if (started) mode = group_start(hand, decide, j, pg, a.tag_base | 0xFFFFu, a.wait_ticks);
+    if (lane == 0) modes[0] = mode;
+  }
+
+  bool near = false, seen_mode = false;
+  for (int lb = g; lb < a.L * B; lb += ng) {
+    const int lev = lb / B, b = lb - lev * B;
+    const PairLevel& v = a.lv[lev];
+    const int P = v.P, K = v.K, OM = v.OM, RU = v.RU, zst = v.zst, kst = v.kst, kpl = v.kpl;
+    if (j >= P) continue;
+    const bool local = P == 1 || K == 0;   // nothing exchanged
+    const int r0 = j * RU, rc = max(0, min(RU, H - r0));
+    const int n_owned = max(0, min(OM, v.slots - j * OM));
+    const int S = __builtin_amdgcn_readfirstlane(v.S), lgS = __builtin_amdgcn_readfirstlane(v.lgS);
+    // Slot w of the z exchange is entry k = w % kpl of lane sl of a row of group
+    // g (w / kpl = g*S + sl), the term n = sl + S*k: a lane's terms are
+    // consecutive, and so are a workgroup's slots [j*OM, j*OM + OM).  In LDS
+    // the entry sits at zs[g*zst + sl*kst + k].  tau < 0: no term (n >= K).
+    auto slot_tau = [&](int w) {
+      const int blk = w / kpl, n = (blk & (S - 1)) + S * (w - blk * kpl);
+      return n < K ? n * G + (blk >> lgS) : -1;
+    };
+    auto slot_pos = [&](int w) {
+      const int blk = w / kpl;
+      return (blk >> lgS) * zst + (blk & (S - 1)) * kst + (w - blk * kpl);
+    };
+    if (lb != g) __syncthreads();   // the previous pair's LDS is done with
+
+    // Prologue loads, ordered so that every independent load is in flight
+    // before the first wait: the first share of P_x and h0, sigma and the
+    // h/x split of the owned terms, the U entries, bias and c0; then the
+    // h-part entries (their addresses need the split).
+    const int npx = T * n_owned, TB = T * B;
+    float px0 = 0.0f, h00 = 0.0f;
+    if (tid < npx) {
+      const int io0 = tid / T, tau = slot_tau(j * OM + io0);
+      if (tau >= 0) px0 = a.px[(size_t)tau * TB + (tid - io0 * T) * B + b];
     }
-  }
+    if (tid < H && a.h0) h00 = a.h0[(size_t)b * H + tid];
 
-  // ---- exchange roles: z slots tid + 512 r (slot s = j'*OM + i' carries
-  // term j' + i'*P), h words tid + 512 r
-  int zsi[NWMAX], zdi[NWMAX], hsi[NWMAX];
-  const int nslot = P * OM;
-  const int nwz = (nslot + kPollThreads - 1) / kPollThreads, nwh = (H + kPollThreads - 1) / kPollThreads;
-#pragma unroll
-  for (int r = 0; r < NWMAX; ++r) {
-    const int s = tid + kPollThreads * r;
-    const int jj = s / (OM > 0 ? OM : 1), ii = s - jj * OM;
-    const int tau = jj + ii * P;
-    const bool v = !local && !publisher && r < nwz && s < nslot && tau < GK;
-    zsi[r] = v ? s : -1;
-    zdi[r] = v ? zpos(tau) : 0;
-    hsi[r] = (!local && !publisher && r < nwh && s < H) ? s : -1;
-  }
-
-  // ---- LDS: initial state, P_x of every timestep when it fits
-  if (tid < H) hs[tid] = h00;
-  for (int i = tid + kThreads; i < H; i += kThreads) hs[i] = a.h0 ? a.h0[i] : 0.0f;
-  // z slots of terms past the budget (n >= K in a lane's last entry) are
-  // never written and must read 0 (their u entries are 0 as well)
-  for (int i = tid; i < G * zst; i += kThreads) zs[i] = 0.0f;
-  if (tid < npx) pxs[(tid / n_owned) * OM + tid % n_owned] = px0;
-  for (int i = tid + kThreads; i < npx; i += kThreads) {
-    const int t = i / n_owned, io = i - t * n_owned;
-    pxs[t * OM + io] = a.px[(size_t)(j + io * P) * T + t];
-  }
-  __syncthreads();
-
-  const bool stamp = a.stamps && j == 0 && tid == 0;
-  // stamps of short runs stay in LDS until the end (no stores on the way)
-  unsigned long long* st = (T <= kLdsStamps) ? lstamp : a.stamps;
-  if (stamp) {
-    st[0] = wall_clock64();
-    st[1] = clock64();
-  }
-  for (int t = 0; t < T; ++t) {
-    const unsigned tag = a.tag_base | (unsigned)(t + 1);
-    if (stamp) st[2 + 4 * t] = clock64();
-
-    // ---- phase A: z = sigma * (P_x + prune(v)_h . h_{t-1}) ----
+    // ---- phase-A roles: lane group sub (16 lanes) takes owned terms sub + 32p
+    const int sub = tid >> 4, sla = tid & 15;
+    float hv[APASS][HMAX];
+    int hi[APASS][HMAX];
+    float sg[APASS];
+    int e0v[APASS], tauv[APASS];
 #pragma unroll
     for (int p = 0; p < APASS; ++p) {
-      if (p * 32 >= n_owned) break;
-      float acc = 0.0f;
-#pragma unroll
-      for (int k0 = 0; k0 < HMAX; k0 += kChunk) {
-        // the bound k0 + k < HMAX is a constant once unrolled (a last chunk
-        // may be partial: HMAX = 24)
-        float hg[kChunk];
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k)
-          if (k0 + k < HMAX) hg[k] = *reinterpret_cast<const float*>(lds_raw + hi[p][k0 + k]);
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k)
-          if (k0 + k < HMAX) acc += hv[p][k0 + k] * hg[k];
-      }
-      acc = group_sum<16>(acc);
-      if (sla == 0 && slot[p] >= 0) {
-        const float pxv = pxs[t * OM + sub + 32 * p];
-        const float z = sg[p] * (pxv + acc);
-        if (local) zs[zdst[p]] = z;
-        else zown[sub + 32 * p] = z;
-      }
+      const int ia = sub + 32 * p;
+      const int tau = ia < n_owned ? slot_tau(j * OM + ia) : -1;
+      tauv[p] = max(tau, 0);
+      sg[p] = tau >= 0 ? a.sigma[tau] : 0.0f;
+      e0v[p] = tau >= 0 ? (int)a.nx[tau] : NZ;
     }
-    if (stamp) st[3 + 4 * t] = clock64();
-    if (!local) {
-      lds_barrier();
-      if (publisher) {
-        for (int i = lane; i < n_owned; i += 64) publish(a.zx + j * OM + i, zown[i], tag);
-      } else {
-        poll_words<NWMAX>(zs, a.zx, zsi, zdi, nwz, tag, a.err);
-      }
-    }
-    lds_barrier();
-    if (stamp) st[4 + 4 * t] = clock64();
 
-    // ---- phase B: y = b + sum_n u_n z_n, then the cell update ----
-    float y[OPT], acc[OPT];
+    // ---- phase-B roles: row slot rs = tid / S, rows rs + o * (512 / S); row ol
+    // is gate q = ol & 3 of owned unit ol >> 2 (gate-minor: a unit's four rows
+    // are four adjacent lane groups of one wave)
+    const int rs = tid >> lgS, sl = tid & (S - 1);
+    const int nslots = kThreads >> lgS;
+    float uv[OPT][UMAX];
+    float bq[OPT];
+    // every row of a thread has gate q = rs & 3 (row slots per pass are a
+    // multiple of 4): one z base for all of them
+    const int zb = (G == 4 ? (rs & 3) : 0) * zst + sl * kst;
+    // ---- cell roles: a wave holds the rows of 16 * OPT / S units (row slots
+    // [w * 64/S, (w+1) * 64/S) in each of the OPT passes); its lane cl takes
+    // unit cl, pass co = cl / (16/S), row slots 4 ck .. 4 ck + 3 (ck = cl %
+    // (16/S)), and keeps that unit's c in a register.  The rows' sums reach
+    // it through the wave's LDS block ysw[o][64/S] (no cross-wave traffic).
+    const int rpw = 64 >> lgS, upw = (16 * OPT) >> lgS;
+    const int co = lane >> (4 - lgS), ck = lane & ((16 >> lgS) - 1);
+    const int cunit = (wv * rpw + 4 * ck + co * nslots) >> 2;
+    const bool cell_ok = lane < upw && cunit < rc;
+    float cst = (cell_ok && a.c0) ? a.c0[(size_t)b * H + r0 + cunit] : 0.0f;
+    float* ysw = ldsf + lay.ys + (size_t)wv * OPT * rpw;
 #pragma unroll
-    for (int o = 0; o < OPT; ++o) acc[o] = 0.0f;
+    for (int o = 0; o < OPT; ++o) {
+      const int ol = rs + o * nslots, ul = ol >> 2, q = ol & 3;
+      const bool rowv = ul < rc;
+      const size_t row = (size_t)q * H + r0 + ul;
+      bq[o] = rowv ? a.bias[row] : 0.0f;
+      const float* urow = a.Ut + (rowv ? row : 0) * N;
 #pragma unroll
-    for (int k0 = 0; k0 < UMAX; k0 += kChunk) {
-      float zv[kChunk];
+      for (int k = 0; k < UMAX; ++k) uv[o][k] = urow[max(0, min(sl + S * k, K - 1))];
 #pragma unroll
-      for (int k = 0; k < kChunk; ++k)
-        if (k0 + k < UMAX) zv[k] = zs[zb + k0 + k];
-#pragma unroll
-      for (int o = 0; o < OPT; ++o)
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k)
-          if (k0 + k < UMAX) acc[o] += uv[o][k0 + k] * zv[k];
+      for (int k = 0; k < UMAX; ++k) uv[o][k] = (rowv && sl + S * k < K) ? uv[o][k] : 0.0f;
     }
+
 #pragma unroll
-    for (int o = 0; o < OPT; ++o) y[o] = group_sum_rt(acc[o], S) + bq[o];
-    // the rows' sums go to the wave's block (lane sl == 0 of each row), then
-    // each unit's lane reads its four gate rows at once and updates c and h
-    if (sl == 0) {
+    for (int p = 0; p < APASS; ++p) {
+      const int e0 = e0v[p], cnt = NZ - e0;
+      const size_t src = (size_t)tauv[p] * NZ;
+      // every load issued (index clamped into the term's entries), then masked
 #pragma unroll
-      for (int o = 0; o < OPT; ++o) ysw[o * rpw + ((tid & 63) >> lgS)] = y[o];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (lane < upw) {
-      const float4 g4 = *reinterpret_cast<const float4*>(ysw + co * rpw + 4 * ck);
-      float h2;
-      cell_update(g4.x, g4.y, g4.z, g4.w, cst, h2);
-      if (cell_ok) {
-        if (local) {
-          hs[r0 + cunit] = h2;
-          a.h_out[(size_t)t * H + r0 + cunit] = h2;
-        } else {
-          hown[cunit] = h2;
-        }
+      for (int k = 0; k < HMAX; ++k) {
+        const int e = min(e0 + sla + 16 * k, NZ - 1);
+        hv[p][k] = a.vval[src + e];
+        hi[p][k] = (int)a.vidx[src + e];
+      }
+#pragma unroll
+      for (int k = 0; k < HMAX; ++k) {
+        const bool live = sla + 16 * k < cnt;
+        hv[p][k] = live ? hv[p][k] : 0.0f;
+        hi[p][k] = 4 * lay.hs + (live ? 4 * (hi[p][k] - D) : 0);   // byte offset of h[k - D] in LDS
       }
     }
-    if (stamp) st[5 + 4 * t] = clock64();
-    if (!local) {
+
+    // ---- exchange roles: 16-byte units tid + 512 r of z (a lane's slots are a
+    // multiple of 4, so a unit's four go to consecutive LDS places) and of h
+    int zdi[kMaxUnits], hdi[kMaxUnits];
+    unsigned zpend = 0, hpend = 0;
+#pragma unroll
+    for (int r = 0; r < kMaxUnits; ++r) {
+      const int u = tid + kThreads * r;
+      if (4 * u < v.slots) zpend |= 1u << r;
+      if (4 * u < H) hpend |= 1u << r;
+      zdi[r] = 4 * u < v.slots ? slot_pos(4 * u) : 0;
+      hdi[r] = 4 * u;
+    }
+    float* zx = a.ex + lb * exf;
+    float* hx = zx + 2 * a.zslots;
+
+    // ---- LDS: initial state, P_x of every timestep
+    if (tid < H) hs[tid] = h00;
+    for (int i = tid + kThreads; i < H; i += kThreads) hs[i] = a.h0 ? a.h0[(size_t)b * H + i] : 0.0f;
+    // z slots of terms past the budget (n >= K in a lane's last entry) are
+    // never written and must read 0 (their u entries are 0 as well)
+    for (int i = tid; i < a.zfloats; i += kThreads) zs[i] = 0.0f;
+    if (tid < npx) pxs[(tid % T) * OM + tid / T] = px0;
+    for (int i = tid + kThreads; i < npx; i += kThreads) {
+      const int io = i / T, t = i - io * T, tau = slot_tau(j * OM + io);
+      pxs[t * OM + io] = tau >= 0 ? a.px[(size_t)tau * TB + t * B + b] : 0.0f;
+    }
+    __syncthreads();
+    if (lb == g || !seen_mode) {
+      const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+      if (mode >= kAlone) break;   // the whole group's outcome: nothing of any pair has begun
+      near = mode == kNear;
+      seen_mode = true;
+    }
+
+    const bool stamp = a.stamps && lb == 0 && j == 0 && tid == 0;
+    // stamps of short runs stay in LDS until the end (no stores on the way)
+    unsigned long long* st = (T <= kLdsStamps) ? lstamp : a.stamps;
+    if (stamp) {
+      st[0] = wall_clock64();
+      st[1] = clock64();
+    }
+    float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + cunit;
+    for (int t = 0; t < T; ++t) {
+      float* zxt = zx + (t & 1) * a.zslots;
+      float* hxt = hx + (t & 1) * a.hpad;
+      if (stamp) st[2 + 4 * t] = clock64();
+
+      // ---- phase A: z = sigma * (P_x + prune(v)_h . h_{t-1}) ----
+#pragma unroll
+      for (int p = 0; p < APASS; ++p) {
+        if (p * 32 >= n_owned) break;
+        float acc = 0.0f;
+#pragma unroll
+        for (int k0 = 0; k0 < HMAX; k0 += kChunk) {
+          // the bound k0 + k < HMAX is a constant once unrolled (a last chunk
+          // may be partial: HMAX = 24)
+          float hg[kChunk];
+#pragma unroll
+          for (int k = 0; k < kChunk; ++k)
+            if (k0 + k < HMAX) hg[k] = *reinterpret_cast<const float*>(lds_raw + hi[p][k0 + k]);
+#pragma unroll
+          for (int k = 0; k < kChunk; ++k)
+            if (k0 + k < HMAX) acc += hv[p][k0 + k] * hg[k];
+        }
+        acc = group_sum<16>(acc);
+        const int ia = sub + 32 * p;
+        if (sla == 0 && ia < n_owned) {
+          const float z = sg[p] * (pxs[t * OM + ia] + acc);
+          if (local) {
+            zs[slot_pos(j * OM + ia)] = z;
+          } else {
+            publish_slot(zxt + j * OM + ia, z, near);
+            // z_{t-1}: everyone's h_{t-1} is here, so everyone has read it
+            store_slot(zx + ((t + 1) & 1) * a.zslots + j * OM + ia, kEmpty, near);
+          }
+        }
+      }
+      if (stamp) st[3 + 4 * t] = clock64();
+      if (!local) {
+        poll_units(zs, zxt, a.zslots * 4, zdi, zpend, a.err);
+        wait_memory();   // the emptied slots too, before this workgroup's h_t
+      }
       lds_barrier();
-      if (publisher) {
-        for (int u = lane; u < rc; u += 64) {
-          const float h2 = hown[u];
-          a.h_out[(size_t)t * H + r0 + u] = h2;
-          publish(a.hx + r0 + u, h2, tag);
-        }
-      } else {
-        poll_words<NWMAX>(hs, a.hx, hsi, hsi, nwh, tag, a.err);
+      if (stamp) st[4 + 4 * t] = clock64();
+
+      // ---- phase B: y = b + sum_n u_n z_n, then the cell update ----
+      float y[OPT], acc[OPT];
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) acc[o] = 0.0f;
+#pragma unroll
+      for (int k0 = 0; k0 < UMAX; k0 += kChunk) {
+        float4 z4[kChunk / 4];
+#pragma unroll
+        for (int k = 0; k < kChunk; k += 4)
+          if (k0 + k < UMAX) z4[k / 4] = *reinterpret_cast<const float4*>(zs + zb + k0 + k);
+#pragma unroll
+        for (int o = 0; o < OPT; ++o)
+#pragma unroll
+          for (int k = 0; k < kChunk; k += 4)
+            if (k0 + k < UMAX) {
+              acc[o] += uv[o][k0 + k] * z4[k / 4].x;
+              acc[o] += uv[o][k0 + k + 1] * z4[k / 4].y;
+              acc[o] += uv[o][k0 + k + 2] * z4[k / 4].z;
+              acc[o] += uv[o][k0 + k + 3] * z4[k / 4].w;
+            }
       }
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) y[o] = group_sum_rt(acc[o], S) + bq[o];
+      // the rows' sums go to the wave's block (lane sl == 0 of each row), then
+      // each unit's lane reads its four gate rows at once and updates c and h
+      if (sl == 0) {
+#pragma unroll
+        for (int o = 0; o < OPT; ++o) ysw[o * rpw + (lane >> lgS)] = y[o];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (lane < upw) {
+        const float4 g4 = *reinterpret_cast<const float4*>(ysw + co * rpw + 4 * ck);
+        float h2;
+        cell_update(g4.x, g4.y, g4.z, g4.w, cst, h2);
+        if (cell_ok) {
+          if (local) {
+            hs[r0 + cunit] = h2;
+          } else {
+            publish_slot(hxt + r0 + cunit, h2, near);
+            // h_{t-1}: everyone's z_t is here, so everyone has read it
+            store_slot(hx + ((t + 1) & 1) * a.hpad + r0 + cunit, kEmpty, near);
+          }
+          hout[(size_t)t * B * H] = h2;
+        }
+      }
+      if (stamp) st[5 + 4 * t] = clock64();
+      if (!local) {
+        poll_units(hs, hxt, a.hpad * 4, hdi, hpend, a.err);
+        wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
+      }
+      lds_barrier();
     }
-    lds_barrier();
+    if (stamp) {
+      st[2 + 4 * T] = clock64();
+      st[3 + 4 * T] = wall_clock64();
+      if (st == lstamp)
+        for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = lstamp[i];
+    }
+    if (a.c_out && cell_ok) a.c_out[((size_t)lev * B + b) * H + r0 + cunit] = cst;
   }
-  if (stamp) {
-    st[2 + 4 * T] = clock64();
-    st[3 + 4 * T] = wall_clock64();
-    if (st == lstamp)
-      for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = lstamp[i];
+  if (!started) return;
+  __syncthreads();
+  const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+  if (mode == kAlone) {
+    for (int lb = g; lb < a.L * B; lb += ng) {
+      for (int i = tid; i < a.zfloats; i += kThreads) zs[i] = 0.0f;
+      __syncthreads();
+      run_alone(a, lb / B, lb % B, hs, zs, ldsf + lay.cs, ldsf + lay.ys);
+    }
   }
-  if (a.c_out && cell_ok) a.c_out[r0 + cunit] = cst;
+  if (mode >= kAlone) {
+    group_leave(hand, decide, pg);
+  } else if (tid == 0) {
+    // the widest pair's exchanges are over, so every workgroup of the group
+    // has read the decision and everyone's words: open for the next start
+    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 template <int OPT, int UMAX, int APASS, int HMAX>
 hipError_t launch_pair_kernel(const PairArgs& a, int P, size_t lds, hipStream_t stream) {
+  // at most 128 registers where the slices are small (two workgroups per
+  // compute unit, near groups of up to kNearWidth workgroups)
+  constexpr bool kTwo = OPT == 1 && APASS == 1 && HMAX <= kTwoHmax;
   static bool attr_set = false;
-  const void* fn = (const void*)pair_lstm_kernel<OPT, UMAX, APASS, HMAX>;
+  const void* fn = (const void*)pair_lstm_kernel<OPT, UMAX, APASS, HMAX, kTwo>;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  pair_lstm_kernel<OPT, UMAX, APASS, HMAX><<<dim3(P), dim3(kThreads), lds, stream>>>(a);
+  pair_lstm_kernel<OPT, UMAX, APASS, HMAX, kTwo><<<dim3(P * a.groups), dim3(kThreads), lds, stream>>>(a);
   return hipGetLastError();
 }
 
-}  // namespace
+// One level's launch shape on P workgroups, output rows per thread at most
+// `optcap`; false when its slices do not fit the registers.
+struct LevelShape {
+  int apass, opt, need_h, upt;
+};
+bool level_fits(const PairArgs& a, PairLevel& v, int hcap, int P, int optcap, LevelShape& s) {
+  const int OM = (v.slots + P - 1) / P, RU = (a.H + P - 1) / P;
+  s.apass = OM <= 32 ? 1 : (OM <= 64 ? 2 : 0);
+  s.need_h = (hcap + 15) / 16;             // h-part entries per lane
+  s.upt = (v.K + v.S - 1) / v.S;           // U entries per row and lane
+  if (!s.apass || s.need_h > (s.apass == 1 ? 32 : 16)) return false;
+  const int slots = kThreads / v.S;        // row slots per pass of the threads
+  const int opt = (4 * RU + slots - 1) / slots;
+  s.opt = opt <= 1 ? 1 : (opt <= 2 ? 2 : (opt <= 4 ? 4 : 0));
+  if (!s.opt || s.opt > optcap || s.upt > 32 / (s.opt == 4 ? 2 : 1)) return false;
+  // the four gate rows of a unit must be adjacent lane groups of one wave
+  if (4 * v.S > 64) return false;
+  if (v.slots > 4 * kMaxUnits * kThreads || a.H > 4 * kMaxUnits * kThreads) return false;
+  v.P = P;
+  v.OM = OM;
+  v.RU = RU;
+  return true;
+}
 
-int plan_pair(PairArgs& a, int num_cu, int want, size_t* lds) {
-  *lds = 0;
-  if (a.K < 1 || a.GK < 1 || a.G < 1) return 0;
-  a.S = lanes_for_level(a.K);
-  a.lgS = 31 - __builtin_clz((unsigned)a.S);
-  a.upt = (a.K + a.S - 1) / a.S;
-  const int need_h = (a.hcap + 15) / 16;   // h-part entries per lane
-  const int cap = std::max(1, num_cu);
-  auto fits = [&](int P) -> bool {
-    const int OM = (a.GK + P - 1) / P;
-    const int apass = OM <= 32 ? 1 : (OM <= 64 ? 2 : 0);
-    if (!apass) return false;
-    if (need_h > (apass == 1 ? 32 : 16)) return false;
-    const int RU = (a.H + P - 1) / P;
-    const int slots = kThreads / a.S;      // row slots per pass of the threads
-    const int opt = (4 * RU + slots - 1) / slots;
-    const int opt_b = opt <= 1 ? 1 : (opt <= 2 ? 2 : (opt <= 4 ? 4 : 0));
-    if (!opt_b || a.upt > 32 / (opt_b == 4 ? 2 : 1)) return false;
-    // register budget: two phase-A passes hold at most 16 h-part entries per
-    // lane (every instance fits its registers without spilling)
-    if (apass == 2 && need_h > 16) return false;
-    // the four gate rows of a unit must be adjacent lane groups of one wave
-    if (4 * a.S > 64) return false;
-    if ((size_t)P * OM > (size_t)kMaxWords * kPollThreads || a.H > kMaxWords * kPollThreads) return false;
-    a.OM = OM;
-    a.RU = RU;
-    a.apass = apass;
-    a.opt = opt_b;
-    return true;
-  };
+// Width of one level (0: none up to `cap` fits).
+int level_width(const PairArgs& a, PairLevel& v, int hcap, int cap, int want, int optcap, LevelShape& s) {
+  if (want > 0) return want <= cap && level_fits(a, v, hcap, want, optcap, s) ? want : 0;
+  if (level_fits(a, v, hcap, 1, optcap, s)) return 1;   // one workgroup: nothing exchanged
+  // the exchanges cost about the same at 16 and at 32 workgroups (0.47 and
+  // 0.50 us at K = 64), so take the narrowest width at which each thread has
+  // one phase-A term group and one output row, else the narrowest that fits
   int P = 0;
-  if (want > 0) {
-    if (want > cap || !fits(want)) return 0;
-    P = want;
-  } else if (fits(1)) {
-    P = 1;   // one workgroup: nothing exchanged
-  } else {
-    // the exchanges cost about the same at any width (their latency is
-    // that of device-scope visibility, not of the words moved), so take the
-    // narrowest width at which each thread has one phase-A term group and one
-    // output row (MI355X, driving shape, K = 512: 5.5 us per timestep on 64
-    // workgroups against 6.3 on 32 and 5.7 on 128), else the narrowest that fits
-    for (int p = 2; p <= cap && !P; ++p)
-      if (fits(p) && a.apass == 1 && a.opt == 1) P = p;
-    for (int p = 2; p <= cap && !P; ++p)
-      if (fits(p)) P = p;
-    if (!P) return 0;
-    // below 64 terms per group that width leaves each workgroup hundreds of
-    // output rows, and phase B then takes longer than the wider exchange
-    // costs: at least 16 workgroups from 17 terms per group, 32 from 64
-    // (each keeping 16 rows or more).  MI355X, driving shape, us per
-    // timestep at P = 4 / 8 / 16 / 32 / 64: K = 32 5.70 / 5.12 / 4.80 / 4.84
-    // / 5.42; K = 64 6.28 / 5.19 / 4.81 / 4.71 / 4.92; K = 128 - / 5.70 /
-    // 4.94 / 4.79 / 4.91; K = 256 32 and 64 equal (5.28, 5.27), K = 512 best
-    // at its own 64; outputs bitwise equal at every width.
-    const int floor_p = std::min({a.K >= 64 ? 32 : (a.K > 16 ? 16 : 0), (4 * a.H) / 16, cap});
-    if (P < floor_p && fits(floor_p)) P = floor_p;
-    fits(P);
+  for (int p = 2; p <= cap && !P; ++p)
+    if (level_fits(a, v, hcap, p, optcap, s) && s.apass == 1 && s.opt == 1) P = p;
+  // beyond one workgroup per compute unit of an XCD, several rows per thread
+  // cost less than the wider exchange as long as phase A keeps to one pass
+  if ((P == 0 || P > kXcdCus) && kXcdCus <= cap && level_fits(a, v, hcap, kXcdCus, optcap, s) && s.apass == 1)
+    P = kXcdCus;
+  for (int p = 2; p <= cap && !P; ++p)
+    if (level_fits(a, v, hcap, p, optcap, s)) P = p;
+  if (!P) return 0;
+  // a narrow layer: at least 16 workgroups from 17 terms per group and 32 from
+  // 64, each keeping 16 rows or more (driving shape, us per run on 16 / 32 /
+  // 64 workgroups: K = 32 40.8 / 41.1 / 48.2, K = 64 43.7 / 42.8 / 48.9,
+  // K = 256 62.1 / 54.2 / 59.8)
+  const int floor_p = std::min({v.K >= 64 ? 32 : (v.K > 16 ? 16 : 0), (4 * a.H) / 16, cap});
+  if (P < floor_p && level_fits(a, v, hcap, floor_p, optcap, s)) return floor_p;
+  return level_fits(a, v, hcap, P, optcap, s) ? P : 0;
+}
+
+// Shapes of every level with widths up to `cap` and up to `optcap` rows per
+// thread, and the instance (register buckets) that holds them all.
+int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
+  int pmax = 0, need_h = 0, upt = 0;
+  a.opt = a.apass = 1;
+  a.OMmax = a.zslots = 0;
+  for (int l = 0; l < a.L; ++l) {
+    PairLevel& v = a.lv[l];
+    v.S = lanes_for_level(v.K);
+    v.lgS = 31 - __builtin_clz((unsigned)v.S);
+    v.kpl = ((v.K + v.S - 1) / v.S + 3) & ~3;
+    v.slots = a.G * v.S * v.kpl;
+    LevelShape s;
+    if (!level_width(a, v, hcap[l], cap, want, optcap, s)) return 0;
+    pmax = std::max(pmax, v.P);
+    a.opt = std::max(a.opt, s.opt);
+    a.apass = std::max(a.apass, s.apass);
+    need_h = std::max(need_h, s.need_h);
+    upt = std::max(upt, s.upt);
+    a.OMmax = std::max(a.OMmax, v.OM);
+    a.zslots = std::max(a.zslots, v.slots);
   }
   // register buckets: h-part entries per lane, U entries per row and lane
   a.hpl = need_h <= 4 ? 4 : need_h <= 8 ? 8 : need_h <= 12 ? 12 : need_h <= 16 ? 16 : need_h <= 24 ? 24 : 32;
   if (a.apass == 2 && a.hpl > 16) return 0;
-  a.umax = a.opt == 4 ? (a.upt <= 8 ? 8 : 16) : a.opt == 2 ? (a.upt <= 16 ? 16 : 32)
-                      : (a.upt <= 8 ? 8 : a.upt <= 16 ? 16 : 32);
-  // lane sl's terms at stride kstride (odd, and covering the lane's whole
-  // register bucket: every read stays in the lane's zero-filled slots); gates
-  // at zstride = 16 (mod 64) apart (the four gate rows of a unit, in one
-  // wave, read distinct banks)
-  a.kstride = a.umax | 1;
-  a.zstride = ((a.S * a.kstride + 63) / 64) * 64 + 16;
+  if (a.opt == 4 && upt > 16) return 0;
+  a.upt = upt;
+  a.umax = a.opt == 4 ? (upt <= 8 ? 8 : 16) : a.opt == 2 ? (upt <= 16 ? 16 : 32) : (upt <= 8 ? 8 : upt <= 16 ? 16 : 32);
+  // lane sl's terms at stride kst: it covers the lane's whole register bucket
+  // (every read stays in the lane's zero-filled places), and 12, 20 or 36
+  // floats put the 16-byte reads of consecutive lanes in distinct banks
+  a.zfloats = 0;
+  for (int l = 0; l < a.L; ++l) {
+    PairLevel& v = a.lv[l];
+    v.kst = a.umax + 4;
+    v.zst = v.S * v.kst;
+    a.zfloats = std::max(a.zfloats, a.G * v.zst);
+  }
   a.hpad = (a.H + 3) & ~3;
-  // P_x of every timestep in LDS (no loads inside the recurrence); longer
-  // sequences take the general kernel
-  a.px_lds = 1;
-  const size_t bytes = 4 * pair_lds_floats(a);
-  if (bytes > kLdsCap) return 0;
-  *lds = bytes;
-  return P;
+  return pmax;
+}
+
+}  // namespace
+
+int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
+  *lds = 0;
+  int kmax = 0;
+  for (int l = 0; l < a.L; ++l) kmax = std::max(kmax, a.lv[l].K);
+  if (kmax < 1 || a.G < 1 || a.L > kMaxLevels) return 0;
+  const int pairs = a.L * a.B;
+  const bool xcds = num_cu >= kXcds * kXcdCus;   // the whole device: one group per XCD
+  if (pairs > 1 && (want > 0 || !xcds)) return 0;
+  // near groups: up to kNearWidth workgroups where two share a compute unit,
+  // up to kXcdCus otherwise; a single pair that needs more runs on every XCD
+  for (int optcap : {4, 2, 1}) {
+    for (int cap : {kNearWidth, kXcdCus, num_cu}) {
+      if (cap == num_cu && (pairs > 1 || num_cu > kSpreadWords)) continue;
+      const int P = plan_levels(a, hcap, std::min(cap, std::max(1, num_cu)), want, optcap);
+      if (!P) continue;
+      const bool two = a.opt == 1 && a.apass == 1 && a.hpl <= kTwoHmax;
+      const bool near = xcds && P <= (two ? kNearWidth : kXcdCus);
+      if (!near && cap != num_cu) continue;
+      a.stamps = reinterpret_cast<unsigned long long*>(1);   // sized with the stamps' block
+      const size_t bytes = 4 * (size_t)pair_layout(a).total;
+      a.stamps = nullptr;
+      if (bytes > (P > kXcdCus && near ? kLdsCap / 2 : kLdsCap)) {
+        if (cap != num_cu && pairs == 1) continue;
+        return 0;
+      }
+      a.groups = pairs > 1 || (near && P > 1) ? kXcds : 1;
+      *lds = bytes;
+      return P;
+    }
+  }
+  return 0;
 }
 
 template <int APASS, int HMAX>
@@ -484,7 +777,7 @@ hipError_t launch_pair_u(const PairArgs& a, int P, size_t lds, hipStream_t strea
 hipError_t launch_pair(const RunArgs& proj, const PairArgs& a, int P, hipStream_t stream) {
   hipError_t e = launch_input_proj(proj, stream);
   if (e != hipSuccess) return e;
-  const size_t lds = 4 * pair_lds_floats(a);
+  const size_t lds = 4 * (size_t)pair_layout(a).total;
   if (a.apass == 2) {
     switch (a.hpl) {
       case 4: return launch_pair_u<2, 4>(a, P, lds, stream);
