@@ -1584,7 +1584,7 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
   alstm::ExactArgs a{};
   a.x = x; a.h0 = h0; a.c0 = c0; a.h_out = h_out; a.c_out = c_out;
   a.Wx = m->d_Wx; a.Wh = m->d_Wh; a.bias = m->d_bias;
-  a.D = m->D; a.H = m->H; a.T = T; a.B = B; a.rows = rows;
+  a.D = m->D; a.H = m->H; a.T = T; a.B = B; a.rows = rows; a.num_cu = m->num_cu;
   a.xvec = (m->D % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   const int maxP = std::max(1, m->num_cu);
   int P = m->launch_blocks > 0 ? std::min(m->launch_blocks, maxP) : std::min(maxP, std::max(1, (m->H + 7) / 8));

@@ -27,85 +27,231 @@ namespace {
 constexpr int kExactLanes = 16;   // lanes per W_h row
 constexpr int kExactRows = kThreads / kExactLanes;   // rows per pass (32)
 constexpr int kExactWpl = 32;     // W_h entries per lane held in registers (H <= 512)
-constexpr int kExactCols = 16;    // x columns per staging pass of the x projection
-constexpr int kExactXprojRegs = 32;   // weights per lane of the x projection held in registers (D <= 2048)
+constexpr int kSkinnyCols = 64;   // x columns per workgroup of the narrow x projection
+constexpr int kSkinnyUnits = 16;  // 16-byte units of a W_x row per lane held in registers there
+constexpr int kTile = 128;        // gate rows and x columns per workgroup of the tiled x projection
+constexpr int kTileK = 32;        // contraction slice staged in LDS there
+constexpr int kTileLd = kTileK + 4;   // LDS row (floats): 16-byte reads of 16 rows in distinct banks
 constexpr int kExactSeq = 8;      // sequences sharing one read of a W_h row in the recurrence
 
 }  // namespace
 
-// px[tb][o] = b[o] + W_x[o] . x[tb] for every computed gate row o = q*H + r
-// (r < rows) and column tb = t*B + b; the px entries of the other rows are
-// not written.  One wave per row; the workgroup stages up to `cols` x
-// columns (contiguous in x) in LDS, read by the lanes at consecutive k.  The
-// lane's first 32 weights of its row are loaded into registers before the
-// staging, so that their latency overlaps it; the staging keeps 8 16-byte
-// loads in flight per thread when x rows are 16-byte aligned.  The column
-// chunks are dealt over gridDim.y workgroups per row group.
-__global__ void __launch_bounds__(kThreads) exact_xproj_kernel(ExactArgs a, int cols) {
-  extern __shared__ __align__(16) float xs[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ol = blockIdx.x * kWaves + wave;     // index among the 4*rows computed rows
+// The x part: px[tb][o] = b[o] + W_x[o] . x[tb] for every computed gate row o =
+// q*H + r (r < rows) and column tb = t*B + b; the px entries of the other rows
+// are not written.  Both kernels run it on v_mfma_f32_16x16x4_f32 (fp32
+// operands and sums; A = W_x rows, B = x columns): lane l holds
+// A[l%16][l/16], B[l/16][l%16] and result rows 4*(l/16) .. +3 of column l%16.
+// The four contraction indices of an instruction may be any four as long as
+// both operands agree, so a lane reads 16 bytes (k .. k+3 of its row, k = 4 *
+// (l/16)) and feeds four instructions from them.
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// row index of the ol-th of the 4*rows computed gate rows (clamped)
+__device__ __forceinline__ int gate_row(const ExactArgs& a, int ol) {
+  const int c = min(ol, 4 * a.rows - 1), q = c / a.rows;
+  return q * a.H + (c - q * a.rows);
+}
+
+// p[k .. k+3], zeros from index n on (V: p + k is 16-byte aligned and n a
+// multiple of 4)
+template <bool V>
+__device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
+  if constexpr (V) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + (k < n ? k : 0));
+    return k < n ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+  } else {
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = k + i < n ? p[k + i] : 0.f;
+    return v;
+  }
+}
+
+}  // namespace
+
+// Few columns or few rows: what bounds it is reading W_x once (16.8 MB at D =
+// 2048, H = 512), so the bytes in flight count.  A workgroup takes 16 gate
+// rows and up to 64 columns, its 8 waves an eighth of the contraction each:
+// a wave's whole slice of W_x (up to 16 units per lane) is loaded at once,
+// x comes straight from L2, and the partial sums of the waves meet in LDS in
+// a fixed order.  WV, XV: 16-byte aligned rows of W_x and of x.  MI355X, D =
+// 2048, H = 512, 16 columns: 30.5 us (one wave per row, x staged by every
+// workgroup) -> 10.5 us.
+template <bool WV, bool XV>
+__global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs a, int nrow) {
+  __shared__ float part[kWaves][4][16][17];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = 4 * (lane >> 4);
   const int TB = a.T * a.B, D = a.D, R = 4 * a.H;
-  const bool live = ol < 4 * a.rows;
-  const int q = live ? ol / a.rows : 0;
-  const int o = live ? q * a.H + (ol - q * a.rows) : 0;
-  const float* w = a.Wx + (size_t)o * D;
-  float wv[kExactXprojRegs];
+  const int ol0 = (blockIdx.x % nrow) * 16, c0 = (blockIdx.x / nrow) * kSkinnyCols;
+  const int nct = min(4, (TB - c0 + 15) / 16);
+  const float* w = a.Wx + (size_t)gate_row(a, ol0 + li) * D;
+  // contraction span of a wave: a multiple of 16, passes of 16 * kSkinnyUnits
+  const int span = ((D + 16 * kWaves - 1) / (16 * kWaves)) * 16;
+  const int k0 = wave * span, k1 = min(D, k0 + span);
+  f32x4 acc[4];
 #pragma unroll
-  for (int i = 0; i < kExactXprojRegs; ++i) wv[i] = w[min(lane + 64 * i, D - 1)];   // masked at use
-  for (int c0 = blockIdx.y * cols; c0 < TB; c0 += gridDim.y * cols) {
-    const int cn = min(cols, TB - c0);
-    __syncthreads();
-    const float* xsrc = a.x + (size_t)c0 * D;
-    const int n = cn * D;
-    if (a.xvec) {
-      typedef float f4 __attribute__((ext_vector_type(4)));
-      const int n4 = n >> 2;
-      for (int base = 0; base < n4; base += 8 * kThreads) {
-        f4 v[8];
+  for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = k0; kb < k1; kb += 16 * kSkinnyUnits) {
+    f32x4 wv[kSkinnyUnits];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = base + u * kThreads + (int)threadIdx.x;
-          v[u] = reinterpret_cast<const f4*>(xsrc)[i < n4 ? i : 0];
-        }
+    for (int u = 0; u < kSkinnyUnits; ++u) wv[u] = load4<WV>(w, kb + 16 * u + lk, k1);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = base + u * kThreads + (int)threadIdx.x;
-          if (i < n4) reinterpret_cast<f4*>(xs)[i] = v[u];
-        }
-      }
-    } else {
-      for (int i = threadIdx.x; i < n; i += kThreads) xs[i] = xsrc[i];
-    }
-    __syncthreads();
-    if (live) {
-      float acc[kExactCols];
+    for (int c = 0; c < 4; ++c) {
+      if (c >= nct) break;
+      const float* x = a.x + (size_t)min(c0 + 16 * c + li, TB - 1) * D;
 #pragma unroll
-      for (int c = 0; c < kExactCols; ++c) acc[c] = 0.0f;
+      for (int u0 = 0; u0 < kSkinnyUnits; u0 += 8) {
+        if (kb + 16 * u0 >= k1) break;
+        f32x4 xv[8];
 #pragma unroll
-      for (int i = 0; i < kExactXprojRegs; ++i) {
-        const int k = lane + 64 * i;
-        if (k < D) {
+        for (int u = 0; u < 8; ++u) xv[u] = load4<XV>(x, kb + 16 * (u0 + u) + lk, k1);
+        // chains of 32 products, added up pairwise
+        f32x4 p[4];
 #pragma unroll
-          for (int c = 0; c < kExactCols; ++c)
-            if (c < cn) acc[c] += wv[i] * xs[c * D + k];
-        }
-      }
-      for (int k = lane + 64 * kExactXprojRegs; k < D; k += 64) {
-        const float wk = w[k];
+        for (int i = 0; i < 4; ++i) p[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < kExactCols; ++c)
-          if (c < cn) acc[c] += wk * xs[c * D + k];
-      }
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-      for (int c = 0; c < kExactCols; ++c) {
-        if (c < cn) {
-          const float s = wave_sum(acc[c]);
-          if (lane == 0) a.px[(size_t)(c0 + c) * R + o] = s + a.bias[o];
-        }
+          for (int i = 0; i < 4; ++i) p[i] = mfma4(wv[u0 + u][i], xv[u][i], p[i]);
+        acc[c] += (p[0] + p[1]) + (p[2] + p[3]);
       }
     }
   }
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c < nct) {
+      const f32x4 s = acc[c];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) part[wave][c][li][(lane >> 4) * 4 + i] = s[i];
+    }
+  __syncthreads();
+  for (int e = tid; e < nct * 256; e += kThreads) {
+    const int c = e >> 8, col = (e >> 4) & 15, r = e & 15;
+    float s = 0.0f;
+#pragma unroll
+    for (int wv = 0; wv < kWaves; ++wv) s += part[wv][c][col][r];
+    const int ol = ol0 + r, tb = c0 + 16 * c + col;
+    if (ol < 4 * a.rows && tb < TB) {
+      const int o = gate_row(a, ol);
+      a.px[(size_t)tb * R + o] = s + a.bias[o];
+    }
+  }
+}
+
+// Many rows and columns: bound by the matrix cores' fp32 rate.  128 x 128 tile
+// per workgroup of 8 waves (64 x 32 each, 2 x 4 waves), contraction in
+// slices of 32 through double-buffered LDS; a slice is fetched into registers
+// while the one before is multiplied.  A slice is summed apart, eight slices
+// apart from the rest, so that no chain of additions is longer than 32
+// products, 8 slices or the number of such eights (the error against float64
+// is then that of one wave per row, whose lanes summed 32 products each).
+// MI355X, D = H = 2048, 512 columns: 3260 us (one wave per row) -> 185 us, 93
+// TFLOP/s; a large library product reaches 152.
+template <bool WV, bool XV>
+__global__ void __launch_bounds__(kThreads) exact_xproj_tile_kernel(ExactArgs a, int nrow) {
+  __shared__ __align__(16) float As[2][kTile * kTileLd];
+  __shared__ __align__(16) float Bs[2][kTile * kTileLd];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = 4 * (lane >> 4);
+  const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
+  const int TB = a.T * a.B, D = a.D, R = 4 * a.H;
+  // row tiles vary fastest: the workgroups in flight share few column tiles
+  const int ol0 = (blockIdx.x % nrow) * kTile, c0 = (blockIdx.x / nrow) * kTile;
+  const int sr = tid >> 3, sk = 4 * (tid & 7);
+  const float* wp[2];
+  const float* xp[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    wp[j] = a.Wx + (size_t)gate_row(a, ol0 + sr + 64 * j) * D;
+    xp[j] = a.x + (size_t)min(c0 + sr + 64 * j, TB - 1) * D;
+  }
+  f32x4 ra[2], rb[2];
+  auto fetch = [&](int k) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      ra[j] = load4<WV>(wp[j], k + sk, D);
+      rb[j] = load4<XV>(xp[j], k + sk, D);
+    }
+  };
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      *reinterpret_cast<f32x4*>(&As[buf][(sr + 64 * j) * kTileLd + sk]) = ra[j];
+      *reinterpret_cast<f32x4*>(&Bs[buf][(sr + 64 * j) * kTileLd + sk]) = rb[j];
+    }
+  };
+  f32x4 sum[4][2], pair[4][2], acc[4][2];
+  int slices = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) sum[i][j] = pair[i][j] = acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  fetch(0);
+  stash(0);
+  lds_barrier();
+  int buf = 0;
+  for (int k = 0; k < D; k += kTileK, buf ^= 1) {
+    if (k + kTileK < D) fetch(k + kTileK);
+#pragma unroll
+    for (int kk = 0; kk < kTileK; kk += 16) {
+      f32x4 av[4], bv[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        av[i] = *reinterpret_cast<const f32x4*>(&As[buf][(wm + 16 * i + li) * kTileLd + kk + lk]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        bv[j] = *reinterpret_cast<const f32x4*>(&Bs[buf][(wn + 16 * j + li) * kTileLd + kk + lk]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = mfma4(av[i][e], bv[j][e], acc[i][j]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        pair[i][j] += acc[i][j];
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    if ((++slices & 7) == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          sum[i][j] += pair[i][j];
+          pair[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    if (k + kTileK < D) {
+      stash(buf ^ 1);   // its readers passed the last barrier
+      lds_barrier();
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const f32x4 s = sum[i][j] + pair[i][j];
+      const int tb = c0 + wn + 16 * j + li;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ol = ol0 + wm + 16 * i + (lane >> 4) * 4 + e;
+        if (ol < 4 * a.rows && tb < TB) {
+          const int o = gate_row(a, ol);
+          a.px[(size_t)tb * R + o] = s[e] + a.bias[o];
+        }
+      }
+    }
 }
 
 // The recurrence.  Workgroup j owns hidden units [j*RP, j*RP + rc) and the
@@ -296,23 +442,35 @@ size_t plan_exact(ExactArgs& a, int P) {
   return base + (a.px_lds ? pxb : 0);
 }
 
+template <bool WV, bool XV>
+static void launch_xproj(const ExactArgs& a, hipStream_t stream) {
+  const int TB = a.T * a.B, R = 4 * a.rows;
+  // the tiles take the same time until there is more than one per compute
+  // unit, the 16-row workgroups time in proportion to the columns: equal at
+  // about half a device of tiles (MI355X, 2048 rows, tiles / 16-row groups in
+  // us: D = 2048, 512 columns 179 / 103, 1024 185 / 205, 2048 195 / 405; D =
+  // 512, 512 columns 55 / 56, 1024 57 / 108)
+  const long long nrow = (R + kTile - 1) / kTile, ncol = (TB + kTile - 1) / kTile;
+  if (2 * nrow * ncol >= a.num_cu)
+    exact_xproj_tile_kernel<WV, XV><<<dim3((unsigned)(nrow * ncol)), dim3(kThreads), 0, stream>>>(a, (int)nrow);
+  else
+    exact_xproj_skinny_kernel<WV, XV><<<dim3((unsigned)((long long)((R + 15) / 16) * ((TB + kSkinnyCols - 1) / kSkinnyCols))),
+                                        dim3(kThreads), 0, stream>>>(a, (R + 15) / 16);
+}
+
 hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
-  const int TB = a.T * a.B;
-  const int cols = std::max(1, std::min(kExactCols, (int)(kLdsCap / (4 * (size_t)a.D))));
   static bool attr = false;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)exact_xproj_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)kLdsCap);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)exact_lstm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
+    const hipError_t e =
+        hipFuncSetAttribute((const void*)exact_lstm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
     if (e != hipSuccess) return e;
     attr = true;
   }
   if (a.rows > 0) {
-    const size_t xl = 4 * (size_t)std::min(cols, TB) * a.D;
-    const int gx = (4 * a.rows + kWaves - 1) / kWaves;
-    const int gy = column_slices(gx, (TB + cols - 1) / cols);
-    exact_xproj_kernel<<<dim3(gx, gy), dim3(kThreads), xl, stream>>>(a, cols);
+    const bool wv = a.D % 4 == 0;
+    if (wv && a.xvec) launch_xproj<true, true>(a, stream);
+    else if (wv) launch_xproj<true, false>(a, stream);
+    else launch_xproj<false, false>(a, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
