@@ -437,8 +437,10 @@ approx_lstm_status approx_lstm_get_factors_f64(const approx_lstm_model* m, int32
  * approx_lstm_exact_check -- synchronise hip_stream and report an expired
  *   device wait (APPROX_LSTM_ERR_DEVICE); clears the flag.
  * approx_lstm_exact_set_launch -- workgroups of the recurrence kernel from
- *   the next run on (0 = automatic: one per 8 hidden units, at most the
- *   device's compute units); results do not depend on it.
+ *   the next run on (0 = automatic: W_h in registers where it fits, else one
+ *   workgroup per 8 hidden units, at most the device's compute units); results
+ *   do not depend on it.
+ * approx_lstm_exact_set_start_wait -- as approx_lstm_set_start_wait.
  */
 typedef struct approx_lstm_exact approx_lstm_exact;   /* opaque */
 
@@ -453,6 +455,7 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
                                               float* c_out, void* hip_stream);
 approx_lstm_status approx_lstm_exact_check(approx_lstm_exact* m, void* hip_stream);
 approx_lstm_status approx_lstm_exact_set_launch(approx_lstm_exact* m, int32_t blocks);
+approx_lstm_status approx_lstm_exact_set_start_wait(approx_lstm_exact* m, double wait_us);
 void approx_lstm_exact_destroy(approx_lstm_exact* m);
 
 /* approx_lstm_destroy -- free the model and its device memory (NULL is a no-op). */

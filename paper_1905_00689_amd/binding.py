@@ -81,6 +81,7 @@ _sigs = {
     "approx_lstm_exact_run_rows": [_vp, _vp, _i32, _i32, _vp, _vp, _i32, _vp, _vp, _vp],
     "approx_lstm_exact_check": [_vp, _vp],
     "approx_lstm_exact_set_launch": [_vp, _i32],
+    "approx_lstm_exact_set_start_wait": [_vp, ctypes.c_double],
 }
 for _name, _args in _sigs.items():
     getattr(lib, _name).argtypes = _args
@@ -379,3 +380,7 @@ def approx_lstm_exact_check(model, stream=None):
 
 def approx_lstm_exact_set_launch(model, blocks):
     return _check(lib.approx_lstm_exact_set_launch(model.handle, int(blocks)))
+
+
+def approx_lstm_exact_set_start_wait(model, wait_us):
+    return _check(lib.approx_lstm_exact_set_start_wait(model.handle, float(wait_us)))

@@ -23,6 +23,11 @@ namespace {
 
 thread_local std::string g_last_error;
 
+// The device-side error word's allocation: the word's block, then the start
+// words of the groups (zero between runs).
+constexpr size_t kErrBytes = 64;
+constexpr size_t kCtlBytes = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;
+
 approx_lstm_status fail(approx_lstm_status s, const char* fmt, ...) {
   char buf[512];
   va_list ap;
@@ -117,7 +122,7 @@ struct approx_lstm_model {
   unsigned* d_err = nullptr;
   float* d_pex = nullptr;                // pair kernel's exchange slots
   size_t pex_cap = 0;                    // floats
-  unsigned long long* d_ctl = nullptr;   // start words of the pair kernel's groups, zero between runs
+  unsigned long long* d_ctl = nullptr;   // start words of the pair kernel's groups (in d_err's allocation)
   unsigned start_wait_ticks = 200000;    // wall ticks (10 ns) a group waits for all its workgroups
   unsigned long long* d_stamps = nullptr;
   size_t stamps_cap = 0;             // words
@@ -153,7 +158,7 @@ struct approx_lstm_model {
 
   ~approx_lstm_model() {
     if (!has_dev && !d_px && !d_zx && !d_hx && !d_hbx && !d_hflag && !d_err && !d_stamps && !d_stack && !d_bz &&
-        !d_bh && !d_bc && !d_kt && !d_ctl && !d_pex && !d_pzx && !d_phx && !d_pflag && !d_ppart)
+        !d_bh && !d_bc && !d_kt && !d_pex && !d_pzx && !d_phx && !d_pflag && !d_ppart)
       return;
     DeviceScope ds(device);
     dfree(d_pzx);
@@ -178,7 +183,6 @@ struct approx_lstm_model {
     dfree(d_hbx);
     dfree(d_hflag);
     dfree(d_err);
-    dfree(d_ctl);
     dfree(d_pex);
     dfree(d_stamps);
     dfree(d_kt);
@@ -191,10 +195,6 @@ namespace {
 approx_lstm_status ensure_workspace(approx_lstm_model* m, size_t px_floats, size_t zx_words, size_t hx_words,
                                     hipStream_t stream) {
   bool fresh = false;
-  if (!m->d_err) {
-    HIP_TRY(hipMalloc(&m->d_err, 64), "hipMalloc(err)");
-    HIP_TRY(hipMemsetAsync(m->d_err, 0, 64, stream), "hipMemsetAsync(err)");
-  }
   if (px_floats > m->px_cap) {
     HIP_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
     dfree(m->d_px);
@@ -307,10 +307,6 @@ constexpr int kZtagTerms = 0;
 // 0xFFFF.
 approx_lstm_status ensure_persistent(approx_lstm_model* m, size_t zx, size_t hx, size_t flags, int n_levels,
                                      hipStream_t stream) {
-  if (!m->d_err) {
-    HIP_TRY(hipMalloc(&m->d_err, 64), "hipMalloc(err)");
-    HIP_TRY(hipMemsetAsync(m->d_err, 0, 64, stream), "hipMemsetAsync(err)");
-  }
   approx_lstm_status st = APPROX_LSTM_OK;
   if (round_up(zx, 4) > m->pzx_cap) {
     st = grow(m->d_pzx, m->pzx_cap, round_up(zx, 4), stream, "hipMalloc(zx)");
@@ -706,7 +702,6 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
 // address is used (kernel arguments, fills).  Every call on a device shares
 // its array, which keeps the last call's contents.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-constexpr size_t kCtlBytes = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;   // behind the workspace
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kCtlBytes];
 
 namespace {
@@ -916,13 +911,10 @@ approx_lstm_status approx_lstm_prepare(const float* w_ih, const float* w_hh, con
     }
     // the device-side error word, cleared once here: runs (including those
     // that may not allocate) only set it, approx_lstm_check reads and clears it
-    if (st == APPROX_LSTM_OK) step(hipMalloc(&m->d_err, 64), "hipMalloc(err)");
-    if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_err, 0, 64, stream), "clear(err)");
-    if (!bf && st == APPROX_LSTM_OK) {
-      const size_t ctl = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;
-      step(hipMalloc(&m->d_ctl, ctl), "hipMalloc(ctl)");
-      if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_ctl, 0, ctl, stream), "clear(ctl)");
-    }
+    // and behind it the start words of the pair kernel's groups
+    if (st == APPROX_LSTM_OK) step(hipMalloc(&m->d_err, kErrBytes + kCtlBytes), "hipMalloc(err)");
+    if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_err, 0, kErrBytes + kCtlBytes, stream), "clear(err)");
+    m->d_ctl = reinterpret_cast<unsigned long long*>(m->d_err + kErrBytes / sizeof(unsigned));
     if (st == APPROX_LSTM_OK) step(hipStreamSynchronize(stream), "hipStreamSynchronize");
     if (st != APPROX_LSTM_OK) {
       delete m;
@@ -1509,6 +1501,10 @@ struct approx_lstm_exact {
   unsigned long long* d_hx = nullptr;
   size_t hx_cap = 0;
   unsigned* d_err = nullptr;
+  float* d_ex = nullptr;               // h slots of the register kernels
+  size_t ex_cap = 0;
+  unsigned long long* d_ctl = nullptr; // start words of their groups (in d_err's allocation)
+  unsigned start_wait_ticks = 200000;  // as approx_lstm_model's
   unsigned seq = 0;
   int launch_blocks = 0;
 
@@ -1521,6 +1517,7 @@ struct approx_lstm_exact {
     dfree(d_px);
     dfree(d_hx);
     dfree(d_err);
+    dfree(d_ex);
   }
 };
 
@@ -1557,8 +1554,9 @@ approx_lstm_status approx_lstm_exact_prepare(const float* w_ih, const float* w_h
   up(m->d_Wx, w_ih, R * m->D, "W_ih");
   up(m->d_Wh, w_hh, R * m->H, "W_hh");
   up(m->d_bias, b.data(), R, "bias");
-  step(hipMalloc(&m->d_err, 64), "hipMalloc(err)");
-  if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_err, 0, 64, stream), "clear(err)");
+  step(hipMalloc(&m->d_err, kErrBytes + kCtlBytes), "hipMalloc(err)");
+  if (st == APPROX_LSTM_OK) step(hipMemsetAsync(m->d_err, 0, kErrBytes + kCtlBytes, stream), "clear(err)");
+  m->d_ctl = reinterpret_cast<unsigned long long*>(m->d_err + kErrBytes / sizeof(unsigned));
   if (st == APPROX_LSTM_OK) step(hipStreamSynchronize(stream), "hipStreamSynchronize");
   if (st != APPROX_LSTM_OK) {
     delete m;
@@ -1586,9 +1584,12 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
   a.Wx = m->d_Wx; a.Wh = m->d_Wh; a.bias = m->d_bias;
   a.D = m->D; a.H = m->H; a.T = T; a.B = B; a.rows = rows; a.num_cu = m->num_cu;
   a.xvec = (m->D % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
+  // the register kernels on their own widths; a width given by the caller
+  // runs exact_lstm_kernel
+  const size_t ex_floats = m->launch_blocks == 0 ? alstm::plan_exact_group(a) : 0;
   const int maxP = std::max(1, m->num_cu);
   int P = m->launch_blocks > 0 ? std::min(m->launch_blocks, maxP) : std::min(maxP, std::max(1, (m->H + 7) / 8));
-  size_t lds = alstm::plan_exact(a, P);
+  size_t lds = ex_floats ? 0 : alstm::plan_exact(a, P);
   if (m->launch_blocks == 0)
     while (lds > alstm::kLdsCap && P < maxP) {
       P = std::min(maxP, 2 * P);
@@ -1610,6 +1611,12 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
     m->seq = 1;
   }
   a.tag_base = m->seq << 16;
+  if (ex_floats) {
+    st = grow(m->d_ex, m->ex_cap, ex_floats, stream, "hipMalloc(h slots)");
+    if (st != APPROX_LSTM_OK) return st;
+    a.ex = m->d_ex; a.ctl = m->d_ctl; a.wait_ticks = m->start_wait_ticks;
+    a.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)B, std::memory_order_relaxed) % alstm::kXcds);
+  }
   a.px = m->d_px; a.hx = m->d_hx; a.err = m->d_err;
   HIP_TRY(alstm::launch_exact(a, P, stream), "launch exact_lstm_kernel");
   return APPROX_LSTM_OK;
@@ -1643,6 +1650,14 @@ approx_lstm_status approx_lstm_exact_set_launch(approx_lstm_exact* m, int32_t bl
   g_last_error.clear();
   if (!m || blocks < 0) return fail(APPROX_LSTM_ERR_INVALID_ARG, "bad arguments");
   m->launch_blocks = blocks;
+  return APPROX_LSTM_OK;
+}
+
+approx_lstm_status approx_lstm_exact_set_start_wait(approx_lstm_exact* m, double wait_us) {
+  g_last_error.clear();
+  if (!m) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null model");
+  if (!(wait_us >= 0.0 && wait_us <= 1e7)) return fail(APPROX_LSTM_ERR_INVALID_ARG, "wait must be in [0, 1e7] us");
+  m->start_wait_ticks = (unsigned)(wait_us * 100.0);   // the device's 100 MHz wall clock
   return APPROX_LSTM_OK;
 }
 

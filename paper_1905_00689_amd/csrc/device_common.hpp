@@ -186,6 +186,133 @@ __device__ __forceinline__ void read_coherent(float* dst, const float* src, int 
   }
 }
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Slot exchange between the workgroups of a group.  A slot holds this pattern
+// (a NaN that publish_slot never stores) until its value is there, so that
+// every 4-byte value tells by itself whether it has arrived and a poll takes
+// four of them with one load.  A slot exists once for each timestep that may
+// be under way; its owner empties it when everyone is past reading it, before
+// anyone can poll it again.
+constexpr unsigned kEmpty = 0xFFFFFFFFu;
+
+// Stores of the exchange: plain (the L2 of the group's XCD) when the whole
+// group sits on one XCD, agent scope otherwise.
+__device__ __forceinline__ void store_slot(float* p, unsigned bits, bool near) {
+  unsigned* q = reinterpret_cast<unsigned*>(p);
+  if (near) __hip_atomic_store(q, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(q, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish_slot(float* p, float v, bool near) {
+  const unsigned bits = __float_as_uint(v);
+  store_slot(p, bits == kEmpty ? 0x7FC00000u : bits, near);
+}
+
+// Poll the 16-byte units tid + 512 r of src (uniform; `bytes` long) whose bit
+// r is set in `pending` until none of their slots is empty; unit r goes to
+// dst + map[r] (LDS, 16-byte aligned).  Agent-scope loads pass the L1 by.
+// Bounded: past the spin limit, or once another wait has failed, the failure
+// is recorded and the missing values read 0.
+template <int kMaxUnits>
+__device__ __forceinline__ void poll_units(float* dst, const float* src, int bytes, const int* map, unsigned pending,
+                                           unsigned* err) {
+  const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(addr >> 32));
+  void* base = reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo);
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(base, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  const int tid = threadIdx.x;
+  unsigned spins = 0;
+  while (pending) {
+    u32x4 w[kMaxUnits];
+#pragma unroll
+    for (int r = 0; r < kMaxUnits; ++r)
+      if ((pending >> r) & 1u) w[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + kThreads * r) * 16, 0, 16 /* sc1 */);
+    asm volatile("" ::: "memory");   // the loads of the next round are new ones
+#pragma unroll
+    for (int r = 0; r < kMaxUnits; ++r)
+      if (((pending >> r) & 1u) && w[r][0] != kEmpty && w[r][1] != kEmpty && w[r][2] != kEmpty && w[r][3] != kEmpty) {
+        *reinterpret_cast<u32x4*>(dst + map[r]) = w[r];
+        pending &= ~(1u << r);
+      }
+    if ((++spins & 255u) == 0u && pending &&
+        (spins >= kSpinLimit || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
+      __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int r = 0; r < kMaxUnits; ++r)
+        if ((pending >> r) & 1u) *reinterpret_cast<u32x4*>(dst + map[r]) = u32x4{0u, 0u, 0u, 0u};
+      break;
+    }
+  }
+}
+
+// this wave's loads and stores have completed
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// How a group starts: all present (on one XCD, or not), one workgroup alone,
+// or nothing left to do here.
+enum StartMode { kNear = 0, kFar = 1, kAlone = 2, kLeave = 3 };
+
+// The start of a group, run by one wave of each of its P workgroups:
+// workgroup j's word gets (tag, XCD id), the lanes wait for everyone's words.
+// decide[0]: 0 open, 1 everyone goes, 2 one workgroup alone; decide[1] counts
+// the workgroups that left, the last of which reopens the group's words.
+__device__ int group_start(unsigned long long* hand, unsigned* decide, int j, int P, unsigned tag,
+                           unsigned wait_ticks) {
+  const int lane = threadIdx.x & 63;
+  unsigned xcc;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+  xcc &= 15u;
+  if (lane == 0)
+    __hip_atomic_store(hand + j, ((unsigned long long)tag << 32) | xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long t0 = wall_clock64();
+  bool same = true, late = false;
+  int next = lane;   // words lane, lane + 64, ... of the group, in turn
+  while (true) {
+    if (next < P) {
+      const unsigned long long w = load_tagged(hand + next);
+      if ((unsigned)(w >> 32) == tag) {
+        same = same && (unsigned)w == xcc;
+        next += 64;
+      }
+    }
+    if (__all(next >= P)) break;
+    if (!late && (wall_clock64() - t0 >= (unsigned long long)wait_ticks ||
+                  __hip_atomic_load(decide, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u)) {
+      // one outcome for the whole group: whoever swaps first decides
+      late = true;
+      unsigned seen = 0u;
+      if (lane == 0)
+        __hip_atomic_compare_exchange_strong(decide, &seen, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+      seen = __builtin_amdgcn_readfirstlane(seen);
+      if (seen != 1u) return seen == 0u ? kAlone : kLeave;
+      // someone saw everyone: all are resident, their words are coming
+    }
+  }
+  if (!late) {
+    unsigned seen = 0u;
+    if (lane == 0)
+      __hip_atomic_compare_exchange_strong(decide, &seen, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(seen) == 2u) return kLeave;
+  }
+  return __all(same) ? kNear : kFar;
+}
+
+// A workgroup of a group that does not go: the last of its P to come through
+// here (the one that ran alone among them) reopens the group's words.
+__device__ void group_leave(unsigned long long* hand, unsigned* decide, int P) {
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(decide + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(P - 1)) {
+    for (int i = 0; i < P; ++i)
+      __hip_atomic_store(hand + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(decide + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 // Workgroup barrier that orders LDS only.  __syncthreads() would also wait
 // for every outstanding global store of the wave (gfx9 counts stores in
 // vmcnt), i.e. for the agent-scope exchange stores to reach memory.

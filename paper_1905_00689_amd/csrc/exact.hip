@@ -27,6 +27,9 @@ namespace {
 constexpr int kExactLanes = 16;   // lanes per W_h row
 constexpr int kExactRows = kThreads / kExactLanes;   // rows per pass (32)
 constexpr int kExactWpl = 32;     // W_h entries per lane held in registers (H <= 512)
+constexpr int kNearH = 768;       // hidden units up to which a sequence's W_h fits the registers of one XCD
+constexpr int kWideH = 2048;      // and up to which it fits those of the device
+constexpr int kWideSeq = 8;       // sequences of a run whose W_h is spread over the device
 constexpr int kSkinnyCols = 64;   // x columns per workgroup of the narrow x projection
 constexpr int kSkinnyUnits = 16;  // 16-byte units of a W_x row per lane held in registers there
 constexpr int kTile = 128;        // gate rows and x columns per workgroup of the tiled x projection
@@ -254,9 +257,400 @@ __global__ void __launch_bounds__(kThreads) exact_xproj_tile_kernel(ExactArgs a,
     }
 }
 
-// The recurrence.  Workgroup j owns hidden units [j*RP, j*RP + rc) and the
-// gate rows q*H + r of each (q = i, f, g, o); 16 lanes per row, rows in
-// passes of 32.  Per timestep and sequence: y = px + W_h . h_{t-1} (lane
+// The recurrence with W_h in registers.  A sum over h_{t-1} is taken by 16
+// lanes (H <= kNearH) or 64 (beyond), lane sl the entries k = sl + L*i with i
+// ascending, then the lanes pairwise; then the x part and bias.  The same
+// order in every kernel here, so the results do not depend on which one runs.
+//
+// Slot w of the h exchange is entry i = w % kpl of lane sl = w / kpl (kpl =
+// ceil(H / L) rounded up to 4), the unit k = sl + L*i; a workgroup owns RU
+// consecutive slots and the four W_h rows of each one's unit.  A slot exists
+// three times, for timesteps t mod 3: at timestep t its owner empties the one
+// of timesteps t-2 and t+1 (everyone's h_{t-1} is here, so everyone has read
+// h_{t-2}) and stores h_t only when that is done.
+
+namespace {
+
+// unit of slot w for L lanes (H or more: none)
+__device__ __forceinline__ int slot_unit(int w, int kpl, int L) { return w / kpl + L * (w % kpl); }
+
+// One sequence by one workgroup, W_h read from memory; hs [2][H], cs [H], ys
+// [32] in LDS.
+template <int L>
+__device__ void exact_alone(const ExactArgs& a, int b, float* hs, float* cs, float* ys) {
+  const int tid = threadIdx.x, H = a.H, sl = tid % L, rs = tid / L;
+  constexpr int units = kThreads / L / 4;   // per pass; rows gate-minor
+  for (int i = tid; i < H; i += kThreads) {
+    hs[i] = a.h0 ? a.h0[(size_t)b * H + i] : 0.0f;
+    cs[i] = a.c0 ? a.c0[(size_t)b * H + i] : 0.0f;
+  }
+  __syncthreads();
+  for (int t = 0; t < a.T; ++t) {
+    const float* h = hs + (t & 1) * H;
+    float* hn = hs + ((t + 1) & 1) * H;
+    const size_t tb = (size_t)t * a.B + b;
+    for (int u0 = 0; u0 < H; u0 += units) {
+      const int u = u0 + (rs >> 2), o = (rs & 3) * H + u;
+      float acc = 0.0f;
+      if (u < H && u < a.rows) {
+        const float* w = a.Wh + (size_t)o * H;
+        for (int k = sl; k < H; k += L) acc += w[k] * h[k];
+      }
+      if constexpr (L == 16) acc = group_sum<16>(acc);
+      else acc = wave_sum(acc);
+      if (sl == 0 && u < H) ys[rs] = acc + (u < a.rows ? a.px[tb * 4 * H + o] : a.bias[o]);
+      __syncthreads();
+      if (tid < units && u0 + tid < H) {
+        float c = cs[u0 + tid], hv;
+        cell_update(ys[4 * tid], ys[4 * tid + 1], ys[4 * tid + 2], ys[4 * tid + 3], c, hv);
+        cs[u0 + tid] = c;
+        hn[u0 + tid] = hv;
+        a.h_out[tb * H + u0 + tid] = hv;
+      }
+      __syncthreads();
+    }
+  }
+  if (a.c_out)
+    for (int i = tid; i < H; i += kThreads) a.c_out[(size_t)b * H + i] = cs[i];
+  __syncthreads();
+}
+
+// LDS floats of the near kernel: mode [4], x part [T][4*RU], h [2][16][WPL + 4],
+// c [H] (alone) and the rows' sums per wave
+__host__ __device__ inline size_t near_lds(const ExactArgs& a, int wpl) {
+  return 4 + (((size_t)a.T * 4 * a.RU + 3) & ~(size_t)3) + 2 * 16 * (wpl + 4) + ((a.H + 3) & ~3) + kWaves * 16;
+}
+
+__device__ __forceinline__ float dpp_swap1(float v) {   // lane ^ 1
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float dpp_swap2(float v) {   // lane ^ 2
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float dpp_swap4(float v) {   // lane ^ 4: mirrored half rows, quads reversed back
+  const int m = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float dpp_swap8(float v) {   // lane ^ 8: rows rotated by 8
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, false));
+}
+
+// v[b] summed over the wave for NB = 1, 2, 4 or 8 values at once; lane l gets
+// the sum of v[l % NB].  The pairs are those of wave_sum (lanes 1, 2, 4, 8, 16
+// and 32 apart, in that order); while there is more than one value a lane
+// hands half of them to its partner and goes on with the other half.
+template <int NB>
+__device__ __forceinline__ float wave_sums(const float* v, int lane) {
+  float r[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) r[i] = v[i];
+  if constexpr (NB >= 2) {
+#pragma unroll
+    for (int i = 0; i < NB / 2; ++i) {
+      const float keep = (lane & 1) ? r[2 * i + 1] : r[2 * i], give = (lane & 1) ? r[2 * i] : r[2 * i + 1];
+      r[i] = keep + dpp_swap1(give);
+    }
+  } else {
+    r[0] += dpp_swap1(r[0]);
+  }
+  if constexpr (NB >= 4) {
+#pragma unroll
+    for (int i = 0; i < NB / 4; ++i) {
+      const float keep = (lane & 2) ? r[2 * i + 1] : r[2 * i], give = (lane & 2) ? r[2 * i] : r[2 * i + 1];
+      r[i] = keep + dpp_swap2(give);
+    }
+  } else {
+    r[0] += dpp_swap2(r[0]);
+  }
+  if constexpr (NB >= 8) {
+    const float keep = (lane & 4) ? r[1] : r[0], give = (lane & 4) ? r[0] : r[1];
+    r[0] = keep + dpp_swap4(give);
+  } else {
+    r[0] += dpp_swap4(r[0]);
+  }
+  r[0] += dpp_swap8(r[0]);
+  r[0] += __shfl_xor(r[0], 16, 64);
+  r[0] += __shfl_xor(r[0], 32, 64);
+  return r[0];
+}
+
+}  // namespace
+
+// Near groups: one sequence per XCD (more take turns), 32 workgroups (fewer
+// for narrow layers) holding its W_h in registers: OPT rows per thread, 16
+// lanes per row, WPL entries per lane.  One exchange per timestep, through the
+// XCD's L2 (see pair_lstm_kernel on what that saves, and group_start on a
+// group that is not all resident).  MI355X, D = 2048, H = 512, T = 16, one
+// sequence: the recurrence 43 us on exact_lstm_kernel, 27.4 here.
+template <int OPT, int WPL>
+__global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  constexpr int LD = WPL + 4;   // 16-byte reads of the lanes in distinct banks
+  const int g = (int)((blockIdx.x + kXcds - a.first_xcd) % kXcds), j = blockIdx.x / kXcds;
+  if (g >= a.B) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int H = a.H, B = a.B, T = a.T, R4 = 4 * a.H, RU = a.RU, kpl = a.kpl;
+  const bool local = a.P == 1;
+  int* modes = reinterpret_cast<int*>(lds);
+  float* pxs = lds + 4;
+  float* hs = pxs + ((T * 4 * RU + 3) & ~3);
+  float* cs = hs + 2 * 16 * LD;
+  float* ys = cs + ((H + 3) & ~3);
+  const size_t exf = 3 * (size_t)a.slots;
+  unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
+  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  if (wv == kWaves - 1) {
+    int mode = kFar;
+    if (!local) {
+      for (int b = g; b < B; b += kXcds)
+        for (int i = lane; i < 3 * RU; i += 64) {
+          const int w = j * RU + i % RU;
+          if (w < a.slots) store_slot(a.ex + b * exf + (size_t)(i / RU) * a.slots + w, kEmpty, false);
+        }
+      wait_memory();
+      mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks);
+    }
+    if (lane == 0) modes[0] = mode;
+  }
+  // rows ol = rs + 32 o: gate ol & 3 of owned slot ol >> 2
+  const int sl = tid & 15, rs = tid >> 4;
+  float wr[OPT][WPL];
+#pragma unroll
+  for (int o = 0; o < OPT; ++o) {
+    const int ol = rs + 32 * o, ul = ol >> 2, w = j * RU + ul, k = slot_unit(w, kpl, 16);
+    const bool live = ul < RU && w < a.slots && k < a.rows;
+    const float* wrow = a.Wh + (live ? (size_t)((ol & 3) * H + k) * H : 0);
+#pragma unroll
+    for (int i = 0; i < WPL; ++i) wr[o][i] = wrow[min(sl + 16 * i, H - 1)];
+#pragma unroll
+    for (int i = 0; i < WPL; ++i) wr[o][i] = live && sl + 16 * i < H ? wr[o][i] : 0.0f;
+  }
+  // cell role: lane o < OPT updates owned slot wv + 8 o, whose rows this wave sums
+  const int cul = wv + 8 * lane, cw = j * RU + cul, cunit = slot_unit(cw, kpl, 16);
+  const bool cell = lane < OPT && cul < RU && cw < a.slots;
+  const bool cell_ok = cell && cunit < H;
+  // 16-byte unit of the exchange polled by this thread (slots <= 1024)
+  const bool upoll = 4 * tid < a.slots;
+  int udst[1];
+
+  bool near = false, seen_mode = false;
+  for (int b = g; b < B; b += kXcds) {
+    if (b != g) __syncthreads();
+    float c = (cell_ok && a.c0) ? a.c0[(size_t)b * H + cunit] : 0.0f;
+    for (int i = tid; i < 2 * 16 * LD; i += kThreads) {
+      const int l = (i / LD) & 15, e = i % LD, k = l + 16 * e;
+      hs[i] = (i < 16 * LD && e < WPL && k < H && a.h0) ? a.h0[(size_t)b * H + k] : 0.0f;
+    }
+    for (int i = tid; i < T * 4 * RU; i += kThreads) {
+      const int t = i / (4 * RU), ol = i - t * 4 * RU, w = j * RU + (ol >> 2), k = slot_unit(w, kpl, 16);
+      const int o = (ol & 3) * H + k;
+      float v = 0.0f;
+      if (w < a.slots && k < H) v = k < a.rows ? a.px[((size_t)t * B + b) * R4 + o] : a.bias[o];
+      pxs[i] = v;
+    }
+    __syncthreads();
+    if (!seen_mode) {
+      const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+      if (mode >= kAlone) break;
+      near = mode == kNear;
+      seen_mode = true;
+    }
+    float* ex = a.ex + b * exf;
+    for (int t = 0; t < T; ++t) {
+      const float* hc = hs + (t & 1) * 16 * LD + sl * LD;
+      float* hn = hs + ((t + 1) & 1) * 16 * LD;
+      if (cell && !local) store_slot(ex + (size_t)((t + 1) % 3) * a.slots + cw, kEmpty, near);
+      float acc[OPT];
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) acc[o] = 0.0f;
+#pragma unroll
+      for (int i0 = 0; i0 < WPL; i0 += 8) {
+        const float4 h0 = *reinterpret_cast<const float4*>(hc + i0), h1 = *reinterpret_cast<const float4*>(hc + i0 + 4);
+#pragma unroll
+        for (int o = 0; o < OPT; ++o) {
+          acc[o] += wr[o][i0] * h0.x;
+          acc[o] += wr[o][i0 + 1] * h0.y;
+          acc[o] += wr[o][i0 + 2] * h0.z;
+          acc[o] += wr[o][i0 + 3] * h0.w;
+          acc[o] += wr[o][i0 + 4] * h1.x;
+          acc[o] += wr[o][i0 + 5] * h1.y;
+          acc[o] += wr[o][i0 + 6] * h1.z;
+          acc[o] += wr[o][i0 + 7] * h1.w;
+        }
+      }
+#pragma unroll
+      for (int o = 0; o < OPT; ++o) {
+        const float s = group_sum<16>(acc[o]);
+        if (sl == 0 && rs + 32 * o < 4 * RU) ys[wv * 16 + o * 4 + (lane >> 4)] = s + pxs[t * 4 * RU + rs + 32 * o];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (cell) {
+        const float4 y = *reinterpret_cast<const float4*>(ys + wv * 16 + lane * 4);
+        float hv;
+        cell_update(y.x, y.y, y.z, y.w, c, hv);
+        if (local) {
+          hn[(cw / kpl) * LD + cw % kpl] = hv;
+        } else {
+          wait_memory();   // the emptied slot
+          publish_slot(ex + (size_t)(t % 3) * a.slots + cw, cell_ok ? hv : 0.0f, near);
+        }
+        if (cell_ok) a.h_out[((size_t)t * B + b) * H + cunit] = hv;
+      }
+      // nobody reads the last timestep's h (one step: the exchange still
+      // tells that everyone has started)
+      if (!local && (t + 1 < T || T == 1)) {
+        udst[0] = upoll ? (4 * tid / kpl) * LD + (4 * tid) % kpl : 0;
+        poll_units<1>(hn, ex + (size_t)(t % 3) * a.slots, a.slots * 4, udst, upoll ? 1u : 0u, a.err);
+      }
+      lds_barrier();
+    }
+    if (a.c_out && cell_ok) a.c_out[(size_t)b * H + cunit] = c;
+  }
+  if (local) return;
+  __syncthreads();
+  const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+  if (mode == kAlone) {
+    for (int b = g; b < B; b += kXcds) exact_alone<16>(a, b, hs, cs, ys);
+  }
+  if (mode >= kAlone) {
+    group_leave(hand, decide, a.P);
+  } else if (tid == 0) {
+    // an exchange is over, so every workgroup of the group has read the
+    // decision and everyone's words: open for the next start
+    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Wide layers: W_h in the registers of the whole device (64 MB at H = 2048),
+// every workgroup eight slots, a wave the four rows of one unit: 64 lanes per
+// row, WPL entries per lane, each applied to all NB sequences (the run's,
+// padded to a power of two).  h of all sequences in LDS, 16-byte reads shared
+// by four rows.  What bounds a timestep at eight sequences is the fp32 rate
+// (1024 multiply-adds per lane, 3.4 us) and then the exchange of h between
+// XCDs (64 KB to every workgroup).  MI355X, D = H = 2048, eight sequences:
+// 28.7 us per timestep with W_h read from memory, 8.1 here.
+template <int WPL, int NB>
+__global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  constexpr int LD = WPL + 4, kUnits = (NB * WPL + 31) / 32;   // polled per thread
+  const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int H = a.H, B = a.B, T = a.T, R4 = 4 * a.H, kpl = a.kpl, slots = a.slots;
+  int* modes = reinterpret_cast<int*>(lds);
+  float* hown = lds + 4;                 // [NB][8] h of the owned slots
+  float* hs = hown + NB * 8;             // [NB][64][LD]
+  unsigned long long* hand = a.ctl;
+  unsigned* decide = reinterpret_cast<unsigned*>(a.ctl + kSpreadWords);
+  const size_t third = (size_t)NB * slots;
+  if (wv == kWaves - 1) {
+    for (int i = lane; i < 3 * NB * 8; i += 64)
+      store_slot(a.ex + (i / 8) * (size_t)slots + j * 8 + (i & 7), kEmpty, false);
+    wait_memory();
+    const int mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks);
+    if (lane == 0) modes[0] = mode;
+  }
+  const int w = j * 8 + wv, unit = slot_unit(w, kpl, 64);
+  const bool live = unit < H, computed = unit < a.rows;
+  float wr[4][WPL];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float* wrow = a.Wh + (computed ? (size_t)(q * H + unit) * H : 0);
+#pragma unroll
+    for (int i = 0; i < WPL; ++i) wr[q][i] = wrow[min(lane + 64 * i, H - 1)];
+#pragma unroll
+    for (int i = 0; i < WPL; ++i) wr[q][i] = computed && lane + 64 * i < H ? wr[q][i] : 0.0f;
+  }
+  // cell role: lane b < NB updates this wave's unit for sequence b
+  const bool cell_ok = lane < B && live;
+  float c = (cell_ok && a.c0) ? a.c0[(size_t)lane * H + unit] : 0.0f;
+  float pxv[4];
+  auto fetch_px = [&](int t) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      pxv[q] = cell_ok ? (computed ? a.px[((size_t)t * B + lane) * R4 + q * H + unit] : a.bias[q * H + unit]) : 0.0f;
+  };
+  fetch_px(0);
+  for (int i = tid; i < NB * 64 * LD; i += kThreads) {
+    const int b = i / (64 * LD), l = (i / LD) & 63, e = i % LD, k = l + 64 * e;
+    hs[i] = (b < B && e < WPL && k < H && a.h0) ? a.h0[(size_t)b * H + k] : 0.0f;
+  }
+  int udst[kUnits];
+  unsigned upend = 0;
+#pragma unroll
+  for (int r = 0; r < kUnits; ++r) {
+    const int s4 = 4 * (tid + kThreads * r), b = s4 / slots, s = s4 - b * slots;
+    if (b < NB) upend |= 1u << r;
+    udst[r] = b < NB ? (b * 64 + s / kpl) * LD + s % kpl : 0;
+  }
+  __syncthreads();
+  const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+  if (mode >= kAlone) {
+    __syncthreads();
+    if (mode == kAlone)
+      for (int b = 0; b < B; ++b) exact_alone<64>(a, b, lds + 4, lds + 4 + 2 * H, lds + 4 + 3 * H);
+    group_leave(hand, decide, a.P);
+    return;
+  }
+  for (int t = 0; t < T; ++t) {
+    float* out = a.ex + (t % 3) * third;
+    // first wave: the owned slots of timestep t+1 emptied (16 bytes a lane)
+    const int eb = lane >> 1, es = j * 8 + 4 * (lane & 1);
+    if (wv == 0 && lane < 2 * NB) {
+      float* e = a.ex + ((t + 1) % 3) * third + (size_t)eb * slots + es;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) store_slot(e + i, kEmpty, false);
+    }
+    float acc[4][NB];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[q][b] = 0.0f;
+    const float* hl = hs + lane * LD;
+#pragma unroll
+    for (int i = 0; i < WPL; i += 4) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const float4 h = *reinterpret_cast<const float4*>(hl + b * 64 * LD + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[q][b] += wr[q][i] * h.x;
+          acc[q][b] += wr[q][i + 1] * h.y;
+          acc[q][b] += wr[q][i + 2] * h.z;
+          acc[q][b] += wr[q][i + 3] * h.w;
+        }
+      }
+    }
+    float y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = wave_sums<NB>(acc[q], lane) + pxv[q];
+    float hv;
+    cell_update(y[0], y[1], y[2], y[3], c, hv);
+    if (lane < NB) hown[lane * 8 + wv] = cell_ok ? hv : 0.0f;
+    if (wv == 0) wait_memory();   // the emptied slots
+    lds_barrier();                // every read of hs is done, hown complete
+    if (wv == 0 && lane < 2 * NB) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        publish_slot(out + (size_t)eb * slots + es + i, hown[eb * 8 + 4 * (lane & 1) + i], false);
+    }
+    if (cell_ok) a.h_out[((size_t)t * B + lane) * H + unit] = hv;
+    if (t + 1 < T) fetch_px(t + 1);
+    if (t + 1 < T || T == 1) poll_units<kUnits>(hs, out, (int)(third * 4), udst, upend, a.err);
+    lds_barrier();
+  }
+  if (a.c_out && cell_ok) a.c_out[(size_t)lane * H + unit] = c;
+  if (tid == 0) {
+    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The recurrence on any width, for the shapes and launches the kernels above do
+// not take.  Workgroup j owns hidden units [j*RP, j*RP + rc) and the
+// gate rows q*H + r of each (q = i, f, g, o); 16 lanes per row (64 past
+// kNearH), rows in passes of 32 (8).  Per timestep and sequence: y = px + W_h . h_{t-1} (lane
 // partial sums, fixed-order reduction), the cell update, h published as
 // tagged words, then the full h_t gathered by every workgroup.
 __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
@@ -351,10 +745,12 @@ __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
       // applied to every sequence of the group (NB a compile-time group size,
       // so the inner loop carries no predicates); every (row, sequence) sum
       // keeps the per-sequence order
-      auto group = [&](auto nbc, int b0) {
-        constexpr int NB = decltype(nbc)::value;
+      auto group = [&](auto nbc, auto lanes, int b0) {
+        constexpr int NB = decltype(nbc)::value, L = decltype(lanes)::value;
+        constexpr int rows = kThreads / L;
+        const int sl = threadIdx.x % L, ob = threadIdx.x / L, passes = (outs + rows - 1) / rows;
         for (int ps = 0; ps < passes; ++ps) {
-          const int ol = ob + ps * kExactRows;
+          const int ol = ob + ps * rows;
           float acc[NB];
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[j] = 0.0f;
@@ -363,19 +759,19 @@ __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
             const float* wrow = a.Wh + (size_t)(q * H + r0 + rr) * H;
             if (rr < rlive && NB == 1) {
 #pragma unroll 4
-              for (int k = sl; k < H; k += kExactLanes) acc[0] += wrow[k] * hs[(size_t)b0 * H + k];
+              for (int k = sl; k < H; k += L) acc[0] += wrow[k] * hs[(size_t)b0 * H + k];
             } else if (rr < rlive) {
               // 8 entries of the row in flight, then each applied to the group
-              for (int k0 = sl; k0 < H; k0 += 8 * kExactLanes) {
+              for (int k0 = sl; k0 < H; k0 += 8 * L) {
                 float wk[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                  const int k = k0 + i * kExactLanes;
+                  const int k = k0 + i * L;
                   wk[i] = wrow[k < H ? k : sl];
                 }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                  const int k = k0 + i * kExactLanes;
+                  const int k = k0 + i * L;
                   if (k < H) {
 #pragma unroll
                     for (int j = 0; j < NB; ++j) acc[j] += wk[i] * hs[(size_t)(b0 + j) * H + k];
@@ -386,23 +782,29 @@ __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
           }
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
-            const float sum = group_sum<kExactLanes>(acc[j]);
+            float sum;
+            if constexpr (L == 16) sum = group_sum<16>(acc[j]);
+            else sum = wave_sum(acc[j]);
             if (sl == 0 && ol < outs) store_y(t, b0 + j, ol, sum);
           }
         }
       };
-      for (int b0 = 0; b0 < B; b0 += kExactSeq) {
-        switch (min(kExactSeq, B - b0)) {
-          case 1: group(std::integral_constant<int, 1>{}, b0); break;
-          case 2: group(std::integral_constant<int, 2>{}, b0); break;
-          case 3: group(std::integral_constant<int, 3>{}, b0); break;
-          case 4: group(std::integral_constant<int, 4>{}, b0); break;
-          case 5: group(std::integral_constant<int, 5>{}, b0); break;
-          case 6: group(std::integral_constant<int, 6>{}, b0); break;
-          case 7: group(std::integral_constant<int, 7>{}, b0); break;
-          default: group(std::integral_constant<int, 8>{}, b0); break;
+      auto run = [&](auto lanes) {
+        for (int b0 = 0; b0 < B; b0 += kExactSeq) {
+          switch (min(kExactSeq, B - b0)) {
+            case 1: group(std::integral_constant<int, 1>{}, lanes, b0); break;
+            case 2: group(std::integral_constant<int, 2>{}, lanes, b0); break;
+            case 3: group(std::integral_constant<int, 3>{}, lanes, b0); break;
+            case 4: group(std::integral_constant<int, 4>{}, lanes, b0); break;
+            case 5: group(std::integral_constant<int, 5>{}, lanes, b0); break;
+            case 6: group(std::integral_constant<int, 6>{}, lanes, b0); break;
+            case 7: group(std::integral_constant<int, 7>{}, lanes, b0); break;
+            default: group(std::integral_constant<int, 8>{}, lanes, b0); break;
+          }
         }
-      }
+      };
+      if (H <= kNearH) run(std::integral_constant<int, 16>{});
+      else run(std::integral_constant<int, 64>{});
     }
     lds_barrier();
     for (int i = threadIdx.x; i < B * rc; i += kThreads) {
@@ -458,6 +860,73 @@ static void launch_xproj(const ExactArgs& a, hipStream_t stream) {
                                         dim3(kThreads), 0, stream>>>(a, (R + 15) / 16);
 }
 
+// Shape of the register kernels: fills P, kpl, slots and RU; returns the floats
+// of the exchange (0: neither takes the run).  Both hold W_h in registers, one
+// sequence per XCD up to kNearH units, over the whole device up to kWideH.
+size_t plan_exact_group(ExactArgs& a) {
+  a.P = 0;
+  if (a.num_cu < kXcds * kXcdCus || a.num_cu > kSpreadWords) return 0;
+  const int H = a.H;
+  if (H <= kNearH) {
+    const int e = (H + 15) / 16;
+    // up to 32 units one workgroup holds every row (four per thread)
+    a.kpl = H <= 32 ? e : (e + 3) & ~3;
+    a.slots = 16 * a.kpl;
+    a.P = H <= 32 ? 1 : std::min(kXcdCus, (a.slots + 7) / 8);
+    a.RU = (a.slots + a.P - 1) / a.P;
+    if (4 * near_lds(a, H <= 128 ? 8 : H <= 256 ? 16 : H <= 512 ? 32 : 48) > kLdsCap) return a.P = 0;
+    return (size_t)a.B * 3 * a.slots;
+  }
+  if (H <= kWideH && a.B <= kWideSeq) {
+    a.kpl = ((H + 63) / 64 + 3) & ~3;
+    a.slots = 64 * a.kpl;
+    a.P = a.slots / 8;
+    a.RU = 8;
+    return (size_t)3 * kWideSeq * a.slots;
+  }
+  return 0;
+}
+
+namespace {
+
+template <int OPT, int WPL>
+hipError_t launch_near(const ExactArgs& a, hipStream_t stream) {
+  static bool attr = false;
+  if (!attr) {
+    const hipError_t e = hipFuncSetAttribute((const void*)exact_near_kernel<OPT, WPL>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  exact_near_kernel<OPT, WPL><<<dim3(kXcds * a.P), dim3(kThreads), 4 * near_lds(a, WPL), stream>>>(a);
+  return hipGetLastError();
+}
+
+template <int WPL, int NB>
+hipError_t launch_wide(const ExactArgs& a, hipStream_t stream) {
+  static bool attr = false;
+  if (!attr) {
+    const hipError_t e = hipFuncSetAttribute((const void*)exact_wide_kernel<WPL, NB>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  // h of every sequence, or (alone) h twice, c and a pass of sums
+  const size_t fl = 4 + std::max<size_t>(NB * 8 + (size_t)NB * 64 * (WPL + 4), 3 * (size_t)a.H + 32);
+  exact_wide_kernel<WPL, NB><<<dim3(a.P), dim3(kThreads), 4 * fl, stream>>>(a);
+  return hipGetLastError();
+}
+
+template <int WPL>
+hipError_t launch_wide_seq(const ExactArgs& a, hipStream_t stream) {
+  if (a.B <= 1) return launch_wide<WPL, 1>(a, stream);
+  if (a.B <= 2) return launch_wide<WPL, 2>(a, stream);
+  if (a.B <= 4) return launch_wide<WPL, 4>(a, stream);
+  return launch_wide<WPL, 8>(a, stream);
+}
+
+}  // namespace
+
 hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
   static bool attr = false;
   if (!attr) {
@@ -473,6 +942,14 @@ hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
     else launch_xproj<false, false>(a, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+  }
+  if (a.P > 0) {
+    if (a.H > kNearH) return a.kpl <= 16 ? launch_wide_seq<16>(a, stream) : launch_wide_seq<32>(a, stream);
+    if (a.P == 1) return a.RU <= 8 ? launch_near<1, 8>(a, stream) : launch_near<4, 8>(a, stream);
+    if (a.H <= 128) return launch_near<1, 8>(a, stream);
+    if (a.H <= 256) return launch_near<1, 16>(a, stream);
+    if (a.H <= 512) return launch_near<2, 32>(a, stream);
+    return launch_near<3, 48>(a, stream);
   }
   ExactArgs c = a;
   const size_t lds = plan_exact(c, blocks);

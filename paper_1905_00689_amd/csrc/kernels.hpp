@@ -326,14 +326,27 @@ struct ExactArgs {
   int wreg;        // 1: the first 32 rows of each workgroup keep their W_h entries in registers
   int px_lds;      // 1: x parts of the owned rows for every timestep in LDS
   unsigned tag_base;
+  // register kernels (plan_exact_group)
+  int P;           // workgroups of a group (0: exact_lstm_kernel runs)
+  int kpl;         // exchange slots of a lane: ceil(H / lanes) rounded up to 4
+  int slots;       // exchange slots of a sequence: lanes * kpl
+  int RU;          // slots owned per workgroup
+  int first_xcd;   // XCD of group 0
+  unsigned wait_ticks;        // as PairArgs::wait_ticks
+  float* ex;                  // [B][3][slots], or [3][sequences up to 8][slots] over the device
+  unsigned long long* ctl;    // as PairArgs::ctl
 };
+
+// Shape of the kernels that hold W_h in registers: fills P .. RU (B, T, H and
+// num_cu given) and returns the floats of ex (0: they do not take the run).
+size_t plan_exact_group(ExactArgs& a);
 
 // Fills rows_per / wreg / px_lds for P workgroups; returns the LDS bytes the
 // recurrence kernel needs (> kLdsCap: does not fit).
 size_t plan_exact(ExactArgs& a, int P);
 
-// Launches the x projection and the persistent recurrence (`blocks`
-// workgroups) on `stream`.
+// Launches the x projection and the recurrence on `stream` (a.P > 0: the
+// register kernels, else exact_lstm_kernel on `blocks` workgroups).
 hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream);
 
 // Launches, on `stream`, the x-projection once and then, for every level,
