@@ -612,11 +612,13 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
                                    float* c_out, hipStream_t stream, const OnlineCfg* on,
                                    const CallerScratch* ws = nullptr) {
   if (on && ws) return fail(APPROX_LSTM_ERR_UNSUPPORTED, "online runs need the model's own workspace");
-  if (!on && pair_allowed(m, n_levels * B, kmax)) {
+  // (a schedule fixes every K_t beforehand, so each pair can follow it by itself)
+  if ((!on || (on->sched && m->launch_blocks == 0)) && pair_allowed(m, n_levels * B, kmax)) {
     alstm::PairArgs pa{};
     size_t plds = 0;
     const int Pp = plan_pair_run(m, pa, T, B, levels, n_levels, m->num_cu, &plds);
     if (Pp > 0) {
+      pa.sched = on ? on->sched : nullptr;
       bool taken = false;
       const approx_lstm_status st = run_pair(m, pa, Pp, x, h0, c0, kmax, h_out, c_out, stream, ws, &taken);
       if (taken || st != APPROX_LSTM_OK) return st;

@@ -185,6 +185,7 @@ struct PairArgs {
   unsigned long long* ctl;
   unsigned* err;
   unsigned long long* stamps;   // as RunArgs::stamps (pair 0, workgroup 0), or null
+  const int* sched;             // null, or device [T]: budget of every timestep (one level, at most its K)
   int D, H, G, N, NZ, T, B, L;
   PairLevel lv[kMaxLevels];
   // launch plan (plan_pair)

@@ -78,17 +78,19 @@ constexpr int kLdsStamps = 255;
 constexpr int kStampFloats = 2 * (4 + 4 * kLdsStamps);
 
 // LDS carve-up (floats): with stamps their block first (8-byte aligned), the
-// group's start mode [4], P_x [T][OM], h [hpad], z [G][zst], c [H] (of a
+// group's start mode [4], P_x [T][OM], the owned terms' places in their groups
+// [64], h [hpad], z [G][zst], c [H] (of a
 // workgroup that runs its pairs alone) and per wave the gate pre-activations
 // of its rows [opt][64 / S] (16-byte aligned).
 struct PairLayout {
-  int mode, px, hs, zs, cs, ys, total;
+  int mode, px, nown, hs, zs, cs, ys, total;
 };
 __host__ __device__ inline PairLayout pair_layout(const PairArgs& a) {
   PairLayout l;
   l.mode = a.stamps ? kStampFloats : 0;
   l.px = l.mode + 4;
-  l.hs = l.px + ((a.T * a.OMmax + 3) & ~3);
+  l.nown = l.px + ((a.T * a.OMmax + 3) & ~3);
+  l.hs = l.nown + 64;
   l.zs = l.hs + a.hpad;
   l.cs = l.zs + a.zfloats;
   l.ys = l.cs + a.hpad;
@@ -113,10 +115,11 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
   float* ysw = ys + wv * rpw;
   float* hout = a.h_out + ((size_t)lev * T * a.B + b) * H;
   for (int t = 0; t < T; ++t) {
+    const int kt = a.sched ? a.sched[t] : K;
     for (int base = 0; base < G * K; base += kThreads / 16) {
       const int tau = base + sub;
       float acc = 0.0f;
-      if (tau < G * K) {
+      if (tau < G * kt) {
         const size_t src = (size_t)tau * a.NZ;
         for (int e = a.nx[tau] + sla; e < a.NZ; e += 16) acc += a.vval[src + e] * hs[(int)a.vidx[src + e] - a.D];
       }
@@ -124,7 +127,7 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
       if (sla == 0 && tau < G * K) {
         const int g = tau % G, n = tau / G;
         zs[g * v.zst + (n & (S - 1)) * v.kst + (n >> lgS)] =
-            a.sigma[tau] * (a.px[(size_t)tau * TB + t * a.B + b] + acc);
+            tau < G * kt ? a.sigma[tau] * (a.px[(size_t)tau * TB + t * a.B + b] + acc) : 0.0f;
       }
     }
     __syncthreads();
@@ -181,6 +184,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   unsigned long long* lstamp = reinterpret_cast<unsigned long long*>(lds_raw);
   int* modes = reinterpret_cast<int*>(ldsf + lay.mode);
   float* pxs = ldsf + lay.px;      // P_x [T][OM]
+  int* nown = reinterpret_cast<int*>(ldsf + lay.nown);
   float* hs = ldsf + lay.hs;       // h_{t-1} [H]
   float* zs = ldsf + lay.zs;       // z of this timestep [G][zst]
   const int wv = tid >> 6;
@@ -266,6 +270,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       const int ia = sub + 32 * p;
       const int tau = ia < n_owned ? slot_tau(j * OM + ia) : -1;
       tauv[p] = max(tau, 0);
+      if (sla == 0) nown[ia] = tau >= 0 ? tau / G : K;
       sg[p] = tau >= 0 ? a.sigma[tau] : 0.0f;
       e0v[p] = tau >= 0 ? (int)a.nx[tau] : NZ;
     }
@@ -365,6 +370,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       st[1] = clock64();
     }
     float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + cunit;
+    int kt = a.sched ? a.sched[0] : K;
     for (int t = 0; t < T; ++t) {
       float* zxt = zx + (t & 1) * a.zslots;
       float* hxt = hx + (t & 1) * a.hpad;
@@ -390,7 +396,8 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
         acc = group_sum<16>(acc);
         const int ia = sub + 32 * p;
         if (sla == 0 && ia < n_owned) {
-          const float z = sg[p] * (pxs[t * OM + ia] + acc);
+          float z = sg[p] * (pxs[t * OM + ia] + acc);
+          if (a.sched && nown[ia] >= kt) z = 0.0f;   // past this timestep's budget
           if (local) {
             zs[slot_pos(j * OM + ia)] = z;
           } else {
@@ -400,6 +407,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
           }
         }
       }
+      if (a.sched && t + 1 < T) kt = a.sched[t + 1];   // its latency passes in the exchange
       if (stamp) st[3 + 4 * t] = clock64();
       if (!local) {
         poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err);
