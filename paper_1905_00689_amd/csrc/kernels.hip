@@ -878,9 +878,8 @@ __global__ void __launch_bounds__(kThreads) progressive_lstm_kernel(RunArgs a) {
 // x-part projections P_x[tau][t*B+b] = prune(v_tau)[k<D] . x_t[b] for every
 // term in use and every (t, b).  They do not depend on h, so they are taken
 // off the recurrence (the x part holds most of each term's non-zeros) and
-// spread over the GPU: each wave takes one term and each workgroup stages a
-// chunk of x transposed in LDS, xt[k][c] with a padded
-// row of xrow floats, so that one entry's values for every (t, b) of the
+// spread over the GPU: each wave takes PT terms and each workgroup stages a
+// chunk of x transposed in LDS, xt[k][c] with a row of xrow floats, so that one entry's values for every (t, b) of the
 // chunk are adjacent.  The term's entries are read once from HBM.  The
 // chunks are dealt over gridDim.y workgroups per term group, so that few
 // terms with long sequences (or wide x, hence small chunks) still fill the
@@ -888,7 +887,7 @@ __global__ void __launch_bounds__(kThreads) progressive_lstm_kernel(RunArgs a) {
 // the vector path (xrow a multiple of 4), anything else the scalar one.  The
 // per-(t, b) sums run in the same order at every XC.
 // PT terms per wave (consecutive terms of the workgroup's PT*8): with many
-// terms, several share each staged chunk of x.
+// terms, several share each staged chunk of x (launch_input_proj picks).
 template <int XC, int PT>
 __global__ void __launch_bounds__(kThreads) input_proj_kernel(RunArgs a, int xchunk, int xrow) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1192,35 +1191,45 @@ hipError_t launch_input_proj_xc(const RunArgs& a, int gx, int gy, int xchunk, in
 hipError_t launch_input_proj(const RunArgs& a, hipStream_t stream) {
   if (a.GK <= 0) return hipSuccess;
   const int TB = a.T * a.B;
-  const int gx = (a.GK + kWaves - 1) / kWaves;   // one term per wave
-  // few terms over a short sequence: chunks of 4 (t, b) pairs, each its own
-  // workgroup, so that the staging latency is spread over more workgroups
-  // (driving shape, T = 16, up to 512 terms: 6 us against 11 with one
-  // workgroup per term group); otherwise chunks of 16
-  const int c4 = (TB + 3) / 4;
-  if ((size_t)a.D * 4 * 4 <= kLdsCap && (long long)gx * c4 <= (long long)std::max(1, a.num_cu))
-    return launch_input_proj_xc<4>(a, gx, c4, 4, 4, (size_t)a.D * 4 * 4, stream);
-  // full chunks of 16 (t, b) pairs use a 16-byte aligned row of 20 floats
-  // (a wave's 64 writes of one component land in distinct banks); x too
-  // wide for that takes the largest smaller chunk that fits, with an odd row
-  // (the lanes' rows then fall in different banks)
-  int xchunk = kMaxXChunk, xrow = kMaxXChunk + 4;
-  if ((size_t)a.D * xrow * 4 > kLdsCap) {
-    xchunk = kMaxXChunk - 1;
-    while (xchunk > 1 && (size_t)a.D * (xchunk | 1) * 4 > kLdsCap) --xchunk;
-    xrow = xchunk | 1;
+  const int ncu = std::max(1, a.num_cu);
+  // A workgroup takes 8 * PT terms and XC (t, b) pairs at a time.  What bounds
+  // it is the latency of staging x, so the smallest tile whose workgroups are
+  // at most one per compute unit is the fastest, and past that the largest
+  // (two of 64 KB to a compute unit, one staging while the other multiplies).
+  // MI355X, D = 2048, us for tiles of (XC, PT) = (4, 1) / (4, 2) / (8, 2) / (8,
+  // 4) / (16, 1): 768 terms, 16 pairs 10.3 / 7.1 / 9.6 / 15.5 / 10.7; 2048
+  // terms, 16 pairs 19.4 / 12.6 / 10.1 / 16.2 / 11.2; 512 terms, 128 pairs
+  // 36.2 / 22.7 / 18.1 / 15.3 / 20.2; 256 terms, 512 pairs 70.4 / 41.1 / 30.6
+  // / 21.3 / 32.5.
+  static const struct {
+    int xc, pt;
+    hipError_t (*launch)(const RunArgs&, int, int, int, int, size_t, hipStream_t);
+  } tiles[] = {{4, 1, launch_input_proj_xc<4, 1>},
+               {4, 2, launch_input_proj_xc<4, 2>},
+               {8, 2, launch_input_proj_xc<8, 2>},
+               {8, 4, launch_input_proj_xc<8, 4>}};
+  int pick = -1;
+  for (int i = 0; i < 4; ++i) {
+    if ((size_t)a.D * tiles[i].xc * 4 > kLdsCap) continue;   // x too wide
+    pick = i;
+    const long long gx = (a.GK + kWaves * tiles[i].pt - 1) / (kWaves * tiles[i].pt);
+    if (gx * ((TB + tiles[i].xc - 1) / tiles[i].xc) <= ncu) break;
   }
-  const size_t plds = (size_t)a.D * xrow * 4;
-  // terms enough for every compute unit at 4 terms per wave: each staged
-  // chunk of x then serves 32 terms instead of 8 (deadline shape, 8192
-  // terms over 32 chunks: the staging was 4 GB over the device)
-  if (gx >= 4 * std::max(1, a.num_cu)) {
-    const int gx4 = (a.GK + 4 * kWaves - 1) / (4 * kWaves);
-    const int gy4 = column_slices(gx4, (TB + xchunk - 1) / xchunk);
-    return launch_input_proj_xc<kMaxXChunk, 4>(a, gx4, gy4, xchunk, xrow, plds, stream);
+  if (pick >= 0) {
+    const int xc = tiles[pick].xc, pt = tiles[pick].pt;
+    const int gx = (a.GK + kWaves * pt - 1) / (kWaves * pt), chunks = (TB + xc - 1) / xc;
+    // at most 16 workgroups per compute unit, each then taking several chunks
+    const int gy = std::max(1, std::min(chunks, std::max(column_slices(gx, chunks), 16 * ncu / gx)));
+    return tiles[pick].launch(a, gx, gy, xc, xc, (size_t)a.D * xc * 4, stream);
   }
+  // wider x: the largest chunk that fits, with an odd row (the lanes' rows
+  // then fall in different banks)
+  int xchunk = 3;
+  while (xchunk > 1 && (size_t)a.D * (xchunk | 1) * 4 > kLdsCap) --xchunk;
+  const int xrow = xchunk | 1;
+  const int gx = (a.GK + kWaves - 1) / kWaves;
   const int gy = column_slices(gx, (TB + xchunk - 1) / xchunk);
-  return launch_input_proj_xc<kMaxXChunk>(a, gx, gy, xchunk, xrow, plds, stream);
+  return launch_input_proj_xc<4>(a, gx, gy, xchunk, xrow, (size_t)a.D * xrow * 4, stream);
 }
 
 hipError_t launch_progressive(const RunArgs& a, int blocks, int cooperative, hipStream_t stream) {

@@ -12,7 +12,6 @@ constexpr int kTileEntries = 16;        // U entries per lane and row in one til
 constexpr int kTileWords = 16;          // z words per gathering thread in one tile of it
 constexpr int kMaxOptions = 24;        // candidate budgets of an online (anytime) run
 constexpr int kThreads = 512;          // 8 wave64 per workgroup
-constexpr int kMaxXChunk = 16;         // (t, b) pairs accumulated per pass of the input projection
 constexpr size_t kLdsCap = 160 * 1024; // LDS per CU on gfx950
 
 // Everything one launch of the progressive-LSTM kernel needs.  Device
