@@ -29,14 +29,15 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
+// the same for S = 1, 4, 8 or 16 (uniform; lanes_for_level gives no other)
 __device__ __forceinline__ float group_sum_rt(float v, int S) {
-  switch (S) {
-    case 1: return v;
-    case 2: return group_sum<2>(v);
-    case 4: return group_sum<4>(v);
-    case 8: return group_sum<8>(v);
-    default: return group_sum<16>(v);
-  }
+  if (S == 1) return v;
+  v = group_sum<4>(v);
+  if (S == 4) return v;
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false));
+  if (S == 8) return v;
+  v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x140, 0xF, 0xF, false));
+  return v;
 }
 
 // Full-wave sum (input projection): 16-lane rows, then (r0 + r1) + (r2 + r3)
@@ -333,18 +334,25 @@ __device__ __forceinline__ float tanh_fast(float x) {
   return __builtin_fmaf(2.0f, sigmoid_fast(2.0f * x), -1.0f);
 }
 
+// A gate's value from its pre-activation: tanh for the cell candidate,
+// sigmoid for the others (one exponential and one reciprocal either way).
+__device__ __forceinline__ float gate_value(float y, bool candidate) {
+  const float s = sigmoid_fast(candidate ? 2.0f * y : y);
+  return candidate ? __builtin_fmaf(2.0f, s, -1.0f) : s;
+}
+
 // The cell update of Sec. II from the four gate pre-activations (rows i, f,
 // g, o): c' = sigmoid(y_f) c + sigmoid(y_i) tanh(y_g), h = sigmoid(y_o)
 // tanh(c').  Every kernel takes it from here, with its one fused
 // multiply-add written out, so that the rounding never depends on how a
 // kernel's surrounding code lets the compiler contract the expression.
-__device__ __forceinline__ void cell_update(float yi, float yf, float yg, float yo, float& c, float& h) {
-  const float gi = sigmoid_fast(yi);
-  const float gf = sigmoid_fast(yf);
-  const float gg = tanh_fast(yg);
-  const float go = sigmoid_fast(yo);
+__device__ __forceinline__ void cell_from_gates(float gi, float gf, float gg, float go, float& c, float& h) {
   c = __builtin_fmaf(gf, c, gi * gg);
   h = go * tanh_fast(c);
+}
+
+__device__ __forceinline__ void cell_update(float yi, float yf, float yg, float yo, float& c, float& h) {
+  cell_from_gates(sigmoid_fast(yi), sigmoid_fast(yf), tanh_fast(yg), sigmoid_fast(yo), c, h);
 }
 
 }  // namespace

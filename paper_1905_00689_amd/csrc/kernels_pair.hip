@@ -20,7 +20,9 @@
 //            lanes apply the gate nonlinearities and the c/h update and store
 //            h into its exchange slot and to h_out;
 //   h        every thread polls its share of the units' h into LDS.
-// With one workgroup (P = 1) nothing is exchanged: z and h go through LDS.
+// With one workgroup (P = 1) nothing is exchanged: z and h go through LDS
+// (H = 64, K = 16, T = 100: 1.08 -> 0.78 us per timestep, once the rows applied
+// their own gates' nonlinearities and no wait for LDS was one for h_out).
 //
 // What bounds a timestep is the latency of its two exchanges.  Two things
 // make them short:
@@ -39,12 +41,12 @@
 //   words and a quarter of the loads.
 // Driving shape (D = 2048, H = 512, 75% pruning, T = 16, one sequence), whole
 // run, us, with tagged words across XCDs / near groups with tagged words /
-// near groups with slots: K = 32 75.2 / 60.3 / 40.8, K = 128 76.9 / 63.2 /
-// 45.5, K = 512 87.5 / 92.3 / 70.1; phases at K = 64 (A, z, B, h) 0.25, 1.31,
-// 0.70, 1.69 -> 0.33, 0.51, 0.49, 0.47 us.  Several pairs, against the general
-// kernel's one launch for all of them: eight sequences at K = 128 389 -> 60,
-// levels 16, 64, 128, 192 201 -> 53; H = 2048, K = 64, T = 64, eight sequences
-// 1499 -> 173.
+// near groups with slots: K = 32 75.2 / 60.3 / 40.6, K = 128 76.9 / 63.2 /
+// 43.0, K = 512 87.5 / 92.3 / 67.1; phases at K = 64 (A, z, B, h) 0.25, 1.31,
+// 0.70, 1.69 -> 0.36, 0.39, 0.40, 0.58 us.  Several pairs, against the general
+// kernel's one launch for all of them: eight sequences at K = 128 389 -> 54,
+// levels 16, 64, 128, 192 202 -> 49; H = 2048, K = 64, T = 64, eight sequences
+// 1505 -> 155.
 //
 // Residency.  A group's workgroups wait for each other, so all of them must
 // be resident.  When another stream's kernels hold part of an XCD that may
@@ -64,6 +66,7 @@
 #include "device_common.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace alstm {
 
@@ -181,7 +184,6 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   const int D = a.D, H = a.H, G = a.G, N = a.N, NZ = a.NZ, T = a.T, B = a.B;
   const PairLayout lay = pair_layout(a);
   float* ldsf = reinterpret_cast<float*>(lds_raw);
-  unsigned long long* lstamp = reinterpret_cast<unsigned long long*>(lds_raw);
   int* modes = reinterpret_cast<int*>(ldsf + lay.mode);
   float* pxs = ldsf + lay.px;      // P_x [T][OM]
   int* nown = reinterpret_cast<int*>(ldsf + lay.nown);
@@ -285,6 +287,10 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     // every row of a thread has gate q = rs & 3 (row slots per pass are a
     // multiple of 4): one z base for all of them
     const int zb = (G == 4 ? (rs & 3) : 0) * zst + sl * kst;
+    const bool cand = (rs & 3) == 2;   // the cell candidate's rows: tanh
+    int zown[APASS];                   // LDS places of the owned slots (one workgroup)
+#pragma unroll
+    for (int p = 0; p < APASS; ++p) zown[p] = sub + 32 * p < n_owned ? slot_pos(j * OM + sub + 32 * p) : 0;
     // ---- cell roles: a wave holds the rows of 16 * OPT / S units (row slots
     // [w * 64/S, (w+1) * 64/S) in each of the OPT passes); its lane cl takes
     // unit cl, pass co = cl / (16/S), row slots 4 ck .. 4 ck + 3 (ck = cl %
@@ -363,118 +369,149 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     }
 
     const bool stamp = a.stamps && lb == 0 && j == 0 && tid == 0;
-    // stamps of short runs stay in LDS until the end (no stores on the way)
-    unsigned long long* st = (T <= kLdsStamps) ? lstamp : a.stamps;
+    // stamps of short runs stay in LDS until the end (no stores on the way);
+    // two plain stores rather than one through a generic pointer, after which
+    // every wait for LDS would wait for outstanding memory stores too
+    const bool lds_stamps = T <= kLdsStamps;
+    auto put_stamp = [&](int i, unsigned long long v) {
+      if (lds_stamps) reinterpret_cast<unsigned long long*>(lds_raw)[i] = v;
+      else a.stamps[i] = v;
+    };
     if (stamp) {
-      st[0] = wall_clock64();
-      st[1] = clock64();
+      put_stamp(0, wall_clock64());
+      put_stamp(1, clock64());
     }
-    float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + cunit;
-    int kt = a.sched ? a.sched[0] : K;
-    for (int t = 0; t < T; ++t) {
-      float* zxt = zx + (t & 1) * a.zslots;
-      float* hxt = hx + (t & 1) * a.hpad;
-      if (stamp) st[2 + 4 * t] = clock64();
+    // one loop for a single workgroup and one for an exchanging group
+    auto steps = [&](auto lone) {
+      constexpr bool kLocal = decltype(lone)::value;
+      float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + cunit;
+      const size_t hstep = (size_t)B * H;
+      int kt = a.sched ? a.sched[0] : K;
+      int half = 0;   // t & 1
+      for (int t = 0; t < T; ++t, half ^= 1, hout += hstep) {
+        float* zxt = zx + (half ? a.zslots : 0);
+        float* zxe = zx + (half ? 0 : a.zslots);
+        float* hxt = hx + (half ? a.hpad : 0);
+        float* hxe = hx + (half ? 0 : a.hpad);
+        if (stamp) put_stamp(2 + 4 * t, clock64());
 
-      // ---- phase A: z = sigma * (P_x + prune(v)_h . h_{t-1}) ----
+        // ---- phase A: z = sigma * (P_x + prune(v)_h . h_{t-1}) ----
+        float z[APASS], pxv[APASS];
 #pragma unroll
-      for (int p = 0; p < APASS; ++p) {
-        if (p * 32 >= n_owned) break;
-        float acc = 0.0f;
+        for (int p = 0; p < APASS; ++p) pxv[p] = pxs[t * OM + min(sub + 32 * p, OM - 1)];
 #pragma unroll
-        for (int k0 = 0; k0 < HMAX; k0 += kChunk) {
-          // the bound k0 + k < HMAX is a constant once unrolled (a last chunk
-          // may be partial: HMAX = 24)
-          float hg[kChunk];
+        for (int p = 0; p < APASS; ++p) {
+          float acc = 0.0f;
 #pragma unroll
-          for (int k = 0; k < kChunk; ++k)
-            if (k0 + k < HMAX) hg[k] = *reinterpret_cast<const float*>(lds_raw + hi[p][k0 + k]);
+          for (int k0 = 0; k0 < HMAX; k0 += kChunk) {
+            // the bound k0 + k < HMAX is a constant once unrolled (a last chunk
+            // may be partial: HMAX = 24)
+            float hg[kChunk];
 #pragma unroll
-          for (int k = 0; k < kChunk; ++k)
-            if (k0 + k < HMAX) acc += hv[p][k0 + k] * hg[k];
+            for (int k = 0; k < kChunk; ++k)
+              if (k0 + k < HMAX) hg[k] = *reinterpret_cast<const float*>(lds_raw + hi[p][k0 + k]);
+#pragma unroll
+            for (int k = 0; k < kChunk; ++k)
+              if (k0 + k < HMAX) acc += hv[p][k0 + k] * hg[k];
+          }
+          z[p] = sg[p] * (pxv[p] + group_sum<16>(acc));
         }
-        acc = group_sum<16>(acc);
-        const int ia = sub + 32 * p;
-        if (sla == 0 && ia < n_owned) {
-          float z = sg[p] * (pxs[t * OM + ia] + acc);
-          if (a.sched && nown[ia] >= kt) z = 0.0f;   // past this timestep's budget
-          if (local) {
-            zs[slot_pos(j * OM + ia)] = z;
-          } else {
-            publish_slot(zxt + j * OM + ia, z, near);
-            // z_{t-1}: everyone's h_{t-1} is here, so everyone has read it
-            store_slot(zx + ((t + 1) & 1) * a.zslots + j * OM + ia, kEmpty, near);
+        if (a.sched) {
+          // terms past this timestep's budget
+#pragma unroll
+          for (int p = 0; p < APASS; ++p)
+            if (sub + 32 * p < n_owned && nown[sub + 32 * p] >= kt) z[p] = 0.0f;
+          if (t + 1 < T) kt = a.sched[t + 1];   // on its way while the exchanges wait
+        }
+        if (sla == 0) {
+#pragma unroll
+          for (int p = 0; p < APASS; ++p) {
+            const int ia = sub + 32 * p;
+            if (ia >= n_owned) break;
+            if constexpr (kLocal) {
+              zs[zown[p]] = z[p];
+            } else {
+              publish_slot(zxt + j * OM + ia, z[p], near);
+              // z_{t-1}: everyone's h_{t-1} is here, so everyone has read it
+              store_slot(zxe + j * OM + ia, kEmpty, near);
+            }
           }
         }
-      }
-      if (a.sched && t + 1 < T) kt = a.sched[t + 1];   // its latency passes in the exchange
-      if (stamp) st[3 + 4 * t] = clock64();
-      if (!local) {
-        poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err);
-        wait_memory();   // the emptied slots too, before this workgroup's h_t
-      }
-      lds_barrier();
-      if (stamp) st[4 + 4 * t] = clock64();
+        if (stamp) put_stamp(3 + 4 * t, clock64());
+        if constexpr (!kLocal) {
+          poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err);
+          wait_memory();   // the emptied slots too, before this workgroup's h_t
+        }
+        lds_barrier();
+        if (stamp) put_stamp(4 + 4 * t, clock64());
 
-      // ---- phase B: y = b + sum_n u_n z_n, then the cell update ----
-      float y[OPT], acc[OPT];
+        // ---- phase B: y = b + sum_n u_n z_n, then the cell update ----
+        float acc[OPT];
 #pragma unroll
-      for (int o = 0; o < OPT; ++o) acc[o] = 0.0f;
+        for (int o = 0; o < OPT; ++o) acc[o] = 0.0f;
 #pragma unroll
-      for (int k0 = 0; k0 < UMAX; k0 += kChunk) {
-        float4 z4[kChunk / 4];
-#pragma unroll
-        for (int k = 0; k < kChunk; k += 4)
-          if (k0 + k < UMAX) z4[k / 4] = *reinterpret_cast<const float4*>(zs + zb + k0 + k);
-#pragma unroll
-        for (int o = 0; o < OPT; ++o)
+        for (int k0 = 0; k0 < UMAX; k0 += kChunk) {
+          float4 z4[kChunk / 4];
 #pragma unroll
           for (int k = 0; k < kChunk; k += 4)
-            if (k0 + k < UMAX) {
-              acc[o] += uv[o][k0 + k] * z4[k / 4].x;
-              acc[o] += uv[o][k0 + k + 1] * z4[k / 4].y;
-              acc[o] += uv[o][k0 + k + 2] * z4[k / 4].z;
-              acc[o] += uv[o][k0 + k + 3] * z4[k / 4].w;
-            }
-      }
+            if (k0 + k < UMAX) z4[k / 4] = *reinterpret_cast<const float4*>(zs + zb + k0 + k);
 #pragma unroll
-      for (int o = 0; o < OPT; ++o) y[o] = group_sum_rt(acc[o], S) + bq[o];
-      // the rows' sums go to the wave's block (lane sl == 0 of each row), then
-      // each unit's lane reads its four gate rows at once and updates c and h
-      if (sl == 0) {
+          for (int o = 0; o < OPT; ++o)
 #pragma unroll
-        for (int o = 0; o < OPT; ++o) ysw[o * rpw + (lane >> lgS)] = y[o];
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (lane < upw) {
-        const float4 g4 = *reinterpret_cast<const float4*>(ysw + co * rpw + 4 * ck);
-        float h2;
-        cell_update(g4.x, g4.y, g4.z, g4.w, cst, h2);
-        if (cell_ok) {
-          if (local) {
-            hs[r0 + cunit] = h2;
-          } else {
-            publish_slot(hxt + r0 + cunit, h2, near);
-            // h_{t-1}: everyone's z_t is here, so everyone has read it
-            store_slot(hx + ((t + 1) & 1) * a.hpad + r0 + cunit, kEmpty, near);
-          }
-          hout[(size_t)t * B * H] = h2;
+            for (int k = 0; k < kChunk; k += 4)
+              if (k0 + k < UMAX) {
+                acc[o] += uv[o][k0 + k] * z4[k / 4].x;
+                acc[o] += uv[o][k0 + k + 1] * z4[k / 4].y;
+                acc[o] += uv[o][k0 + k + 2] * z4[k / 4].z;
+                acc[o] += uv[o][k0 + k + 3] * z4[k / 4].w;
+              }
         }
+        // every row applies its own gate's nonlinearity (the four gates of a
+        // unit side by side rather than one after the other in the unit's
+        // lane), then the results go to the wave's block and each unit's lane
+        // reads its four at once and updates c and h
+#pragma unroll
+        for (int o = 0; o < OPT; ++o) acc[o] = gate_value(group_sum_rt(acc[o], S) + bq[o], cand);
+        if (sl == 0) {
+#pragma unroll
+          for (int o = 0; o < OPT; ++o) ysw[o * rpw + (lane >> lgS)] = acc[o];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const bool more = t + 1 < T;   // nobody reads the last timestep's h
+        if (lane < upw) {
+          const float4 g4 = *reinterpret_cast<const float4*>(ysw + co * rpw + 4 * ck);
+          float h2;
+          cell_from_gates(g4.x, g4.y, g4.z, g4.w, cst, h2);
+          if (cell_ok) {
+            if constexpr (kLocal) {
+              hs[r0 + cunit] = h2;
+            } else if (more) {
+              publish_slot(hxt + r0 + cunit, h2, near);
+              // h_{t-1}: everyone's z_t is here, so everyone has read it
+              store_slot(hxe + r0 + cunit, kEmpty, near);
+            }
+            *hout = h2;
+          }
+        }
+        if (stamp) put_stamp(5 + 4 * t, clock64());
+        if constexpr (!kLocal) {
+          if (more) {
+            poll_units<kMaxUnits>(hs, hxt, a.hpad * 4, hdi, hpend, a.err);
+            wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
+          }
+        }
+        lds_barrier();
       }
-      if (stamp) st[5 + 4 * t] = clock64();
-      if (!local) {
-        poll_units<kMaxUnits>(hs, hxt, a.hpad * 4, hdi, hpend, a.err);
-        wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
-      }
-      lds_barrier();
-    }
+    };
+    if (local) steps(std::true_type{});
+    else steps(std::false_type{});
     if (stamp) {
-      st[2 + 4 * T] = clock64();
-      st[3 + 4 * T] = wall_clock64();
-      if (st == lstamp)
-        for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = lstamp[i];
+      put_stamp(2 + 4 * T, clock64());
+      put_stamp(3 + 4 * T, wall_clock64());
+      if (lds_stamps)
+        for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = reinterpret_cast<unsigned long long*>(lds_raw)[i];
     }
     if (a.c_out && cell_ok) a.c_out[((size_t)lev * B + b) * H + r0 + cunit] = cst;
   }
