@@ -365,15 +365,14 @@ approx_lstm_status approx_lstm_set_start_wait(approx_lstm_model* m, double wait_
  * per gate with bf16 operands, then the Sec. II cell update), from the next
  * run on.  persistent = 1 (the default): one persistent launch per level
  * where the shape allows it (H and every K at most 512; sequences in cohorts
- * of 16, each run by ceil(H/32) workgroups that exchange z and h through
- * device memory every timestep); other shapes, and persistent = 0, run two
- * kernels per timestep.  2 and 3 force the persistent launch's z exchange to
- * tagged words or to flagged plain bf16 (tuning; 1 picks by the number of
- * terms).  All compute the same products with fp32 sums; they differ only in
- * the order of those sums.  The persistent launch relies on each cohort's
- * workgroups being resident at once; if they are not, its bounded waits
- * expire and approx_lstm_check reports APPROX_LSTM_ERR_DEVICE.  No effect on
- * fp32 models.  Errors: null model, persistent outside 0..3.
+ * of 16, each run by ceil(H/32) workgroups of one XCD that exchange z and h
+ * through its L2 every timestep); other shapes, and persistent = 0, run two
+ * kernels per timestep.  2 and 3 are accepted and mean 1.  All compute the same
+ * products with fp32 sums; they differ only in the order of those sums.  The
+ * persistent launch relies on each cohort's workgroups being resident at once;
+ * if they are not, its bounded waits expire and approx_lstm_check reports
+ * APPROX_LSTM_ERR_DEVICE.  No effect on fp32 models.  Errors: null model,
+ * persistent outside 0..3.
  */
 approx_lstm_status approx_lstm_set_batched_path(approx_lstm_model* m, int32_t persistent);
 

@@ -145,25 +145,24 @@ struct approx_lstm_model {
   int cooperative = 0;               // 1: cooperative launch API
   int recurrence = 0;                // 0: pair kernel where it applies, 1: general kernel only
   // persistent batched recurrence (bf16 models): cohort exchange buffers
-  int batched_persistent = 1;        // 0: per-timestep kernel pairs only; 1: persistent where it
-                                     // fits; 2, 3: persistent with z always tagged / always flagged
-  uint16_t* d_pzx = nullptr;         // [slots][G][16][Kp] bf16
+  int batched_persistent = 1;        // 0: per-timestep kernel pairs only; else persistent where it fits
+  uint16_t* d_pzx = nullptr;         // [slots][2][G][16][Kp] bf16
   size_t pzx_cap = 0;                // elements
-  uint16_t* d_phx = nullptr;         // [slots][16][Hp] bf16, padding columns zero
+  uint16_t* d_phx = nullptr;         // [slots][2][16][Hp] bf16
   size_t phx_cap = 0;
-  unsigned* d_pflag = nullptr;       // [2][slots][W]
-  size_t pflag_cap = 0;
+  unsigned long long* d_pctl = nullptr;   // [slots][kCtlWords] start words
+  size_t pctl_cap = 0;
   float* d_ppart = nullptr;          // partial x-projections of a split contraction
   size_t ppart_cap = 0;              // floats
 
   ~approx_lstm_model() {
     if (!has_dev && !d_px && !d_zx && !d_hx && !d_hbx && !d_hflag && !d_err && !d_stamps && !d_stack && !d_bz &&
-        !d_bh && !d_bc && !d_kt && !d_pex && !d_pzx && !d_phx && !d_pflag && !d_ppart)
+        !d_bh && !d_bc && !d_kt && !d_pex && !d_pzx && !d_phx && !d_pctl && !d_ppart)
       return;
     DeviceScope ds(device);
     dfree(d_pzx);
     dfree(d_phx);
-    dfree(d_pflag);
+    dfree(d_pctl);
     dfree(d_ppart);
     dfree(d_Vx);
     dfree(d_Vh);
@@ -292,53 +291,20 @@ approx_lstm_status ensure_bulk(approx_lstm_model* m, size_t floats, hipStream_t 
   return APPROX_LSTM_OK;
 }
 
-// z of a persistent batched launch travel as tagged words (no flag round
-// trip, twice the bytes) up to this many terms in use (G times K rounded up
-// to 32), as plain bf16 behind flags beyond.  Measured on MI355X at the
-// batched workload (H=512, 256 sequences), the flagged form is as fast or
-// faster at every K from 32 to 512 (the tagged polls wait as long as the
-// flag round trip), so the automatic choice is always flagged.
-constexpr int kZtagTerms = 0;
-
 // Exchange buffers of the persistent batched recurrence: z and h of every
-// cohort in flight (zeroed when new, so that no stale tag can match) and the
-// flag words (zeroed when new and when the launch sequence would wrap).
-// Reserves n_levels launch sequence numbers: on return m->seq + n_levels <=
-// 0xFFFF.
-approx_lstm_status ensure_persistent(approx_lstm_model* m, size_t zx, size_t hx, size_t flags, int n_levels,
+// cohort in flight (each launch empties its slots itself) and the groups'
+// start words (zeroed when new; every launch leaves them zero).  Reserves
+// n_levels launch sequence numbers: on return m->seq + n_levels <= 0xFFFF.
+approx_lstm_status ensure_persistent(approx_lstm_model* m, size_t zx, size_t hx, size_t ctl, int n_levels,
                                      hipStream_t stream) {
-  approx_lstm_status st = APPROX_LSTM_OK;
-  if (round_up(zx, 4) > m->pzx_cap) {
-    st = grow(m->d_pzx, m->pzx_cap, round_up(zx, 4), stream, "hipMalloc(zx)");
-    if (st == APPROX_LSTM_OK)
-      HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(m->d_pzx), m->pzx_cap / 4, stream),
-              "clear(zx)");
+  approx_lstm_status st = grow(m->d_pzx, m->pzx_cap, zx, stream, "hipMalloc(zx)");
+  if (st == APPROX_LSTM_OK) st = grow(m->d_phx, m->phx_cap, hx, stream, "hipMalloc(hx)");
+  if (st == APPROX_LSTM_OK && ctl > m->pctl_cap) {
+    st = grow(m->d_pctl, m->pctl_cap, ctl, stream, "hipMalloc(start words)");
+    if (st == APPROX_LSTM_OK) HIP_TRY(alstm::launch_clear_u64(m->d_pctl, m->pctl_cap, stream), "clear(start words)");
   }
-  if (st == APPROX_LSTM_OK && round_up(hx, 4) > m->phx_cap) {
-    st = grow(m->d_phx, m->phx_cap, round_up(hx, 4), stream, "hipMalloc(hx)");
-    if (st == APPROX_LSTM_OK)
-      HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(m->d_phx), m->phx_cap / 4, stream),
-              "clear(hx)");
-  }
-  bool clear_flags = false;
-  if (st == APPROX_LSTM_OK && round_up(flags, 2) > m->pflag_cap) {
-    st = grow(m->d_pflag, m->pflag_cap, round_up(flags, 2), stream, "hipMalloc(flags)");
-    clear_flags = true;
-  }
-  if (st != APPROX_LSTM_OK) return st;
-  if (m->seq == 0 || m->seq + (unsigned)n_levels > 0xFFFFu) {
-    clear_flags = true;
-    m->seq = 1;
-  }
-  if (clear_flags) {
-    HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(m->d_pflag), m->pflag_cap / 2, stream),
-            "clear(flags)");
-    HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(m->d_pzx), m->pzx_cap / 4, stream),
-            "clear(zx)");
-    HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(m->d_phx), m->phx_cap / 4, stream),
-            "clear(hx)");
-  }
-  return APPROX_LSTM_OK;
+  if (m->seq + (unsigned)n_levels > 0xFFFFu) m->seq = 0;
+  return st;
 }
 
 // The batched bf16 run (factor_dtype 1): arguments already checked.
@@ -367,11 +333,11 @@ approx_lstm_status run_batched(approx_lstm_model* m, const float* x, int T, int 
   int W = 0, slots = 0;
   if (m->batched_persistent && alstm::plan_batched_persistent(a, kmax, &W, &slots)) {
     st = ensure_persistent(m, (size_t)slots * 2 * m->G * alstm::kCohort * m->Kp,
-                           (size_t)slots * 2 * alstm::kCohort * m->Hp, (size_t)slots * W, n_levels, stream);
+                           (size_t)slots * 2 * alstm::kCohort * m->Hp, (size_t)slots * alstm::kCtlWords, n_levels,
+                           stream);
     if (st != APPROX_LSTM_OK) return st;
-    a.zx = m->d_pzx; a.hx = m->d_phx; a.zflag = m->d_pflag;
+    a.zx = m->d_pzx; a.hx = m->d_phx; a.ctl = m->d_pctl;
     a.err = m->d_err;
-    a.ztag_terms = m->batched_persistent == 2 ? (1 << 30) : m->batched_persistent == 3 ? 0 : kZtagTerms;
     a.tag_base = m->seq << 16;
     m->seq += (unsigned)n_levels;
   }
@@ -876,7 +842,7 @@ approx_lstm_status approx_lstm_prepare(const float* w_ih, const float* w_hh, con
         for (int e = 0; e < nz; ++e) {
           const int k = vi_h[tau * nz + e];
           const uint16_t bits = bf16_bits_of(vv_h[tau * nz + e]);
-          if (k < D) vx16[tau * m->Dp + k] = bits;
+          if (k < D) vx16[((tau % G) * m->Kp + tau / G) * m->Dp + k] = bits;
           else vh16[tau * m->Hp + (k - D)] = bits;
         }
       for (int o = 0; o < 4 * H; ++o)

@@ -43,7 +43,8 @@ __device__ __forceinline__ float tanh_b(float x) { return 2.0f * sigmoid_b(2.0f 
 }  // namespace
 
 // ---------------------------------------------------------------- x-projection
-// P[t*Bp + b][tau] = sum_k Vx[tau][k] * x[t][b][k] for tau < a.rows.
+// P[t*Bp + b][r] = sum_k Vx[.][k] * x[t][b][k] for the rows r < a.rows (term
+// n of group g at r = g*km + n, km = pld / G).
 // One 128 (tau) x 128 (t, b) tile per workgroup of 4 waves, each wave a
 // 64 x 64 quadrant (4 x 4 MFMA blocks); the contraction runs in slices of 32
 // staged through LDS, double-buffered: slice s+1 is fetched into registers
@@ -85,7 +86,11 @@ __global__ void __launch_bounds__(256) batched_xproj_kernel(BatchedArgs a, int n
   // plus these, so no per-fetch 64-bit address arithmetic is needed
   unsigned aoff[2], xoff[4];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) aoff[j] = (unsigned)(row0 + ar + 64 * j) * (unsigned)a.Dp + 8u * ac;
+  for (int j = 0; j < 2; ++j) {
+    // output row g*km + n is panel row g*Kp + n (km: terms per group of this run)
+    const int km = a.pld / a.G, r = min(row0 + ar + 64 * j, a.pld - 1);
+    aoff[j] = (unsigned)((r / km) * a.Kp + r % km) * (unsigned)a.Dp + 8u * ac;
+  }
   unsigned live = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -182,7 +187,7 @@ __global__ void __launch_bounds__(256) batched_xproj_kernel(BatchedArgs a, int n
 #undef XPROJ_MUL
 #undef XPROJ_FETCH
 #undef XPROJ_STASH
-  // P is column-major in tau: the 4 result rows a lane holds are adjacent
+  // P is column-major in r: the 4 result rows a lane holds are adjacent
   float* dst = nsplit > 1 ? a.Ppart + (size_t)part * NB * a.pld : a.P;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -213,7 +218,7 @@ __global__ void __launch_bounds__(256) batched_xproj_sum_kernel(BatchedArgs a) {
 
 // ---------------------------------------------------------------- h-projection
 // z of timestep t for panel rows [32*blockIdx.x, +32) and sequences
-// [32*blockIdx.y, +32): z[tau][b] = sigma_tau (P[t*Bp+b][tau] + Vh[tau][:] .
+// [32*blockIdx.y, +32): z[tau][b] = sigma_tau (P[t*Bp+b] of tau + Vh[tau][:] .
 // h[b][:]) for tau < GKl, 0 for the padding rows; stored as bf16 in
 // Z[g][b][n] (tau = n*G + g).  The contraction over H is split over the 4
 // waves (k-steps w, w+4, ...), each issuing the loads of up to 4 k-steps
@@ -235,7 +240,7 @@ __global__ void __launch_bounds__(256) batched_hproj_kernel(BatchedArgs a, int t
   for (int i = 0; i < 4; ++i) {
     const int tau = tau0 + (nl0 + i) * a.G + g;
     const bool live = tau < GKl;
-    pv[i] = live ? prow[tau] : 0.0f;
+    pv[i] = live ? prow[g * (a.pld / a.G) + tau / a.G] : 0.0f;
     sg[i] = live ? a.sigma[tau] : 0.0f;
   }
   f32x4 acc[2][2];
@@ -363,148 +368,112 @@ __global__ void batched_init_kernel(BatchedArgs a) {
 
 // ---------------------------------------------------------------- persistent recurrence
 // The whole recurrence of one level in one launch.  Sequences go in cohorts
-// of 16 (one MFMA tile wide); a cohort is run by W workgroups of 8 waves,
-// workgroup w owning hidden units [32w, 32w+32) of all four gates.  Every
-// wave keeps two operand slices in registers for the whole launch:
+// of 16 (one MFMA tile wide); a cohort is run by a group of W workgroups of 8
+// waves, workgroup w owning hidden units [32w, 32w+32) of all four gates.
+// Every wave keeps two operand slices in registers for the whole launch:
 //   * one h-projection tile: the 16 terms (g, n0 .. n0+15) of tile w*8 + wave
 //     (tiles numbered group-major, so the 4 results a lane holds are
 //     consecutive n of one group), their Vh rows over all of H;
 //   * one accumulation tile: U rows q*H + 32w + 16*(wave>>2) + (0..15) of gate
 //     q = wave & 3 over the K terms of group g(q).
 // Per timestep: z tile = sigma (P + Vh . h_{t-1}) -> bf16, published to the
-// cohort; every workgroup gathers all z of the cohort into LDS; y = U . z +
+// group; every workgroup gathers all z of the cohort into LDS; y = U . z +
 // bias on MFMA; the cell update (one thread per (unit, sequence), c in a
-// register); h to h_out and, as bf16, published to the cohort; every
-// workgroup gathers h_t into LDS.  P of the next timestep is fetched while
-// the exchanges wait.
-// Exchanges go through device memory with agent-scope (sc1) stores and loads,
-// coherent across XCDs.  h, and z when the cohort's z are few, travel as
-// tagged 64-bit words (two bf16 values | tag << 32) that readers poll
-// directly; many z travel as plain bf16 behind one flag word per workgroup
-// (half the bytes, one more round trip).  The exchange buffers are single: a
-// workgroup writes z of step t+1 only after every workgroup has published
-// h_t, which each does after it has read all of z_t (and likewise for h).
-// Results equal the per-timestep kernels' up to the fp32 summation order of
-// each product.
-constexpr int kMaxKs = 16;   // register-resident contraction steps of 32 (H and K up to 512)
+// register); h to h_out and, as bf16, published to the group; every
+// workgroup gathers h_t into LDS.  P of the next timestep is fetched before
+// the h-projection, so that it has arrived when the exchange polls (loads
+// complete in order).
+//
+// What bounds a timestep is the two exchanges.  They are those of the pair
+// kernel: a group sits on one XCD (two cohorts of 16 workgroups fill its 32
+// compute units at H = 512), values travel through its L2 as plain stores
+// (agent scope where a group finds itself on several XCDs), in slots that are
+// empty until written: pairs of bf16 here, polled 16 bytes (eight values) at a
+// time.  Two halves of z and h by timestep parity; z_{t-1} is emptied once
+// h_{t-1} of everyone is here, h_{t-1} once z_t is.  MI355X, H = 512, 256
+// sequences, 16 timesteps, K = 512: flagged and tagged exchanges between XCDs
+// 150 us, now 80; per timestep h-projection 0.6, z 1.5 (64 KB to every
+// workgroup), accumulation and cell 0.9, h 0.9 us.
+//
+// The group's workgroups must be resident at once; if they are not within a
+// second the group leaves and the error word is set.
+constexpr int kMaxKs = 16;     // register-resident contraction steps of 32 (H and K up to 512)
+constexpr int kZUnits = 8;     // 16-byte units of z polled per thread (G * K up to 2048 terms of 16 sequences)
+constexpr int kHUnits = 2;     // and of h (H up to 512)
+constexpr unsigned kCohortWait = 100000000u;   // wall ticks (a second)
 
-// dst (LDS, row stride dld) <- src (global, row stride sld), `rows` rows of
-// 8*c8 bf16, with agent-scope (sc1) 16-byte loads, four in flight per thread
-__device__ __forceinline__ void copy_rows_coherent(uint16_t* dst, int dld, const uint16_t* src, int sld, int rows,
-                                                   int c8, int tid, int nthr) {
-  const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(addr >> 32));
-  const int nbytes = __builtin_amdgcn_readfirstlane(rows * sld * 2);
-  uint16_t* base = reinterpret_cast<uint16_t*>(((unsigned long long)hi << 32) | lo);
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, nbytes, 0x00020000);
-  const int n = rows * c8;
-  for (int i0 = 0; i0 < n; i0 += 4 * nthr) {
-    u32x4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * nthr + tid;
-      const int r = i < n ? i / c8 : 0, c = i < n ? i - r * c8 : 0;
-      v[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (r * sld + 8 * c) * 2, 0, 16 /* sc1 */));
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * nthr + tid;
-      if (i < n) {
-        const int r = i / c8, c = i - r * c8;
-        *reinterpret_cast<u32x4*>(dst + r * dld + 8 * c) = v[u];
-      }
-    }
-  }
+__device__ __forceinline__ unsigned full_pair(unsigned v) { return v == kEmpty ? 0x7FC07FC0u : v; }
+
+// two slots (four bf16), 8-byte aligned
+__device__ __forceinline__ void store_slots(uint16_t* p, unsigned lo, unsigned hi, bool near) {
+  const unsigned long long v = ((unsigned long long)hi << 32) | lo;
+  unsigned long long* q = reinterpret_cast<unsigned long long*>(p);
+  if (near) __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Tagged pairs: word p of row r of src (row stride swr words) holds bf16
-// values 2p and 2p+1 of that row and the tag in its upper half.  dst (LDS, row
-// stride dld bf16) <- the values of pairs p < npairs of `rows` rows, each once
-// its word carries `tag`; up to 8 words in flight per thread, polled until
-// they arrive.  Bounded: past the spin limit, or once another wait has failed,
-// it records the failure and stores zeros.
-__device__ void gather_pairs_tagged(uint16_t* dst, int dld, const unsigned long long* src, int swr, int rows,
-                                    int npairs, unsigned tag, unsigned* err, int tid, int nthr) {
-  const int n = rows * npairs;
-  for (int base = 0; base < n; base += 8 * nthr) {
-    const unsigned long long* sp[8];
-    int dp[8];
-    unsigned pending = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int i = base + k * nthr + tid;
-      const int r = i < n ? i / npairs : 0, pr = i < n ? i - r * npairs : 0;
-      sp[k] = src + (size_t)r * swr + pr;
-      dp[k] = r * dld + 2 * pr;
-      if (i < n) pending |= 1u << k;
-    }
-    unsigned long long wv[8];
-    unsigned spins = 0;
-    while (pending) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if ((pending >> k) & 1u) wv[k] = load_tagged(sp[k]);
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (((pending >> k) & 1u) && (unsigned)(wv[k] >> 32) == tag) {
-          *reinterpret_cast<unsigned*>(dst + dp[k]) = (unsigned)wv[k];
-          pending &= ~(1u << k);
-        }
-      if (pending && (++spins & 255u) == 0u &&
-          (spins >= kSpinLimit || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
-        __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-          if ((pending >> k) & 1u) *reinterpret_cast<unsigned*>(dst + dp[k]) = 0u;
-        pending = 0;
-      }
-    }
-  }
+// LDS bytes of a persistent launch with kh and ku contraction steps (h and z
+// tiles, y staging, start mode)
+__host__ __device__ inline size_t persistent_lds(int G, int kh, int ku) {
+  return (size_t)2 * kCohort * ((32 * kh + 8) + (size_t)G * (32 * ku + 8)) + sizeof(float) * 4 * 32 * 17 + 16;
 }
 
-__device__ __forceinline__ void store_coherent_u32(unsigned* p, unsigned v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// contraction steps a wave holds: the smallest of 4, 8 and 16 that covers n
+__host__ inline int step_bucket(int n) { return n <= 4 ? 4 : n <= 8 ? 8 : 16; }
 
-__device__ __forceinline__ void store_pair_tagged(unsigned long long* p, unsigned pair, unsigned tag) {
-  __hip_atomic_store(p, ((unsigned long long)tag << 32) | pair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// LDS bytes of a persistent launch at Kl32 (h and z tiles, y staging)
-__host__ __device__ inline size_t persistent_lds(int G, int Hp, int Kl32) {
-  return (size_t)2 * kCohort * ((Hp + 8) + (size_t)G * (Kl32 + 8)) + sizeof(float) * 4 * 32 * 17;
-}
-
+// KH and KU: contraction steps of 32 over H and over the terms, held in
+// registers; steps past Hp and Kl32 multiply zeros by zeros.  (With the counts
+// at run time every step waited for its own LDS read: h-projection 1.1 us
+// instead of 0.6 at H = 512.)
+template <int KH, int KU>
 __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, int K, int Kl32, int level,
-                                                                 int W, int slots, int ztag) {
+                                                                 int W, int slots, int nx) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  const int slot = blockIdx.x / W, w = blockIdx.x - slot * W;
+  // groups are dealt to nx XCDs (consecutive blocks go to the XCDs in turn)
+  const int x = blockIdx.x % nx, i0 = blockIdx.x / nx;
+  const int slot = x + nx * (i0 / W), w = i0 % W;
+  if (slot >= slots) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lq = lane >> 4, lk = lq * 8;
   const int G = a.G, H = a.H, Hp = a.Hp, Kp = a.Kp;
-  const int hld = Hp + 8, zld = Kl32 + 8;
+  constexpr int hld = 32 * KH + 8, zld = 32 * KU + 8;
   uint16_t* hs = reinterpret_cast<uint16_t*>(lds_raw);                      // [16][hld]
   uint16_t* zs = hs + kCohort * hld;                                        // [G][16][zld]
   float* ys = reinterpret_cast<float*>(zs + (size_t)G * kCohort * zld);     // [4][32][17]
-  // a slot's exchange: z as [G*16][Kp] bf16 (flagged) or [G*16][Kp/2] tagged
-  // words; h as [16][Hp/2] tagged words
-  uint16_t* zx = a.zx + (size_t)slot * G * kCohort * Kp * 2;
-  unsigned long long* zxw = reinterpret_cast<unsigned long long*>(zx);
-  unsigned long long* hxw = reinterpret_cast<unsigned long long*>(a.hx + (size_t)slot * kCohort * Hp * 2);
-  unsigned* zflag = a.zflag + slot * W;
-  const int nkh = Hp >> 5, nku = Kl32 >> 5;
+  int* modes = reinterpret_cast<int*>(ys + 4 * 32 * 17);
+  // the group's exchange: z [2][G*16][Kl32], h [2][16][Hp]
+  const int zhalf = G * kCohort * Kl32, hhalf = kCohort * Hp;
+  uint16_t* zx = a.zx + (size_t)slot * 2 * G * kCohort * Kp;
+  uint16_t* hx = a.hx + (size_t)slot * 2 * hhalf;
+  unsigned long long* hand = a.ctl + (size_t)slot * kCtlWords;
+  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  const int nkh = Hp >> 5, nku = Kl32 >> 5;   // live steps
   const int u0 = w * 32;
   const bool exch = K > 0;   // without terms no workgroup reads another's z or h
+
+  if (exch) {
+    // this workgroup's share of the slots empty before the others hear of it
+    for (int i = w * 512 + tid; i < zhalf; i += W * 512)   // two halves of zhalf / 2 words
+      store_slot(reinterpret_cast<float*>(zx) + i, kEmpty, false);
+    for (int i = w * 512 + tid; i < hhalf; i += W * 512) store_slot(reinterpret_cast<float*>(hx) + i, kEmpty, false);
+    wait_memory();
+    lds_barrier();
+    if (wave == 7) {
+      const int mode = group_start(hand, decide, w, W, a.tag_base | 0xFFFFu, kCohortWait);
+      if (lane == 0) modes[0] = mode;
+    }
+  } else if (tid == 0) {
+    modes[0] = kNear;
+  }
 
   // h-projection tile of this wave and its operands
   const int ntn = Kl32 >> 4;
   const int tile = w * 8 + wave;
   const bool has_tile = tile < G * ntn;
   const int tg = has_tile ? tile / ntn : 0, tn0 = has_tile ? (tile - tg * ntn) * 16 : 0;
-  bf16x8 va[kMaxKs];
+  bf16x8 va[KH];
 #pragma unroll
-  for (int ks = 0; ks < kMaxKs; ++ks) {
+  for (int ks = 0; ks < KH; ++ks) {
     va[ks] = bf16x8{};
     if (has_tile && ks < nkh) va[ks] = load8(a.Vh + (size_t)((tn0 + li) * G + tg) * Hp + 32 * ks + lk);
   }
@@ -515,11 +484,11 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
     sg[r] = (has_tile && n < K) ? a.sigma[n * G + tg] : 0.0f;
   }
   // accumulation tile of this wave
-  const int q = wave & 3, half = wave >> 2;
-  const int urow = u0 + 16 * half + li;
-  bf16x8 ua[kMaxKs];
+  const int q = wave & 3, half16 = wave >> 2;
+  const int urow = u0 + 16 * half16 + li;
+  bf16x8 ua[KU];
 #pragma unroll
-  for (int ks = 0; ks < kMaxKs; ++ks) {
+  for (int ks = 0; ks < KU; ++ks) {
     ua[ks] = bf16x8{};
     if (urow < H && ks < nku) ua[ks] = load8(a.Ut + (size_t)(q * H + urow) * Kp + 32 * ks + lk);
   }
@@ -530,78 +499,87 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   const bool gu_live = gu < H;
   const int gur = gu_live ? gu : 0;
   const float bi = a.bias[gur], bfg = a.bias[H + gur], bgg = a.bias[2 * H + gur], bo = a.bias[3 * H + gur];
+  // exchange roles: unit tid + 512 r of z (row of Kl32 / 8 units) and of h
+  int zdst[kZUnits], hdst[kHUnits];
+  unsigned zpend = 0, hpend = 0;
+#pragma unroll
+  for (int r = 0; r < kZUnits; ++r) {
+    const int u = tid + 512 * r, row = Kl32 ? u / (Kl32 >> 3) : 0;
+    if (8 * u < zhalf) zpend |= 1u << r;
+    zdst[r] = 8 * u < zhalf ? (row * zld + 8 * (u - row * (Kl32 >> 3))) >> 1 : 0;
+  }
+#pragma unroll
+  for (int r = 0; r < kHUnits; ++r) {
+    const int u = tid + 512 * r, row = u / (Hp >> 3);
+    if (8 * u < hhalf) hpend |= 1u << r;
+    hdst[r] = 8 * u < hhalf ? (row * hld + 8 * (u - row * (Hp >> 3))) >> 1 : 0;
+  }
+  // columns of z past Kl32 are never written and must read zero
+  for (int i = tid; i < G * kCohort * zld / 2; i += 512) reinterpret_cast<unsigned*>(zs)[i] = 0u;
+  const size_t zoff = (size_t)(tg * kCohort + li) * Kl32 + tn0 + 4 * lq;
+  const size_t hoff = (size_t)gs * Hp + gu;   // even units carry the pair
+  __syncthreads();
+  const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
+  if (mode >= kAlone) {
+    if (tid == 0) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    group_leave(hand, decide, W);
+    return;
+  }
+  const bool near = mode == kNear;
 
-  int iter = 0;
-  for (int coh = slot; coh < (a.B + kCohort - 1) / kCohort; coh += slots, ++iter) {
+  const int ncoh = (a.B + kCohort - 1) / kCohort;
+  int par = 0;   // parity of the timestep, counted over the group's cohorts
+  for (int coh = slot; coh < ncoh; coh += slots) {
     const int b0 = coh * kCohort;
-    // h_{-1}; columns past H stay zero (the h gather writes units < H only)
-    for (int i = tid; i < kCohort * Hp; i += 512) {
-      const int sq = i / Hp, k = i - sq * Hp;
+    // h_{-1}; columns past H are zero
+    for (int i = tid; i < kCohort * 32 * KH; i += 512) {
+      const int sq = i / (32 * KH), k = i - sq * (32 * KH);
       const int b = b0 + sq;
       const float v = (a.h0 && b < a.B && k < H) ? a.h0[(size_t)b * H + k] : 0.0f;
       hs[sq * hld + k] = bf16_bits(v);
     }
     float c = 0.0f;
     if (a.c0 && b0 + gs < a.B && gu_live) c = a.c0[(size_t)(b0 + gs) * H + gu];
-    // P of the lane's 4 result terms (sequence li), one timestep ahead
-    float pv[4] = {0.f, 0.f, 0.f, 0.f};
+    // P of the lane's 4 result terms (sequence li)
+    const int km = a.pld / G;
     auto fetch_p = [&](int t) {
-      const float* prow = a.P + (size_t)(t * a.Bp + b0 + li) * a.pld;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int n = tn0 + 4 * lq + r;
-        pv[r] = (has_tile && n < K) ? prow[n * G + tg] : 0.0f;
-      }
+      return *reinterpret_cast<const f32x4*>(a.P + (size_t)(t * a.Bp + b0 + li) * a.pld + tg * km + tn0 + 4 * lq);
     };
-    fetch_p(0);
+    f32x4 pv = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (has_tile) pv = fetch_p(0);
     lds_barrier();
-    for (int t = 0; t < a.T; ++t) {
-      const unsigned tag = a.tag_base | (unsigned)(iter * a.T + t + 1);
+    for (int t = 0; t < a.T; ++t, par ^= 1) {
+      uint16_t* zt = zx + par * zhalf;
+      uint16_t* ht = hx + par * hhalf;
+      f32x4 pn = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (has_tile) pn = fetch_p(min(t + 1, a.T - 1));
       // ---- h-projection of the wave's tile, published as bf16
       if (has_tile) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < kMaxKs; ++ks)
-          if (ks < nkh) acc = mfma(va[ks], *reinterpret_cast<const bf16x8*>(hs + li * hld + 32 * ks + lk), acc);
+        for (int ks = 0; ks < KH; ++ks)
+          acc = mfma(va[ks], *reinterpret_cast<const bf16x8*>(hs + li * hld + 32 * ks + lk), acc);
         unsigned zb[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) zb[r] = bf16_bits(sg[r] * (pv[r] + acc[r]));
-        const size_t zoff = (size_t)(tg * kCohort + li) * Kp + tn0 + 4 * lq;   // even
-        if (ztag) {
-          store_pair_tagged(zxw + zoff / 2, zb[0] | (zb[1] << 16), tag);
-          store_pair_tagged(zxw + zoff / 2 + 1, zb[2] | (zb[3] << 16), tag);
-        } else {
-          unsigned* zp = reinterpret_cast<unsigned*>(zx + zoff);
-          store_coherent_u32(zp, zb[0] | (zb[1] << 16));
-          store_coherent_u32(zp + 1, zb[2] | (zb[3] << 16));
-        }
+        for (int r = 0; r < 4; ++r) zb[r] = tn0 + 4 * lq + r < K ? bf16_bits(sg[r] * (pv[r] + acc[r])) : 0u;
+        store_slots(zt + zoff, full_pair(zb[0] | (zb[1] << 16)), full_pair(zb[2] | (zb[3] << 16)), near);
+        store_slots(zx + (par ^ 1) * zhalf + zoff, kEmpty, kEmpty, near);
       }
+      pv = pn;
       if (exch) {
-        if (ztag) {
-          if (t + 1 < a.T) fetch_p(t + 1);
-          gather_pairs_tagged(zs, zld, zxw, Kp / 2, G * kCohort, Kl32 / 2, tag, a.err, tid, 512);
-        } else {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's z stores acknowledged
-          lds_barrier();
-          if (tid == 0) __hip_atomic_store(zflag + w, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (t + 1 < a.T) fetch_p(t + 1);
-          await_flags(zflag, W, tag, a.err, tid, 512);
-          lds_barrier();
-          copy_rows_coherent(zs, zld, zx, Kp, G * kCohort, Kl32 >> 3, tid, 512);
-        }
-      } else if (t + 1 < a.T) {
-        fetch_p(t + 1);
+        poll_units<kZUnits>(reinterpret_cast<float*>(zs), reinterpret_cast<const float*>(zt), zhalf * 2, zdst, zpend,
+                            a.err);
+        wait_memory();   // the emptied slots too, before this workgroup's h_t
       }
       lds_barrier();
       // ---- y = U . z for the wave's rows
       {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < kMaxKs; ++ks)
-          if (ks < nku)
-            acc = mfma(ua[ks], *reinterpret_cast<const bf16x8*>(zs + (zg * kCohort + li) * zld + 32 * ks + lk), acc);
+        for (int ks = 0; ks < KU; ++ks)
+          acc = mfma(ua[ks], *reinterpret_cast<const bf16x8*>(zs + (zg * kCohort + li) * zld + 32 * ks + lk), acc);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ys[(q * 32 + 16 * half + 4 * lq + r) * 17 + li] = acc[r];
+        for (int r = 0; r < 4; ++r) ys[(q * 32 + 16 * half16 + 4 * lq + r) * 17 + li] = acc[r];
       }
       lds_barrier();
       // ---- gates and cell update
@@ -612,20 +590,35 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
       c = sigmoid_b(yf) * c + sigmoid_b(yi) * tanh_b(yg);
       const float h = sigmoid_b(yo) * tanh_b(c);
       const int b = b0 + gs;
-      if (gu_live && b < a.B) {
-        a.h_out[(((size_t)level * a.T + t) * a.B + b) * H + gu] = h;
-        if (a.c_out && t == a.T - 1) a.c_out[((size_t)level * a.B + b) * H + gu] = c;
-      }
-      if (exch) {
+      // the group's very last h is read by nobody
+      const bool more = exch && (t + 1 < a.T || coh + slots < ncoh);
+      if (more) {
         // units in pairs (lanes l and l+16 hold units 2m and 2m+1 of one
         // sequence); a unit past H travels as zero
         const unsigned hb = gu_live ? (unsigned)bf16_bits(h) : 0u;
         const unsigned hn = (unsigned)__shfl_down((int)hb, 16, 64);
-        if ((lq & 1) == 0 && gu_live) store_pair_tagged(hxw + ((size_t)gs * Hp + gu) / 2, hb | (hn << 16), tag);
-        gather_pairs_tagged(hs, hld, hxw, Hp / 2, kCohort, (H + 1) / 2, tag, a.err, tid, 512);
+        if ((lq & 1) == 0) {
+          store_slot(reinterpret_cast<float*>(ht + hoff), full_pair(hb | (hn << 16)), near);
+          store_slot(reinterpret_cast<float*>(hx + (par ^ 1) * hhalf + hoff), kEmpty, near);
+        }
+      }
+      if (gu_live && b < a.B) {
+        a.h_out[(((size_t)level * a.T + t) * a.B + b) * H + gu] = h;
+        if (a.c_out && t == a.T - 1) a.c_out[((size_t)level * a.B + b) * H + gu] = c;
+      }
+      if (more) {
+        poll_units<kHUnits>(reinterpret_cast<float*>(hs), reinterpret_cast<const float*>(ht), hhalf * 2, hdst, hpend,
+                            a.err);
+        wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
       }
       lds_barrier();
     }
+  }
+  // z of every timestep was exchanged, so everyone has read the decision and
+  // everyone's words: open for the next start
+  if (exch && tid == 0) {
+    __hip_atomic_store(hand + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -643,14 +636,52 @@ int plan_batched_persistent(const BatchedArgs& a, int K, int* W, int* slots) {
   const int ncoh = (a.B + kCohort - 1) / kCohort;
   if (a.Hp > 32 * kMaxKs || Kl32 > 32 * kMaxKs || a.G * (Kl32 / 16) > 8 * w) return 0;
   if (w > a.max_wg || a.Bp % kCohort != 0) return 0;
-  if (persistent_lds(a.G, a.Hp, Kl32) > kLdsCap) return 0;
-  const int s = std::max(1, std::min(ncoh, a.max_wg / w));
-  const long long iters = (ncoh + s - 1) / s;
-  if (iters * a.T >= 65535) return 0;
+  if (persistent_lds(a.G, step_bucket(a.Hp / 32), step_bucket(Kl32 / 32)) > kLdsCap) return 0;
+  // whole groups per XCD (w <= 16)
+  const int fit = a.max_wg >= kXcds * kXcdCus ? kXcds * (kXcdCus / w) : a.max_wg / w;
+  const int s = std::max(1, std::min(ncoh, fit));
   *W = w;
   *slots = s;
   return 1;
 }
+
+namespace {
+
+template <int KH, int KU>
+hipError_t launch_persistent_steps(const BatchedArgs& p, int K, int Kl32, int level, int W, int slots, int nx,
+                                   hipStream_t stream) {
+  static bool attr = false;
+  if (!attr) {
+    const hipError_t e = hipFuncSetAttribute((const void*)batched_persistent_kernel<KH, KU>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  batched_persistent_kernel<KH, KU><<<dim3(nx * W * ((slots + nx - 1) / nx)), dim3(512), persistent_lds(p.G, KH, KU),
+                                      stream>>>(p, K, Kl32, level, W, slots, nx);
+  return hipGetLastError();
+}
+
+template <int KH>
+hipError_t launch_persistent_h(const BatchedArgs& p, int K, int Kl32, int level, int W, int slots, int nx,
+                               hipStream_t stream) {
+  switch (step_bucket(Kl32 / 32)) {
+    case 4: return launch_persistent_steps<KH, 4>(p, K, Kl32, level, W, slots, nx, stream);
+    case 8: return launch_persistent_steps<KH, 8>(p, K, Kl32, level, W, slots, nx, stream);
+    default: return launch_persistent_steps<KH, 16>(p, K, Kl32, level, W, slots, nx, stream);
+  }
+}
+
+hipError_t launch_persistent(const BatchedArgs& p, int K, int Kl32, int level, int W, int slots, int nx,
+                             hipStream_t stream) {
+  switch (step_bucket(p.Hp / 32)) {
+    case 4: return launch_persistent_h<4>(p, K, Kl32, level, W, slots, nx, stream);
+    case 8: return launch_persistent_h<8>(p, K, Kl32, level, W, slots, nx, stream);
+    default: return launch_persistent_h<16>(p, K, Kl32, level, W, slots, nx, stream);
+  }
+}
+
+}  // namespace
 
 hipError_t launch_batched(const BatchedArgs& a, const int* levels, int n_levels, hipStream_t stream) {
   if (a.Bp % kBatchAlign != 0 || a.Bp < a.B || a.Bp > (1 << 20) || a.Dp % kPanelDAlign != 0 || a.Dp < a.D ||
@@ -686,13 +717,11 @@ hipError_t launch_batched(const BatchedArgs& a, const int* levels, int n_levels,
     const int Kl32 = ((K + 31) / 32) * 32;
     p.rows = a.G * Kl32;
     int W = 0, slots = 0;
-    if (a.zx && a.hx && a.zflag && a.err && plan_batched_persistent(p, K, &W, &slots)) {
+    if (a.zx && a.hx && a.ctl && a.err && plan_batched_persistent(p, K, &W, &slots)) {
       // one launch sequence number per level: its tags differ from every earlier launch's
       p.tag_base = a.tag_base + ((unsigned)l << 16);
-      const int ztag = (a.G * Kl32 <= a.ztag_terms) ? 1 : 0;
-      batched_persistent_kernel<<<dim3(W * slots), dim3(512), persistent_lds(a.G, a.Hp, Kl32), stream>>>(
-          p, K, Kl32, l, W, slots, ztag);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+      const int nx = a.ncu >= kXcds * kXcdCus ? kXcds : 1;
+      if ((e = launch_persistent(p, K, Kl32, l, W, slots, nx, stream)) != hipSuccess) return e;
       continue;
     }
     if (init) {

@@ -211,12 +211,15 @@ __device__ __forceinline__ void publish_slot(float* p, float v, bool near) {
 
 // Poll the 16-byte units tid + 512 r of src (uniform; `bytes` long) whose bit
 // r is set in `pending` until none of their slots is empty; unit r goes to
-// dst + map[r] (LDS, 16-byte aligned).  Agent-scope loads pass the L1 by.
-// Bounded: past the spin limit, or once another wait has failed, the failure
-// is recorded and the missing values read 0.
-template <int kMaxUnits>
+// dst + map[r] (LDS, 16-byte aligned).  Agent-scope loads pass the L1 by.  The
+// first round loads every unit without a branch, so that each is looked at
+// as it arrives; later rounds load what is missing.  Bounded: past the spin
+// limit, or once another wait has failed, the failure is recorded and the
+// missing values read 0.
+template <int kUnits>
 __device__ __forceinline__ void poll_units(float* dst, const float* src, int bytes, const int* map, unsigned pending,
                                            unsigned* err) {
+  if (!pending) return;
   const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(addr >> 32));
@@ -224,16 +227,32 @@ __device__ __forceinline__ void poll_units(float* dst, const float* src, int byt
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(base, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
   const int tid = threadIdx.x;
+  auto load = [&](int r) {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + kThreads * r) * 16, 0, 16 /* sc1 */);
+  };
+  // empty is the largest unsigned value
+  auto full = [](const u32x4& w) { return max(max(w[0], w[1]), max(w[2], w[3])) != kEmpty; };
+  {
+    u32x4 w[kUnits];
+#pragma unroll
+    for (int r = 0; r < kUnits; ++r) w[r] = load(r);   // past the end: zeros, not looked at
+#pragma unroll
+    for (int r = 0; r < kUnits; ++r)
+      if (((pending >> r) & 1u) && full(w[r])) {
+        *reinterpret_cast<u32x4*>(dst + map[r]) = w[r];
+        pending &= ~(1u << r);
+      }
+  }
   unsigned spins = 0;
   while (pending) {
-    u32x4 w[kMaxUnits];
+    asm volatile("" ::: "memory");   // the loads of this round are new ones
+    u32x4 w[kUnits];
 #pragma unroll
-    for (int r = 0; r < kMaxUnits; ++r)
-      if ((pending >> r) & 1u) w[r] = __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + kThreads * r) * 16, 0, 16 /* sc1 */);
-    asm volatile("" ::: "memory");   // the loads of the next round are new ones
+    for (int r = 0; r < kUnits; ++r)
+      if ((pending >> r) & 1u) w[r] = load(r);
 #pragma unroll
-    for (int r = 0; r < kMaxUnits; ++r)
-      if (((pending >> r) & 1u) && w[r][0] != kEmpty && w[r][1] != kEmpty && w[r][2] != kEmpty && w[r][3] != kEmpty) {
+    for (int r = 0; r < kUnits; ++r)
+      if (((pending >> r) & 1u) && full(w[r])) {
         *reinterpret_cast<u32x4*>(dst + map[r]) = w[r];
         pending &= ~(1u << r);
       }
@@ -241,7 +260,7 @@ __device__ __forceinline__ void poll_units(float* dst, const float* src, int byt
         (spins >= kSpinLimit || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
       __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-      for (int r = 0; r < kMaxUnits; ++r)
+      for (int r = 0; r < kUnits; ++r)
         if ((pending >> r) & 1u) *reinterpret_cast<u32x4*>(dst + map[r]) = u32x4{0u, 0u, 0u, 0u};
       break;
     }

@@ -230,11 +230,11 @@ hipError_t launch_clear_u64(unsigned long long* p, size_t n, hipStream_t stream)
 //   x      [T][B][D] fp32           h0, c0 [B][H] fp32 or null
 //   h_out  [L][T][B][H]             c_out  [L][B][H] or null
 //   sigma  [N*G] fp32               term tau = n*G + g
-//   Vx     [rows][Dp] bf16          x-part of prune(v) of term tau (zeros off the mask)
+//   Vx     [rows][Dp] bf16          x-part of prune(v), term n of group g at row g*Kp + n (zeros off the mask)
 //   Vh     [rows][Hp] bf16          h-part of prune(v) of term tau
 //   Ut     [4H][Kp] bf16            Ut[o][n] = u of term (n, g(o)) at row o within its group
 //   bias   [4H] fp32
-//   P      [T*Bp][pld] fp32         x-part projections: P[t*Bp + b][tau] (workspace)
+//   P      [T*Bp][pld] fp32         x-part projections: term n of group g at column g*(pld/G) + n (workspace)
 //   Z      [G][Bp][Kp] bf16         sigma * s of the current timestep (workspace)
 //   hb     [Bp][Hp] bf16            h of the previous timestep (workspace)
 //   c      [Bp][H] fp32             cell state (workspace)
@@ -264,14 +264,12 @@ struct BatchedArgs {
   int xvec;        // 1: x rows may be read as 16-byte vectors (D % 4 == 0, x 16-byte aligned)
   // persistent recurrence (one launch per level instead of T kernel pairs);
   // null zx selects the per-timestep kernels
-  uint16_t* zx;      // [slots][2*G*16*Kp] bf16 slots: z of a cohort's current timestep, as
-                     // [G*16][Kp] bf16 behind flags or [G*16][Kp/2] tagged 64-bit words
-  uint16_t* hx;      // [slots][2*16*Hp]: h of a cohort's current timestep, [16][Hp/2] tagged words
-  unsigned* zflag;   // [slots][W]: workgroup w's tag once its (untagged) z tile is stored
+  uint16_t* zx;      // [slots][2*G*16*Kp] bf16: z of a cohort's timesteps t and t-1
+  uint16_t* hx;      // [slots][2*16*Hp]: h of them
+  unsigned long long* ctl;   // [slots][kCtlWords]: start words of the groups, all zero between launches
   unsigned* err;     // set when a bounded wait expires
   unsigned tag_base; // launch sequence << 16 of level 0; level l uses tag_base + (l << 16)
   int max_wg;        // workgroups that may be resident at once (one per compute unit)
-  int ztag_terms;    // z travel as tagged words when G * K (rounded up to 32) <= this
   // x-projection with its contraction over D split in xsplit parts when it
   // has fewer output tiles than the device has compute units: each part's
   // tile goes to Ppart[part] ([T*Bp][pld]), then the parts are added in part
@@ -298,9 +296,9 @@ constexpr int kCohort = 16;
 // (32 hidden units each), `slots` cohorts in flight.  Returns 0 when the
 // shape does not fit (then the per-timestep kernels run): H and K each at
 // most 512 (their contraction steps are held in registers), at most one
-// h-projection tile of 16 terms per wave, a cohort's workgroups resident at
-// once, and fewer than 2^16 tagged timesteps per launch.  Exchange sizes (in
-// 16-bit elements): zx slots*2*G*16*Kp, hx slots*2*16*Hp; flags slots*W.
+// h-projection tile of 16 terms per wave, and a cohort's workgroups resident
+// at once (whole groups per XCD).  Exchange sizes (in 16-bit elements): zx
+// slots*2*G*16*Kp, hx slots*2*16*Hp; start words slots*kCtlWords.
 int plan_batched_persistent(const BatchedArgs& a, int K, int* W, int* slots);
 
 // Exact (dense) LSTM: x [T][B][D], h0, c0 [B][H] or null, h_out [T][B][H],

@@ -1,0 +1,48 @@
+"""The persistent batched recurrence at the edges of its register buckets (4, 8
+and 16 contraction steps of 32 over the units and over the terms), of its
+groups (one workgroup, several groups per XCD, more cohorts than groups) and
+with one group of terms for all gates; against the oracle with bf16 operands,
+and one sequence's output beside different numbers of others bit for bit."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1905_00689_amd import synth
+from paper_1905_00689_amd import binding as B
+
+from .gpu_helpers import exported_factors, rel_err, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+@pytest.mark.parametrize("H,rank,G,T,Bs", [
+    (32, 20, 4, 3, (16, 300)),       # one workgroup per cohort
+    (129, 129, 4, 3, (17, 90)),      # five contraction steps either way
+    (257, 33, 4, 2, (5, 420)),       # nine steps over the units; more cohorts than groups fit
+    (128, 128, 1, 1, (33, 70)),      # one timestep
+    (512, 257, 4, 3, (16, 40)),
+])
+def test_buckets_and_groups(H, rank, G, T, Bs):
+    D = 40
+    w = synth.make(D, H, T, max(Bs), index=99)
+    say("batched groups H", H, "rank", rank, "G", G)
+    m = B.approx_lstm_prepare(w.W[:, :D], w.W[:, D:], w.b, D, H, rank, prune_ratio=0.5, groups=G, factor_dtype=1,
+                              flags=B.FLAG_DEVICE_FACTORISE)
+    f = exported_factors(m)
+    levels = [rank, 3]
+    first = None
+    for Bn in Bs:
+        x = np.ascontiguousarray(w.x[:, :Bn])
+        h, c = run_gpu(m, x, levels, want_c=True)
+        n = min(Bn, 24)
+        ho, co = oracle.run(f, w.b, np.ascontiguousarray(x[:, :n]), levels, operand_round="bf16")
+        for j in range(len(levels)):
+            assert rel_err(h[j:j + 1, :, :n], ho[j:j + 1]) < TOL, (Bn, levels[j])
+            assert np.abs(c[j, :n] - co[j]).max() < TOL * max(1.0, np.abs(co[j]).max())
+        again, _ = run_gpu(m, x, levels)
+        assert np.array_equal(h, again)
+        # the last sequence too: a cohort that ran after another on its group
+        hl, _ = oracle.run(f, w.b, np.ascontiguousarray(x[:, -1:]), levels, operand_round="bf16")
+        assert rel_err(h[:, :, -1:], hl) < TOL
