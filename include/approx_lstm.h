@@ -69,6 +69,10 @@ typedef enum {
                                                        pruned on its own and the pruning error never
                                                        corrected by a later term */
 
+#define APPROX_LSTM_FLAG_STEPWISE       (1ull << 4) /* device factorisation with one kernel per step of a
+                                                       Lanczos iteration also where one launch would run
+                                                       a whole block of them (for tests: same bits) */
+
 typedef struct approx_lstm_model approx_lstm_model;   /* opaque */
 
 typedef struct {

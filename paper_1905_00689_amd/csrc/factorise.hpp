@@ -29,6 +29,7 @@ struct FactoriseOptions {
   int max_lanczos = 0;          // 0: up to the Gram size
   bool residual = true;         // false: each term is deflated with its whole v (successive
                                 // approximations of the original matrix), not its pruned v
+  bool fused = true;            // device: blocks of Lanczos iterations in one launch where they fit
 };
 
 // Factorise W (rows x cols, row-major, float64) into `rank` terms keeping
@@ -49,6 +50,9 @@ void store_term(GroupFactors& out, int t, double s, std::vector<double>& uu, std
 // tridiag_top: largest eigenvalue and unit eigenvector s of the m x m
 // symmetric tridiagonal matrix with diagonal a and off-diagonal b.
 double tridiag_top(const double* a, const double* b, int m, std::vector<double>& s);
+// tridiag_tops: tridiag_top of `count` matrices of size m, a thread for each.
+void tridiag_tops(int count, const double* const* a, const double* const* b, int m, std::vector<double>* s,
+                  double* theta);
 // tridiag_second: the second largest eigenvalue and a unit eigenvector.
 double tridiag_second(const double* a, const double* b, int m, std::vector<double>& s);
 // lanczos_start: the fixed unit start vector of every host Lanczos solve

@@ -14,7 +14,8 @@
 //     factorisation's fixed start and each later one from the previous
 //     solve's top and second Ritz vectors plus that fixed vector (a warm
 //     start: fewer iterations to the same tolerance), in blocks of 8 iterations
-//     captured once as a HIP graph; the host reads the tridiagonal
+//     (one launch, or for large Gram matrices kernels captured once as a HIP
+//     graph); the host reads the tridiagonal
 //     coefficients after each block (one block behind the device) and solves
 //     the small tridiagonal eigenproblem for the convergence test and the
 //     Ritz vector.  The test runs every 8 iterations where the host
@@ -37,6 +38,7 @@
 #include <vector>
 
 #include "factorise.hpp"
+#include "device_common.hpp"
 
 namespace alstm {
 
@@ -225,12 +227,13 @@ __global__ void __launch_bounds__(kFT) combine_kernel(const double* __restrict__
 
 // After the reorthogonalisation of w: beta_k = |w|, q_{k+1} = w / beta_k (0
 // when beta_k is 0), alpha_k = q_k . (G q_k) (the first pass's coefficient
-// of q_k), and k advances.  One workgroup per group.
+// of q_k), and k advances.  alpha, beta and prog are host memory.  One
+// workgroup per group.
 __global__ void __launch_bounds__(kFT) lanczos_next_kernel(const double* __restrict__ w, double* __restrict__ Q,
                                                             const double* __restrict__ c1, double* __restrict__ alpha,
                                                             double* __restrict__ beta, int* __restrict__ kk, int kmax,
                                                             int n, size_t sw, size_t sQ, size_t sc,
-                                                            const int* __restrict__ act) {
+                                                            const int* __restrict__ act, int* __restrict__ prog) {
   __shared__ double red[kFW];
   const int g = blockIdx.z;
   if (!act[g]) return;
@@ -246,6 +249,319 @@ __global__ void __launch_bounds__(kFT) lanczos_next_kernel(const double* __restr
     alpha[g * sc + k] = c1[g * sc + k];
     beta[g * sc + k] = b;
     kk[g] = k + 1;
+    prog[g] = k + 1;
+  }
+}
+
+// ---- kIterBlock Lanczos iterations in one launch, for Gram matrices of up to
+// kFusedN rows: one group of P workgroups per gate group, on one XCD each.  The
+// steps are those of the kernels above, every sum in their order (the results
+// are theirs bit for bit); what they leave is the kernel boundaries, 4-5 us
+// each, of which an iteration has six.  Workgroup j keeps its rows of G and the
+// same columns of the basis in LDS, every wave its basis vectors for the dot
+// products in registers.  Five exchanges per iteration (w, the coefficients,
+// w, the coefficients, w) of doubles in slots that are empty until written (see
+// poll_units; here a slot is 8 bytes), each with a buffer of its own that is
+// emptied when everyone is past reading it: the first w and its coefficients
+// once the second w of everyone is here, the second once the third is, the
+// third once the next first is.  The clearing wave always publishes rows of the
+// next w, after its stores have completed, so whoever polls a buffer again has
+// heard from every workgroup that cleared it.  MI355X, four groups, a block of
+// 8 iterations: 45 us at n = 256 and 51 at n = 512, 8 to 10 of it for the
+// launch's start; the kernels above take 22 us per iteration at n = 256 (six of
+// 3 to 5 us).  Factorising D = 512, H = 256 to rank 16: 29.8 -> 15.1 ms, 13.1
+// with the tridiagonal eigenpairs of the groups side by side on the host.
+constexpr int kFusedN = 512;
+constexpr int kFusedRows = 16;                       // rows of a workgroup, at most
+constexpr unsigned long long kEmpty64 = ~0ull;       // a NaN that publish64 never stores
+constexpr unsigned kFusedWait = 200000u;             // wall ticks a group waits to be present (2 ms)
+
+struct FusedArgs {
+  const double* G;
+  double* Q;
+  int* kk;                    // [G] iteration index
+  const int* act;
+  double *alpha, *beta;       // host memory
+  int* prog;                  // host memory: [G] iterations done
+  unsigned long long* ex;     // [G][5][kFusedN] slots
+  unsigned long long* ctl;    // start words
+  size_t sG, sQ, sc;
+  int groups, n, kmax, P, rows;   // rows per workgroup (every one of the P has some)
+  unsigned tag;
+};
+
+__device__ __forceinline__ void publish64(unsigned long long* p, double v, bool near) {
+  unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  if (b == kEmpty64) b = 0x7FF8000000000000ull;
+  if (near) __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void clear64(unsigned long long* p, bool near) {
+  if (near) __hip_atomic_store(p, kEmpty64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else __hip_atomic_store(p, kEmpty64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// dst[i] (LDS) = slot i of src for i < cnt (at most 1024), two to a load.
+// Bounded as poll_units: past the spin limit the wait is given up, and *bad
+// (LDS) tells the workgroup.
+__device__ __forceinline__ void poll64(double* dst, const unsigned long long* src, int cnt, int* bad) {
+  const int u = threadIdx.x;
+  if (2 * u >= cnt) return;
+  const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(addr >> 32));
+  void* base = reinterpret_cast<void*>(((unsigned long long)hi << 32) | lo);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, kFusedN * 8, 0x00020000);
+  const bool two = 2 * u + 1 < cnt;
+  unsigned spins = 0;
+  while (true) {
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, u * 16, 0, 16 /* sc1 */);
+    asm volatile("" ::: "memory");
+    const unsigned long long a = ((unsigned long long)w[1] << 32) | w[0], b = ((unsigned long long)w[3] << 32) | w[2];
+    if (a != kEmpty64 && (!two || b != kEmpty64)) {
+      dst[2 * u] = __builtin_bit_cast(double, a);
+      if (two) dst[2 * u + 1] = __builtin_bit_cast(double, b);
+      return;
+    }
+    if (++spins >= kSpinLimit) {
+      *bad = 1;
+      return;
+    }
+  }
+}
+
+// wave_sum_f64 with lane moves that stay in the registers: halves and rows
+// swapped (the lanes 32 and 16 apart), then moves within a row; the pairs, and
+// so the bits, are the same.
+__device__ __forceinline__ double wave_sum_f64_fast(double v) {
+  auto both = [](double x, auto swap) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    unsigned l0 = (unsigned)b, h0 = (unsigned)(b >> 32);
+    const auto l = swap(l0), h = swap(h0);
+    const double p = __builtin_bit_cast(double, ((unsigned long long)h[0] << 32) | l[0]);
+    const double q = __builtin_bit_cast(double, ((unsigned long long)h[1] << 32) | l[1]);
+    return p + q;
+  };
+  v = both(v, [](unsigned x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+  v = both(v, [](unsigned x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+  auto dpp = [](double x, auto move) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const unsigned l = (unsigned)move((int)(unsigned)b), h = (unsigned)move((int)(unsigned)(b >> 32));
+    return x + __builtin_bit_cast(double, ((unsigned long long)h << 32) | l);
+  };
+  v = dpp(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false); });   // 8 apart
+  v = dpp(v, [](int x) {                                                                         // 4 apart
+    return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, false), 0x1B, 0xF, 0xF,
+                                       false);
+  });
+  v = dpp(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false); });    // 2 apart
+  v = dpp(v, [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false); });    // 1 apart
+  return v;
+}
+
+// LDS doubles: rows of G, columns of the basis, q, w, coefficients, partials
+__host__ __device__ inline size_t fused_lds(int n, int kmax, int rows) {
+  return (size_t)rows * n + (size_t)(kmax + 1) * kFusedRows + 2 * (size_t)(n + 1) + kmax + 2 + 16 * kFusedRows + kFW + 2;
+}
+
+__global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
+  extern __shared__ __align__(16) double ld[];
+  const int g = blockIdx.x % kXcds, j = blockIdx.x / kXcds;   // group g on XCD g
+  const int n = a.n, kmax = a.kmax, P = a.P;
+  if (g >= a.groups || !a.act[g]) return;
+  const int k0 = a.kk[g];
+  if (k0 >= kmax) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r0 = j * a.rows, rc = max(0, min(a.rows, n - r0));
+  double* Gr = ld;                                  // [rows][n]
+  double* Qt = Gr + (size_t)a.rows * n;             // [kmax + 1][kFusedRows]: basis at the owned rows
+  double* q = Qt + (size_t)(kmax + 1) * kFusedRows; // q_k
+  double* w = q + n + 1;
+  double* c = w + n + 1;                            // coefficients
+  double* part = c + kmax + 2;                      // [16][kFusedRows]
+  double* red = part + 16 * kFusedRows;
+  int* flags = reinterpret_cast<int*>(red + kFW);   // start mode, a wait given up
+  unsigned long long* ex = a.ex + (size_t)g * 5 * kFusedN;
+  unsigned long long *xw1 = ex, *xw2 = ex + kFusedN, *xw3 = ex + 2 * kFusedN, *xc1 = ex + 3 * kFusedN,
+                     *xc2 = ex + 4 * kFusedN;
+  unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
+  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  const int cn = (kmax - j + P - 1) / P;            // coefficient slots j + P*i cleared here
+
+  double* Qg = a.Q + g * a.sQ;
+  if (wave == kFW - 1) {
+    for (int i = lane; i < rc; i += 64) {
+      clear64(xw1 + r0 + i, false);
+      clear64(xw2 + r0 + i, false);
+      clear64(xw3 + r0 + i, false);
+    }
+    for (int i = lane; i < cn; i += 64) {
+      clear64(xc1 + j + P * i, false);
+      clear64(xc2 + j + P * i, false);
+    }
+    wait_memory();
+    const int mode = group_start(hand, decide, j, P, a.tag, kFusedWait);
+    if (lane == 0) {
+      flags[0] = mode;
+      flags[1] = 0;
+    }
+  }
+  for (int i = tid; i < rc * n; i += kFT) Gr[i] = a.G[g * a.sG + (size_t)r0 * n + i];
+  for (int i = tid; i < n; i += kFT) q[i] = Qg[(size_t)k0 * n + i];
+  for (int i = tid; i < (k0 + 1) * kFusedRows; i += kFT) {
+    const int v = i / kFusedRows, r = i % kFusedRows;
+    Qt[i] = r < rc ? Qg[(size_t)v * n + r0 + r] : 0.0;
+  }
+  // this wave's basis vectors wid and wid + nw
+  const int wid = j * kFW + wave, nw = P * kFW;
+  double qr[2][8];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int v = wid + nw * s, i = lane + 64 * e;
+      qr[s][e] = (v <= k0 && i < n) ? Qg[(size_t)v * n + i] : 0.0;
+    }
+  __syncthreads();
+  if (flags[0] >= kAlone) {   // not all resident: nothing done, the host sees no progress
+    group_leave(hand, decide, P);
+    return;
+  }
+  const bool near = flags[0] == kNear;
+
+  // c[j] = q_j . w of the waves' basis vectors (dots_kernel's order), published
+  auto dots = [&](int k, unsigned long long* xc) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int v = wid + nw * s;
+      if (v > k) break;
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int i = lane + 256 * h;
+        if (i + 192 < n) {
+          a0 = fma(qr[s][4 * h], w[i], a0);
+          a1 = fma(qr[s][4 * h + 1], w[i + 64], a1);
+          a2 = fma(qr[s][4 * h + 2], w[i + 128], a2);
+          a3 = fma(qr[s][4 * h + 3], w[i + 192], a3);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (i + 64 * e < n) a0 = fma(qr[s][4 * h + e], w[i + 64 * e], a0);
+        }
+      }
+      const double acc = wave_sum_f64_fast((a0 + a1) + (a2 + a3));
+      if (lane == 0) publish64(xc + v, acc, near);
+    }
+  };
+  // w[i] -= sum_j c[j] Q[j][i] of the owned rows (combine_kernel's order: 16
+  // chains, 8 waves of two), published by the first wave
+  auto combine = [&](int k, unsigned long long* xw) {
+    const int i = tid % kFusedRows, r = tid / kFusedRows;
+    if (r < 16) {
+      double acc = 0.0;
+      for (int v = r; v <= k; v += 16) acc = fma(c[v], Qt[v * kFusedRows + i], acc);
+      part[r * kFusedRows + i] = acc;
+    }
+    if (wave == 0) wait_memory();   // the slots cleared since the last publication
+    lds_barrier();
+    if (tid < rc) {
+      double s = 0.0;
+#pragma unroll
+      for (int v = 0; v < 8; ++v) s += part[v * kFusedRows + tid] + part[(v + 8) * kFusedRows + tid];
+      publish64(xw + r0 + tid, w[r0 + tid] - s, near);
+    }
+    lds_barrier();                  // the published values read w before it is overwritten
+  };
+  auto clear_rows = [&](unsigned long long* xw) {
+    if (wave == 0 && lane < rc) clear64(xw + r0 + lane, near);
+  };
+  auto clear_coef = [&](unsigned long long* xc) {
+    if (wave == 0)
+      for (int i = lane; i < cn; i += 64) clear64(xc + j + P * i, near);
+  };
+
+  int k = k0;
+  for (int it = 0; it < kIterBlock && k < kmax; ++it, ++k) {
+    if (it > 0) {   // everyone's third w of the last iteration is here
+      clear_rows(xw2);
+      clear_coef(xc2);
+    }
+    // w = G q_k (symv_kernel's order)
+    for (int r = wave; r < rc; r += kFW) {
+      const double* row = Gr + (size_t)r * n;
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+      int i = lane;
+      for (; i + 192 < n; i += 256) {
+        a0 = fma(row[i], q[i], a0);
+        a1 = fma(row[i + 64], q[i + 64], a1);
+        a2 = fma(row[i + 128], q[i + 128], a2);
+        a3 = fma(row[i + 192], q[i + 192], a3);
+      }
+      for (; i < n; i += 64) a0 = fma(row[i], q[i], a0);
+      const double acc = wave_sum_f64_fast((a0 + a1) + (a2 + a3));
+      if (wave == 0) wait_memory();
+      if (lane == 0) publish64(xw1 + r0 + r, acc, near);
+    }
+    poll64(w, xw1, n, flags + 1);
+    lds_barrier();
+    if (it > 0) clear_rows(xw3);
+    dots(k, xc1);
+    poll64(c, xc1, k + 1, flags + 1);
+    lds_barrier();
+    const double al = c[k];
+    combine(k, xw2);
+    poll64(w, xw2, n, flags + 1);
+    lds_barrier();
+    clear_rows(xw1);
+    clear_coef(xc1);
+    dots(k, xc2);
+    poll64(c, xc2, k + 1, flags + 1);
+    lds_barrier();
+    combine(k, xw3);
+    poll64(w, xw3, n, flags + 1);
+    lds_barrier();
+    // beta = |w|, q_{k+1} = w / beta (lanczos_next_kernel's order; n <= 512: one
+    // element per thread), in every workgroup
+    double ss = 0.0;
+    if (tid < n) ss = fma(w[tid], w[tid], ss);
+    ss = wave_sum_f64_fast(ss);
+    if (lane == 0) red[wave] = ss;
+    lds_barrier();
+    double bs = 0.0;
+#pragma unroll
+    for (int v = 0; v < kFW; ++v) bs += red[v];
+    const double be = sqrt(bs);
+    if (tid < n) {
+      const double x = be > 0.0 ? w[tid] / be : 0.0;
+      q[tid] = x;
+      if (tid >= r0 && tid < r0 + rc) {
+        Qg[(size_t)(k + 1) * n + tid] = x;
+        Qt[(k + 1) * kFusedRows + tid - r0] = x;
+      }
+    }
+    if (j == 0 && tid == 0) {
+      a.alpha[g * a.sc + k] = al;
+      a.beta[g * a.sc + k] = be;
+    }
+    lds_barrier();
+    if (flags[1]) break;   // a bounded wait was given up: the host sees no progress
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (k + 1 == wid + nw * s) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qr[s][e] = lane + 64 * e < n ? q[lane + 64 * e] : 0.0;
+      }
+  }
+  if (tid == 0) {
+    // (everyone has published several w since the start)
+    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (j == 0) {
+      a.kk[g] = k;
+      a.prog[g] = k;
+      __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
@@ -372,7 +688,7 @@ struct Resources {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
-  double* coef = nullptr;   // pinned host: two slots of [alpha | beta] for every group
+  double* coef = nullptr;   // pinned host: [alpha | beta] for every group, then the iterations done
   void* stage = nullptr;    // pinned host: the per-term uploads and reads (see factorise_groups_device)
   DevBuf buf;
   ~Resources() {
@@ -419,7 +735,7 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   FD_TRY(hipStreamCreateWithFlags(&res.stream, hipStreamNonBlocking), "hipStreamCreate");
   hipStream_t stream = res.stream;
   DevBuf& buf = res.buf;
-  double *dM, *dG, *dQ, *dw, *dc1, *dc2, *dal, *dbe, *dy, *dx, *dpart, *da, *db, *dw2, *dsb, *dq0, *dqf, *dritz, *dritz2;
+  double *dM, *dG, *dQ, *dw, *dc1, *dc2, *dy, *dx, *dpart, *da, *db, *dw2, *dsb, *dq0, *dqf, *dritz, *dritz2;
   int *dact, *dact2, *dcnt, *dk;
   FD_TRY(buf.alloc(dM, G * sM), "hipMalloc(residual)");
   FD_TRY(buf.alloc(dG, G * sG), "hipMalloc(Gram)");
@@ -427,8 +743,6 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   FD_TRY(buf.alloc(dw, (size_t)G * n), "hipMalloc");
   FD_TRY(buf.alloc(dc1, G * sc), "hipMalloc");
   FD_TRY(buf.alloc(dc2, G * sc), "hipMalloc");
-  FD_TRY(buf.alloc(dal, G * sc), "hipMalloc");
-  FD_TRY(buf.alloc(dbe, G * sc), "hipMalloc");
   FD_TRY(buf.alloc(dritz, G * sc), "hipMalloc");
   FD_TRY(buf.alloc(dy, (size_t)G * n), "hipMalloc");
   FD_TRY(buf.alloc(dx, (size_t)G * m), "hipMalloc");
@@ -444,8 +758,43 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   FD_TRY(buf.alloc(dact, (size_t)G), "hipMalloc");
   FD_TRY(buf.alloc(dcnt, (size_t)G), "hipMalloc");
   FD_TRY(buf.alloc(dk, (size_t)G), "hipMalloc");
-  FD_TRY(hipHostMalloc((void**)&res.coef, (size_t)4 * G * sc * sizeof(double), hipHostMallocDefault),
+  // alpha and beta of every group, and the iterations done: written by the
+  // device as it goes (entries are only added), read after a block's event
+  FD_TRY(hipHostMalloc((void**)&res.coef, (size_t)2 * G * sc * sizeof(double) + G * sizeof(int), hipHostMallocDefault),
          "hipHostMalloc");
+  double *hal = res.coef, *hbe = hal + G * sc;
+  int* hprog = reinterpret_cast<int*>(hbe + G * sc);
+  double *dal = nullptr, *dbe = nullptr;   // their device addresses
+  int* dprog = nullptr;
+  {
+    void* p = nullptr;
+    FD_TRY(hipHostGetDevicePointer(&p, res.coef, 0), "hipHostGetDevicePointer");
+    dal = static_cast<double*>(p);
+    dbe = dal + G * sc;
+    dprog = reinterpret_cast<int*>(dbe + G * sc);
+  }
+  // one launch per block of iterations where the Gram rows of a group fit the
+  // LDS of one XCD, else one kernel per step
+  FusedArgs fa{};
+  int device = 0, num_cu = 0;
+  FD_TRY(hipGetDevice(&device), "hipGetDevice");
+  FD_TRY(hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, device), "compute units");
+  bool fused = opt.fused && n <= kFusedN && num_cu >= kXcds * kXcdCus;
+  if (fused) {
+    fa.groups = G; fa.n = n; fa.kmax = kmax;
+    fa.rows = (n + std::min(kXcdCus, (n + 7) / 8) - 1) / std::min(kXcdCus, (n + 7) / 8);
+    fa.P = (n + fa.rows - 1) / fa.rows;
+    const size_t words = (size_t)G * 5 * kFusedN + (size_t)kXcds * kCtlWords;
+    FD_TRY(buf.alloc(fa.ex, words), "hipMalloc(Lanczos exchange)");
+    fa.ctl = fa.ex + (size_t)G * 5 * kFusedN;
+    FD_TRY(hipMemsetAsync(fa.ctl, 0, sizeof(unsigned long long) * kXcds * kCtlWords, stream), "clear start words");
+    fa.G = dG; fa.Q = dQ; fa.kk = dk; fa.act = dact; fa.alpha = dal; fa.beta = dbe; fa.prog = dprog;
+    fa.sG = sG; fa.sQ = sQ; fa.sc = sc;
+    FD_TRY(hipFuncSetAttribute((const void*)lanczos_fused_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kLdsCap),
+           "hipFuncSetAttribute");
+    fused = fused_lds(n, kmax, fa.rows) * 8 <= kLdsCap;
+  }
   for (hipEvent_t& e : res.ev) FD_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
 
   {  // residual M of every group, and the fixed Lanczos start
@@ -470,8 +819,13 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   }
 
   // kIterBlock Lanczos iterations as one graph: w = G q_k, two classical
-  // Gram-Schmidt passes against q_0 .. q_k, then beta_k, q_{k+1}, k + 1
-  {
+  // Gram-Schmidt passes against q_0 .. q_k, then beta_k, q_{k+1}, k + 1 (made
+  // when first needed)
+  auto stepwise_block = [&]() -> int {
+    if (res.exec) {
+      FD_TRY(hipGraphLaunch(res.exec, stream), "Lanczos block");
+      return 0;
+    }
     FD_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeRelaxed), "hipStreamBeginCapture");
     const unsigned dgx = (unsigned)std::min<size_t>(cdiv(kmax, kFW), kDotGroups);
     for (int it = 0; it < kIterBlock; ++it) {
@@ -483,13 +837,15 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
       combine_kernel<<<dim3(cdiv(n, 64), 1, G), dim3(kFT), 0, stream>>>(dQ, dc2, dw, dk, 1, kmax, n, sQ, sc, n, 0,
                                                                         dact);
       lanczos_next_kernel<<<dim3(1, 1, G), dim3(kFT), 0, stream>>>(dw, dQ, dc1, dal, dbe, dk, kmax, n, n, sQ, sc,
-                                                                   dact);
+                                                                   dact, dprog);
     }
     hipError_t e = hipStreamEndCapture(stream, &res.graph);
     if (e == hipSuccess) e = hipGetLastError();
     FD_TRY(e, "capture of the Lanczos iterations");
     FD_TRY(hipGraphInstantiate(&res.exec, res.graph, nullptr, nullptr, 0), "hipGraphInstantiate");
-  }
+    FD_TRY(hipGraphLaunch(res.exec, stream), "Lanczos block");
+    return 0;
+  };
 
   // Pinned staging for the per-term transfers, one region per purpose, so
   // that the copies run asynchronously and no extra synchronisation is
@@ -529,7 +885,8 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   std::vector<double> tau(G, 0.0), hy((size_t)G * n), hx((size_t)G * m);
   std::vector<double> ha((size_t)G * n), hb((size_t)G * m), hsb(2 * G), hritz(G * sc, 0.0), hritz2(G * sc, 0.0);
   std::vector<int> hcnt(G), idx(cols), has2(G, 0);
-  std::vector<double> uu(rows), vv(cols), s, s2;
+  std::vector<double> uu(rows), vv(cols), s, s2, top_theta(G);
+  std::vector<std::vector<double>> top_s(G);
 
   for (int t = 0; t < rank; ++t) {
     if (std::none_of(live.begin(), live.end(), [](int v) { return v != 0; })) break;
@@ -546,13 +903,17 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
     start_kernel<<<dim3(cdiv(n, kFT), 1, G), dim3(kFT), 0, stream>>>(dQ, dq0, dk, n, sQ, dact);
     FD_TRY(hipGetLastError(), "start_kernel");
     const int nblk = (kmax + kIterBlock - 1) / kIterBlock;
-    auto enqueue_block = [&](int b) -> hipError_t {
-      hipError_t e = hipGraphLaunch(res.exec, stream);
-      double* slot = res.coef + (size_t)(b & 1) * 2 * G * sc;
-      if (e == hipSuccess) e = hipMemcpyAsync(slot, dal, G * sc * 8, hipMemcpyDeviceToHost, stream);
-      if (e == hipSuccess) e = hipMemcpyAsync(slot + G * sc, dbe, G * sc * 8, hipMemcpyDeviceToHost, stream);
-      if (e == hipSuccess) e = hipEventRecord(res.ev[b & 1], stream);
-      return e;
+    std::fill(hprog, hprog + G, 0);   // no block is under way
+    auto enqueue_block = [&](int b) -> int {
+      if (fused) {
+        if (++fa.tag == 0) fa.tag = 1;
+        lanczos_fused_kernel<<<dim3(kXcds * fa.P), dim3(kFT), fused_lds(n, kmax, fa.rows) * 8, stream>>>(fa);
+        FD_TRY(hipGetLastError(), "lanczos_fused_kernel");
+      } else if (stepwise_block() < 0) {
+        return -1;
+      }
+      FD_TRY(hipEventRecord(res.ev[b & 1], stream), "hipEventRecord");
+      return 0;
     };
     // Block b + 1 is queued before block b is examined unless every group
     // still iterating is expected to converge within block b (its relative
@@ -563,30 +924,68 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
     // depend on this.
     std::vector<double> rel(G, HUGE_VAL), rate(G, 1.0);
     int queued = 0;
-    FD_TRY(enqueue_block(0), "Lanczos block");
+    if (enqueue_block(0) < 0) return -1;
     for (int b = 0; b < nblk; ++b) {
       if (b + 1 < nblk && queued < b + 1) {
         bool ahead = false;
         for (int g = 0; g < G; ++g)
           if (lz[g] && !(rel[g] * rate[g] <= opt.lanczos_tol)) ahead = true;
         if (ahead) {
-          FD_TRY(enqueue_block(b + 1), "Lanczos block");
+          if (enqueue_block(b + 1) < 0) return -1;
           queued = b + 1;
         }
       }
       FD_TRY(hipEventSynchronize(res.ev[b & 1]), "hipEventSynchronize");
-      const double* slot = res.coef + (size_t)(b & 1) * 2 * G * sc;
       const int prev = b * kIterBlock, done_k = std::min(kmax, prev + kIterBlock);
+      // a fused launch whose group was not all resident did nothing: the
+      // missing iterations by one kernel per step (another group may then be
+      // ahead, whose later vectors are not looked at before their block)
+      auto behind = [&]() {
+        for (int g = 0; g < G; ++g)
+          if (lz[g] && hprog[g] < done_k) return true;
+        return false;
+      };
+      if (fused && behind()) {
+        FD_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
+        while (behind()) {
+          if (stepwise_block() < 0) return -1;
+          FD_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
+        }
+      }
+      // the eigenpairs at the end of the block, of every group still iterating
+      {
+        std::vector<const double*> pa, pb;
+        std::vector<int> of;
+        for (int g = 0; g < G; ++g)
+          if (lz[g]) {
+            pa.push_back(hal + g * sc);
+            pb.push_back(hbe + g * sc);
+            of.push_back(g);
+          }
+        std::vector<std::vector<double>> sv(of.size());
+        std::vector<double> tv(of.size());
+        tridiag_tops((int)of.size(), pa.data(), pb.data(), done_k, sv.data(), tv.data());
+        for (size_t i = 0; i < of.size(); ++i) {
+          top_s[of[i]].swap(sv[i]);
+          top_theta[of[i]] = tv[i];
+        }
+      }
       bool any = false;
       for (int g = 0; g < G; ++g) {
         if (!lz[g]) continue;
-        const double* al = slot + g * sc;
-        const double* be = slot + G * sc + g * sc;
+        const double* al = hal + g * sc;
+        const double* be = hbe + g * sc;
         for (int mm = prev + 1; mm <= done_k; ++mm) {
           const bool last = mm == done_k;
           const double bt = be[mm - 1];
           if (!last && bt != 0.0) continue;
-          const double theta = tridiag_top(al, be, mm, s);
+          double theta;
+          if (last) {
+            theta = top_theta[g];
+            s.swap(top_s[g]);
+          } else {
+            theta = tridiag_top(al, be, mm, s);
+          }
           const double resid = bt * std::fabs(s[mm - 1]);
           {  // the relative residual and its factor over the last block
             const double r = theta != 0.0 ? resid / std::fabs(theta) : HUGE_VAL;
@@ -616,7 +1015,7 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
       }
       if (!any) break;
       if (b + 1 < nblk && queued < b + 1) {   // not queued ahead, and still needed
-        FD_TRY(enqueue_block(b + 1), "Lanczos block");
+        if (enqueue_block(b + 1) < 0) return -1;
         queued = b + 1;
       }
     }
