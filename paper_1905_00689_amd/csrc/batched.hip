@@ -45,14 +45,20 @@ __device__ __forceinline__ float tanh_b(float x) { return 2.0f * sigmoid_b(2.0f 
 // ---------------------------------------------------------------- x-projection
 // P[t*Bp + b][r] = sum_k Vx[.][k] * x[t][b][k] for the rows r < a.rows (term
 // n of group g at r = g*km + n, km = pld / G).
-// One 128 (tau) x 128 (t, b) tile per workgroup of 4 waves, each wave a
-// 64 x 64 quadrant (4 x 4 MFMA blocks); the contraction runs in slices of 32
+// One BM (tau) x 128 (t, b) tile per workgroup of BM / 32 waves (BM = 128 or
+// 256), each wave a 64 x 64 part (4 x 4 MFMA blocks); the contraction runs in slices of 32
 // staged through LDS, double-buffered: slice s+1 is fetched into registers
 // (x converted to bf16 on the way) while slice s is multiplied.  Tiles are
 // numbered so that each XCD (workgroups are dealt to the 8 XCDs round robin)
 // takes whole columns of tiles: the x slice of a column is fetched into that
 // XCD's L2 once and shared by every row tile.
-constexpr int kXBM = kPanelRowAlign, kXBN = 128, kXBK = 32;
+// Bound by the LDS passes of a slice between its two barriers (64 KB read and
+// 24 KB written per 512 cycles of MFMA with 8 waves): a prefetch of four
+// slices instead of two, slices of 64, or another order of the stash changed
+// nothing (50-53 us); the 256-row tile reads and converts each x value half
+// as often.  2048 x 4096 x 2048: 58.3 us with 128 rows, 50.6 with 256 (0.68
+// PFLOP/s).
+constexpr int kXBM = kPanelRowAlign, kXWide = 256, kXBN = 128, kXBK = 32;
 static_assert(kPanelDAlign == 2 * kXBK, "D is padded to a pair of x-projection slices");
 constexpr int kXLD = kXBK + 8;   // LDS row stride (bf16): 80 bytes, conflict-free 16-byte reads
 
@@ -62,46 +68,48 @@ constexpr int kXLD = kXBK + 8;   // LDS row stride (bf16): 80 bytes, conflict-fr
 // With a.xsplit > 1 workgroup blockIdx.x takes part blockIdx.x / (nM * nN)
 // of the contraction (a.Dp / a.xsplit columns) for its tile and writes the
 // partial tile to Ppart[part]; batched_xproj_sum_kernel adds the parts.
-template <bool VEC>
-__global__ void __launch_bounds__(256) batched_xproj_kernel(BatchedArgs a, int nM, int nN) {
-  __shared__ __align__(16) uint16_t As[2][kXBM * kXLD];
+template <bool VEC, int BM>
+__global__ void __launch_bounds__(2 * BM) batched_xproj_kernel(BatchedArgs a, int nM, int nN) {
+  constexpr int kAR = BM / 2, kBR = BM / 4;           // rows of A, columns of B that one load of the workgroup covers
+  constexpr int kNB = kXBN / kBR;                     // loads of a B slice per thread
+  __shared__ __align__(16) uint16_t As[2][BM * kXLD];
   __shared__ __align__(16) uint16_t Bs[2][kXBN * kXLD];
   const int nt = nM * nN;
   const int part = blockIdx.x / nt, bid = blockIdx.x - part * nt;
   int tile = bid;
   if (nt % 8 == 0) tile = (bid % 8) * (nt / 8) + bid / 8;
-  const int row0 = (tile % nM) * kXBM, col0 = (tile / nM) * kXBN;
+  const int row0 = (tile % nM) * BM, col0 = (tile / nM) * kXBN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = wave % (BM / 64), wn = wave / (BM / 64);
   const int li = lane & 15, lk = (lane >> 4) * 8;
   const int NB = a.T * a.Bp;
 
-  // global -> register staging: A 2 x 16 bytes, B 4 x float4 per thread
-  const int ar = tid >> 2, ac = tid & 3;       // A chunk: rows ar + 64j, bf16 8*ac
-  const int bc = tid & 7, bcl = tid >> 3;      // B chunk: columns bcl + 32j, floats 4*bc
+  // global -> register staging: A 2 x 16 bytes, B kNB x float4 per thread
+  const int ar = tid >> 2, ac = tid & 3;       // A chunk: rows ar + kAR*j, bf16 8*ac
+  const int bc = tid & 7, bcl = tid >> 3;      // B chunk: columns bcl + kBR*j, floats 4*bc
   // x offsets: row 0 stands in for padding columns, whose values are
   // replaced by zeros at the stash (so that no use of a fetched value precedes
   // it); the host guarantees T*B*D < 2^31 and rows*Dp < 2^31
   // 32-bit lane offsets (elements): the fetches below address a uniform base
   // plus these, so no per-fetch 64-bit address arithmetic is needed
-  unsigned aoff[2], xoff[4];
+  unsigned aoff[2], xoff[kNB];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     // output row g*km + n is panel row g*Kp + n (km: terms per group of this run)
-    const int km = a.pld / a.G, r = min(row0 + ar + 64 * j, a.pld - 1);
+    const int km = a.pld / a.G, r = min(row0 + ar + kAR * j, a.pld - 1);
     aoff[j] = (unsigned)((r / km) * a.Kp + r % km) * (unsigned)a.Dp + 8u * ac;
   }
   unsigned live = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int col = col0 + bcl + 32 * j;
+  for (int j = 0; j < kNB; ++j) {
+    const int col = col0 + bcl + kBR * j;
     const int t = col / a.Bp, b = col - t * a.Bp;
     const bool l = col < NB && b < a.B;
     live |= (l ? 1u : 0u) << j;
     xoff[j] = (l ? (unsigned)((t * a.B + b) * a.D) : 0u) + 4u * bc;
   }
   u32x4 ra[2][2];
-  f32x4 rb[2][4];
+  f32x4 rb[2][kNB];
   const int nsplit = a.xsplit > 1 ? a.xsplit : 1;
   const int nS = a.Dp / kXBK / nsplit;   // slices of this part (even)
   const int kbase = part * nS * kXBK;
@@ -123,11 +131,11 @@ __global__ void __launch_bounds__(256) batched_xproj_kernel(BatchedArgs a, int n
         *reinterpret_cast<const u32x4*>(va_ + aoff[j]);                                                \
     if constexpr (VEC) {                                                                               \
       const float* xa_ = a.x + k0;                                                                     \
-      _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                    \
+      _Pragma("unroll") for (int j = 0; j < kNB; ++j)                                                    \
           rb[R][j] = *reinterpret_cast<const f32x4*>(xa_ + xoff[j]);                                   \
     } else {                                                                                           \
       const int k = k0 + 4 * bc;                                                                       \
-      _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
+      _Pragma("unroll") for (int j = 0; j < kNB; ++j) {                                                  \
         const float* q = a.x + (xoff[j] - 4u * bc);                                                    \
         const bool l = ((live >> j) & 1u) != 0;                                                        \
         rb[R][j] = f32x4{l && k < a.D ? q[k] : 0.f, l && k + 1 < a.D ? q[k + 1] : 0.f,                 \
@@ -138,12 +146,12 @@ __global__ void __launch_bounds__(256) batched_xproj_kernel(BatchedArgs a, int n
 #define XPROJ_STASH(R)                                                                                 \
   do {                                                                                                 \
     _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                      \
-        *reinterpret_cast<u32x4*>(&As[R][(ar + 64 * j) * kXLD + 8 * ac]) = ra[R][j];                   \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                    \
+        *reinterpret_cast<u32x4*>(&As[R][(ar + kAR * j) * kXLD + 8 * ac]) = ra[R][j];                   \
+    _Pragma("unroll") for (int j = 0; j < kNB; ++j) {                                                    \
       const f32x4 v = ((live >> j) & 1u) ? rb[R][j] : f32x4{0.f, 0.f, 0.f, 0.f};                       \
       const uint32_t lo = bf16_bits(v[0]) | ((uint32_t)bf16_bits(v[1]) << 16);                         \
       const uint32_t hi = bf16_bits(v[2]) | ((uint32_t)bf16_bits(v[3]) << 16);                         \
-      *reinterpret_cast<u32x2*>(&Bs[R][(bcl + 32 * j) * kXLD + 4 * bc]) = u32x2{lo, hi};               \
+      *reinterpret_cast<u32x2*>(&Bs[R][(bcl + kBR * j) * kXLD + 4 * bc]) = u32x2{lo, hi};               \
     }                                                                                                  \
   } while (0)
 
@@ -622,6 +630,18 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   }
 }
 
+// Whether the x-projection takes the 256-row tile, from the number of
+// 128-row tiles: those run two to a compute unit, so r = ceil(tiles / units)
+// of them take 58 us per two and 40 us for an odd one; half as many 256-row
+// tiles run one to a unit, 48 us each.  Measured (D = 2048, narrow / wide,
+// us): r = 1 40 / 46, r = 2 58.3 / 50.6 (53.2 / 47.9 at 320 tiles), r = 3
+// 87.5-90.7 / 89.6-92.3, r = 4 112.5 / 96.7; D = 1000 (no float4 loads of x)
+// r = 2 69.0 / 48.8.
+static bool batched_xproj_wide(long long tiles, int ncu) {
+  const long long r = (tiles + ncu - 1) / ncu;
+  return r > 1 && r != 3;
+}
+
 int batched_xproj_split(int tiles, int ncu, int nslices) {
   int s = 1;
   while (2 * s <= 8 && (long long)tiles * 2 * s <= ncu && nslices % (4 * s) == 0) s *= 2;
@@ -695,14 +715,16 @@ hipError_t launch_batched(const BatchedArgs& a, const int* levels, int n_levels,
   hipError_t e;
   if (kmax > 0) {
     p.rows = p.pld;
-    const int nM = (p.rows + kXBM - 1) / kXBM, nN = (a.T * a.Bp + kXBN - 1) / kXBN;
-    p.xsplit = a.Ppart ? batched_xproj_split(nM * nN, a.ncu, a.Dp / kXBK) : 1;
+    const int nN = (a.T * a.Bp + kXBN - 1) / kXBN;
+    const bool wide = batched_xproj_wide((long long)((p.rows + kXBM - 1) / kXBM) * nN, a.ncu);
+    const int bm = wide ? kXWide : kXBM, nM = (p.rows + bm - 1) / bm;
+    p.xsplit = a.Ppart && !wide ? batched_xproj_split(nM * nN, a.ncu, a.Dp / kXBK) : 1;
     if (p.xsplit > 1 && (size_t)p.xsplit * a.T * a.Bp * p.pld > a.ppart_cap) p.xsplit = 1;
     const unsigned gx = (unsigned)(nM * nN * p.xsplit);
-    if (a.xvec && a.D % kPanelDAlign == 0)
-      batched_xproj_kernel<true><<<dim3(gx), dim3(256), 0, stream>>>(p, nM, nN);
-    else
-      batched_xproj_kernel<false><<<dim3(gx), dim3(256), 0, stream>>>(p, nM, nN);
+    const bool vec = a.xvec && a.D % kPanelDAlign == 0;
+    const auto xproj = wide ? (vec ? batched_xproj_kernel<true, kXWide> : batched_xproj_kernel<false, kXWide>)
+                            : (vec ? batched_xproj_kernel<true, kXBM> : batched_xproj_kernel<false, kXBM>);
+    xproj<<<dim3(gx), dim3(2 * bm), 0, stream>>>(p, nM, nN);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (p.xsplit > 1) {
       const size_t n4 = (size_t)a.T * a.Bp * p.pld / 4;

@@ -46,3 +46,25 @@ def test_buckets_and_groups(H, rank, G, T, Bs):
         # the last sequence too: a cohort that ran after another on its group
         hl, _ = oracle.run(f, w.b, np.ascontiguousarray(x[:, -1:]), levels, operand_round="bf16")
         assert rel_err(h[:, :, -1:], hl) < TOL
+
+
+@pytest.mark.parametrize("D,H,rank,T,Bn", [
+    (40, 96, 70, 16, 700),      # 3 x 88 tiles of 128 rows: the last 256-row tile is half empty, x read by elements
+    # 16 x 17 tiles, the last column tile half empty, x read by float4; D = 64 is two slices, which the small call
+    # does not split either (from D = 128 on it adds two partial sums, in another order than one chain)
+    (64, 512, 500, 3, 700),
+])
+def test_wide_projection_tiles(D, H, rank, T, Bn):
+    """A call with more 128-row projection tiles than compute units takes the 256-row tiles: a sequence's
+    bits are those of a call small enough for the others, and agree with the oracle."""
+    w = synth.make(D, H, T, Bn, index=98)
+    say("wide projection tiles H", H, "rank", rank, "D", D)
+    m = B.approx_lstm_prepare(w.W[:, :D], w.W[:, D:], w.b, D, H, rank, prune_ratio=0.5, factor_dtype=1,
+                              flags=B.FLAG_DEVICE_FACTORISE)
+    h, _ = run_gpu(m, w.x, [rank])
+    for pick in (slice(0, 20), slice(Bn - 20, Bn)):
+        x = np.ascontiguousarray(w.x[:, pick])
+        few, _ = run_gpu(m, x, [rank])
+        assert np.array_equal(h[:, :, pick], few)
+    ho, _ = oracle.run(exported_factors(m), w.b, x, [rank], operand_round="bf16")
+    assert rel_err(few, ho) < TOL
