@@ -244,10 +244,12 @@ approx_lstm_status approx_lstm_run_anytime(approx_lstm_model* m, const float* x,
 /*
  * approx_lstm_run_schedule -- progressive LSTM with a caller-given budget K_t
  * for every timestep (Sec. VI-B: the computation of each prediction cut to the
- * budget available for it).  Runs the same online launch as
- * approx_lstm_run_anytime (sized for the largest K_t), with K_t taken from
- * k_sched instead of the device clock: the result is the recurrence of Eq. (1)
- * with K_t terms per gate at timestep t, then the Sec. II cell update.
+ * budget available for it): the recurrence of Eq. (1) with K_t = k_sched[t]
+ * terms per gate at timestep t, then the Sec. II cell update.  The launch is
+ * sized for the largest K_t: the pair kernel where a fixed-budget run at that
+ * K takes it on the automatic launch width (approx_lstm_set_recurrence), else
+ * the online launch of approx_lstm_run_anytime with K_t taken from k_sched
+ * instead of the device clock.  Both give the same bits.
  *
  *   x, T, B, h0, c0  as for approx_lstm_run (1 <= T <= 65534)
  *   k_sched          host [T]: K_t, each in [0, rank]
@@ -269,8 +271,8 @@ approx_lstm_status approx_lstm_run_schedule(approx_lstm_model* m, const float* x
  *
  *   T, B               sequence length and count (>= 1)
  *   levels, n_levels   host [n_levels] budgets as for approx_lstm_run
- *                      (ignored when online != 0: the plan of an anytime or
- *                      scheduled run sized for the whole rank)
+ *                      (ignored when online != 0: the plan of an anytime
+ *                      run, sized for the whole rank)
  *   num_cu             compute units to plan for (0 = the model's device)
  *   out                host [10]: workgroups (of a pair-kernel run: of one
  *                      group, widest level), all-timestep P_x resident in LDS

@@ -493,8 +493,8 @@ approx_lstm_status ensure_stamps(approx_lstm_model* m, int T, hipStream_t stream
 // caller keeps a run of several pairs on the general kernel, and timed runs
 // of more pairs than there are XCDs too (their pairs would take turns, so
 // that no single stamp covered a timestep of all).
-bool pair_allowed(const approx_lstm_model* m, int pairs, int kmax) {
-  return kmax > 0 && m->recurrence == 0 && !m->cooperative && (pairs == 1 || m->launch_blocks == 0) &&
+bool pair_allowed(const approx_lstm_model* m, int pairs) {
+  return m->recurrence == 0 && !m->cooperative && (pairs == 1 || m->launch_blocks == 0) &&
          !(m->timing && pairs > alstm::kXcds);
 }
 
@@ -523,7 +523,7 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
                             const float* c0, int kmax, float* h_out, float* c_out, hipStream_t stream,
                             const CallerScratch* ws, bool* taken) {
   const size_t pairs = (size_t)pa.L * pa.B, GK = (size_t)m->G * kmax;
-  const size_t px_floats = GK * pa.T * pa.B, ex_floats = pairs * 2 * ((size_t)pa.zslots + pa.hpad);
+  const size_t px_floats = std::max<size_t>(1, GK * pa.T * pa.B), ex_floats = pairs * 2 * ((size_t)pa.zslots + pa.hpad);
   size_t exch_off = 0;
   float* pxw = nullptr;   // x-part projections: written by the input projection, read by the recurrence
   *taken = true;
@@ -555,7 +555,7 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
     if (st != APPROX_LSTM_OK) return st;
     pa.stamps = m->d_stamps;
   }
-  if (pa.groups > 1) pa.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)pairs, std::memory_order_relaxed) % alstm::kXcds);
+  if (pa.groups == alstm::kXcds) pa.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)pairs, std::memory_order_relaxed) % alstm::kXcds);
   pa.wait_ticks = m->start_wait_ticks;
   pa.h0 = h0; pa.c0 = c0; pa.h_out = h_out; pa.c_out = c_out;
   pa.sigma = m->d_sigma; pa.Ut = m->d_Ut; pa.vidx = m->d_vidx; pa.vval = m->d_vval; pa.nx = m->d_nx;
@@ -578,8 +578,43 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
                                    float* c_out, hipStream_t stream, const OnlineCfg* on,
                                    const CallerScratch* ws = nullptr) {
   if (on && ws) return fail(APPROX_LSTM_ERR_UNSUPPORTED, "online runs need the model's own workspace");
+  const size_t LB = (size_t)n_levels * B;
+  const size_t kword = on ? 1 : 0;   // K_t of an online run rides with h
+  alstm::RunArgs a{};
+  int P = 1;
+  size_t px_floats = 0, zx_words = 0, hx_words = 0;
+  ScratchLayout sl{};
+  // the general kernel's plan and its limits
+  auto plan_general = [&]() -> approx_lstm_status {
+    const size_t lds = plan_run(m, a, T, B, levels, n_levels, kmax, on, m->num_cu, &P);
+    if (lds > alstm::kLdsCap)
+      return fail(APPROX_LSTM_ERR_UNSUPPORTED, "LDS need %zu bytes exceeds 160 KiB (H=%d, levels*B=%zu, G*K=%d)",
+                  lds, m->H, LB, a.GK);
+    // h words per step parity (tagged words in hx, floats in the bulk hbx)
+    a.hb_stride = (int)round_up(LB * m->H + kword, 4);
+    a.bulk_h = alstm::use_bulk_h(n_levels, B, m->H);
+    px_floats = std::max<size_t>(1, (size_t)a.GK * T * B);
+    // z words, then (K-tiled phase B) the y words of every pair's gate rows
+    zx_words = std::max<size_t>(1, LB * P * a.owned_max + (a.ktile > 0 ? LB * 4 * (size_t)m->H : 0));
+    hx_words = 2 * (size_t)a.hb_stride;
+    if (ws) {
+      sl = scratch_layout(px_floats, zx_words, hx_words, a.bulk_h ? hx_words : 0, (size_t)P);
+      if (sl.total > ws->bytes)
+        return fail(APPROX_LSTM_ERR_UNSUPPORTED,
+                    "run needs %zu bytes of workspace, above the %zu-byte static scratch of the allocation-free entry "
+                    "point (T=%d, B=%d, levels=%d, G*K=%d)",
+                    sl.total, ws->bytes, T, B, n_levels, a.GK);
+    }
+    return APPROX_LSTM_OK;
+  };
+  // The limits of a run do not depend on the kernel that takes it: those of the
+  // general one, except for one pair with terms at a fixed budget, which needs
+  // them only where the pair kernel does not take it.
+  const bool single = LB == 1 && kmax > 0 && !on;
+  approx_lstm_status gst = single ? APPROX_LSTM_OK : plan_general();
+  if (gst != APPROX_LSTM_OK) return gst;
   // (a schedule fixes every K_t beforehand, so each pair can follow it by itself)
-  if ((!on || (on->sched && m->launch_blocks == 0)) && pair_allowed(m, n_levels * B, kmax)) {
+  if ((!on || (on->sched && m->launch_blocks == 0)) && pair_allowed(m, n_levels * B)) {
     alstm::PairArgs pa{};
     size_t plds = 0;
     const int Pp = plan_pair_run(m, pa, T, B, levels, n_levels, m->num_cu, &plds);
@@ -590,31 +625,10 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
       if (taken || st != APPROX_LSTM_OK) return st;
     }
   }
-  alstm::RunArgs a{};
-  int P = 1;
-  const size_t lds = plan_run(m, a, T, B, levels, n_levels, kmax, on, m->num_cu, &P);
-  const size_t LB = (size_t)n_levels * B;
-  if (lds > alstm::kLdsCap)
-    return fail(APPROX_LSTM_ERR_UNSUPPORTED, "LDS need %zu bytes exceeds 160 KiB (H=%d, levels*B=%zu, G*K=%d)",
-                lds, m->H, LB, a.GK);
-
-  const size_t kword = on ? 1 : 0;   // K_t of an online run rides with h
-  // h words per step parity (tagged words in hx, floats in the bulk hbx)
-  a.hb_stride = (int)round_up(LB * m->H + kword, 4);
-  a.bulk_h = alstm::use_bulk_h(n_levels, B, m->H);
-  const size_t px_floats = std::max<size_t>(1, (size_t)a.GK * T * B);
-  // z words, then (K-tiled phase B) the y words of every pair's gate rows
-  const size_t zx_words = std::max<size_t>(1, LB * P * a.owned_max + (a.ktile > 0 ? LB * 4 * (size_t)m->H : 0));
-  const size_t hx_words = 2 * (size_t)a.hb_stride;
+  if (single && (gst = plan_general()) != APPROX_LSTM_OK) return gst;
   unsigned tag_seq = 0;
   size_t exch_off = 0;
   if (ws) {
-    const ScratchLayout sl = scratch_layout(px_floats, zx_words, hx_words, a.bulk_h ? hx_words : 0, (size_t)P);
-    if (sl.total > ws->bytes)
-      return fail(APPROX_LSTM_ERR_UNSUPPORTED,
-                  "run needs %zu bytes of workspace, above the %zu-byte static scratch of the allocation-free entry "
-                  "point (T=%d, B=%d, levels=%d, G*K=%d)",
-                  sl.total, ws->bytes, T, B, n_levels, a.GK);
     a.px = reinterpret_cast<float*>(ws->base + sl.px);
     a.zx = reinterpret_cast<unsigned long long*>(ws->base + sl.zx);
     a.hx = reinterpret_cast<unsigned long long*>(ws->base + sl.hx);
@@ -1352,7 +1366,15 @@ approx_lstm_status approx_lstm_plan(const approx_lstm_model* m, int32_t T, int32
   }
   const int ncu = num_cu > 0 ? num_cu : m->num_cu;
   for (int i = 0; i < 10; ++i) out[i] = 0;
-  if (!online && pair_allowed(m, (int)lv.size() * B, kmax)) {
+  OnlineCfg cfg;
+  cfg.n = 1;
+  cfg.k[0] = kmax;
+  alstm::RunArgs a{};
+  int P = 1;
+  const size_t lds = plan_run(m, a, T, B, lv.data(), (int)lv.size(), kmax, online ? &cfg : nullptr, ncu, &P);
+  // (the general kernel's limit holds for every run but one pair with terms)
+  const bool single = lv.size() * B == 1 && kmax > 0;
+  if (!online && (single || lds <= alstm::kLdsCap) && pair_allowed(m, (int)lv.size() * B)) {
     alstm::PairArgs pa{};
     size_t plds = 0;
     const int Pp = plan_pair_run(m, pa, T, B, lv.data(), (int)lv.size(), ncu, &plds);
@@ -1368,12 +1390,6 @@ approx_lstm_status approx_lstm_plan(const approx_lstm_model* m, int32_t T, int32
       return APPROX_LSTM_OK;
     }
   }
-  OnlineCfg cfg;
-  cfg.n = 1;
-  cfg.k[0] = kmax;
-  alstm::RunArgs a{};
-  int P = 1;
-  const size_t lds = plan_run(m, a, T, B, lv.data(), (int)lv.size(), kmax, online ? &cfg : nullptr, ncu, &P);
   out[0] = P;
   out[1] = a.px_all;
   out[2] = a.allpairs;

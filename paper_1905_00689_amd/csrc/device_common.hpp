@@ -218,7 +218,7 @@ __device__ __forceinline__ void publish_slot(float* p, float v, bool near) {
 // missing values read 0.
 template <int kUnits>
 __device__ __forceinline__ void poll_units(float* dst, const float* src, int bytes, const int* map, unsigned pending,
-                                           unsigned* err) {
+                                           unsigned* err, int stride = kThreads) {
   if (!pending) return;
   const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
   const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)addr);
@@ -228,7 +228,7 @@ __device__ __forceinline__ void poll_units(float* dst, const float* src, int byt
       __builtin_amdgcn_make_buffer_rsrc(base, (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
   const int tid = threadIdx.x;
   auto load = [&](int r) {
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + kThreads * r) * 16, 0, 16 /* sc1 */);
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + stride * r) * 16, 0, 16 /* sc1 */);
   };
   // empty is the largest unsigned value
   auto full = [](const u32x4& w) { return max(max(w[0], w[1]), max(w[2], w[3])) != kEmpty; };

@@ -188,7 +188,8 @@ struct PairArgs {
   int D, H, G, N, NZ, T, B, L;
   PairLevel lv[kMaxLevels];
   // launch plan (plan_pair)
-  int groups;    // groups the blocks are dealt to (kXcds, or 1)
+  int groups;    // groups the blocks are dealt to (kXcds, or 1; without terms any number)
+  int spread;    // 1: the one group exchanges across XCDs
   int first_xcd; // XCD of group 0
   int OMmax;     // largest OM
   int zslots;    // largest slots

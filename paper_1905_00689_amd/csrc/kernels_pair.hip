@@ -46,7 +46,14 @@
 // 0.70, 1.69 -> 0.36, 0.39, 0.40, 0.58 us.  Several pairs, against the general
 // kernel's one launch for all of them: eight sequences at K = 128 389 -> 54,
 // levels 16, 64, 128, 192 202 -> 49; H = 2048, K = 64, T = 64, eight sequences
-// 1505 -> 155.
+// 1505 -> 155; K = 256, T = 32 943 -> 142.
+// * Spread groups (SPREAD; a single pair whose slices one XCD cannot hold).
+//   Across XCDs a store's acknowledgement takes as long as the exchange, and a
+//   wave's loads and stores retire in order, so a wave that polls after storing
+//   waits for its own stores first.  There the last wave alone publishes, from
+//   LDS, and the others only poll.  H = 1024, K = 512, 75% pruning, T = 32, on
+//   128 workgroups: 175 us with tagged words and 185 with slots published by
+//   every wave, 152 so; the driving shape without pruning, K = 512: 97, 105, 97.
 //
 // Residency.  A group's workgroups wait for each other, so all of them must
 // be resident.  When another stream's kernels hold part of an XCD that may
@@ -75,26 +82,30 @@ namespace {
 // 16-byte units polled per thread and exchange (up to 4096 values).
 constexpr int kMaxUnits = 2;
 
+// Threads of a spread group's workgroup that poll (the last wave publishes).
+constexpr int kSpreadPollers = kThreads - 64;
+
 // Timestep stamps are kept in LDS (written out at the end) up to this many
 // timesteps; beyond, they go straight to memory.
 constexpr int kLdsStamps = 255;
 constexpr int kStampFloats = 2 * (4 + 4 * kLdsStamps);
 
-// LDS carve-up (floats): with stamps their block first (8-byte aligned), the
-// group's start mode [4], P_x [T][OM], the owned terms' places in their groups
-// [64], h [hpad], z [G][zst], c [H] (of a
-// workgroup that runs its pairs alone) and per wave the gate pre-activations
+// LDS carve-up (floats): h [hpad], with stamps their block (8-byte aligned),
+// the group's start mode [4], own z of this timestep [64] (spread groups), P_x [T][OM], the owned terms' places in their groups
+// [64], z [G][zst], c [H] (of a
+// workgroup that runs its pairs alone; own h of this timestep, spread groups)
+// and per wave the gate pre-activations
 // of its rows [opt][64 / S] (16-byte aligned).
 struct PairLayout {
-  int mode, px, nown, hs, zs, cs, ys, total;
+  int st, mode, px, nown, zs, cs, ys, total;
 };
 __host__ __device__ inline PairLayout pair_layout(const PairArgs& a) {
   PairLayout l;
-  l.mode = a.stamps ? kStampFloats : 0;
-  l.px = l.mode + 4;
+  l.st = a.hpad;
+  l.mode = l.st + (a.stamps ? kStampFloats : 0);
+  l.px = l.mode + 4 + 64;
   l.nown = l.px + ((a.T * a.OMmax + 3) & ~3);
-  l.hs = l.nown + 64;
-  l.zs = l.hs + a.hpad;
+  l.zs = l.nown + 64;
   l.cs = l.zs + a.zfloats;
   l.ys = l.cs + a.hpad;
   l.total = l.ys + kThreads * a.opt;   // [8 waves][opt][64 / S], S >= 1
@@ -172,7 +183,8 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
 // nothing, so the sums equal those over the live entries in the same order.
 // TWO: the instance keeps to 128 registers, so that two workgroups share a
 // compute unit (near groups of more than 32 workgroups).
-template <int OPT, int UMAX, int APASS, int HMAX, bool TWO>
+// SPREAD: the group of a single pair over more than one XCD.
+template <int OPT, int UMAX, int APASS, int HMAX, bool TWO, bool SPREAD>
 __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr int kChunk = 16;   // LDS reads in flight per batch
@@ -187,7 +199,9 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   int* modes = reinterpret_cast<int*>(ldsf + lay.mode);
   float* pxs = ldsf + lay.px;      // P_x [T][OM]
   int* nown = reinterpret_cast<int*>(ldsf + lay.nown);
-  float* hs = ldsf + lay.hs;       // h_{t-1} [H]
+  float* zpub = ldsf + lay.mode + 4;   // own z of this timestep [64]
+  float* hpub = ldsf + lay.cs;         // own h of this timestep [RU]
+  float* hs = ldsf;                // h_{t-1} [H]
   float* zs = ldsf + lay.zs;       // z of this timestep [G][zst]
   const int wv = tid >> 6;
 
@@ -330,7 +344,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       for (int k = 0; k < HMAX; ++k) {
         const bool live = sla + 16 * k < cnt;
         hv[p][k] = live ? hv[p][k] : 0.0f;
-        hi[p][k] = 4 * lay.hs + (live ? 4 * (hi[p][k] - D) : 0);   // byte offset of h[k - D] in LDS
+        hi[p][k] = live ? 4 * (hi[p][k] - D) : 0;   // byte offset of h[k - D] in LDS
       }
     }
 
@@ -338,11 +352,12 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     // multiple of 4, so a unit's four go to consecutive LDS places) and of h
     int zdi[kMaxUnits], hdi[kMaxUnits];
     unsigned zpend = 0, hpend = 0;
+    constexpr int pollers = SPREAD ? kSpreadPollers : kThreads;
 #pragma unroll
     for (int r = 0; r < kMaxUnits; ++r) {
-      const int u = tid + kThreads * r;
-      if (4 * u < v.slots) zpend |= 1u << r;
-      if (4 * u < H) hpend |= 1u << r;
+      const int u = tid + pollers * r;
+      if (tid < pollers && 4 * u < v.slots) zpend |= 1u << r;
+      if (tid < pollers && 4 * u < H) hpend |= 1u << r;
       zdi[r] = 4 * u < v.slots ? slot_pos(4 * u) : 0;
       hdi[r] = 4 * u;
     }
@@ -374,17 +389,20 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     // every wait for LDS would wait for outstanding memory stores too
     const bool lds_stamps = T <= kLdsStamps;
     auto put_stamp = [&](int i, unsigned long long v) {
-      if (lds_stamps) reinterpret_cast<unsigned long long*>(lds_raw)[i] = v;
+      if (lds_stamps) reinterpret_cast<unsigned long long*>(ldsf + lay.st)[i] = v;
       else a.stamps[i] = v;
     };
     if (stamp) {
       put_stamp(0, wall_clock64());
       put_stamp(1, clock64());
     }
-    // one loop for a single workgroup and one for an exchanging group
-    auto steps = [&](auto lone) {
-      constexpr bool kLocal = decltype(lone)::value;
-      float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + cunit;
+    // one loop for a single workgroup, one for a group on one XCD and one for a
+    // spread group.  There a store's acknowledgement takes as long as the
+    // exchange, and a wave's loads and stores retire in order: so the last wave
+    // alone publishes (and stores h_out) and the others only poll.
+    auto steps = [&](auto kind) {
+      constexpr bool kLocal = decltype(kind)::value == 0, kSpread = decltype(kind)::value == 2;
+      float* hout = a.h_out + ((size_t)lev * TB + b) * H + r0 + (kSpread ? 0 : cunit);
       const size_t hstep = (size_t)B * H;
       int kt = a.sched ? a.sched[0] : K;
       int half = 0;   // t & 1
@@ -430,6 +448,8 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
             if (ia >= n_owned) break;
             if constexpr (kLocal) {
               zs[zown[p]] = z[p];
+            } else if constexpr (kSpread) {
+              zpub[ia] = z[p];
             } else {
               publish_slot(zxt + j * OM + ia, z[p], near);
               // z_{t-1}: everyone's h_{t-1} is here, so everyone has read it
@@ -438,7 +458,17 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
           }
         }
         if (stamp) put_stamp(3 + 4 * t, clock64());
-        if constexpr (!kLocal) {
+        if constexpr (kSpread) {
+          lds_barrier();
+          if (wv == kWaves - 1) {
+            wait_memory();   // the emptied h slots, before this workgroup's z_t
+            if (lane < n_owned) {
+              publish_slot(zxt + j * OM + lane, zpub[lane], false);
+              store_slot(zxe + j * OM + lane, kEmpty, false);
+            }
+          }
+          poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err, kSpreadPollers);
+        } else if constexpr (!kLocal) {
           poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err);
           wait_memory();   // the emptied slots too, before this workgroup's h_t
         }
@@ -487,16 +517,32 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
           if (cell_ok) {
             if constexpr (kLocal) {
               hs[r0 + cunit] = h2;
+            } else if constexpr (kSpread) {
+              hpub[cunit] = h2;
             } else if (more) {
               publish_slot(hxt + r0 + cunit, h2, near);
               // h_{t-1}: everyone's z_t is here, so everyone has read it
               store_slot(hxe + r0 + cunit, kEmpty, near);
             }
-            *hout = h2;
+            if constexpr (!kSpread) *hout = h2;
           }
         }
         if (stamp) put_stamp(5 + 4 * t, clock64());
-        if constexpr (!kLocal) {
+        if constexpr (kSpread) {
+          lds_barrier();
+          if (wv == kWaves - 1) {
+            wait_memory();   // the emptied z slots, before this workgroup's h_t
+            for (int i = lane; i < rc; i += 64) {
+              const float h2 = hpub[i];
+              if (more) {
+                publish_slot(hxt + r0 + i, h2, false);
+                store_slot(hxe + r0 + i, kEmpty, false);
+              }
+              hout[i] = h2;
+            }
+          }
+          if (more) poll_units<kMaxUnits>(hs, hxt, a.hpad * 4, hdi, hpend, a.err, kSpreadPollers);
+        } else if constexpr (!kLocal) {
           if (more) {
             poll_units<kMaxUnits>(hs, hxt, a.hpad * 4, hdi, hpend, a.err);
             wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
@@ -505,13 +551,14 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
         lds_barrier();
       }
     };
-    if (local) steps(std::true_type{});
-    else steps(std::false_type{});
+    if constexpr (SPREAD) steps(std::integral_constant<int, 2>{});
+    else if (local) steps(std::integral_constant<int, 0>{});
+    else steps(std::integral_constant<int, 1>{});
     if (stamp) {
       put_stamp(2 + 4 * T, clock64());
       put_stamp(3 + 4 * T, wall_clock64());
       if (lds_stamps)
-        for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = reinterpret_cast<unsigned long long*>(lds_raw)[i];
+        for (int i = 0; i < 4 + 4 * T; ++i) a.stamps[i] = reinterpret_cast<unsigned long long*>(ldsf + lay.st)[i];
     }
     if (a.c_out && cell_ok) a.c_out[((size_t)lev * B + b) * H + r0 + cunit] = cst;
   }
@@ -535,20 +582,26 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   }
 }
 
-template <int OPT, int UMAX, int APASS, int HMAX>
-hipError_t launch_pair_kernel(const PairArgs& a, int P, size_t lds, hipStream_t stream) {
-  // at most 128 registers where the slices are small (two workgroups per
-  // compute unit, near groups of up to kNearWidth workgroups)
-  constexpr bool kTwo = OPT == 1 && APASS == 1 && HMAX <= kTwoHmax;
+template <int OPT, int UMAX, int APASS, int HMAX, bool TWO, bool SPREAD>
+hipError_t launch_pair_instance(const PairArgs& a, int P, size_t lds, hipStream_t stream) {
   static bool attr_set = false;
-  const void* fn = (const void*)pair_lstm_kernel<OPT, UMAX, APASS, HMAX, kTwo>;
+  const void* fn = (const void*)pair_lstm_kernel<OPT, UMAX, APASS, HMAX, TWO, SPREAD>;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsCap);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  pair_lstm_kernel<OPT, UMAX, APASS, HMAX, kTwo><<<dim3(P * a.groups), dim3(kThreads), lds, stream>>>(a);
+  pair_lstm_kernel<OPT, UMAX, APASS, HMAX, TWO, SPREAD><<<dim3(P * a.groups), dim3(kThreads), lds, stream>>>(a);
   return hipGetLastError();
+}
+
+template <int OPT, int UMAX, int APASS, int HMAX>
+hipError_t launch_pair_kernel(const PairArgs& a, int P, size_t lds, hipStream_t stream) {
+  // at most 128 registers where the slices are small (two workgroups per
+  // compute unit, near groups of up to kNearWidth workgroups)
+  constexpr bool kTwo = OPT == 1 && APASS == 1 && HMAX <= kTwoHmax;
+  if (a.spread) return launch_pair_instance<OPT, UMAX, APASS, HMAX, false, true>(a, P, lds, stream);
+  return launch_pair_instance<OPT, UMAX, APASS, HMAX, kTwo, false>(a, P, lds, stream);
 }
 
 // One level's launch shape on P workgroups, output rows per thread at most
@@ -556,16 +609,33 @@ hipError_t launch_pair_kernel(const PairArgs& a, int P, size_t lds, hipStream_t 
 struct LevelShape {
   int apass, opt, need_h, upt;
 };
+
+// Four rows per thread with 17 to 32 U entries each (128 registers) leave room
+// for 64 registers of h parts, and two phase-A passes of long h parts take them
+// next to at most 64 of U: 24 entries per lane.  Near groups of 32 workgroups
+// that hold this much: H = 2048, K = 256, 90% pruning, T = 32: 167 us on 128
+// workgroups before, 113 now; the driving shape at 50% pruning, K = 512: 92 on
+// 64 workgroups before, 79 now.  What is left out spilled
+// inside the loop: two passes of 32 entries, 107 us on 32 workgroups against
+// 97 on a spread group (driving shape, no pruning, K = 512); keeping two
+// entries' places in one register cost more (115) than it saved.
+bool in_registers(int opt, int upt, int apass, int need_h) {
+  if (apass == 2 && need_h > 24) return false;
+  return opt < 4 || upt <= 16 || need_h <= (apass == 2 ? 16 : 32);
+}
+
 bool level_fits(const PairArgs& a, PairLevel& v, int hcap, int P, int optcap, LevelShape& s) {
   const int OM = (v.slots + P - 1) / P, RU = (a.H + P - 1) / P;
   s.apass = OM <= 32 ? 1 : (OM <= 64 ? 2 : 0);
   s.need_h = (hcap + 15) / 16;             // h-part entries per lane
   s.upt = (v.K + v.S - 1) / v.S;           // U entries per row and lane
-  if (!s.apass || s.need_h > (s.apass == 1 ? 32 : 16)) return false;
+  // (two passes of long h parts on one workgroup cost more than an exchange)
+  if (!s.apass || s.need_h > (s.apass == 2 && P == 1 ? 16 : 32)) return false;
   const int slots = kThreads / v.S;        // row slots per pass of the threads
   const int opt = (4 * RU + slots - 1) / slots;
   s.opt = opt <= 1 ? 1 : (opt <= 2 ? 2 : (opt <= 4 ? 4 : 0));
-  if (!s.opt || s.opt > optcap || s.upt > 32 / (s.opt == 4 ? 2 : 1)) return false;
+  if (!s.opt || s.opt > optcap || s.upt > 32) return false;
+  if (!in_registers(s.opt, s.upt, s.apass, s.need_h)) return false;
   // the four gate rows of a unit must be adjacent lane groups of one wave
   if (4 * v.S > 64) return false;
   if (v.slots > 4 * kMaxUnits * kThreads || a.H > 4 * kMaxUnits * kThreads) return false;
@@ -625,10 +695,9 @@ int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
   }
   // register buckets: h-part entries per lane, U entries per row and lane
   a.hpl = need_h <= 4 ? 4 : need_h <= 8 ? 8 : need_h <= 12 ? 12 : need_h <= 16 ? 16 : need_h <= 24 ? 24 : 32;
-  if (a.apass == 2 && a.hpl > 16) return 0;
-  if (a.opt == 4 && upt > 16) return 0;
   a.upt = upt;
-  a.umax = a.opt == 4 ? (upt <= 8 ? 8 : 16) : a.opt == 2 ? (upt <= 16 ? 16 : 32) : (upt <= 8 ? 8 : upt <= 16 ? 16 : 32);
+  if (!in_registers(a.opt, upt, a.apass, a.hpl)) return 0;
+  a.umax = a.opt == 4 ? (upt <= 8 ? 8 : upt <= 16 ? 16 : 32) : a.opt == 2 ? (upt <= 16 ? 16 : 32) : (upt <= 8 ? 8 : upt <= 16 ? 16 : 32);
   // lane sl's terms at stride kst: it covers the lane's whole register bucket
   // (every read stays in the lane's zero-filled places), and 12, 20 or 36
   // floats put the 16-byte reads of consecutive lanes in distinct banks
@@ -649,7 +718,7 @@ int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
   *lds = 0;
   int kmax = 0;
   for (int l = 0; l < a.L; ++l) kmax = std::max(kmax, a.lv[l].K);
-  if (kmax < 1 || a.G < 1 || a.L > kMaxLevels) return 0;
+  if (a.G < 1 || a.L > kMaxLevels) return 0;
   const int pairs = a.L * a.B;
   const bool xcds = num_cu >= kXcds * kXcdCus;   // the whole device: one group per XCD
   if (pairs > 1 && (want > 0 || !xcds)) return 0;
@@ -663,6 +732,8 @@ int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
       const bool two = a.opt == 1 && a.apass == 1 && a.hpl <= kTwoHmax;
       const bool near = xcds && P <= (two ? kNearWidth : kXcdCus);
       if (!near && cap != num_cu) continue;
+      // a spread group's polling threads
+      if (!near && P > 1 && std::max(a.zslots, a.hpad) > 4 * kMaxUnits * kSpreadPollers) return 0;
       a.stamps = reinterpret_cast<unsigned long long*>(1);   // sized with the stamps' block
       const size_t bytes = 4 * (size_t)pair_layout(a).total;
       a.stamps = nullptr;
@@ -670,7 +741,13 @@ int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
         if (cap != num_cu && pairs == 1) continue;
         return 0;
       }
-      a.groups = pairs > 1 || (near && P > 1) ? kXcds : 1;
+      a.spread = !near && P > 1 && kmax > 0;
+      // without terms nothing is exchanged and a group may lie anywhere: as many
+      // side by side as there are compute units (T = 16, H = 512, one sequence:
+      // 19 us against the general kernel's 28; T = 32, H = 2048, eight: 22 against
+      // 131)
+      if (kmax == 0) a.groups = std::min(pairs, std::max(1, num_cu / P));
+      else a.groups = pairs > 1 || (near && P > 1) ? kXcds : 1;
       *lds = bytes;
       return P;
     }
@@ -682,7 +759,8 @@ template <int APASS, int HMAX>
 hipError_t launch_pair_u(const PairArgs& a, int P, size_t lds, hipStream_t stream) {
   if (a.opt == 4) {
     if (a.umax == 8) return launch_pair_kernel<4, 8, APASS, HMAX>(a, P, lds, stream);
-    return launch_pair_kernel<4, 16, APASS, HMAX>(a, P, lds, stream);
+    if (a.umax == 16) return launch_pair_kernel<4, 16, APASS, HMAX>(a, P, lds, stream);
+    if constexpr (APASS == 1 || HMAX <= 16) return launch_pair_kernel<4, 32, APASS, HMAX>(a, P, lds, stream);
   } else if (a.opt == 2) {
     if (a.umax == 16) return launch_pair_kernel<2, 16, APASS, HMAX>(a, P, lds, stream);
     return launch_pair_kernel<2, 32, APASS, HMAX>(a, P, lds, stream);
@@ -695,7 +773,7 @@ hipError_t launch_pair_u(const PairArgs& a, int P, size_t lds, hipStream_t strea
 }
 
 hipError_t launch_pair(const RunArgs& proj, const PairArgs& a, int P, hipStream_t stream) {
-  hipError_t e = launch_input_proj(proj, stream);
+  hipError_t e = proj.GK > 0 ? launch_input_proj(proj, stream) : hipSuccess;
   if (e != hipSuccess) return e;
   const size_t lds = 4 * (size_t)pair_layout(a).total;
   if (a.apass == 2) {
@@ -703,7 +781,8 @@ hipError_t launch_pair(const RunArgs& proj, const PairArgs& a, int P, hipStream_
       case 4: return launch_pair_u<2, 4>(a, P, lds, stream);
       case 8: return launch_pair_u<2, 8>(a, P, lds, stream);
       case 12: return launch_pair_u<2, 12>(a, P, lds, stream);
-      default: return launch_pair_u<2, 16>(a, P, lds, stream);
+      case 16: return launch_pair_u<2, 16>(a, P, lds, stream);
+      default: return launch_pair_u<2, 24>(a, P, lds, stream);
     }
   }
   switch (a.hpl) {

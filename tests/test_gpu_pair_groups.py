@@ -105,3 +105,44 @@ def test_start_wait_range():
         with pytest.raises(B.ApproxLstmError) as ei:
             B.approx_lstm_set_start_wait(m, bad)
         assert ei.value.status == B.ERR_INVALID_ARG
+
+
+# register buckets of narrow groups with much per workgroup: 17 to 32 U entries
+# in each of four rows per thread (one and two phase-A passes), two passes of 24
+# h-part entries; a group over several XCDs at its edges (two phase-A passes do
+# not fit, a last workgroup without terms, with few units); no terms at all
+# (one and several workgroups per pair, more pairs than compute units hold)
+@pytest.mark.parametrize("D,H,T,Bn,rank,p,levels,blocks", [
+    (64, 2048, 4, 2, 131, 0.9, [131], 0),
+    (64, 1024, 5, 1, 300, 0.8, [300], 0),
+    (64, 1024, 3, 3, 300, 0.95, [300, 5], 0),
+    (64, 512, 5, 1, 270, 0.45, [270], 0),
+    (64, 512, 6, 1, 270, 0.0, [270], 0),
+    (64, 512, 3, 1, 270, 0.75, [270], 96),
+    (100, 203, 5, 1, 40, 0.5, [40], 77),
+    (40, 512, 5, 1, 8, 0.5, [0], 0),
+    (40, 700, 3, 5, 8, 0.5, [0, 0], 0),
+    (40, 96, 2, 30, 8, 0.5, [0] * 9, 0),
+])
+def test_wide_buckets_spread_groups_and_no_terms(D, H, T, Bn, rank, p, levels, blocks):
+    w, m = model(D, H, T, Bn, rank, p)
+    rng = np.random.default_rng(6)
+    h0 = rng.normal(size=(Bn, H)).astype(np.float32) * 0.3
+    c0 = rng.normal(size=(Bn, H)).astype(np.float32)
+    ref = general(m, w.x, levels, h0, c0)
+    B.approx_lstm_set_launch(m, blocks)
+    plan = B.approx_lstm_plan(m, T, Bn, levels)
+    say("  plan", plan)
+    assert plan["pair_kernel"] == 1
+    for _ in range(2):
+        assert same(run_gpu(m, w.x, levels, h0, c0, want_c=True), ref)
+
+
+def test_limits_do_not_depend_on_the_kernel():
+    """Many pairs that the general kernel's LDS cannot hold are refused on either kernel."""
+    w, m = model(40, 512, 2, 300, 8, 0.5)
+    for levels in ([0], [8]):
+        for kernel in (0, 1):
+            B.approx_lstm_set_recurrence(m, kernel)
+            with pytest.raises(B.ApproxLstmError):
+                run_gpu(m, w.x, levels)
