@@ -41,9 +41,9 @@
 //   words and a quarter of the loads.
 // Driving shape (D = 2048, H = 512, 75% pruning, T = 16, one sequence), whole
 // run, us, with tagged words across XCDs / near groups with tagged words /
-// near groups with slots: K = 32 75.2 / 60.3 / 40.6, K = 128 76.9 / 63.2 /
-// 43.0, K = 512 87.5 / 92.3 / 67.1; phases at K = 64 (A, z, B, h) 0.25, 1.31,
-// 0.70, 1.69 -> 0.36, 0.39, 0.40, 0.58 us.  Several pairs, against the general
+// near groups with slots: K = 32 75.2 / 60.3 / 38.8, K = 128 76.9 / 63.2 /
+// 41.3, K = 512 87.5 / 92.3 / 66.5; phases at K = 64 (A, z, B, h) 0.25, 1.31,
+// 0.70, 1.69 -> 0.35, 0.43, 0.37, 0.48 us.  Several pairs, against the general
 // kernel's one launch for all of them: eight sequences at K = 128 389 -> 54,
 // levels 16, 64, 128, 192 202 -> 49; H = 2048, K = 64, T = 64, eight sequences
 // 1505 -> 155; K = 256, T = 32 943 -> 142.
@@ -677,6 +677,7 @@ int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
   int pmax = 0, need_h = 0, upt = 0;
   a.opt = a.apass = 1;
   a.OMmax = a.zslots = 0;
+  bool quad = false;   // a level needs both four rows per thread and more than 16 U entries
   for (int l = 0; l < a.L; ++l) {
     PairLevel& v = a.lv[l];
     v.S = lanes_for_level(v.K);
@@ -690,6 +691,7 @@ int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
     a.apass = std::max(a.apass, s.apass);
     need_h = std::max(need_h, s.need_h);
     upt = std::max(upt, s.upt);
+    quad = quad || (s.opt == 4 && s.upt > 16);
     a.OMmax = std::max(a.OMmax, v.OM);
     a.zslots = std::max(a.zslots, v.slots);
   }
@@ -697,6 +699,10 @@ int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
   a.hpl = need_h <= 4 ? 4 : need_h <= 8 ? 8 : need_h <= 12 ? 12 : need_h <= 16 ? 16 : need_h <= 24 ? 24 : 32;
   a.upt = upt;
   if (!in_registers(a.opt, upt, a.apass, a.hpl)) return 0;
+  // a level on one workgroup beside a wide one: fewer rows per thread for the
+  // narrow one, rather than the largest instance for both (driving shape, K =
+  // 16, 64, 128, 192: 48 us, 72 otherwise)
+  if (a.opt == 4 && upt > 16 && !quad) return 0;
   a.umax = a.opt == 4 ? (upt <= 8 ? 8 : upt <= 16 ? 16 : 32) : a.opt == 2 ? (upt <= 16 ? 16 : 32) : (upt <= 8 ? 8 : upt <= 16 ? 16 : 32);
   // lane sl's terms at stride kst: it covers the lane's whole register bucket
   // (every read stays in the lane's zero-filled places), and 12, 20 or 36
