@@ -3,7 +3,7 @@
 // with the full weight matrices (Sec. II, Fig. 1; the augmented matrix of
 // Sec. III without any factorisation), then the same cell update.
 //
-// Two launches per run.  exact_xproj_kernel computes the x part of every
+// Two launches per run.  exact_xproj_*_kernel computes the x part of every
 // gate row for every timestep at once (it does not depend on h).  The
 // persistent exact_lstm_kernel then runs the recurrence: workgroup j owns a
 // slice of hidden units and the four W_h rows of each, held in registers for
@@ -531,7 +531,7 @@ __global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
 // by four rows.  What bounds a timestep at eight sequences is the fp32 rate
 // (1024 multiply-adds per lane, 3.4 us) and then the exchange of h between
 // XCDs (64 KB to every workgroup).  MI355X, D = H = 2048, eight sequences:
-// 28.7 us per timestep with W_h read from memory, 8.1 here.
+// 28.7 us per timestep with W_h read from memory, 8.1-9.1 here.
 template <int WPL, int NB>
 __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   extern __shared__ __align__(16) float lds[];
