@@ -209,14 +209,15 @@ __device__ __forceinline__ void publish_slot(float* p, float v, bool near) {
   store_slot(p, bits == kEmpty ? 0x7FC00000u : bits, near);
 }
 
-// Poll the 16-byte units tid + 512 r of src (uniform; `bytes` long) whose bit
+// Poll the 16-byte units tid + stride r of src (uniform; `bytes` long) whose bit
 // r is set in `pending` until none of their slots is empty; unit r goes to
 // dst + map[r] (LDS, 16-byte aligned).  Agent-scope loads pass the L1 by.  The
 // first round loads every unit without a branch, so that each is looked at
-// as it arrives; later rounds load what is missing.  Bounded: past the spin
+// as it arrives (kFirst; for many units across XCDs it comes too early and only
+// delays the next: see exact_wide_kernel); later rounds load what is missing.  Bounded: past the spin
 // limit, or once another wait has failed, the failure is recorded and the
 // missing values read 0.
-template <int kUnits>
+template <int kUnits, bool kFirst = true>
 __device__ __forceinline__ void poll_units(float* dst, const float* src, int bytes, const int* map, unsigned pending,
                                            unsigned* err, int stride = kThreads) {
   if (!pending) return;
@@ -232,7 +233,7 @@ __device__ __forceinline__ void poll_units(float* dst, const float* src, int byt
   };
   // empty is the largest unsigned value
   auto full = [](const u32x4& w) { return max(max(w[0], w[1]), max(w[2], w[3])) != kEmpty; };
-  {
+  if constexpr (kFirst) {
     u32x4 w[kUnits];
 #pragma unroll
     for (int r = 0; r < kUnits; ++r) w[r] = load(r);   // past the end: zeros, not looked at

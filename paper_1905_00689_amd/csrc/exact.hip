@@ -531,7 +531,8 @@ __global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
 // by four rows.  What bounds a timestep at eight sequences is the fp32 rate
 // (1024 multiply-adds per lane, 3.4 us) and then the exchange of h between
 // XCDs (64 KB to every workgroup).  MI355X, D = H = 2048, eight sequences:
-// 28.7 us per timestep with W_h read from memory, 8.1-9.1 here.
+// 28.7 us per timestep with W_h read from memory, 7.7 here; 8.7 with a first
+// poll round of all units at once (poll_units), which comes too early.
 template <int WPL, int NB>
 __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   extern __shared__ __align__(16) float lds[];
@@ -637,7 +638,7 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
     }
     if (cell_ok) a.h_out[((size_t)t * B + lane) * H + unit] = hv;
     if (t + 1 < T) fetch_px(t + 1);
-    if (t + 1 < T || T == 1) poll_units<kUnits>(hs, out, (int)(third * 4), udst, upend, a.err);
+    if (t + 1 < T || T == 1) poll_units<kUnits, false>(hs, out, (int)(third * 4), udst, upend, a.err);
     lds_barrier();
   }
   if (a.c_out && cell_ok) a.c_out[(size_t)lane * H + unit] = c;
