@@ -293,6 +293,21 @@ approx_lstm_status approx_lstm_plan(const approx_lstm_model* m, int32_t T, int32
                                     int32_t n_levels, int32_t online, int32_t num_cu, int32_t* out);
 
 /*
+ * approx_lstm_plan_shares -- what every workgroup of a pair-kernel group (see
+ * approx_lstm_set_recurrence) owns of one level's exchange; no device work.
+ *
+ *   T, B, levels, n_levels, num_cu   as for approx_lstm_plan
+ *   level    which of the levels
+ *   out      host [2 * cap]: exchange slots of z, then hidden units, of each
+ *            workgroup in turn
+ *   width    host: workgroups of a group at that level, at most cap; 0 when the
+ *            run does not take the pair kernel
+ */
+approx_lstm_status approx_lstm_plan_shares(const approx_lstm_model* m, int32_t T, int32_t B, const int32_t* levels,
+                                           int32_t n_levels, int32_t num_cu, int32_t level, int32_t* out, int32_t cap,
+                                           int32_t* width);
+
+/*
  * approx_lstm_run_stack -- stacked LSTM layers, each progressive: layer l
  * (l >= 1) takes as its input sequence the h_t of layer l-1 at the same level.
  *

@@ -67,6 +67,7 @@ _sigs = {
     "approx_lstm_run_schedule": [_vp, _vp, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp],
     "approx_lstm_run_noalloc": [_vp, _vp, _i32, _i32, _vp, _vp, _vp, _i32, _vp, _vp, _vp],
     "approx_lstm_plan": [_vp, _i32, _i32, _vp, _i32, _i32, _i32, _vp],
+    "approx_lstm_plan_shares": [_vp, _i32, _i32, _vp, _i32, _i32, _i32, _vp, _i32, _vp],
     "approx_lstm_check": [_vp, _vp],
     "approx_lstm_set_launch": [_vp, _i32, _i32],
     "approx_lstm_set_batched_path": [_vp, _i32],
@@ -238,6 +239,16 @@ def approx_lstm_plan(model, T, B, levels=None, online=0, num_cu=0):
     out = np.zeros(len(PLAN_FIELDS), np.int32)
     _check(lib.approx_lstm_plan(model.handle, T, B, ap, len(arr), int(online), int(num_cu), out.ctypes.data))
     return dict(zip(PLAN_FIELDS, (int(v) for v in out)))
+
+
+def approx_lstm_plan_shares(model, T, B, levels, level=0, num_cu=0):
+    """[(z slots, units)] of every workgroup of a pair-kernel group at one level
+    (no device work); empty when the run does not take the pair kernel."""
+    arr, ap = _host(levels, np.int32)
+    out, width = np.zeros((1024, 2), np.int32), ctypes.c_int32()
+    _check(lib.approx_lstm_plan_shares(model.handle, T, B, ap, len(arr), int(num_cu), int(level), out.ctypes.data,
+                                       len(out), ctypes.byref(width)))
+    return [tuple(int(v) for v in r) for r in out[:width.value]]
 
 
 def approx_lstm_run_stack(models, x, levels, h_out, stream=None):

@@ -1402,6 +1402,30 @@ approx_lstm_status approx_lstm_plan(const approx_lstm_model* m, int32_t T, int32
   return APPROX_LSTM_OK;
 }
 
+approx_lstm_status approx_lstm_plan_shares(const approx_lstm_model* m, int32_t T, int32_t B, const int32_t* levels,
+                                           int32_t n_levels, int32_t num_cu, int32_t level, int32_t* out, int32_t cap,
+                                           int32_t* width) {
+  g_last_error.clear();
+  int32_t plan[10];
+  const approx_lstm_status st = approx_lstm_plan(m, T, B, levels, n_levels, 0, num_cu, plan);
+  if (st != APPROX_LSTM_OK) return st;
+  if (!out || !width || cap < 1 || level < 0 || level >= n_levels)
+    return fail(APPROX_LSTM_ERR_INVALID_ARG, "bad arguments");
+  *width = 0;
+  if (!plan[8]) return APPROX_LSTM_OK;   // not a pair-kernel run
+  alstm::PairArgs pa{};
+  size_t lds = 0;
+  plan_pair_run(m, pa, T, B, levels, n_levels, num_cu > 0 ? num_cu : m->num_cu, &lds);
+  const alstm::PairLevel& v = pa.lv[level];
+  if (v.P > cap) return fail(APPROX_LSTM_ERR_INVALID_ARG, "need room for %d workgroups", v.P);
+  *width = v.P;
+  for (int j = 0; j < v.P; ++j) {
+    out[2 * j] = alstm::share_of(v.slots, v.P, j).count;
+    out[2 * j + 1] = alstm::share_of(m->H, v.P, j).count;
+  }
+  return APPROX_LSTM_OK;
+}
+
 approx_lstm_status approx_lstm_get_timing(approx_lstm_model* m, void* hip_stream, double* stamps_us, int32_t n) {
   g_last_error.clear();
   if (!m || !stamps_us) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null pointer argument");

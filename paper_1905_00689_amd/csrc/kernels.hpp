@@ -149,6 +149,18 @@ constexpr int kCtlWords = kNearWidth + 8;   // start words of a group: one per w
 constexpr int kSpreadWords = 512;           // start words of a single group over the whole device, then its decision
 static_assert(kSpreadWords < kXcds * kCtlWords, "the spread group's decision lies within the start words");
 
+// Share j of n things dealt to P workgroups in consecutive runs whose lengths
+// differ by at most one: with P <= n no workgroup goes without.  The exchange
+// of the pair kernel relies on that: its owner empties a slot because everyone
+// has published what it computed from it (see level_fits).
+struct Share {
+  int first, count;
+};
+__host__ __device__ inline Share share_of(int n, int P, int j) {
+  const int q = n / P, r = n - q * P;
+  return Share{j * q + (j < r ? j : r), q + (j < r ? 1 : 0)};
+}
+
 // One level of a pair run: its budget and launch shape.
 struct PairLevel {
   int K;         // terms per group
@@ -156,8 +168,8 @@ struct PairLevel {
   int S, lgS;    // lanes per U row (lanes_for_level(K)) and its log2
   int kpl;       // exchange slots of a lane: ceil(K / S) rounded up to 4
   int slots;     // exchange slots in all: G * S * kpl
-  int OM;        // slots owned per workgroup (at most 32 * apass)
-  int RU;        // hidden units owned per workgroup
+  int OM;        // slots owned per workgroup, at most (share_of; at most 32 * apass)
+  int RU;        // hidden units owned per workgroup, at most (share_of)
   int kst;       // LDS floats between the terms of consecutive lanes of a row
   int zst;       // LDS floats per group of z
 };

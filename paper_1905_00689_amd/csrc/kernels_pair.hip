@@ -3,11 +3,11 @@
 // slice in registers: each (level, sequence) pair of a run is its own
 // recurrence, computed by a group of P workgroups of 512 threads.
 //
-// Workgroup j of a group owns OM consecutive slots of the z exchange (a slot
-// is one term; the slots go lane by lane of a U row, see slot_tau) and the
-// hidden units [j*RU, j*RU + RU): the h-part entries of its terms (16 lanes
-// per term, one or two passes) and the U entries of its 4*RU gate rows (S
-// lanes per row, one, two or four rows per thread) stay in registers for the
+// Workgroup j of a group owns up to OM consecutive slots of the z exchange (a
+// slot is one term; the slots go lane by lane of a U row, see slot_tau) and up
+// to RU consecutive hidden units (share_of, at least one of each): the h-part
+// entries of its terms (16 lanes per term, one or two passes) and the U entries
+// of its units' four gate rows (S lanes per row, one, two or four rows per thread) stay in registers for the
 // whole sequence, P_x of every timestep (input_proj_kernel) in LDS.  Per
 // timestep:
 //   phase A  each term's lane group sums its h-part entries against h_{t-1}
@@ -176,6 +176,17 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
   __syncthreads();
 }
 
+// v, in a vector register and looked at again where it is used: a lane mask kept
+// over the loop instead takes two scalar registers, and those of the loop are
+// spilled already (a spilled mask comes back through v_readlane on the path
+// between the cell update and its store: 3 us in 2 x 32 timesteps at H = 1024).
+// Not where two workgroups share a compute unit, whose vector registers are the
+// scarce ones (driving shape, K = 512: 67.4 us with it, 66.8 without).
+__device__ __forceinline__ int in_register(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // OPT output rows per thread with UMAX U entries each in registers, APASS
 // phase-A passes with HMAX h-part entries per lane each.  Every loop runs to
 // its compile-time bound: entries past a lane's share are zeros (a U entry
@@ -223,13 +234,13 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       // the group's other workgroups hear of this one
       for (int lb = g; lb < a.L * B; lb += ng) {
         const PairLevel& v = a.lv[lb / B];
+        if (j >= v.P) continue;
+        const Share zo = share_of(v.slots, v.P, j), ho = share_of(H, v.P, j);
         float* zx = a.ex + lb * exf;
         float* hx = zx + 2 * a.zslots;
         for (int half = 0; half < 2; ++half) {
-          for (int i = j * v.OM + lane; i < min((j + 1) * v.OM, v.slots); i += 64)
-            store_slot(zx + half * a.zslots + i, kEmpty, false);
-          for (int i = j * v.RU + lane; i < min((j + 1) * v.RU, H); i += 64)
-            store_slot(hx + half * a.hpad + i, kEmpty, false);
+          for (int i = lane; i < zo.count; i += 64) store_slot(zx + half * a.zslots + zo.first + i, kEmpty, false);
+          for (int i = lane; i < ho.count; i += 64) store_slot(hx + half * a.hpad + ho.first + i, kEmpty, false);
           if (j == 0 && H + lane < a.hpad) store_slot(hx + half * a.hpad + H + lane, 0u, false);
         }
       }
@@ -243,15 +254,17 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   for (int lb = g; lb < a.L * B; lb += ng) {
     const int lev = lb / B, b = lb - lev * B;
     const PairLevel& v = a.lv[lev];
-    const int P = v.P, K = v.K, OM = v.OM, RU = v.RU, zst = v.zst, kst = v.kst, kpl = v.kpl;
+    const int P = v.P, K = v.K, OM = v.OM, zst = v.zst, kst = v.kst, kpl = v.kpl;
     if (j >= P) continue;
     const bool local = P == 1 || K == 0;   // nothing exchanged
-    const int r0 = j * RU, rc = max(0, min(RU, H - r0));
-    const int n_owned = max(0, min(OM, v.slots - j * OM));
+    const Share ho = share_of(H, P, j), zo = share_of(v.slots, P, j);
+    // (divisions are vector work: back to scalar registers)
+    const int r0 = __builtin_amdgcn_readfirstlane(ho.first), rc = __builtin_amdgcn_readfirstlane(ho.count);
+    const int s0 = __builtin_amdgcn_readfirstlane(zo.first), n_owned = __builtin_amdgcn_readfirstlane(zo.count);
     const int S = __builtin_amdgcn_readfirstlane(v.S), lgS = __builtin_amdgcn_readfirstlane(v.lgS);
     // Slot w of the z exchange is entry k = w % kpl of lane sl of a row of group
     // g (w / kpl = g*S + sl), the term n = sl + S*k: a lane's terms are
-    // consecutive, and so are a workgroup's slots [j*OM, j*OM + OM).  In LDS
+    // consecutive, and so are a workgroup's slots [s0, s0 + n_owned).  In LDS
     // the entry sits at zs[g*zst + sl*kst + k].  tau < 0: no term (n >= K).
     auto slot_tau = [&](int w) {
       const int blk = w / kpl, n = (blk & (S - 1)) + S * (w - blk * kpl);
@@ -270,7 +283,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     const int npx = T * n_owned, TB = T * B;
     float px0 = 0.0f, h00 = 0.0f;
     if (tid < npx) {
-      const int io0 = tid / T, tau = slot_tau(j * OM + io0);
+      const int io0 = tid / T, tau = slot_tau(s0 + io0);
       if (tau >= 0) px0 = a.px[(size_t)tau * TB + (tid - io0 * T) * B + b];
     }
     if (tid < H && a.h0) h00 = a.h0[(size_t)b * H + tid];
@@ -284,7 +297,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
 #pragma unroll
     for (int p = 0; p < APASS; ++p) {
       const int ia = sub + 32 * p;
-      const int tau = ia < n_owned ? slot_tau(j * OM + ia) : -1;
+      const int tau = ia < n_owned ? slot_tau(s0 + ia) : -1;
       tauv[p] = max(tau, 0);
       if (sla == 0) nown[ia] = tau >= 0 ? tau / G : K;
       sg[p] = tau >= 0 ? a.sigma[tau] : 0.0f;
@@ -303,8 +316,13 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     const int zb = (G == 4 ? (rs & 3) : 0) * zst + sl * kst;
     const bool cand = (rs & 3) == 2;   // the cell candidate's rows: tanh
     int zown[APASS];                   // LDS places of the owned slots (one workgroup)
+    int zput[APASS];                   // the slot that this lane publishes per pass, or -1
 #pragma unroll
-    for (int p = 0; p < APASS; ++p) zown[p] = sub + 32 * p < n_owned ? slot_pos(j * OM + sub + 32 * p) : 0;
+    for (int p = 0; p < APASS; ++p) {
+      const bool own = sub + 32 * p < n_owned;
+      zown[p] = own ? slot_pos(s0 + sub + 32 * p) : 0;
+      zput[p] = own && sla == 0 ? s0 + sub + 32 * p : -1;
+    }
     // ---- cell roles: a wave holds the rows of 16 * OPT / S units (row slots
     // [w * 64/S, (w+1) * 64/S) in each of the OPT passes); its lane cl takes
     // unit cl, pass co = cl / (16/S), row slots 4 ck .. 4 ck + 3 (ck = cl %
@@ -314,6 +332,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     const int co = lane >> (4 - lgS), ck = lane & ((16 >> lgS) - 1);
     const int cunit = (wv * rpw + 4 * ck + co * nslots) >> 2;
     const bool cell_ok = lane < upw && cunit < rc;
+    const int hput = cell_ok ? r0 + cunit : -1;   // the unit that this lane updates
     float cst = (cell_ok && a.c0) ? a.c0[(size_t)b * H + r0 + cunit] : 0.0f;
     float* ysw = ldsf + lay.ys + (size_t)wv * OPT * rpw;
 #pragma unroll
@@ -372,7 +391,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
     for (int i = tid; i < a.zfloats; i += kThreads) zs[i] = 0.0f;
     if (tid < npx) pxs[(tid % T) * OM + tid / T] = px0;
     for (int i = tid + kThreads; i < npx; i += kThreads) {
-      const int io = i / T, t = i - io * T, tau = slot_tau(j * OM + io);
+      const int io = i / T, t = i - io * T, tau = slot_tau(s0 + io);
       pxs[t * OM + io] = tau >= 0 ? a.px[(size_t)tau * TB + t * B + b] : 0.0f;
     }
     __syncthreads();
@@ -441,19 +460,18 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
             if (sub + 32 * p < n_owned && nown[sub + 32 * p] >= kt) z[p] = 0.0f;
           if (t + 1 < T) kt = a.sched[t + 1];   // on its way while the exchanges wait
         }
-        if (sla == 0) {
 #pragma unroll
-          for (int p = 0; p < APASS; ++p) {
-            const int ia = sub + 32 * p;
-            if (ia >= n_owned) break;
+        for (int p = 0; p < APASS; ++p) {
+          const int w = zput[p];
+          if (w >= 0) {
             if constexpr (kLocal) {
               zs[zown[p]] = z[p];
             } else if constexpr (kSpread) {
-              zpub[ia] = z[p];
+              zpub[sub + 32 * p] = z[p];
             } else {
-              publish_slot(zxt + j * OM + ia, z[p], near);
+              publish_slot(zxt + w, z[p], near);
               // z_{t-1}: everyone's h_{t-1} is here, so everyone has read it
-              store_slot(zxe + j * OM + ia, kEmpty, near);
+              store_slot(zxe + w, kEmpty, near);
             }
           }
         }
@@ -463,8 +481,8 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
           if (wv == kWaves - 1) {
             wait_memory();   // the emptied h slots, before this workgroup's z_t
             if (lane < n_owned) {
-              publish_slot(zxt + j * OM + lane, zpub[lane], false);
-              store_slot(zxe + j * OM + lane, kEmpty, false);
+              publish_slot(zxt + s0 + lane, zpub[lane], false);
+              store_slot(zxe + s0 + lane, kEmpty, false);
             }
           }
           poll_units<kMaxUnits>(zs, zxt, a.zslots * 4, zdi, zpend, a.err, kSpreadPollers);
@@ -510,22 +528,21 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const bool more = t + 1 < T;   // nobody reads the last timestep's h
-        if (lane < upw) {
+        const int u = kLocal || TWO ? hput : in_register(hput);
+        if (u >= 0) {
           const float4 g4 = *reinterpret_cast<const float4*>(ysw + co * rpw + 4 * ck);
           float h2;
           cell_from_gates(g4.x, g4.y, g4.z, g4.w, cst, h2);
-          if (cell_ok) {
-            if constexpr (kLocal) {
-              hs[r0 + cunit] = h2;
-            } else if constexpr (kSpread) {
-              hpub[cunit] = h2;
-            } else if (more) {
-              publish_slot(hxt + r0 + cunit, h2, near);
-              // h_{t-1}: everyone's z_t is here, so everyone has read it
-              store_slot(hxe + r0 + cunit, kEmpty, near);
-            }
-            if constexpr (!kSpread) *hout = h2;
+          if constexpr (kLocal) {
+            hs[u] = h2;
+          } else if constexpr (kSpread) {
+            hpub[cunit] = h2;
+          } else if (more) {
+            publish_slot(hxt + u, h2, near);
+            // h_{t-1}: everyone's z_t is here, so everyone has read it
+            store_slot(hxe + u, kEmpty, near);
           }
+          if constexpr (!kSpread) *hout = h2;
         }
         if (stamp) put_stamp(5 + 4 * t, clock64());
         if constexpr (kSpread) {
@@ -638,6 +655,12 @@ bool level_fits(const PairArgs& a, PairLevel& v, int hcap, int P, int optcap, Le
   if (!in_registers(s.opt, s.upt, s.apass, s.need_h)) return false;
   // the four gate rows of a unit must be adjacent lane groups of one wave
   if (4 * v.S > 64) return false;
+  // Everyone owns slots and units.  A slot is emptied once everyone's values
+  // that were computed from it are here (z_{t-1} once h_{t-1} is, h_{t-1} once
+  // z_t is), and is polled again only once its owner's next value of the other
+  // kind is here, which the owner publishes after the emptied slots are stored.
+  // A workgroup without units, or without slots, would take part in neither.
+  if (P > 1 && v.K > 0 && P > std::min(v.slots, a.H)) return false;
   if (v.slots > 4 * kMaxUnits * kThreads || a.H > 4 * kMaxUnits * kThreads) return false;
   v.P = P;
   v.OM = OM;
