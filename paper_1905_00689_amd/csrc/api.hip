@@ -148,7 +148,7 @@ struct approx_lstm_model {
   int batched_persistent = 1;        // 0: per-timestep kernel pairs only; else persistent where it fits
   uint16_t* d_pzx = nullptr;         // [slots][2][G][16][Kp] bf16
   size_t pzx_cap = 0;                // elements
-  uint16_t* d_phx = nullptr;         // [slots][2][16][Hp] bf16
+  uint16_t* d_phx = nullptr;         // [slots][4][16][Hp] bf16
   size_t phx_cap = 0;
   unsigned long long* d_pctl = nullptr;   // [slots][kCtlWords] start words
   size_t pctl_cap = 0;
@@ -333,8 +333,8 @@ approx_lstm_status run_batched(approx_lstm_model* m, const float* x, int T, int 
   int W = 0, slots = 0;
   if (m->batched_persistent && alstm::plan_batched_persistent(a, kmax, &W, &slots)) {
     st = ensure_persistent(m, (size_t)slots * 2 * m->G * alstm::kCohort * m->Kp,
-                           (size_t)slots * 2 * alstm::kCohort * m->Hp, (size_t)slots * alstm::kCtlWords, n_levels,
-                           stream);
+                           (size_t)slots * alstm::kBatchedHParts * alstm::kCohort * m->Hp,
+                           (size_t)slots * alstm::kCtlWords, n_levels, stream);
     if (st != APPROX_LSTM_OK) return st;
     a.zx = m->d_pzx; a.hx = m->d_phx; a.ctl = m->d_pctl;
     a.err = m->d_err;

@@ -397,8 +397,16 @@ __global__ void batched_init_kernel(BatchedArgs a) {
 // compute units at H = 512), values travel through its L2 as plain stores
 // (agent scope where a group finds itself on several XCDs), in slots that are
 // empty until written: pairs of bf16 here, polled 16 bytes (eight values) at a
-// time.  Two halves of z and h by timestep parity; z_{t-1} is emptied once
-// h_{t-1} of everyone is here, h_{t-1} once z_t is.  MI355X, H = 512, 256
+// time.  Everyone publishes h (every workgroup owns units) and polls both z and
+// h, but a workgroup may own no z (its eight waves take the first tiles that are
+// left, so at K < H the later workgroups have none).  So only h tells what a
+// workgroup has read: once everyone's h_{t-1} is here, everyone has read z_{t-1}
+// and h_{t-2}.  z_{t-1} is emptied beside z_t, its store waited for before h_t is
+// published, and z_{t+1}, in its place, is polled by those who have h_t: two
+// halves.  h_{t-2} is emptied beside h_t, its store waited for before h_{t+1} is
+// published, and h_{t+2}, in its place, is polled by those who have h_{t+1}: four
+// parts (with three, and the store before h_t, 132 us instead of 128 at the
+// sizes below).  MI355X, H = 512, 256
 // sequences, 16 timesteps, K = 512: flagged and tagged exchanges between XCDs
 // 150 us, now 80; per timestep h-projection 0.6, z 1.5 (64 KB to every
 // workgroup), accumulation and cell 0.9, h 0.9 us.
@@ -408,6 +416,7 @@ __global__ void batched_init_kernel(BatchedArgs a) {
 constexpr int kMaxKs = 16;     // register-resident contraction steps of 32 (H and K up to 512)
 constexpr int kZUnits = 8;     // 16-byte units of z polled per thread (G * K up to 2048 terms of 16 sequences)
 constexpr int kHUnits = 2;     // and of h (H up to 512)
+constexpr int kHParts = kBatchedHParts;
 constexpr unsigned kCohortWait = 100000000u;   // wall ticks (a second)
 
 __device__ __forceinline__ unsigned full_pair(unsigned v) { return v == kEmpty ? 0x7FC07FC0u : v; }
@@ -449,10 +458,10 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   uint16_t* zs = hs + kCohort * hld;                                        // [G][16][zld]
   float* ys = reinterpret_cast<float*>(zs + (size_t)G * kCohort * zld);     // [4][32][17]
   int* modes = reinterpret_cast<int*>(ys + 4 * 32 * 17);
-  // the group's exchange: z [2][G*16][Kl32], h [2][16][Hp]
-  const int zhalf = G * kCohort * Kl32, hhalf = kCohort * Hp;
+  // the group's exchange: z [2][G*16][Kl32], h [4][16][Hp]
+  const int zhalf = G * kCohort * Kl32, hpart = kCohort * Hp;
   uint16_t* zx = a.zx + (size_t)slot * 2 * G * kCohort * Kp;
-  uint16_t* hx = a.hx + (size_t)slot * 2 * hhalf;
+  uint16_t* hx = a.hx + (size_t)slot * kHParts * hpart;
   unsigned long long* hand = a.ctl + (size_t)slot * kCtlWords;
   unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
   const int nkh = Hp >> 5, nku = Kl32 >> 5;   // live steps
@@ -463,7 +472,8 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
     // this workgroup's share of the slots empty before the others hear of it
     for (int i = w * 512 + tid; i < zhalf; i += W * 512)   // two halves of zhalf / 2 words
       store_slot(reinterpret_cast<float*>(zx) + i, kEmpty, false);
-    for (int i = w * 512 + tid; i < hhalf; i += W * 512) store_slot(reinterpret_cast<float*>(hx) + i, kEmpty, false);
+    for (int i = w * 512 + tid; i < kHParts * hpart / 2; i += W * 512)
+      store_slot(reinterpret_cast<float*>(hx) + i, kEmpty, false);
     wait_memory();
     lds_barrier();
     if (wave == 7) {
@@ -519,8 +529,8 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
 #pragma unroll
   for (int r = 0; r < kHUnits; ++r) {
     const int u = tid + 512 * r, row = u / (Hp >> 3);
-    if (8 * u < hhalf) hpend |= 1u << r;
-    hdst[r] = 8 * u < hhalf ? (row * hld + 8 * (u - row * (Hp >> 3))) >> 1 : 0;
+    if (8 * u < hpart) hpend |= 1u << r;
+    hdst[r] = 8 * u < hpart ? (row * hld + 8 * (u - row * (Hp >> 3))) >> 1 : 0;
   }
   // columns of z past Kl32 are never written and must read zero
   for (int i = tid; i < G * kCohort * zld / 2; i += 512) reinterpret_cast<unsigned*>(zs)[i] = 0u;
@@ -536,7 +546,7 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   const bool near = mode == kNear;
 
   const int ncoh = (a.B + kCohort - 1) / kCohort;
-  int par = 0;   // parity of the timestep, counted over the group's cohorts
+  int par = 0, hpar = 0;   // timestep mod 2 and mod 4, counted over the group's cohorts
   for (int coh = slot; coh < ncoh; coh += slots) {
     const int b0 = coh * kCohort;
     // h_{-1}; columns past H are zero
@@ -556,9 +566,9 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
     f32x4 pv = f32x4{0.f, 0.f, 0.f, 0.f};
     if (has_tile) pv = fetch_p(0);
     lds_barrier();
-    for (int t = 0; t < a.T; ++t, par ^= 1) {
+    for (int t = 0; t < a.T; ++t, par ^= 1, hpar = (hpar + 1) % kHParts) {
       uint16_t* zt = zx + par * zhalf;
-      uint16_t* ht = hx + par * hhalf;
+      uint16_t* ht = hx + hpar * hpart;
       f32x4 pn = f32x4{0.f, 0.f, 0.f, 0.f};
       if (has_tile) pn = fetch_p(min(t + 1, a.T - 1));
       // ---- h-projection of the wave's tile, published as bf16
@@ -607,7 +617,7 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
         const unsigned hn = (unsigned)__shfl_down((int)hb, 16, 64);
         if ((lq & 1) == 0) {
           store_slot(reinterpret_cast<float*>(ht + hoff), full_pair(hb | (hn << 16)), near);
-          store_slot(reinterpret_cast<float*>(hx + (par ^ 1) * hhalf + hoff), kEmpty, near);
+          store_slot(reinterpret_cast<float*>(hx + (hpar ^ 2) * hpart + hoff), kEmpty, near);   // h_{t-2}
         }
       }
       if (gu_live && b < a.B) {
@@ -615,9 +625,9 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
         if (a.c_out && t == a.T - 1) a.c_out[((size_t)level * a.B + b) * H + gu] = c;
       }
       if (more) {
-        poll_units<kHUnits>(reinterpret_cast<float*>(hs), reinterpret_cast<const float*>(ht), hhalf * 2, hdst, hpend,
+        poll_units<kHUnits>(reinterpret_cast<float*>(hs), reinterpret_cast<const float*>(ht), hpart * 2, hdst, hpend,
                             a.err);
-        wait_memory();   // the emptied slots too, before this workgroup's z_{t+1}
+        wait_memory();   // the emptied slots too, before this workgroup's h_{t+1}
       }
       lds_barrier();
     }

@@ -278,7 +278,7 @@ struct BatchedArgs {
   // persistent recurrence (one launch per level instead of T kernel pairs);
   // null zx selects the per-timestep kernels
   uint16_t* zx;      // [slots][2*G*16*Kp] bf16: z of a cohort's timesteps t and t-1
-  uint16_t* hx;      // [slots][2*16*Hp]: h of them
+  uint16_t* hx;      // [slots][4*16*Hp]: h of the last timesteps
   unsigned long long* ctl;   // [slots][kCtlWords]: start words of the groups, all zero between launches
   unsigned* err;     // set when a bounded wait expires
   unsigned tag_base; // launch sequence << 16 of level 0; level l uses tag_base + (l << 16)
@@ -303,6 +303,8 @@ size_t batched_ppart_floats(int ncu);
 
 // Sequences per cohort of the persistent batched recurrence (the MFMA tile width).
 constexpr int kCohort = 16;
+// Timesteps of h held by its exchange (see batched_persistent_kernel).
+constexpr int kBatchedHParts = 4;
 
 
 // Shape of a persistent batched launch at budget K: W workgroups per cohort
@@ -311,7 +313,7 @@ constexpr int kCohort = 16;
 // most 512 (their contraction steps are held in registers), at most one
 // h-projection tile of 16 terms per wave, and a cohort's workgroups resident
 // at once (whole groups per XCD).  Exchange sizes (in 16-bit elements): zx
-// slots*2*G*16*Kp, hx slots*2*16*Hp; start words slots*kCtlWords.
+// slots*2*G*16*Kp, hx slots*4*16*Hp; start words slots*kCtlWords.
 int plan_batched_persistent(const BatchedArgs& a, int K, int* W, int* slots);
 
 // Exact (dense) LSTM: x [T][B][D], h0, c0 [B][H] or null, h_out [T][B][H],

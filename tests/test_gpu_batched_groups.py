@@ -48,6 +48,22 @@ def test_buckets_and_groups(H, rank, G, T, Bs):
         assert rel_err(h[:, :, -1:], hl) < TOL
 
 
+# few terms beside many units: the first workgroup (one of 16, one of 10) owns every z tile, the others only poll
+@pytest.mark.parametrize("H,rank,G,T,Bn", [(512, 20, 4, 12, 40), (300, 20, 1, 12, 330), (512, 100, 4, 2, 16)])
+def test_workgroups_without_terms(H, rank, G, T, Bn):
+    D = 40
+    w = synth.make(D, H, T, Bn, index=97)
+    say("batched, workgroups without terms H", H, "rank", rank, "G", G)
+    m = B.approx_lstm_prepare(w.W[:, :D], w.W[:, D:], w.b, D, H, rank, prune_ratio=0.5, groups=G, factor_dtype=1,
+                              flags=B.FLAG_DEVICE_FACTORISE)
+    h, c = run_gpu(m, w.x, [rank], want_c=True)
+    ho, co = oracle.run(exported_factors(m), w.b, w.x, [rank], operand_round="bf16")
+    assert rel_err(h, ho) < TOL
+    assert np.abs(c - co).max() < TOL * max(1.0, np.abs(co).max())
+    for _ in range(8):
+        assert np.array_equal(run_gpu(m, w.x, [rank])[0], h)
+
+
 @pytest.mark.parametrize("D,H,rank,T,Bn", [
     (40, 96, 70, 16, 700),      # 3 x 88 tiles of 128 rows: the last 256-row tile is half empty, x read by elements
     # 16 x 17 tiles, the last column tile half empty, x read by float4; D = 64 is two slices, which the small call
