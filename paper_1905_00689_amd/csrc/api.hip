@@ -24,7 +24,7 @@ namespace {
 thread_local std::string g_last_error;
 
 // The device-side error word's allocation: the word's block, then the start
-// words of the groups (zero between runs).
+// words of the groups.
 constexpr size_t kErrBytes = 64;
 constexpr size_t kCtlBytes = sizeof(unsigned long long) * alstm::kXcds * alstm::kCtlWords;
 
@@ -293,16 +293,13 @@ approx_lstm_status ensure_bulk(approx_lstm_model* m, size_t floats, hipStream_t 
 
 // Exchange buffers of the persistent batched recurrence: z and h of every
 // cohort in flight (each launch empties its slots itself) and the groups'
-// start words (zeroed when new; every launch leaves them zero).  Reserves
+// start words (cleared by the x-projection).  Reserves
 // n_levels launch sequence numbers: on return m->seq + n_levels <= 0xFFFF.
 approx_lstm_status ensure_persistent(approx_lstm_model* m, size_t zx, size_t hx, size_t ctl, int n_levels,
                                      hipStream_t stream) {
   approx_lstm_status st = grow(m->d_pzx, m->pzx_cap, zx, stream, "hipMalloc(zx)");
   if (st == APPROX_LSTM_OK) st = grow(m->d_phx, m->phx_cap, hx, stream, "hipMalloc(hx)");
-  if (st == APPROX_LSTM_OK && ctl > m->pctl_cap) {
-    st = grow(m->d_pctl, m->pctl_cap, ctl, stream, "hipMalloc(start words)");
-    if (st == APPROX_LSTM_OK) HIP_TRY(alstm::launch_clear_u64(m->d_pctl, m->pctl_cap, stream), "clear(start words)");
-  }
+  if (st == APPROX_LSTM_OK) st = grow(m->d_pctl, m->pctl_cap, ctl, stream, "hipMalloc(start words)");
   if (m->seq + (unsigned)n_levels > 0xFFFFu) m->seq = 0;
   return st;
 }
@@ -337,6 +334,7 @@ approx_lstm_status run_batched(approx_lstm_model* m, const float* x, int T, int 
                            (size_t)slots * alstm::kCtlWords, n_levels, stream);
     if (st != APPROX_LSTM_OK) return st;
     a.zx = m->d_pzx; a.hx = m->d_phx; a.ctl = m->d_pctl;
+    a.ctl_words = slots * alstm::kCtlWords;
     a.err = m->d_err;
     a.tag_base = m->seq << 16;
     m->seq += (unsigned)n_levels;
@@ -443,7 +441,7 @@ struct CallerScratch {
   unsigned char* base;
   size_t bytes;
   unsigned* seq;
-  unsigned long long* ctl;   // start words of the pair kernel's groups (zero between runs)
+  unsigned long long* ctl;   // start words of the pair kernel's groups
 };
 
 // Launch tag sequence of the next run: the model's own counter, or the
@@ -565,6 +563,7 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
   proj.vidx = m->d_vidx; proj.vval = m->d_vval; proj.nx = m->d_nx; proj.px = pxw;
   proj.xvec = (m->D % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   proj.num_cu = m->num_cu;
+  proj.ctl = pa.ctl;
   HIP_TRY(alstm::launch_pair(proj, pa, P, stream), "launch pair_lstm_kernel");
   return APPROX_LSTM_OK;
 }

@@ -74,6 +74,7 @@ __global__ void __launch_bounds__(2 * BM) batched_xproj_kernel(BatchedArgs a, in
   constexpr int kNB = kXBN / kBR;                     // loads of a B slice per thread
   __shared__ __align__(16) uint16_t As[2][BM * kXLD];
   __shared__ __align__(16) uint16_t Bs[2][kXBN * kXLD];
+  clear_start_words(a.ctl, a.ctl_words);
   const int nt = nM * nN;
   const int part = blockIdx.x / nt, bid = blockIdx.x - part * nt;
   int tile = bid;
@@ -463,7 +464,7 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   uint16_t* zx = a.zx + (size_t)slot * 2 * G * kCohort * Kp;
   uint16_t* hx = a.hx + (size_t)slot * kHParts * hpart;
   unsigned long long* hand = a.ctl + (size_t)slot * kCtlWords;
-  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  unsigned long long* decide = hand + kNearWidth;
   const int nkh = Hp >> 5, nku = Kl32 >> 5;   // live steps
   const int u0 = w * 32;
   const bool exch = K > 0;   // without terms no workgroup reads another's z or h
@@ -477,7 +478,7 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
     wait_memory();
     lds_barrier();
     if (wave == 7) {
-      const int mode = group_start(hand, decide, w, W, a.tag_base | 0xFFFFu, kCohortWait);
+      const int mode = group_start(hand, decide, w, W, a.tag_base | 0xFFFFu, kCohortWait, a.err);
       if (lane == 0) modes[0] = mode;
     }
   } else if (tid == 0) {
@@ -540,7 +541,6 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
   const int mode = __builtin_amdgcn_readfirstlane(modes[0]);
   if (mode >= kAlone) {
     if (tid == 0) __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    group_leave(hand, decide, W);
     return;
   }
   const bool near = mode == kNear;
@@ -631,12 +631,6 @@ __global__ void __launch_bounds__(512) batched_persistent_kernel(BatchedArgs a, 
       }
       lds_barrier();
     }
-  }
-  // z of every timestep was exchanged, so everyone has read the decision and
-  // everyone's words: open for the next start
-  if (exch && tid == 0) {
-    __hip_atomic_store(hand + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (w == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

@@ -275,12 +275,32 @@ __device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)
 // or nothing left to do here.
 enum StartMode { kNear = 0, kFar = 1, kAlone = 2, kLeave = 3 };
 
+// A group's decision: the launch's tag and one of these.
+enum StartOutcome : unsigned { kEveryoneGoes = 1, kOneAlone = 2 };
+
+// One lane: the group's outcome if it is already there (of this launch), else
+// 0, and then it is `mine` from here on.
+__device__ __forceinline__ unsigned decide_start(unsigned long long* decide, unsigned tag, StartOutcome mine) {
+  unsigned long long seen = 0ull;   // as cleared
+  do {                              // (twice at most, past a decision of another launch)
+    if (__hip_atomic_compare_exchange_strong(decide, &seen, ((unsigned long long)tag << 32) | mine, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return 0u;
+  } while ((unsigned)(seen >> 32) != tag);
+  return (unsigned)seen;
+}
+
 // The start of a group, run by one wave of each of its P workgroups:
 // workgroup j's word gets (tag, XCD id), the lanes wait for everyone's words.
-// decide[0]: 0 open, 1 everyone goes, 2 one workgroup alone; decide[1] counts
-// the workgroups that left, the last of which reopens the group's words.
-__device__ int group_start(unsigned long long* hand, unsigned* decide, int j, int P, unsigned tag,
-                           unsigned wait_ticks) {
+// The decision of the group is (tag, StartOutcome).  Words and decisions of
+// other launches carry other tags and are as good as empty, so nothing is
+// cleared at the end of a run, when some workgroup may still be looking; a
+// launch whose tag may have been used before (a replay of a captured one, or
+// after the sequence has wrapped) has the words cleared by the kernel before it
+// on its stream (clear_start_words).  Bounded: `wait_ticks`, and past a decision
+// that everyone goes the spin limit.
+__device__ int group_start(unsigned long long* hand, unsigned long long* decide, int j, int P, unsigned tag,
+                           unsigned wait_ticks, unsigned* err) {
   const int lane = threadIdx.x & 63;
   unsigned xcc;
   asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
@@ -290,6 +310,7 @@ __device__ int group_start(unsigned long long* hand, unsigned* decide, int j, in
   const unsigned long long t0 = wall_clock64();
   bool same = true, late = false;
   int next = lane;   // words lane, lane + 64, ... of the group, in turn
+  unsigned spins = 0;
   while (true) {
     if (next < P) {
       const unsigned long long w = load_tagged(hand + next);
@@ -300,38 +321,34 @@ __device__ int group_start(unsigned long long* hand, unsigned* decide, int j, in
     }
     if (__all(next >= P)) break;
     if (!late && (wall_clock64() - t0 >= (unsigned long long)wait_ticks ||
-                  __hip_atomic_load(decide, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u)) {
+                  load_tagged(decide) == (((unsigned long long)tag << 32) | kOneAlone))) {
       // one outcome for the whole group: whoever swaps first decides
       late = true;
       unsigned seen = 0u;
-      if (lane == 0)
-        __hip_atomic_compare_exchange_strong(decide, &seen, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0) seen = decide_start(decide, tag, kOneAlone);
       seen = __builtin_amdgcn_readfirstlane(seen);
-      if (seen != 1u) return seen == 0u ? kAlone : kLeave;
+      if (seen != kEveryoneGoes) return seen == 0u ? kAlone : kLeave;
       // someone saw everyone: all are resident, their words are coming
+    }
+    if (late && ++spins >= kSpinLimit) {
+      if (lane == 0) __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return kLeave;
     }
   }
   if (!late) {
     unsigned seen = 0u;
-    if (lane == 0)
-      __hip_atomic_compare_exchange_strong(decide, &seen, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-    if (__builtin_amdgcn_readfirstlane(seen) == 2u) return kLeave;
+    if (lane == 0) seen = decide_start(decide, tag, kEveryoneGoes);
+    if (__builtin_amdgcn_readfirstlane(seen) == kOneAlone) return kLeave;
   }
   return __all(same) ? kNear : kFar;
 }
 
-// A workgroup of a group that does not go: the last of its P to come through
-// here (the one that ran alone among them) reopens the group's words.
-__device__ void group_leave(unsigned long long* hand, unsigned* decide, int P) {
-  if (threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(decide + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(P - 1)) {
-    for (int i = 0; i < P; ++i)
-      __hip_atomic_store(hand + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(decide + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+// A grid's part in clearing `n` start words for the next kernel of its stream.
+__device__ __forceinline__ void clear_start_words(unsigned long long* ctl, int n) {
+  if (!ctl) return;
+  const int blk = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  for (int i = blk * (int)blockDim.x + (int)threadIdx.x; i < n; i += (int)(gridDim.x * gridDim.y * blockDim.x))
+    __hip_atomic_store(ctl + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Workgroup barrier that orders LDS only.  __syncthreads() would also wait

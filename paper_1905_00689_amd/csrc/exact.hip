@@ -90,6 +90,7 @@ __device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
 template <bool WV, bool XV>
 __global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs a, int nrow) {
   __shared__ float part[kWaves][4][16][17];
+  clear_start_words(a.ctl, kXcds * kCtlWords);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int TB = a.T * a.B, D = a.D, R = 4 * a.H;
@@ -162,6 +163,7 @@ template <bool WV, bool XV>
 __global__ void __launch_bounds__(kThreads) exact_xproj_tile_kernel(ExactArgs a, int nrow) {
   __shared__ __align__(16) float As[2][kTile * kTileLd];
   __shared__ __align__(16) float Bs[2][kTile * kTileLd];
+  clear_start_words(a.ctl, kXcds * kCtlWords);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
@@ -398,7 +400,7 @@ __global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
   float* ys = cs + ((H + 3) & ~3);
   const size_t exf = 3 * (size_t)a.slots;
   unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
-  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  unsigned long long* decide = hand + kNearWidth;
   if (wv == kWaves - 1) {
     int mode = kFar;
     if (!local) {
@@ -408,7 +410,7 @@ __global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
           if (w < a.slots) store_slot(a.ex + b * exf + (size_t)(i / RU) * a.slots + w, kEmpty, false);
         }
       wait_memory();
-      mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks);
+      mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks, a.err);
     }
     if (lane == 0) modes[0] = mode;
   }
@@ -514,14 +516,6 @@ __global__ void __launch_bounds__(kThreads) exact_near_kernel(ExactArgs a) {
   if (mode == kAlone) {
     for (int b = g; b < B; b += kXcds) exact_alone<16>(a, b, hs, cs, ys);
   }
-  if (mode >= kAlone) {
-    group_leave(hand, decide, a.P);
-  } else if (tid == 0) {
-    // an exchange is over, so every workgroup of the group has read the
-    // decision and everyone's words: open for the next start
-    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
 }
 
 // Wide layers: W_h in the registers of the whole device (64 MB at H = 2048),
@@ -543,13 +537,13 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   float* hown = lds + 4;                 // [NB][8] h of the owned slots
   float* hs = hown + NB * 8;             // [NB][64][LD]
   unsigned long long* hand = a.ctl;
-  unsigned* decide = reinterpret_cast<unsigned*>(a.ctl + kSpreadWords);
+  unsigned long long* decide = a.ctl + kSpreadWords;
   const size_t third = (size_t)NB * slots;
   if (wv == kWaves - 1) {
     for (int i = lane; i < 3 * NB * 8; i += 64)
       store_slot(a.ex + (i / 8) * (size_t)slots + j * 8 + (i & 7), kEmpty, false);
     wait_memory();
-    const int mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks);
+    const int mode = group_start(hand, decide, j, a.P, a.tag_base | 0xFFFFu, a.wait_ticks, a.err);
     if (lane == 0) modes[0] = mode;
   }
   const int w = j * 8 + wv, unit = slot_unit(w, kpl, 64);
@@ -591,7 +585,6 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
     __syncthreads();
     if (mode == kAlone)
       for (int b = 0; b < B; ++b) exact_alone<64>(a, b, lds + 4, lds + 4 + 2 * H, lds + 4 + 3 * H);
-    group_leave(hand, decide, a.P);
     return;
   }
   for (int t = 0; t < T; ++t) {
@@ -642,10 +635,6 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
     lds_barrier();
   }
   if (a.c_out && cell_ok) a.c_out[(size_t)lane * H + unit] = c;
-  if (tid == 0) {
-    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
 }
 
 // The recurrence on any width, for the shapes and launches the kernels above do
@@ -942,6 +931,9 @@ hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
     else if (wv) launch_xproj<true, false>(a, stream);
     else launch_xproj<false, false>(a, stream);
     const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  } else if (a.ctl) {
+    const hipError_t e = launch_clear_u64(a.ctl, kXcds * kCtlWords, stream);
     if (e != hipSuccess) return e;
   }
   if (a.P > 0) {

@@ -285,6 +285,7 @@ struct FusedArgs {
   int* prog;                  // host memory: [G] iterations done
   unsigned long long* ex;     // [G][5][kFusedN] slots
   unsigned long long* ctl;    // start words
+  unsigned* err;              // set when a bounded wait expires
   size_t sG, sQ, sc;
   int groups, n, kmax, P, rows;   // rows per workgroup (every one of the P has some)
   unsigned tag;
@@ -386,7 +387,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
   unsigned long long *xw1 = ex, *xw2 = ex + kFusedN, *xw3 = ex + 2 * kFusedN, *xc1 = ex + 3 * kFusedN,
                      *xc2 = ex + 4 * kFusedN;
   unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
-  unsigned* decide = reinterpret_cast<unsigned*>(hand + kNearWidth);
+  unsigned long long* decide = hand + kNearWidth;
   const int cn = (kmax - j + P - 1) / P;            // coefficient slots j + P*i cleared here
 
   double* Qg = a.Q + g * a.sQ;
@@ -401,7 +402,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
       clear64(xc2 + j + P * i, false);
     }
     wait_memory();
-    const int mode = group_start(hand, decide, j, P, a.tag, kFusedWait);
+    const int mode = group_start(hand, decide, j, P, a.tag, kFusedWait, a.err);
     if (lane == 0) {
       flags[0] = mode;
       flags[1] = 0;
@@ -425,7 +426,6 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
     }
   __syncthreads();
   if (flags[0] >= kAlone) {   // not all resident: nothing done, the host sees no progress
-    group_leave(hand, decide, P);
     return;
   }
   const bool near = flags[0] == kNear;
@@ -554,14 +554,9 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
         for (int e = 0; e < 8; ++e) qr[s][e] = lane + 64 * e < n ? q[lane + 64 * e] : 0.0;
       }
   }
-  if (tid == 0) {
-    // (everyone has published several w since the start)
-    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (j == 0) {
-      a.kk[g] = k;
-      a.prog[g] = k;
-      __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+  if (j == 0 && tid == 0) {   // (everyone has read kk: all have published several w since)
+    a.kk[g] = k;
+    a.prog[g] = k;
   }
 }
 
@@ -784,10 +779,11 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
     fa.groups = G; fa.n = n; fa.kmax = kmax;
     fa.rows = (n + std::min(kXcdCus, (n + 7) / 8) - 1) / std::min(kXcdCus, (n + 7) / 8);
     fa.P = (n + fa.rows - 1) / fa.rows;
-    const size_t words = (size_t)G * 5 * kFusedN + (size_t)kXcds * kCtlWords;
+    const size_t words = (size_t)G * 5 * kFusedN + (size_t)kXcds * kCtlWords + 1;
     FD_TRY(buf.alloc(fa.ex, words), "hipMalloc(Lanczos exchange)");
     fa.ctl = fa.ex + (size_t)G * 5 * kFusedN;
-    FD_TRY(hipMemsetAsync(fa.ctl, 0, sizeof(unsigned long long) * kXcds * kCtlWords, stream), "clear start words");
+    fa.err = reinterpret_cast<unsigned*>(fa.ctl + kXcds * kCtlWords);
+    FD_TRY(hipMemsetAsync(fa.ctl, 0, sizeof(unsigned long long) * (kXcds * kCtlWords + 1), stream), "clear start words");
     fa.G = dG; fa.Q = dQ; fa.kk = dk; fa.act = dact; fa.alpha = dal; fa.beta = dbe; fa.prog = dprog;
     fa.sG = sG; fa.sQ = sQ; fa.sc = sc;
     FD_TRY(hipFuncSetAttribute((const void*)lanczos_fused_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -891,6 +891,7 @@ __global__ void __launch_bounds__(kThreads) progressive_lstm_kernel(RunArgs a) {
 template <int XC, int PT>
 __global__ void __launch_bounds__(kThreads) input_proj_kernel(RunArgs a, int xchunk, int xrow) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
+  clear_start_words(a.ctl, kXcds * kCtlWords);
   float* xt = reinterpret_cast<float*>(lds_raw);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int TB = a.T * a.B, D = a.D, NZ = a.NZ;

@@ -48,6 +48,7 @@ struct RunArgs {
   float* hbx;      // bulk h exchange: [2][hb_stride] floats, h_t of every (level, seq) at
                    // parity t & 1 (agent-coherent stores and loads); null unless bulk_h
   unsigned* hflag; // bulk h exchange: [P] words, workgroup j's tag once its h_t is stored
+  unsigned long long* ctl = nullptr;   // start words that the input projection clears for the next kernel, or null
   unsigned* err;
   unsigned long long* stamps;  // null, or [4 + 4T] stamps written by workgroup 0: [0] wall clock
                                // and [1] shader clock at the start of the recurrence; shader
@@ -178,7 +179,7 @@ struct PairLevel {
 //   px     [GK][T*B]            x-part projections (input_proj_kernel)
 //   ex     [L*B][2*(zslots + hpad)] float   exchange of every pair: z [2][zslots], h [2][hpad]
 //   ctl    [kXcds][kCtlWords]   start words of the groups (or of one spread over the
-//                               device: kSpreadWords of them), all zero between runs
+//                               device: kSpreadWords of them), cleared by the input projection
 //   h_out  [L][T][B][H]; c_out [L][B][H] or null
 struct PairArgs {
   const float* h0;
@@ -279,7 +280,8 @@ struct BatchedArgs {
   // null zx selects the per-timestep kernels
   uint16_t* zx;      // [slots][2*G*16*Kp] bf16: z of a cohort's timesteps t and t-1
   uint16_t* hx;      // [slots][4*16*Hp]: h of the last timesteps
-  unsigned long long* ctl;   // [slots][kCtlWords]: start words of the groups, all zero between launches
+  unsigned long long* ctl;   // [slots][kCtlWords]: start words of the groups, cleared by the x-projection
+  int ctl_words;     // slots * kCtlWords
   unsigned* err;     // set when a bounded wait expires
   unsigned tag_base; // launch sequence << 16 of level 0; level l uses tag_base + (l << 16)
   int max_wg;        // workgroups that may be resident at once (one per compute unit)

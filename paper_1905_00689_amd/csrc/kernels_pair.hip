@@ -225,7 +225,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   }
   const bool started = pg > 1 && j < pg;
   unsigned long long* hand = a.ctl + (size_t)g * kCtlWords;
-  unsigned* decide = reinterpret_cast<unsigned*>(ng > 1 ? hand + kNearWidth : a.ctl + kSpreadWords);
+  unsigned long long* decide = ng > 1 ? hand + kNearWidth : a.ctl + kSpreadWords;
   const size_t exf = 2 * ((size_t)a.zslots + a.hpad);   // floats of a pair's exchange: z [2][zslots], h [2][hpad]
   if (wv == kWaves - 1) {
     int mode = kFar;
@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       }
       wait_memory();
     }
-    if (started) mode = group_start(hand, decide, j, pg, a.tag_base | 0xFFFFu, a.wait_ticks);
+    if (started) mode = group_start(hand, decide, j, pg, a.tag_base | 0xFFFFu, a.wait_ticks, a.err);
     if (lane == 0) modes[0] = mode;
   }
 
@@ -588,14 +588,6 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
       __syncthreads();
       run_alone(a, lb / B, lb % B, hs, zs, ldsf + lay.cs, ldsf + lay.ys);
     }
-  }
-  if (mode >= kAlone) {
-    group_leave(hand, decide, pg);
-  } else if (tid == 0) {
-    // the widest pair's exchanges are over, so every workgroup of the group
-    // has read the decision and everyone's words: open for the next start
-    __hip_atomic_store(hand + j, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (j == 0) __hip_atomic_store(decide, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
