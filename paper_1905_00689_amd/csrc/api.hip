@@ -435,8 +435,9 @@ ScratchLayout scratch_layout(size_t px_floats, size_t zx_words, size_t hx_words,
 }
 
 // Workspace handed in by the allocation-free entry point: `base` (device,
-// 256-byte aligned) holds `bytes`; launch tags come from `seq` (per device),
-// and the exchange words of the region are cleared whenever it wraps.
+// 256-byte aligned) holds `bytes`; launch tags come from `seq` (per device).
+// Runs of other layouts leave floats anywhere in it, and a float can look like
+// a tag, so the tagged words of a run are cleared before it.
 struct CallerScratch {
   unsigned char* base;
   size_t bytes;
@@ -444,20 +445,12 @@ struct CallerScratch {
   unsigned long long* ctl;   // start words of the pair kernel's groups
 };
 
-// Launch tag sequence of the next run: the model's own counter, or the
-// caller workspace's; on wrap the exchange words are cleared (fill kernels)
-// so that no stale tag can match.
-approx_lstm_status next_tag(approx_lstm_model* m, const CallerScratch* ws, size_t ws_exchange_offset,
-                            hipStream_t stream, unsigned* tag_seq) {
+// Launch tag sequence of the next run: the caller workspace's, or the model's
+// own counter, on whose wrap the model's tagged words are cleared so that no
+// stale tag can match.
+approx_lstm_status next_tag(approx_lstm_model* m, const CallerScratch* ws, hipStream_t stream, unsigned* tag_seq) {
   if (ws) {
-    *ws->seq = (*ws->seq + 1) & 0xFFFFu;
-    if (*ws->seq == 0) {
-      const size_t words = (ws->bytes - ws_exchange_offset) / 8;
-      HIP_TRY(alstm::launch_clear_u64(reinterpret_cast<unsigned long long*>(ws->base + ws_exchange_offset), words,
-                                      stream),
-              "clear(scratch)");
-      *ws->seq = 1;
-    }
+    *ws->seq = *ws->seq == 0xFFFFu ? 1u : *ws->seq + 1;
     *tag_seq = *ws->seq;
     return APPROX_LSTM_OK;
   }
@@ -522,7 +515,6 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
                             const CallerScratch* ws, bool* taken) {
   const size_t pairs = (size_t)pa.L * pa.B, GK = (size_t)m->G * kmax;
   const size_t px_floats = std::max<size_t>(1, GK * pa.T * pa.B), ex_floats = pairs * 2 * ((size_t)pa.zslots + pa.hpad);
-  size_t exch_off = 0;
   float* pxw = nullptr;   // x-part projections: written by the input projection, read by the recurrence
   *taken = true;
   if (ws) {
@@ -534,7 +526,6 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
     pa.ex = reinterpret_cast<float*>(ws->base + sl.zx);
     pa.ctl = ws->ctl;
     pxw = reinterpret_cast<float*>(ws->base + sl.px);
-    exch_off = sl.zx;
   } else {
     approx_lstm_status st = ensure_workspace(m, px_floats, 0, 0, stream);
     if (st == APPROX_LSTM_OK) st = grow(m->d_pex, m->pex_cap, ex_floats, stream, "hipMalloc(pair exchange)");
@@ -544,7 +535,7 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
   }
   pa.px = pxw;
   unsigned tag_seq = 0;
-  approx_lstm_status st = next_tag(m, ws, exch_off, stream, &tag_seq);
+  approx_lstm_status st = next_tag(m, ws, stream, &tag_seq);
   if (st != APPROX_LSTM_OK) return st;
   pa.tag_base = tag_seq << 16;
   pa.stamps = nullptr;
@@ -626,14 +617,13 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
   }
   if (single && (gst = plan_general()) != APPROX_LSTM_OK) return gst;
   unsigned tag_seq = 0;
-  size_t exch_off = 0;
   if (ws) {
     a.px = reinterpret_cast<float*>(ws->base + sl.px);
     a.zx = reinterpret_cast<unsigned long long*>(ws->base + sl.zx);
     a.hx = reinterpret_cast<unsigned long long*>(ws->base + sl.hx);
     a.hbx = a.bulk_h ? reinterpret_cast<float*>(ws->base + sl.hbx) : nullptr;
     a.hflag = a.bulk_h ? reinterpret_cast<unsigned*>(ws->base + sl.hflag) : nullptr;
-    exch_off = sl.zx;
+    HIP_TRY(alstm::launch_clear_u64(a.zx, (sl.total - sl.zx) / 8, stream), "clear(exchange)");
   } else {
     approx_lstm_status st = ensure_workspace(m, px_floats, zx_words, hx_words, stream);
     if (st != APPROX_LSTM_OK) return st;
@@ -646,7 +636,7 @@ approx_lstm_status run_progressive(approx_lstm_model* m, const float* x, int32_t
     a.hflag = a.bulk_h ? m->d_hflag : nullptr;
   }
   {
-    approx_lstm_status st = next_tag(m, ws, exch_off, stream, &tag_seq);
+    approx_lstm_status st = next_tag(m, ws, stream, &tag_seq);
     if (st != APPROX_LSTM_OK) return st;
   }
   a.tag_base = tag_seq << 16;
