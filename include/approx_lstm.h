@@ -72,6 +72,9 @@ typedef enum {
 #define APPROX_LSTM_FLAG_STEPWISE       (1ull << 4) /* device factorisation with one kernel per step of a
                                                        Lanczos iteration also where one launch would run
                                                        a whole block of them (for tests: same bits) */
+#define APPROX_LSTM_FLAG_GIVE_UP        (1ull << 5) /* device factorisation whose block launches give up
+                                                       a wait at the first look (for tests: the
+                                                       factorisation starts over stepwise, same bits) */
 
 typedef struct approx_lstm_model approx_lstm_model;   /* opaque */
 

@@ -28,6 +28,7 @@ FLAG_KEEP_UNPRUNED = 1 << 1
 FLAG_DEVICE_FACTORISE = 1 << 2
 FLAG_NON_RESIDUAL = 1 << 3
 FLAG_STEPWISE = 1 << 4
+FLAG_GIVE_UP = 1 << 5
 
 
 class ApproxLstmError(RuntimeError):

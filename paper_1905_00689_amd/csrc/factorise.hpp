@@ -30,6 +30,7 @@ struct FactoriseOptions {
   bool residual = true;         // false: each term is deflated with its whole v (successive
                                 // approximations of the original matrix), not its pruned v
   bool fused = true;            // device: blocks of Lanczos iterations in one launch where they fit
+  bool give_up = false;         // device: a wait of such a launch is given up at the first look
 };
 
 // Factorise W (rows x cols, row-major, float64) into `rank` terms keeping

@@ -285,7 +285,9 @@ struct FusedArgs {
   int* prog;                  // host memory: [G] iterations done
   unsigned long long* ex;     // [G][5][kFusedN] slots
   unsigned long long* ctl;    // start words
-  unsigned* err;              // set when a bounded wait expires
+  unsigned* err;              // set when a bounded wait expires; fail (host memory) then too
+  int* fail;
+  unsigned spin_limit;
   size_t sG, sQ, sc;
   int groups, n, kmax, P, rows;   // rows per workgroup (every one of the P has some)
   unsigned tag;
@@ -304,9 +306,13 @@ __device__ __forceinline__ void clear64(unsigned long long* p, bool near) {
 }
 
 // dst[i] (LDS) = slot i of src for i < cnt (at most 1024), two to a load.
-// Bounded as poll_units: past the spin limit the wait is given up, and *bad
-// (LDS) tells the workgroup.
-__device__ __forceinline__ void poll64(double* dst, const unsigned long long* src, int cnt, int* bad) {
+// Bounded as poll_units: past the spin limit, or once another wait has been,
+// this one is given up.  *bad (LDS) then tells the workgroup, which publishes
+// nothing more and leaves; the error word tells the others (and the blocks
+// queued behind this one), and a.fail the host, which starts over without block
+// launches.
+__device__ __forceinline__ void poll64(const FusedArgs& a, double* dst, const unsigned long long* src, int cnt,
+                                       int* bad) {
   const int u = threadIdx.x;
   if (2 * u >= cnt) return;
   const unsigned long long addr = reinterpret_cast<unsigned long long>(src);
@@ -319,13 +325,17 @@ __device__ __forceinline__ void poll64(double* dst, const unsigned long long* sr
   while (true) {
     const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, u * 16, 0, 16 /* sc1 */);
     asm volatile("" ::: "memory");
-    const unsigned long long a = ((unsigned long long)w[1] << 32) | w[0], b = ((unsigned long long)w[3] << 32) | w[2];
-    if (a != kEmpty64 && (!two || b != kEmpty64)) {
-      dst[2 * u] = __builtin_bit_cast(double, a);
-      if (two) dst[2 * u + 1] = __builtin_bit_cast(double, b);
+    const unsigned long long v0 = ((unsigned long long)w[1] << 32) | w[0],
+                             v1 = ((unsigned long long)w[3] << 32) | w[2];
+    if (v0 != kEmpty64 && (!two || v1 != kEmpty64)) {
+      dst[2 * u] = __builtin_bit_cast(double, v0);
+      if (two) dst[2 * u + 1] = __builtin_bit_cast(double, v1);
       return;
     }
-    if (++spins >= kSpinLimit) {
+    if (++spins >= a.spin_limit ||
+        ((spins & 255u) == 0u && __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)) {
+      __hip_atomic_fetch_or(a.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.fail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       *bad = 1;
       return;
     }
@@ -363,7 +373,7 @@ __device__ __forceinline__ double wave_sum_f64_fast(double v) {
 
 // LDS doubles: rows of G, columns of the basis, q, w, coefficients, partials
 __host__ __device__ inline size_t fused_lds(int n, int kmax, int rows) {
-  return (size_t)rows * n + (size_t)(kmax + 1) * kFusedRows + 2 * (size_t)(n + 1) + kmax + 2 + 16 * kFusedRows + kFW + 2;
+  return (size_t)rows * n + (size_t)(kmax + 1) * kFusedRows + 2 * (size_t)(n + 1) + kmax + 2 + 16 * kFusedRows + kFW + 3;
 }
 
 __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
@@ -372,7 +382,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
   const int n = a.n, kmax = a.kmax, P = a.P;
   if (g >= a.groups || !a.act[g]) return;
   const int k0 = a.kk[g];
-  if (k0 >= kmax) return;
+  if (k0 >= kmax || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = j * a.rows, rc = max(0, min(a.rows, n - r0));
   double* Gr = ld;                                  // [rows][n]
@@ -382,7 +392,10 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
   double* c = w + n + 1;                            // coefficients
   double* part = c + kmax + 2;                      // [16][kFusedRows]
   double* red = part + 16 * kFusedRows;
-  int* flags = reinterpret_cast<int*>(red + kFW);   // start mode, a wait given up
+  // start mode, and for each of the five exchanges whether a wait was given up.
+  // Written between two barriers and read after the second, so the workgroup
+  // agrees on it; the same exchange of the next iteration is barriers away.
+  int* flags = reinterpret_cast<int*>(red + kFW);
   unsigned long long* ex = a.ex + (size_t)g * 5 * kFusedN;
   unsigned long long *xw1 = ex, *xw2 = ex + kFusedN, *xw3 = ex + 2 * kFusedN, *xc1 = ex + 3 * kFusedN,
                      *xc2 = ex + 4 * kFusedN;
@@ -405,7 +418,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
     const int mode = group_start(hand, decide, j, P, a.tag, kFusedWait, a.err);
     if (lane == 0) {
       flags[0] = mode;
-      flags[1] = 0;
+      for (int i = 1; i <= 5; ++i) flags[i] = 0;
     }
   }
   for (int i = tid; i < rc * n; i += kFT) Gr[i] = a.G[g * a.sG + (size_t)r0 * n + i];
@@ -431,7 +444,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
   const bool near = flags[0] == kNear;
 
   // c[j] = q_j . w of the waves' basis vectors (dots_kernel's order), published
-  auto dots = [&](int k, unsigned long long* xc) {
+  auto dots = [&](int k, unsigned long long* xc, int bad) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int v = wid + nw * s;
@@ -452,12 +465,12 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
         }
       }
       const double acc = wave_sum_f64_fast((a0 + a1) + (a2 + a3));
-      if (lane == 0) publish64(xc + v, acc, near);
+      if (lane == 0 && !bad) publish64(xc + v, acc, near);
     }
   };
   // w[i] -= sum_j c[j] Q[j][i] of the owned rows (combine_kernel's order: 16
   // chains, 8 waves of two), published by the first wave
-  auto combine = [&](int k, unsigned long long* xw) {
+  auto combine = [&](int k, unsigned long long* xw, int bad) {
     const int i = tid % kFusedRows, r = tid / kFusedRows;
     if (r < 16) {
       double acc = 0.0;
@@ -470,7 +483,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
       double s = 0.0;
 #pragma unroll
       for (int v = 0; v < 8; ++v) s += part[v * kFusedRows + tid] + part[(v + 8) * kFusedRows + tid];
-      publish64(xw + r0 + tid, w[r0 + tid] - s, near);
+      if (!bad) publish64(xw + r0 + tid, w[r0 + tid] - s, near);
     }
     lds_barrier();                  // the published values read w before it is overwritten
   };
@@ -504,24 +517,33 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
       if (wave == 0) wait_memory();
       if (lane == 0) publish64(xw1 + r0 + r, acc, near);
     }
-    poll64(w, xw1, n, flags + 1);
+    poll64(a, w, xw1, n, flags + 1);
     lds_barrier();
+    int bad = flags[1];   // (waited for only before the next publication)
     if (it > 0) clear_rows(xw3);
-    dots(k, xc1);
-    poll64(c, xc1, k + 1, flags + 1);
+    dots(k, xc1, bad);
+    if (bad) break;
+    poll64(a, c, xc1, k + 1, flags + 2);
     lds_barrier();
+    bad = flags[2];
     const double al = c[k];
-    combine(k, xw2);
-    poll64(w, xw2, n, flags + 1);
+    combine(k, xw2, bad);
+    if (bad) break;
+    poll64(a, w, xw2, n, flags + 3);
     lds_barrier();
+    bad = flags[3];
     clear_rows(xw1);
     clear_coef(xc1);
-    dots(k, xc2);
-    poll64(c, xc2, k + 1, flags + 1);
+    dots(k, xc2, bad);
+    if (bad) break;
+    poll64(a, c, xc2, k + 1, flags + 4);
     lds_barrier();
-    combine(k, xw3);
-    poll64(w, xw3, n, flags + 1);
+    bad = flags[4];
+    combine(k, xw3, bad);
+    if (bad) break;
+    poll64(a, w, xw3, n, flags + 5);
     lds_barrier();
+    bad = flags[5];
     // beta = |w|, q_{k+1} = w / beta (lanczos_next_kernel's order; n <= 512: one
     // element per thread), in every workgroup
     double ss = 0.0;
@@ -546,7 +568,7 @@ __global__ void __launch_bounds__(kFT) lanczos_fused_kernel(FusedArgs a) {
       a.beta[g * a.sc + k] = be;
     }
     lds_barrier();
-    if (flags[1]) break;   // a bounded wait was given up: the host sees no progress
+    if (bad) break;   // nothing of this iteration counts
 #pragma unroll
     for (int s = 0; s < 2; ++s)
       if (k + 1 == wid + nw * s) {
@@ -711,9 +733,12 @@ struct Resources {
     }                                             \
   } while (0)
 
-int factorise_groups_device(const double* W, int G, int rows, int cols, int rank, int nz,
-                            const FactoriseOptions& opt, std::vector<GroupFactors>& out, void* hip_stream,
-                            std::string* err) {
+namespace {
+
+constexpr int kStartOver = -2;   // a wait of a block launch was given up
+
+int factorise_groups(const double* W, int G, int rows, int cols, int rank, int nz, const FactoriseOptions& opt,
+                     std::vector<GroupFactors>& out, void* hip_stream, std::string* err) {
   out.assign(G, GroupFactors());
   for (int g = 0; g < G; ++g) init_group(out[g], rows, cols, rank, nz, opt.keep_unpruned);
   const bool left = rows <= cols;
@@ -755,10 +780,13 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
   FD_TRY(buf.alloc(dk, (size_t)G), "hipMalloc");
   // alpha and beta of every group, and the iterations done: written by the
   // device as it goes (entries are only added), read after a block's event
-  FD_TRY(hipHostMalloc((void**)&res.coef, (size_t)2 * G * sc * sizeof(double) + G * sizeof(int), hipHostMallocDefault),
+  FD_TRY(hipHostMalloc((void**)&res.coef, (size_t)2 * G * sc * sizeof(double) + (G + 1) * sizeof(int),
+                       hipHostMallocDefault),
          "hipHostMalloc");
   double *hal = res.coef, *hbe = hal + G * sc;
   int* hprog = reinterpret_cast<int*>(hbe + G * sc);
+  int* hfail = hprog + G;
+  *hfail = 0;
   double *dal = nullptr, *dbe = nullptr;   // their device addresses
   int* dprog = nullptr;
   {
@@ -785,6 +813,7 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
     fa.err = reinterpret_cast<unsigned*>(fa.ctl + kXcds * kCtlWords);
     FD_TRY(hipMemsetAsync(fa.ctl, 0, sizeof(unsigned long long) * (kXcds * kCtlWords + 1), stream), "clear start words");
     fa.G = dG; fa.Q = dQ; fa.kk = dk; fa.act = dact; fa.alpha = dal; fa.beta = dbe; fa.prog = dprog;
+    fa.fail = dprog + G; fa.spin_limit = opt.give_up ? 1u : kSpinLimit;
     fa.sG = sG; fa.sQ = sQ; fa.sc = sc;
     FD_TRY(hipFuncSetAttribute((const void*)lanczos_fused_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kLdsCap),
@@ -932,6 +961,10 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
         }
       }
       FD_TRY(hipEventSynchronize(res.ev[b & 1]), "hipEventSynchronize");
+      if (fused && *static_cast<volatile int*>(hfail)) {
+        FD_TRY(hipStreamSynchronize(stream), "hipStreamSynchronize");
+        return kStartOver;
+      }
       const int prev = b * kIterBlock, done_k = std::min(kmax, prev + kIterBlock);
       // a fused launch whose group was not all resident did nothing: the
       // missing iterations by one kernel per step (another group may then be
@@ -1125,5 +1158,19 @@ int factorise_groups_device(const double* W, int G, int rows, int cols, int rank
 }
 
 #undef FD_TRY
+
+}  // namespace
+
+int factorise_groups_device(const double* W, int G, int rows, int cols, int rank, int nz,
+                            const FactoriseOptions& opt, std::vector<GroupFactors>& out, void* hip_stream,
+                            std::string* err) {
+  int r = factorise_groups(W, G, rows, cols, rank, nz, opt, out, hip_stream, err);
+  if (r == kStartOver) {
+    FactoriseOptions stepwise = opt;
+    stepwise.fused = false;
+    r = factorise_groups(W, G, rows, cols, rank, nz, stepwise, out, hip_stream, err);
+  }
+  return r;
+}
 
 }  // namespace alstm

@@ -26,6 +26,23 @@ def test_fused_blocks_equal_stepwise(D, H, G, rank, p):
     ms = [B.approx_lstm_prepare(w.W[:, :D], w.W[:, D:], w.b, D, H, rank, prune_ratio=p, groups=G,
                                 flags=B.FLAG_DEVICE_FACTORISE | B.FLAG_KEEP_UNPRUNED | f) for f in (0, B.FLAG_STEPWISE)]
     assert ms[0].info["eff_rank"] == ms[1].info["eff_rank"]
+    same_factors(ms, G)
+
+
+# one group's factorisation, and one with many workgroups and terms
+@pytest.mark.parametrize("D,H,G,rank,p", [(60, 128, 1, 4, 0.5), (700, 512, 4, 9, 0.75), (64, 33, 4, 40, 0.5)])
+def test_a_wait_given_up_changes_no_factor(D, H, G, rank, p):
+    """The waits of the block launches end at the first look: whatever a workgroup makes of it, the
+    factors are those of the stepwise kernels, to which the host returns."""
+    w = synth.make(D, H, 1, 1, index=102)
+    say("given-up waits D", D, "H", H, "G", G, "rank", rank)
+    ms = [B.approx_lstm_prepare(w.W[:, :D], w.W[:, D:], w.b, D, H, rank, prune_ratio=p, groups=G,
+                                flags=B.FLAG_DEVICE_FACTORISE | B.FLAG_KEEP_UNPRUNED | f)
+          for f in (B.FLAG_GIVE_UP, B.FLAG_STEPWISE)]
+    same_factors(ms, G)
+
+
+def same_factors(ms, G):
     for g in range(G):
         for get in (B.approx_lstm_get_factors, B.approx_lstm_get_factors_f64):
             a, b = (get(m, g) for m in ms)
