@@ -128,7 +128,14 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
   const int wv = tid >> 6, lane = tid & 63, rpw = 64 >> lgS;
   float* ysw = ys + wv * rpw;
   float* hout = a.h_out + ((size_t)lev * T * a.B + b) * H;
+  // the first pair's stamps (nothing is waited for: the z wait ends as it starts)
+  const bool stamp = a.stamps && lev == 0 && b == 0 && tid == 0;
+  if (stamp) {
+    a.stamps[0] = wall_clock64();
+    a.stamps[1] = clock64();
+  }
   for (int t = 0; t < T; ++t) {
+    if (stamp) a.stamps[2 + 4 * t] = clock64();
     const int kt = a.sched ? a.sched[t] : K;
     for (int base = 0; base < G * K; base += kThreads / 16) {
       const int tau = base + sub;
@@ -145,6 +152,7 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
       }
     }
     __syncthreads();
+    if (stamp) a.stamps[3 + 4 * t] = a.stamps[4 + 4 * t] = clock64();
     for (int u0 = 0; u0 < H; u0 += units) {
       const int u = u0 + (rs >> 2);
       float acc = 0.0f, bias = 0.0f;
@@ -170,6 +178,11 @@ __device__ void run_alone(const PairArgs& a, int lev, int b, float* hs, float* z
       }
       __syncthreads();
     }
+    if (stamp) a.stamps[5 + 4 * t] = clock64();
+  }
+  if (stamp) {
+    a.stamps[2 + 4 * T] = clock64();
+    a.stamps[3 + 4 * T] = wall_clock64();
   }
   if (a.c_out)
     for (int i = tid; i < H; i += kThreads) a.c_out[((size_t)lev * a.B + b) * H + i] = cs[i];

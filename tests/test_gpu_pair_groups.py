@@ -99,6 +99,23 @@ def test_runs_on_two_streams_at_once():
             assert np.array_equal(h.cpu().numpy(), ref)
 
 
+def test_stamps_of_a_lone_workgroup():
+    """A timed run whose group falls back to one workgroup has that workgroup's stamps, not an earlier run's."""
+    w, m = model(128, 512, 8, 1, 64, 0.75)
+    B.approx_lstm_set_timing(m, 1)
+    run_gpu(m, w.x, [64])
+    group = B.approx_lstm_get_timing(m, 8)
+    B.approx_lstm_set_start_wait(m, 0.0)
+    totals = []
+    for _ in range(5):   # (all of a group seen at the first look would go ahead)
+        run_gpu(m, w.x, [64])
+        s = B.approx_lstm_get_timing(m, 8)
+        assert s[0] == 0.0 and (np.diff(s) >= 0.0).all(), s
+        totals.append(s[-1])
+    say("group", group[-1], "alone", totals)
+    assert max(totals) > 3.0 * group[-1]
+
+
 def test_start_wait_range():
     _, m = model(64, 32, 2, 1, 4, 0.5)
     for bad in (-1.0, float("nan"), 2e7):
