@@ -123,7 +123,7 @@ struct approx_lstm_model {
   float* d_pex = nullptr;                // pair kernel's exchange slots
   size_t pex_cap = 0;                    // floats
   unsigned long long* d_ctl = nullptr;   // start words of the pair kernel's groups (in d_err's allocation)
-  unsigned start_wait_ticks = 200000;    // wall ticks (10 ns) a group waits for all its workgroups
+  double start_wait_us = -1.0;           // how long a group waits for all its workgroups (< 0: start_wait)
   unsigned long long* d_stamps = nullptr;
   size_t stamps_cap = 0;             // words
   int timing = 0;                    // record per-timestep stamps
@@ -502,6 +502,19 @@ int plan_pair_run(const approx_lstm_model* m, alstm::PairArgs& pa, int T, int B,
   return alstm::plan_pair(pa, hcap, num_cu, m->launch_blocks, lds);
 }
 
+// Wall ticks (10 ns) that a group waits for all its workgroups to be resident,
+// from the caller's setting (us), else a quarter of the time in which one
+// workgroup would do the group's work, between 2 ms and half a second (the waits
+// of the exchange end at about one): waiting costs at most that much more, and
+// another stream's kernels are mostly over sooner.  One workgroup reads `bytes`
+// of slices at 7 to 20 GB/s (MI355X; H = 512, K = 64, 16 timesteps 0.36 ms;
+// exact, H = 2048, eight sequences, 64 timesteps 5.0 s, where the group takes
+// 0.57 ms), so after 2 ms the widest exact runs would go from one to thousands.
+unsigned start_wait(double us, double bytes) {
+  if (us < 0.0) us = std::min(std::max(bytes / 8e3 / 4.0, 2e3), 5e5);
+  return (unsigned)(us * 100.0);
+}
+
 // XCD of the first group of the next pair run: in turn, so that runs on
 // several streams tend to sit on different XCDs (a group whose XCD is taken
 // waits, or runs on one workgroup; see group_start).
@@ -545,7 +558,12 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
     pa.stamps = m->d_stamps;
   }
   if (pa.groups == alstm::kXcds) pa.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)pairs, std::memory_order_relaxed) % alstm::kXcds);
-  pa.wait_ticks = m->start_wait_ticks;
+  double alone = 0.0;   // bytes of the slices that one workgroup reads for a group's pairs
+  for (int l = 0; l < pa.L; ++l) {
+    const double terms = (double)m->G * pa.lv[l].K;
+    alone += terms > 0 ? terms * 6.0 * m->hpre[(size_t)terms - 1] + 16.0 * m->H * pa.lv[l].K : 0.0;
+  }
+  pa.wait_ticks = start_wait(m->start_wait_us, alone * pa.T * pa.B / std::max(1, std::min<int>(pairs, pa.groups)));
   pa.h0 = h0; pa.c0 = c0; pa.h_out = h_out; pa.c_out = c_out;
   pa.sigma = m->d_sigma; pa.Ut = m->d_Ut; pa.vidx = m->d_vidx; pa.vval = m->d_vval; pa.nx = m->d_nx;
   pa.bias = m->d_bias; pa.err = m->d_err;
@@ -1102,7 +1120,7 @@ approx_lstm_status approx_lstm_set_start_wait(approx_lstm_model* m, double wait_
   g_last_error.clear();
   if (!m) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null model");
   if (!(wait_us >= 0.0 && wait_us <= 1e7)) return fail(APPROX_LSTM_ERR_INVALID_ARG, "wait must be in [0, 1e7] us");
-  m->start_wait_ticks = (unsigned)(wait_us * 100.0);   // the device's 100 MHz wall clock
+  m->start_wait_us = wait_us;
   return APPROX_LSTM_OK;
 }
 
@@ -1503,7 +1521,7 @@ struct approx_lstm_exact {
   float* d_ex = nullptr;               // h slots of the register kernels
   size_t ex_cap = 0;
   unsigned long long* d_ctl = nullptr; // start words of their groups (in d_err's allocation)
-  unsigned start_wait_ticks = 200000;  // as approx_lstm_model's
+  double start_wait_us = -1.0;         // as approx_lstm_model's
   unsigned seq = 0;
   int launch_blocks = 0;
 
@@ -1613,7 +1631,9 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
   if (ex_floats) {
     st = grow(m->d_ex, m->ex_cap, ex_floats, stream, "hipMalloc(h slots)");
     if (st != APPROX_LSTM_OK) return st;
-    a.ex = m->d_ex; a.ctl = m->d_ctl; a.wait_ticks = m->start_wait_ticks;
+    a.ex = m->d_ex; a.ctl = m->d_ctl;
+    const int side = m->H <= alstm::kNearH ? std::min<int>(B, alstm::kXcds) : 1;   // groups side by side
+    a.wait_ticks = start_wait(m->start_wait_us, 16.0 * m->H * m->H * T * B / side);
     a.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)B, std::memory_order_relaxed) % alstm::kXcds);
   }
   a.px = m->d_px; a.hx = m->d_hx; a.err = m->d_err;
@@ -1656,7 +1676,7 @@ approx_lstm_status approx_lstm_exact_set_start_wait(approx_lstm_exact* m, double
   g_last_error.clear();
   if (!m) return fail(APPROX_LSTM_ERR_INVALID_ARG, "null model");
   if (!(wait_us >= 0.0 && wait_us <= 1e7)) return fail(APPROX_LSTM_ERR_INVALID_ARG, "wait must be in [0, 1e7] us");
-  m->start_wait_ticks = (unsigned)(wait_us * 100.0);   // the device's 100 MHz wall clock
+  m->start_wait_us = wait_us;
   return APPROX_LSTM_OK;
 }
 

@@ -27,7 +27,6 @@ namespace {
 constexpr int kExactLanes = 16;   // lanes per W_h row
 constexpr int kExactRows = kThreads / kExactLanes;   // rows per pass (32)
 constexpr int kExactWpl = 32;     // W_h entries per lane held in registers (H <= 512)
-constexpr int kNearH = 768;       // hidden units up to which a sequence's W_h fits the registers of one XCD
 constexpr int kWideH = 2048;      // and up to which it fits those of the device
 constexpr int kWideSeq = 8;       // sequences of a run whose W_h is spread over the device
 constexpr int kSkinnyCols = 64;   // x columns per workgroup of the narrow x projection

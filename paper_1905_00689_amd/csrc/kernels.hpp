@@ -352,6 +352,7 @@ struct ExactArgs {
   unsigned long long* ctl;    // as PairArgs::ctl
 };
 
+constexpr int kNearH = 768;       // hidden units up to which a sequence's W_h fits the registers of one XCD
 // Shape of the kernels that hold W_h in registers: fills P .. RU (B, T, H and
 // num_cu given) and returns the floats of ex (0: they do not take the run).
 size_t plan_exact_group(ExactArgs& a);

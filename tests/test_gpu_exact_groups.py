@@ -53,3 +53,35 @@ def test_register_kernels_equal_any_width(H, T, Bn, rows):
     he, ce = oracle.row_tile_lstm(w.W, w.b, w.x, rows, h0, c0)
     assert rel_err(ref[0], he) < TOL
     assert np.abs(ref[1] - ce).max() < TOL * max(1.0, np.abs(ce).max())
+
+
+def test_the_wide_start_outlasts_a_neighbour():
+    """Another stream's products hold the compute units for tens of milliseconds when a run over the device
+    starts: it waits for them instead of falling to one workgroup, which would take over a second."""
+    T, Bn, H = 16, 8, 2048
+    w = synth.make(24, H, T, Bn, index=96)
+    m = B.approx_lstm_exact_prepare(w.W[:, :24], w.W[:, 24:], w.b, 24, H)
+    zero = np.zeros((Bn, H), np.float32)
+    ref = run(m, w, zero, zero, H)
+    x, h = torch.from_numpy(w.x).cuda(), torch.empty(T, Bn, H, device="cuda")
+    a = torch.randn(8192, 8192, device="cuda")
+    a @ a
+    torch.cuda.synchronize()
+    other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    say("wide start beside another stream's products")
+    with torch.cuda.stream(other):
+        ev[0].record()
+        for _ in range(4):
+            a @ a
+        ev[1].record()
+    with torch.cuda.stream(mine):
+        ev[2].record()
+        B.approx_lstm_exact_run(m, x, h)
+        ev[3].record()
+    torch.cuda.synchronize()
+    B.approx_lstm_exact_check(m)
+    busy, took = ev[0].elapsed_time(ev[1]), ev[2].elapsed_time(ev[3])
+    say("  products ms", busy, "run ms", took)
+    assert np.array_equal(h.cpu().numpy(), ref[0])
+    assert took < 400.0 + 2.0 * busy
