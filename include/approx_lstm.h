@@ -379,8 +379,7 @@ approx_lstm_status approx_lstm_set_recurrence(approx_lstm_model* m, int32_t kern
  * pair-kernel group wait at the start of a run for each other to be resident,
  * from the next run on.  When the wait runs out (another stream's kernels hold
  * the compute units) one workgroup computes the group's pairs alone, slowly and
- * with the same bits, and the others leave; 0 does so unless all are there at
- * once.  Until set, the wait is a quarter of the time that one workgroup is
+ * with the same bits, and the others leave; 0 does so in any case.  Until set, the wait is a quarter of the time that one workgroup is
  * estimated to take, at least 2 ms and at most 0.5 s.  Errors: null model, wait_us not in [0, 1e7].
  */
 approx_lstm_status approx_lstm_set_start_wait(approx_lstm_model* m, double wait_us);

@@ -572,7 +572,9 @@ approx_lstm_status run_pair(approx_lstm_model* m, alstm::PairArgs& pa, int P, co
   proj.vidx = m->d_vidx; proj.vval = m->d_vval; proj.nx = m->d_nx; proj.px = pxw;
   proj.xvec = (m->D % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   proj.num_cu = m->num_cu;
-  proj.ctl = pa.ctl;
+  for (int l = 0; l < pa.L; ++l)   // where a group starts
+    if (pa.lv[l].K > 0 && pa.lv[l].P > 1) proj.ctl = pa.ctl;
+  proj.ex = pa.ex; proj.ex_pairs = (int)pairs; proj.ex_zslots = pa.zslots; proj.ex_hpad = pa.hpad; proj.H = m->H;
   HIP_TRY(alstm::launch_pair(proj, pa, P, stream), "launch pair_lstm_kernel");
   return APPROX_LSTM_OK;
 }
@@ -1631,7 +1633,8 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
   if (ex_floats) {
     st = grow(m->d_ex, m->ex_cap, ex_floats, stream, "hipMalloc(h slots)");
     if (st != APPROX_LSTM_OK) return st;
-    a.ex = m->d_ex; a.ctl = m->d_ctl;
+    a.ex = m->d_ex;
+    if (a.P > 1) a.ctl = m->d_ctl;
     const int side = m->H <= alstm::kNearH ? std::min<int>(B, alstm::kXcds) : 1;   // groups side by side
     a.wait_ticks = start_wait(m->start_wait_us, 16.0 * m->H * m->H * T * B / side);
     a.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)B, std::memory_order_relaxed) % alstm::kXcds);

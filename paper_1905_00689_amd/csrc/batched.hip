@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(2 * BM) batched_xproj_kernel(BatchedArgs a, in
   constexpr int kNB = kXBN / kBR;                     // loads of a B slice per thread
   __shared__ __align__(16) uint16_t As[2][BM * kXLD];
   __shared__ __align__(16) uint16_t Bs[2][kXBN * kXLD];
-  clear_start_words(a.ctl, a.ctl_words);
+  if (clear_start_words(a.ctl, a.ctl_words)) return;
   const int nt = nM * nN;
   const int part = blockIdx.x / nt, bid = blockIdx.x - part * nt;
   int tile = bid;
@@ -728,7 +728,7 @@ hipError_t launch_batched(const BatchedArgs& a, const int* levels, int n_levels,
     const bool vec = a.xvec && a.D % kPanelDAlign == 0;
     const auto xproj = wide ? (vec ? batched_xproj_kernel<true, kXWide> : batched_xproj_kernel<false, kXWide>)
                             : (vec ? batched_xproj_kernel<true, kXBM> : batched_xproj_kernel<false, kXBM>);
-    xproj<<<dim3(gx), dim3(2 * bm), 0, stream>>>(p, nM, nN);
+    xproj<<<dim3(gx + (a.ctl ? 1 : 0)), dim3(2 * bm), 0, stream>>>(p, nM, nN);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (p.xsplit > 1) {
       const size_t n4 = (size_t)a.T * a.Bp * p.pld / 4;

@@ -297,8 +297,8 @@ __device__ __forceinline__ unsigned decide_start(unsigned long long* decide, uns
 // cleared at the end of a run, when some workgroup may still be looking; a
 // launch whose tag may have been used before (a replay of a captured one, or
 // after the sequence has wrapped) has the words cleared by the kernel before it
-// on its stream (clear_start_words).  Bounded: `wait_ticks`, and past a decision
-// that everyone goes the spin limit.
+// on its stream (clear_start_words).  Bounded: `wait_ticks` (0: one workgroup
+// alone in any case), and past a decision that everyone goes the spin limit.
 __device__ int group_start(unsigned long long* hand, unsigned long long* decide, int j, int P, unsigned tag,
                            unsigned wait_ticks, unsigned* err) {
   const int lane = threadIdx.x & 63;
@@ -309,17 +309,23 @@ __device__ int group_start(unsigned long long* hand, unsigned long long* decide,
     __hip_atomic_store(hand + j, ((unsigned long long)tag << 32) | xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const unsigned long long t0 = wall_clock64();
   bool same = true, late = false;
-  int next = lane;   // words lane, lane + 64, ... of the group, in turn
   unsigned spins = 0;
   while (true) {
-    if (next < P) {
-      const unsigned long long w = load_tagged(hand + next);
-      if ((unsigned)(w >> 32) == tag) {
-        same = same && (unsigned)w == xcc;
-        next += 64;
+    // words lane, lane + 64, ... of the group at once (one after the other took
+    // 3 us longer for 250 workgroups)
+    unsigned long long w[kSpreadWords / 64];
+#pragma unroll
+    for (int k = 0; k < kSpreadWords / 64; ++k)
+      if (64 * k < P) w[k] = load_tagged(hand + min(lane + 64 * k, P - 1));
+    bool all = true;
+    same = true;
+#pragma unroll
+    for (int k = 0; k < kSpreadWords / 64; ++k)
+      if (64 * k < P) {
+        all = all && (unsigned)(w[k] >> 32) == tag;
+        same = same && (unsigned)w[k] == xcc;
       }
-    }
-    if (__all(next >= P)) break;
+    if (__all(all) && wait_ticks != 0) break;
     if (!late && (wall_clock64() - t0 >= (unsigned long long)wait_ticks ||
                   load_tagged(decide) == (((unsigned long long)tag << 32) | kOneAlone))) {
       // one outcome for the whole group: whoever swaps first decides
@@ -336,19 +342,29 @@ __device__ int group_start(unsigned long long* hand, unsigned long long* decide,
     }
   }
   if (!late) {
+    // workgroup 0 decides for everyone, the others look (250 swaps of one word
+    // take 5 us); it is there, so the decision is coming
     unsigned seen = 0u;
-    if (lane == 0) seen = decide_start(decide, tag, kEveryoneGoes);
+    if (j == 0) {
+      if (lane == 0) seen = decide_start(decide, tag, kEveryoneGoes);
+    } else if (lane == 0) {
+      unsigned long long w = load_tagged(decide);
+      for (; (unsigned)(w >> 32) != tag && spins < kSpinLimit; ++spins) w = load_tagged(decide);
+      seen = (unsigned)(w >> 32) == tag ? (unsigned)w : kOneAlone;
+      if ((unsigned)(w >> 32) != tag) __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (__builtin_amdgcn_readfirstlane(seen) == kOneAlone) return kLeave;
   }
   return __all(same) ? kNear : kFar;
 }
 
-// A grid's part in clearing `n` start words for the next kernel of its stream.
-__device__ __forceinline__ void clear_start_words(unsigned long long* ctl, int n) {
-  if (!ctl) return;
-  const int blk = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-  for (int i = blk * (int)blockDim.x + (int)threadIdx.x; i < n; i += (int)(gridDim.x * gridDim.y * blockDim.x))
-    __hip_atomic_store(ctl + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Clears `n` start words (null: none) for the next kernel of the stream, in the
+// last workgroup of the grid, which is launched for that alone: true there.
+// (Beside a workgroup's own work its loads or its end would wait for the stores.)
+__device__ __forceinline__ bool clear_start_words(unsigned long long* ctl, int n) {
+  if (!ctl || blockIdx.x != gridDim.x - 1) return false;
+  for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) ctl[i] = 0ull;
+  return true;
 }
 
 // Workgroup barrier that orders LDS only.  __syncthreads() would also wait

@@ -89,7 +89,7 @@ __device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
 template <bool WV, bool XV>
 __global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs a, int nrow) {
   __shared__ float part[kWaves][4][16][17];
-  clear_start_words(a.ctl, kXcds * kCtlWords);
+  if (clear_start_words(a.ctl, kXcds * kCtlWords)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int TB = a.T * a.B, D = a.D, R = 4 * a.H;
@@ -162,7 +162,7 @@ template <bool WV, bool XV>
 __global__ void __launch_bounds__(kThreads) exact_xproj_tile_kernel(ExactArgs a, int nrow) {
   __shared__ __align__(16) float As[2][kTile * kTileLd];
   __shared__ __align__(16) float Bs[2][kTile * kTileLd];
-  clear_start_words(a.ctl, kXcds * kCtlWords);
+  if (clear_start_words(a.ctl, kXcds * kCtlWords)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
@@ -841,11 +841,11 @@ static void launch_xproj(const ExactArgs& a, hipStream_t stream) {
   // about half a device of tiles (MI355X, 2048 rows, tiles / 16-row groups in
   // us: D = 2048, 512 columns 179 / 103, 1024 185 / 205, 2048 195 / 405; D =
   // 512, 512 columns 55 / 56, 1024 57 / 108)
-  const long long nrow = (R + kTile - 1) / kTile, ncol = (TB + kTile - 1) / kTile;
+  const long long nrow = (R + kTile - 1) / kTile, ncol = (TB + kTile - 1) / kTile, clear = a.ctl ? 1 : 0;
   if (2 * nrow * ncol >= a.num_cu)
-    exact_xproj_tile_kernel<WV, XV><<<dim3((unsigned)(nrow * ncol)), dim3(kThreads), 0, stream>>>(a, (int)nrow);
+    exact_xproj_tile_kernel<WV, XV><<<dim3((unsigned)(nrow * ncol + clear)), dim3(kThreads), 0, stream>>>(a, (int)nrow);
   else
-    exact_xproj_skinny_kernel<WV, XV><<<dim3((unsigned)((long long)((R + 15) / 16) * ((TB + kSkinnyCols - 1) / kSkinnyCols))),
+    exact_xproj_skinny_kernel<WV, XV><<<dim3((unsigned)((long long)((R + 15) / 16) * ((TB + kSkinnyCols - 1) / kSkinnyCols) + clear)),
                                         dim3(kThreads), 0, stream>>>(a, (R + 15) / 16);
 }
 

@@ -886,12 +886,35 @@ __global__ void __launch_bounds__(kThreads) progressive_lstm_kernel(RunArgs a) {
 // device.  XC is the widest chunk: xchunk == XC with 16-byte x rows takes
 // the vector path (xrow a multiple of 4), anything else the scalar one.  The
 // per-(t, b) sums run in the same order at every XC.
+// Workgroups past the projection's prepare the pair kernel's groups (a.ctl; part
+// `blk` of `nblk`): start words clear, every slot of the exchange empty, the
+// padding of h zero.  Their stores are no part of the other workgroups, whose
+// loads or end would wait for them (0.5 us of an input projection of 5), and the
+// pair kernel's start does without them (driving shape, K = 512: 65.4 -> 64.2 us).
+__device__ __forceinline__ void prepare_groups(const RunArgs& a, int blk, int nblk) {
+  const int first = blk * kThreads + (int)threadIdx.x, step = nblk * kThreads;
+  for (int i = first; i < kXcds * kCtlWords; i += step) a.ctl[i] = 0ull;
+  const int nz = 2 * a.ex_zslots, n = nz + 2 * a.ex_hpad;
+  float* ex = a.ex;
+  for (int p = 0; p < a.ex_pairs; ++p, ex += n)
+    for (int i = first; i < n; i += step) {
+      const int h = i - nz;   // (>= 0: among the units)
+      ex[i] = __uint_as_float(h >= 0 && (h >= a.ex_hpad ? h - a.ex_hpad : h) >= a.H ? 0u : kEmpty);
+    }
+}
+
 // PT terms per wave (consecutive terms of the workgroup's PT*8): with many
 // terms, several share each staged chunk of x (launch_input_proj picks).
 template <int XC, int PT>
 __global__ void __launch_bounds__(kThreads) input_proj_kernel(RunArgs a, int xchunk, int xrow) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  clear_start_words(a.ctl, kXcds * kCtlWords);
+  const int rows = gridDim.y > 1 ? gridDim.y - (a.ctl ? 1 : 0) : 1;   // of the grid, without the extra one
+  const int extra = gridDim.y > 1 ? (blockIdx.y >= rows ? (int)blockIdx.x : -1)
+                                  : (int)blockIdx.x - (int)(gridDim.x - a.ex_blocks);
+  if (extra >= 0 && a.ctl) {
+    prepare_groups(a, extra, gridDim.y > 1 ? gridDim.x : a.ex_blocks);
+    return;
+  }
   float* xt = reinterpret_cast<float*>(lds_raw);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int TB = a.T * a.B, D = a.D, NZ = a.NZ;
@@ -924,7 +947,7 @@ __global__ void __launch_bounds__(kThreads) input_proj_kernel(RunArgs a, int xch
         ev[w][q] = 0.0f;
         ek[w][q] = 0;
       }
-  for (int cb = blockIdx.y * xchunk; cb < TB; cb += gridDim.y * xchunk) {
+  for (int cb = blockIdx.y * xchunk; cb < TB; cb += rows * xchunk) {
     const int cnt = min(xchunk, TB - cb);
     __syncthreads();
     if (a.xvec && xchunk == XC) {
@@ -1185,7 +1208,16 @@ hipError_t launch_input_proj_xc(const RunArgs& a, int gx, int gy, int xchunk, in
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  input_proj_kernel<XC, PT><<<dim3(gx, gy), dim3(kThreads), plds, stream>>>(a, xchunk, xrow);
+  // the extra workgroups come last (between the others they would move some of
+  // those two to a compute unit): a few, or in a grid of several rows one more row
+  RunArgs r = a;
+  r.ex_blocks = 0;
+  if (a.ctl) {
+    const size_t n = (size_t)a.ex_pairs * 2 * (a.ex_zslots + a.ex_hpad);
+    r.ex_blocks = (int)std::min<size_t>(16, std::max<size_t>(1, (n + 4 * kThreads - 1) / (4 * kThreads)));
+  }
+  input_proj_kernel<XC, PT><<<gy == 1 ? dim3(gx + r.ex_blocks) : dim3(gx, gy + (a.ctl ? 1 : 0)), dim3(kThreads), plds,
+                              stream>>>(r, xchunk, xrow);
   return hipGetLastError();
 }
 

@@ -48,7 +48,12 @@ struct RunArgs {
   float* hbx;      // bulk h exchange: [2][hb_stride] floats, h_t of every (level, seq) at
                    // parity t & 1 (agent-coherent stores and loads); null unless bulk_h
   unsigned* hflag; // bulk h exchange: [P] words, workgroup j's tag once its h_t is stored
-  unsigned long long* ctl = nullptr;   // start words that the input projection clears for the next kernel, or null
+  // what the input projection prepares for the next kernel, the pair kernel, where
+  // its groups start: start words to clear (null: none) and exchange slots to empty
+  unsigned long long* ctl = nullptr;
+  float* ex;               // [ex_pairs][2*(zslots + hpad)], see PairArgs
+  int ex_pairs, ex_zslots, ex_hpad;
+  int ex_blocks;           // workgroups for it past those of a one-row grid (launch_input_proj)
   unsigned* err;
   unsigned long long* stamps;  // null, or [4 + 4T] stamps written by workgroup 0: [0] wall clock
                                // and [1] shader clock at the start of the recurrence; shader
@@ -177,7 +182,8 @@ struct PairLevel {
 
 // Device pointers:
 //   px     [GK][T*B]            x-part projections (input_proj_kernel)
-//   ex     [L*B][2*(zslots + hpad)] float   exchange of every pair: z [2][zslots], h [2][hpad]
+//   ex     [L*B][2*(zslots + hpad)] float   exchange of every pair: z [2][zslots], h [2][hpad],
+//                               emptied by the input projection
 //   ctl    [kXcds][kCtlWords]   start words of the groups (or of one spread over the
 //                               device: kSpreadWords of them), cleared by the input projection
 //   h_out  [L][T][B][H]; c_out [L][B][H] or null

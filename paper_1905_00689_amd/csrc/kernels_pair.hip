@@ -242,23 +242,6 @@ __global__ void __launch_bounds__(kThreads, TWO ? 4 : 2) pair_lstm_kernel(PairAr
   const size_t exf = 2 * ((size_t)a.zslots + a.hpad);   // floats of a pair's exchange: z [2][zslots], h [2][hpad]
   if (wv == kWaves - 1) {
     int mode = kFar;
-    if (started) {
-      // own slots of both halves empty (the padding of h holds zeros) before
-      // the group's other workgroups hear of this one
-      for (int lb = g; lb < a.L * B; lb += ng) {
-        const PairLevel& v = a.lv[lb / B];
-        if (j >= v.P) continue;
-        const Share zo = share_of(v.slots, v.P, j), ho = share_of(H, v.P, j);
-        float* zx = a.ex + lb * exf;
-        float* hx = zx + 2 * a.zslots;
-        for (int half = 0; half < 2; ++half) {
-          for (int i = lane; i < zo.count; i += 64) store_slot(zx + half * a.zslots + zo.first + i, kEmpty, false);
-          for (int i = lane; i < ho.count; i += 64) store_slot(hx + half * a.hpad + ho.first + i, kEmpty, false);
-          if (j == 0 && H + lane < a.hpad) store_slot(hx + half * a.hpad + H + lane, 0u, false);
-        }
-      }
-      wait_memory();
-    }
     if (started) mode = group_start(hand, decide, j, pg, a.tag_base | 0xFFFFu, a.wait_ticks, a.err);
     if (lane == 0) modes[0] = mode;
   }
@@ -757,22 +740,32 @@ int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
   const bool xcds = num_cu >= kXcds * kXcdCus;   // the whole device: one group per XCD
   if (pairs > 1 && (want > 0 || !xcds)) return 0;
   // near groups: up to kNearWidth workgroups where two share a compute unit,
-  // up to kXcdCus otherwise; a single pair that needs more runs on every XCD
+  // up to kXcdCus otherwise; a single pair that needs more runs on every XCD.
+  // So does one whose sequence is too short to make up for what its slices cost
+  // one XCD to load: about 2 us more per MB past 2.4 than over the device, where
+  // a timestep takes 1 us longer (driving shape, K = 512, 6 MB: near 23.4 + 2.7 T
+  // us, spread 13.3 + 3.8 T; K = 256, 3 MB: 14.9 + 2.0 T, 13.3 + 3.1 T).
+  const double mb = pairs == 1 ? 1e-6 * a.lv[0].K * (6.0 * a.G * hcap[0] + 16.0 * a.H) : 0.0;
+  const bool quick = a.T < 2.0 * (mb - 2.4);
+  const int caps[2][3] = {{kNearWidth, kXcdCus, num_cu}, {num_cu, kNearWidth, kXcdCus}};
   for (int optcap : {4, 2, 1}) {
-    for (int cap : {kNearWidth, kXcdCus, num_cu}) {
+    for (int cap : caps[quick]) {
       if (cap == num_cu && (pairs > 1 || num_cu > kSpreadWords)) continue;
       const int P = plan_levels(a, hcap, std::min(cap, std::max(1, num_cu)), want, optcap);
       if (!P) continue;
       const bool two = a.opt == 1 && a.apass == 1 && a.hpl <= kTwoHmax;
-      const bool near = xcds && P <= (two ? kNearWidth : kXcdCus);
+      const bool near = xcds && P <= (two ? kNearWidth : kXcdCus) && !(quick && cap == num_cu);
       if (!near && cap != num_cu) continue;
       // a spread group's polling threads
-      if (!near && P > 1 && std::max(a.zslots, a.hpad) > 4 * kMaxUnits * kSpreadPollers) return 0;
+      if (!near && P > 1 && std::max(a.zslots, a.hpad) > 4 * kMaxUnits * kSpreadPollers) {
+        if (quick) continue;
+        return 0;
+      }
       a.stamps = reinterpret_cast<unsigned long long*>(1);   // sized with the stamps' block
       const size_t bytes = 4 * (size_t)pair_layout(a).total;
       a.stamps = nullptr;
       if (bytes > (P > kXcdCus && near ? kLdsCap / 2 : kLdsCap)) {
-        if (cap != num_cu && pairs == 1) continue;
+        if ((cap != num_cu || quick) && pairs == 1) continue;
         return 0;
       }
       a.spread = !near && P > 1 && kmax > 0;

@@ -58,8 +58,8 @@ def test_groups_equal_general_kernel(D, H, T, Bn, rank, p, groups, levels):
     assert plan["pair_kernel"] == 1
     ref = general(m, w.x, levels, h0, c0)
     assert same(run_gpu(m, w.x, levels, h0, c0, want_c=True), ref)
-    # nobody waits: unless all of a group arrive at once, one workgroup of it
-    # takes the pairs alone, with the same bits; the next run is as before
+    # nobody waits: one workgroup of a group takes the pairs alone, with the same
+    # bits; the next run is as before
     B.approx_lstm_set_start_wait(m, 0.0)
     assert same(run_gpu(m, w.x, levels, h0, c0, want_c=True), ref)
     B.approx_lstm_set_start_wait(m, 2000.0)
@@ -106,14 +106,11 @@ def test_stamps_of_a_lone_workgroup():
     run_gpu(m, w.x, [64])
     group = B.approx_lstm_get_timing(m, 8)
     B.approx_lstm_set_start_wait(m, 0.0)
-    totals = []
-    for _ in range(5):   # (all of a group seen at the first look would go ahead)
-        run_gpu(m, w.x, [64])
-        s = B.approx_lstm_get_timing(m, 8)
-        assert s[0] == 0.0 and (np.diff(s) >= 0.0).all(), s
-        totals.append(s[-1])
-    say("group", group[-1], "alone", totals)
-    assert max(totals) > 3.0 * group[-1]
+    run_gpu(m, w.x, [64])
+    alone = B.approx_lstm_get_timing(m, 8)
+    say("group", group[-1], "alone", alone[-1])
+    assert alone[0] == 0.0 and (np.diff(alone) >= 0.0).all(), alone
+    assert alone[-1] > 3.0 * group[-1]
 
 
 def test_start_wait_range():

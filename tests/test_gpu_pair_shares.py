@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (300, 203, 1, 64, 0.5, [64], 0),
     (100, 203, 1, 40, 0.5, [40], 77),      # over several XCDs
     (64, 2000, 1, 300, 0.9, [300], 0),     # over the device
+    (64, 512, 1, 510, 0.5, [510], 0),      # over several XCDs because it is short
 ])
 def test_uneven_shares_equal_general_kernel(D, H, Bn, rank, p, levels, blocks):
     w = synth.make(D, H, 2, Bn, index=73)
