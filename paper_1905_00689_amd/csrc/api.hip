@@ -1624,19 +1624,22 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
     HIP_TRY(alstm::launch_clear_u64(m->d_hx, m->hx_cap, stream), "clear(hx)");
     m->seq = 0;
   }
-  m->seq = (m->seq + 1) & 0xFFFFu;
-  if (m->seq == 0) {
+  // launch sequence numbers: one, or one per launch of the wide kernel
+  const unsigned turns = ex_floats && m->H > alstm::kNearH ? (unsigned)((B + alstm::kWideSeq - 1) / alstm::kWideSeq) : 1;
+  m->seq += 1;
+  if (m->seq + turns - 1 > 0xFFFFu) {
     HIP_TRY(alstm::launch_clear_u64(m->d_hx, m->hx_cap, stream), "clear(hx)");
     m->seq = 1;
   }
   a.tag_base = m->seq << 16;
+  m->seq += turns - 1;
   if (ex_floats) {
     st = grow(m->d_ex, m->ex_cap, ex_floats, stream, "hipMalloc(h slots)");
     if (st != APPROX_LSTM_OK) return st;
     a.ex = m->d_ex;
     if (a.P > 1) a.ctl = m->d_ctl;
     const int side = m->H <= alstm::kNearH ? std::min<int>(B, alstm::kXcds) : 1;   // groups side by side
-    a.wait_ticks = start_wait(m->start_wait_us, 16.0 * m->H * m->H * T * B / side);
+    a.wait_ticks = start_wait(m->start_wait_us, 16.0 * m->H * m->H * T * std::min<int>(B, side == 1 ? alstm::kWideSeq : B) / side);
     a.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)B, std::memory_order_relaxed) % alstm::kXcds);
   }
   a.px = m->d_px; a.hx = m->d_hx; a.err = m->d_err;

@@ -15,6 +15,7 @@
 // the dense products stopped after that many rows of every gate, the rows
 // not reached holding the bias alone.  Only the computed rows are projected
 // and multiplied.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -28,7 +29,6 @@ constexpr int kExactLanes = 16;   // lanes per W_h row
 constexpr int kExactRows = kThreads / kExactLanes;   // rows per pass (32)
 constexpr int kExactWpl = 32;     // W_h entries per lane held in registers (H <= 512)
 constexpr int kWideH = 2048;      // and up to which it fits those of the device
-constexpr int kWideSeq = 8;       // sequences of a run whose W_h is spread over the device
 constexpr int kSkinnyCols = 64;   // x columns per workgroup of the narrow x projection
 constexpr int kSkinnyUnits = 16;  // 16-byte units of a W_x row per lane held in registers there
 constexpr int kTile = 128;        // gate rows and x columns per workgroup of the tiled x projection
@@ -86,8 +86,11 @@ __device__ __forceinline__ f32x4 load4(const float* p, int k, int n) {
 // a fixed order.  WV, XV: 16-byte aligned rows of W_x and of x.  MI355X, D =
 // 2048, H = 512, 16 columns: 30.5 us (one wave per row, x staged by every
 // workgroup) -> 10.5 us.
-template <bool WV, bool XV>
+// U: 16-byte units of W_x per lane held at once, 16, or 4 where a wave's span has
+// no more (one column, D = 256: 7.2 us with 16, most of them past the span).
+template <bool WV, bool XV, int U>
 __global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs a, int nrow) {
+  constexpr int kXUnits = U < 8 ? U : 8;   // units of x at a time
   __shared__ float part[kWaves][4][16][17];
   if (clear_start_words(a.ctl, kXcds * kCtlWords)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,32 +99,32 @@ __global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs 
   const int ol0 = (blockIdx.x % nrow) * 16, c0 = (blockIdx.x / nrow) * kSkinnyCols;
   const int nct = min(4, (TB - c0 + 15) / 16);
   const float* w = a.Wx + (size_t)gate_row(a, ol0 + li) * D;
-  // contraction span of a wave: a multiple of 16, passes of 16 * kSkinnyUnits
+  // contraction span of a wave: a multiple of 16, passes of 16 * U
   const int span = ((D + 16 * kWaves - 1) / (16 * kWaves)) * 16;
   const int k0 = wave * span, k1 = min(D, k0 + span);
   f32x4 acc[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kb = k0; kb < k1; kb += 16 * kSkinnyUnits) {
-    f32x4 wv[kSkinnyUnits];
+  for (int kb = k0; kb < k1; kb += 16 * U) {
+    f32x4 wv[U];
 #pragma unroll
-    for (int u = 0; u < kSkinnyUnits; ++u) wv[u] = load4<WV>(w, kb + 16 * u + lk, k1);
+    for (int u = 0; u < U; ++u) wv[u] = load4<WV>(w, kb + 16 * u + lk, k1);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (c >= nct) break;
       const float* x = a.x + (size_t)min(c0 + 16 * c + li, TB - 1) * D;
 #pragma unroll
-      for (int u0 = 0; u0 < kSkinnyUnits; u0 += 8) {
+      for (int u0 = 0; u0 < U; u0 += kXUnits) {
         if (kb + 16 * u0 >= k1) break;
-        f32x4 xv[8];
+        f32x4 xv[kXUnits];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) xv[u] = load4<XV>(x, kb + 16 * (u0 + u) + lk, k1);
+        for (int u = 0; u < kXUnits; ++u) xv[u] = load4<XV>(x, kb + 16 * (u0 + u) + lk, k1);
         // chains of 32 products, added up pairwise
         f32x4 p[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) p[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < kXUnits; ++u)
 #pragma unroll
           for (int i = 0; i < 4; ++i) p[i] = mfma4(wv[u0 + u][i], xv[u][i], p[i]);
         acc[c] += (p[0] + p[1]) + (p[2] + p[3]);
@@ -531,7 +534,7 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   extern __shared__ __align__(16) float lds[];
   constexpr int LD = WPL + 4, kUnits = (NB * WPL + 31) / 32;   // polled per thread
   const int j = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int H = a.H, B = a.B, T = a.T, R4 = 4 * a.H, kpl = a.kpl, slots = a.slots;
+  const int H = a.H, B = a.B, nb = a.nb, T = a.T, R4 = 4 * a.H, kpl = a.kpl, slots = a.slots;
   int* modes = reinterpret_cast<int*>(lds);
   float* hown = lds + 4;                 // [NB][8] h of the owned slots
   float* hs = hown + NB * 8;             // [NB][64][LD]
@@ -557,7 +560,7 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
     for (int i = 0; i < WPL; ++i) wr[q][i] = computed && lane + 64 * i < H ? wr[q][i] : 0.0f;
   }
   // cell role: lane b < NB updates this wave's unit for sequence b
-  const bool cell_ok = lane < B && live;
+  const bool cell_ok = lane < nb && live;
   float c = (cell_ok && a.c0) ? a.c0[(size_t)lane * H + unit] : 0.0f;
   float pxv[4];
   auto fetch_px = [&](int t) {
@@ -568,7 +571,7 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   fetch_px(0);
   for (int i = tid; i < NB * 64 * LD; i += kThreads) {
     const int b = i / (64 * LD), l = (i / LD) & 63, e = i % LD, k = l + 64 * e;
-    hs[i] = (b < B && e < WPL && k < H && a.h0) ? a.h0[(size_t)b * H + k] : 0.0f;
+    hs[i] = (b < nb && e < WPL && k < H && a.h0) ? a.h0[(size_t)b * H + k] : 0.0f;
   }
   int udst[kUnits];
   unsigned upend = 0;
@@ -583,7 +586,7 @@ __global__ void __launch_bounds__(kThreads) exact_wide_kernel(ExactArgs a) {
   if (mode >= kAlone) {
     __syncthreads();
     if (mode == kAlone)
-      for (int b = 0; b < B; ++b) exact_alone<64>(a, b, lds + 4, lds + 4 + 2 * H, lds + 4 + 3 * H);
+      for (int b = 0; b < nb; ++b) exact_alone<64>(a, b, lds + 4, lds + 4 + 2 * H, lds + 4 + 3 * H);
     return;
   }
   for (int t = 0; t < T; ++t) {
@@ -844,9 +847,12 @@ static void launch_xproj(const ExactArgs& a, hipStream_t stream) {
   const long long nrow = (R + kTile - 1) / kTile, ncol = (TB + kTile - 1) / kTile, clear = a.ctl ? 1 : 0;
   if (2 * nrow * ncol >= a.num_cu)
     exact_xproj_tile_kernel<WV, XV><<<dim3((unsigned)(nrow * ncol + clear)), dim3(kThreads), 0, stream>>>(a, (int)nrow);
-  else
-    exact_xproj_skinny_kernel<WV, XV><<<dim3((unsigned)((long long)((R + 15) / 16) * ((TB + kSkinnyCols - 1) / kSkinnyCols) + clear)),
-                                        dim3(kThreads), 0, stream>>>(a, (R + 15) / 16);
+  else {
+    const auto kernel = a.D <= 4 * 16 * kWaves ? exact_xproj_skinny_kernel<WV, XV, 4>
+                                               : exact_xproj_skinny_kernel<WV, XV, kSkinnyUnits>;
+    kernel<<<dim3((unsigned)((long long)((R + 15) / 16) * ((TB + kSkinnyCols - 1) / kSkinnyCols) + clear)),
+             dim3(kThreads), 0, stream>>>(a, (R + 15) / 16);
+  }
 }
 
 // Shape of the register kernels: fills P, kpl, slots and RU; returns the floats
@@ -856,6 +862,12 @@ size_t plan_exact_group(ExactArgs& a) {
   a.P = 0;
   if (a.num_cu < kXcds * kXcdCus || a.num_cu > kSpreadWords) return 0;
   const int H = a.H;
+  // A few timesteps do not make up for one XCD's taking all of W_h (H = 768,
+  // one sequence, 1 / 2 / 3 timesteps: 20.4 / 21.4 / 23.0 us here, 12.8 / 16.7 /
+  // 20.6 by exact_lstm_kernel, every workgroup its rows; H = 512 14.1 / 15.0 / 16.3
+  // and 11.5 / 13.8 / 16.1, two sequences 14.4 / 15.4 and 12.5 / 16.2; H = 256
+  // 11.5 / 12.0 and 11.0 / 13.5).
+  if (H <= kNearH && (H > 512 ? a.T <= 3 && a.T * a.B <= 4 : a.T * a.B <= (H > 256 ? 2 : H > 192 ? 1 : 0))) return 0;
   if (H <= kNearH) {
     const int e = (H + 15) / 16;
     // up to 32 units one workgroup holds every row (four per thread)
@@ -866,7 +878,7 @@ size_t plan_exact_group(ExactArgs& a) {
     if (4 * near_lds(a, H <= 128 ? 8 : H <= 256 ? 16 : H <= 512 ? 32 : 48) > kLdsCap) return a.P = 0;
     return (size_t)a.B * 3 * a.slots;
   }
-  if (H <= kWideH && a.B <= kWideSeq) {
+  if (H <= kWideH) {
     a.kpl = ((H + 63) / 64 + 3) & ~3;
     a.slots = 64 * a.kpl;
     a.P = a.slots / 8;
@@ -908,9 +920,9 @@ hipError_t launch_wide(const ExactArgs& a, hipStream_t stream) {
 
 template <int WPL>
 hipError_t launch_wide_seq(const ExactArgs& a, hipStream_t stream) {
-  if (a.B <= 1) return launch_wide<WPL, 1>(a, stream);
-  if (a.B <= 2) return launch_wide<WPL, 2>(a, stream);
-  if (a.B <= 4) return launch_wide<WPL, 4>(a, stream);
+  if (a.nb <= 1) return launch_wide<WPL, 1>(a, stream);
+  if (a.nb <= 2) return launch_wide<WPL, 2>(a, stream);
+  if (a.nb <= 4) return launch_wide<WPL, 4>(a, stream);
   return launch_wide<WPL, 8>(a, stream);
 }
 
@@ -936,8 +948,25 @@ hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
     if (e != hipSuccess) return e;
   }
   if (a.P > 0) {
-    if (a.H > kNearH) return a.kpl <= 16 ? launch_wide_seq<16>(a, stream) : launch_wide_seq<32>(a, stream);
-    if (a.P == 1) return a.RU <= 8 ? launch_near<1, 8>(a, stream) : launch_near<4, 8>(a, stream);
+    if (a.H > kNearH) {
+      // more than kWideSeq sequences take turns (exact_lstm_kernel, which reads W_h
+      // from memory at every timestep: H = 1024, 32 sequences, T = 16 1570 us)
+      for (int b0 = 0; b0 < a.B; b0 += kWideSeq) {
+        ExactArgs c = a;
+        c.nb = std::min(kWideSeq, a.B - b0);
+        c.tag_base = a.tag_base + ((unsigned)(b0 / kWideSeq) << 16);
+        const size_t off = (size_t)b0 * a.H;
+        c.px += 4 * off;
+        c.h_out += off;
+        if (a.h0) c.h0 += off;
+        if (a.c0) c.c0 += off;
+        if (a.c_out) c.c_out += off;
+        const hipError_t e = a.kpl <= 16 ? launch_wide_seq<16>(c, stream) : launch_wide_seq<32>(c, stream);
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
+    }
+    if (a.P == 1) return launch_near<4, 8>(a, stream);   // 16 or 32 units
     if (a.H <= 128) return launch_near<1, 8>(a, stream);
     if (a.H <= 256) return launch_near<1, 16>(a, stream);
     if (a.H <= 512) return launch_near<2, 32>(a, stream);

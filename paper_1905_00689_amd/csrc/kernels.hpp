@@ -353,11 +353,13 @@ struct ExactArgs {
   int slots;       // exchange slots of a sequence: lanes * kpl
   int RU;          // slots owned per workgroup
   int first_xcd;   // XCD of group 0
+  int nb;          // sequences of this launch (the wide kernel: at most kWideSeq of the B)
   unsigned wait_ticks;        // as PairArgs::wait_ticks
   float* ex;                  // [B][3][slots], or [3][sequences up to 8][slots] over the device
   unsigned long long* ctl;    // as PairArgs::ctl
 };
 
+constexpr int kWideSeq = 8;       // sequences of a launch whose W_h is spread over the device
 constexpr int kNearH = 768;       // hidden units up to which a sequence's W_h fits the registers of one XCD
 // Shape of the kernels that hold W_h in registers: fills P .. RU (B, T, H and
 // num_cu given) and returns the floats of ex (0: they do not take the run).

@@ -35,6 +35,8 @@ def run(m, w, h0, c0, rows):
     (1, 3, 1, 1), (17, 4, 2, 9), (32, 5, 1, 32), (33, 4, 9, 33), (129, 1, 1, 129), (250, 4, 3, 100),
     (257, 5, 1, 257), (512, 7, 8, 512), (513, 4, 2, 0), (768, 4, 1, 768), (769, 4, 1, 500), (1024, 1, 2, 1024),
     (1025, 4, 3, 1025), (2048, 4, 8, 2048),
+    # more than eight sequences over the device take turns; runs too short for the registers of one XCD
+    (900, 3, 19, 900), (512, 2, 1, 512), (700, 3, 1, 700), (250, 2, 1, 250),
 ])
 def test_register_kernels_equal_any_width(H, T, Bn, rows):
     w = synth.make(24, H, T, Bn, index=95)
