@@ -245,11 +245,14 @@ __global__ void __launch_bounds__(256) batched_hproj_kernel(BatchedArgs a, int t
   if (a.G == 4) { g = jj >> 1; nl0 = (jj & 1) * 4; } else { g = 0; nl0 = jj * 4; }
   const float* prow = a.P + (size_t)(t * a.Bp + b0 + b) * a.pld;
   float pv[4], sg[4];
+  const int lgG = a.G == 4 ? 2 : 0;
+  // terms n0 .. n0+3 of the group (in the panel's padding past the budget)
+  const f32x4 p4 = *reinterpret_cast<const f32x4*>(prow + g * (a.pld >> lgG) + (tau0 >> lgG) + nl0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int tau = tau0 + (nl0 + i) * a.G + g;
     const bool live = tau < GKl;
-    pv[i] = live ? prow[g * (a.pld / a.G) + tau / a.G] : 0.0f;
+    pv[i] = live ? p4[i] : 0.0f;
     sg[i] = live ? a.sigma[tau] : 0.0f;
   }
   f32x4 acc[2][2];
