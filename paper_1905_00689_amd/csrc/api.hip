@@ -1608,7 +1608,10 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
   const size_t ex_floats = m->launch_blocks == 0 ? alstm::plan_exact_group(a) : 0;
   const int maxP = std::max(1, m->num_cu);
   int P = m->launch_blocks > 0 ? std::min(m->launch_blocks, maxP) : std::min(maxP, std::max(1, (m->H + 7) / 8));
-  size_t lds = ex_floats ? 0 : alstm::plan_exact(a, P);
+  // (more wide sequences than the device holds at once are still limited as
+  // exact_lstm_kernel is, whichever kernel takes them)
+  const bool unlimited = ex_floats && (m->H <= alstm::kNearH || B <= alstm::kWideSeq);
+  size_t lds = unlimited ? 0 : alstm::plan_exact(a, P);
   if (m->launch_blocks == 0)
     while (lds > alstm::kLdsCap && P < maxP) {
       P = std::min(maxP, 2 * P);

@@ -57,6 +57,17 @@ def test_register_kernels_equal_any_width(H, T, Bn, rows):
     assert np.abs(ref[1] - ce).max() < TOL * max(1.0, np.abs(ce).max())
 
 
+def test_many_wide_sequences_are_refused_on_either_kernel():
+    w = synth.make(24, 1024, 2, 64, index=94)
+    m = B.approx_lstm_exact_prepare(w.W[:, :24], w.W[:, 24:], w.b, 24, 1024)
+    zero = np.zeros((64, 1024), np.float32)
+    for blocks in (0, 128):
+        B.approx_lstm_exact_set_launch(m, blocks)
+        with pytest.raises(B.ApproxLstmError) as ei:
+            run(m, w, zero, zero, 1024)
+        assert ei.value.status == B.ERR_UNSUPPORTED
+
+
 def test_the_wide_start_outlasts_a_neighbour():
     """Another stream's products hold the compute units for tens of milliseconds when a run over the device
     starts: it waits for them instead of falling to one workgroup, which would take over a second."""
