@@ -764,6 +764,7 @@ approx_lstm_status approx_lstm_prepare(const float* w_ih, const float* w_hh, con
       if (v > 0) hw = std::min<unsigned>(hw, (unsigned)v);
     }
     opt.threads = std::max(1, (int)(hw / (unsigned)G));
+    opt.host_threads = (int)hw;
     if (on_device) {
       std::string err;
       if (alstm::factorise_groups_device(W.data(), G, Rg, C, N, nz, opt, gf, hip_stream, &err) < 0) {

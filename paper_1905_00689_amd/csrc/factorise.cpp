@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <numeric>
 
 namespace alstm {
@@ -201,10 +202,20 @@ double tridiag_second(const double* a, const double* b, int m, std::vector<doubl
   return tri_eigen_from_top(a, b, m, 1, s);
 }
 
-void tridiag_tops(int count, const double* const* a, const double* const* b, int m, std::vector<double>* s,
-                  double* theta) {
-#pragma omp parallel for num_threads(count) schedule(static, 1) if (count > 1)
-  for (int i = 0; i < count; ++i) theta[i] = tri_top_eigen(a[i], b[i], m, s[i]);
+void tridiag_tops(int count, int threads, const double* const* a, const double* const* b, int m,
+                  std::vector<double>* s, double* theta) {
+  threads = std::min(count, threads);
+  bool failed = false;   // an exception may not leave the threads
+#pragma omp parallel for num_threads(threads) schedule(static, 1) if (threads > 1)
+  for (int i = 0; i < count; ++i) {
+    try {
+      theta[i] = tri_top_eigen(a[i], b[i], m, s[i]);
+    } catch (const std::bad_alloc&) {
+#pragma omp atomic write
+      failed = true;
+    }
+  }
+  if (failed) throw std::bad_alloc();
 }
 
 void lanczos_start(double* q, int n) {

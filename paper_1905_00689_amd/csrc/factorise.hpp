@@ -24,6 +24,7 @@ struct FactoriseOptions {
   bool keep_unpruned = false;
   int gram_refresh = 32;        // recompute the Gram matrix exactly every this many steps
   int threads = 1;              // threads for the row loops of one group (results do not depend on it)
+  int host_threads = 1;         // threads for all groups together (nor on this)
   double lanczos_tol = 4e-14;   // Ritz residual / Ritz value at which a solve stops
   double stop_rel = 1e-12;      // sigma <= stop_rel * sigma_1 ends the term list
   int max_lanczos = 0;          // 0: up to the Gram size
@@ -51,9 +52,9 @@ void store_term(GroupFactors& out, int t, double s, std::vector<double>& uu, std
 // tridiag_top: largest eigenvalue and unit eigenvector s of the m x m
 // symmetric tridiagonal matrix with diagonal a and off-diagonal b.
 double tridiag_top(const double* a, const double* b, int m, std::vector<double>& s);
-// tridiag_tops: tridiag_top of `count` matrices of size m, a thread for each.
-void tridiag_tops(int count, const double* const* a, const double* const* b, int m, std::vector<double>* s,
-                  double* theta);
+// tridiag_tops: tridiag_top of `count` matrices of size m on up to `threads` threads.
+void tridiag_tops(int count, int threads, const double* const* a, const double* const* b, int m,
+                  std::vector<double>* s, double* theta);
 // tridiag_second: the second largest eigenvalue and a unit eigenvector.
 double tridiag_second(const double* a, const double* b, int m, std::vector<double>& s);
 // lanczos_start: the fixed unit start vector of every host Lanczos solve

@@ -993,7 +993,7 @@ int factorise_groups(const double* W, int G, int rows, int cols, int rank, int n
           }
         std::vector<std::vector<double>> sv(of.size());
         std::vector<double> tv(of.size());
-        tridiag_tops((int)of.size(), pa.data(), pb.data(), done_k, sv.data(), tv.data());
+        tridiag_tops((int)of.size(), opt.host_threads, pa.data(), pb.data(), done_k, sv.data(), tv.data());
         for (size_t i = 0; i < of.size(); ++i) {
           top_s[of[i]].swap(sv[i]);
           top_theta[of[i]] = tv[i];

@@ -3,6 +3,10 @@ against one kernel per step: the same factors bit for bit, at Gram sizes
 around the rows per workgroup, the group width and the largest that fits, with
 more rows than columns and with one group."""
 
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -40,6 +44,27 @@ def test_a_wait_given_up_changes_no_factor(D, H, G, rank, p):
                                 flags=B.FLAG_DEVICE_FACTORISE | B.FLAG_KEEP_UNPRUNED | f)
           for f in (B.FLAG_GIVE_UP, B.FLAG_STEPWISE)]
     same_factors(ms, G)
+
+
+def test_the_thread_budget_holds_for_the_eigenpairs():
+    """With OMP_NUM_THREADS=1 a device factorisation of four groups starts no threads for them."""
+    code = """
+import os, numpy as np
+from paper_1905_00689_amd import binding as B
+W = np.random.default_rng(1).normal(size=(128, 96)).astype(np.float32)
+def threads(groups):
+    B.approx_lstm_prepare(W[:, :64], W[:, 64:], None, 64, 32, 3, prune_ratio=0.5, groups=groups,
+                          flags=B.FLAG_DEVICE_FACTORISE)
+    return len(os.listdir("/proc/self/task"))
+threads(1)   # one group: the runtime's own threads
+print("threads", threads(1), threads(4), threads(4))
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, OMP_NUM_THREADS="1"),
+                         capture_output=True, text=True, timeout=100)
+    say(out.stdout, out.stderr[-500:])
+    n = out.stdout.split("threads ")[1].split()
+    assert n[0] == n[1] == n[2], n
 
 
 def same_factors(ms, G):
