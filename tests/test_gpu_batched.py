@@ -191,8 +191,8 @@ def test_batched_full_size_every_sequence(full):
 # ------------------------------------------- persistent vs per-timestep kernels
 def test_batched_persistent_and_per_timestep_paths_agree(quarter):
     """The quarter-size workload through the persistent recurrence (cohorts of
-    16 sequences over 4 workgroups each, z and h exchanged through device
-    memory) and through the per-timestep kernel pair: both within the bar of
+    16 sequences over 4 workgroups each, z and h exchanged through the L2 of
+    one XCD) and through the per-timestep kernel pair: both within the bar of
     the oracle on the exported terms, and close to each other (they differ
     only in the fp32 summation order of the two products)."""
     w, m = quarter
@@ -207,7 +207,7 @@ def test_batched_persistent_and_per_timestep_paths_agree(quarter):
         B.approx_lstm_set_batched_path(m, 1)
     check_levels(h_pair, ho, levels)
     runs = {}
-    for mode in (1, 2, 3):   # automatic, z as tagged words, z behind flags
+    for mode in (1, 2, 3):   # 2 and 3 are accepted and mean 1
         try:
             B.approx_lstm_set_batched_path(m, mode)
             runs[mode], _ = run_gpu(m, w.x, levels)
@@ -217,7 +217,7 @@ def test_batched_persistent_and_per_timestep_paths_agree(quarter):
         check_levels(runs[mode], ho, levels)
         for j in range(len(levels)):
             assert rel_err(runs[mode][j], h_pair[j]) < TOL
-    # the z exchange's form changes no arithmetic
+    # one kernel, one order of every sum (other numbers of cohorts in flight: the next test)
     assert np.array_equal(runs[2], runs[3])
     assert np.array_equal(runs[1], runs[2])
 
@@ -225,8 +225,7 @@ def test_batched_persistent_and_per_timestep_paths_agree(quarter):
 @pytest.mark.parametrize("blocks", [4, 8])
 def test_batched_persistent_cohorts_in_turn(quarter, blocks):
     """4 cohorts of 16 sequences on one or two cohorts' worth of workgroups:
-    each workgroup runs several cohorts in turn, reusing the exchange buffers
-    with fresh tags; bitwise equal to the run with every cohort in flight."""
+    each workgroup runs several cohorts in turn on the same exchange buffers; bitwise equal to the run with every cohort in flight."""
     w, m = quarter
     levels = [0, 40, 128]
     say("batched quarter persistent, workgroup cap", blocks)
