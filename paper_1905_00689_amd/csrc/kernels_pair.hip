@@ -656,8 +656,9 @@ bool level_fits(const PairArgs& a, PairLevel& v, int hcap, int P, int optcap, Le
   return true;
 }
 
-// Width of one level (0: none up to `cap` fits).
-int level_width(const PairArgs& a, PairLevel& v, int hcap, int cap, int want, int optcap, LevelShape& s) {
+// Width of one level (0: none up to `cap` fits); `quick`: of a short sequence
+// over the device, where more workgroups load the slices sooner.
+int level_width(const PairArgs& a, PairLevel& v, int hcap, int cap, int want, int optcap, bool quick, LevelShape& s) {
   if (want > 0) return want <= cap && level_fits(a, v, hcap, want, optcap, s) ? want : 0;
   if (level_fits(a, v, hcap, 1, optcap, s)) return 1;   // one workgroup: nothing exchanged
   // the exchanges cost about the same at 16 and at 32 workgroups (0.47 and
@@ -668,7 +669,7 @@ int level_width(const PairArgs& a, PairLevel& v, int hcap, int cap, int want, in
     if (level_fits(a, v, hcap, p, optcap, s) && s.apass == 1 && s.opt == 1) P = p;
   // beyond one workgroup per compute unit of an XCD, several rows per thread
   // cost less than the wider exchange as long as phase A keeps to one pass
-  if ((P == 0 || P > kXcdCus) && kXcdCus <= cap && level_fits(a, v, hcap, kXcdCus, optcap, s) && s.apass == 1)
+  if ((P == 0 || (P > kXcdCus && !quick)) && kXcdCus <= cap && level_fits(a, v, hcap, kXcdCus, optcap, s) && s.apass == 1)
     P = kXcdCus;
   for (int p = 2; p <= cap && !P; ++p)
     if (level_fits(a, v, hcap, p, optcap, s)) P = p;
@@ -684,7 +685,7 @@ int level_width(const PairArgs& a, PairLevel& v, int hcap, int cap, int want, in
 
 // Shapes of every level with widths up to `cap` and up to `optcap` rows per
 // thread, and the instance (register buckets) that holds them all.
-int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
+int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap, bool quick) {
   int pmax = 0, need_h = 0, upt = 0;
   a.opt = a.apass = 1;
   a.OMmax = a.zslots = 0;
@@ -696,7 +697,7 @@ int plan_levels(PairArgs& a, const int* hcap, int cap, int want, int optcap) {
     v.kpl = ((v.K + v.S - 1) / v.S + 3) & ~3;
     v.slots = a.G * v.S * v.kpl;
     LevelShape s;
-    if (!level_width(a, v, hcap[l], cap, want, optcap, s)) return 0;
+    if (!level_width(a, v, hcap[l], cap, want, optcap, quick, s)) return 0;
     pmax = std::max(pmax, v.P);
     a.opt = std::max(a.opt, s.opt);
     a.apass = std::max(a.apass, s.apass);
@@ -742,16 +743,19 @@ int plan_pair(PairArgs& a, const int* hcap, int num_cu, int want, size_t* lds) {
   // near groups: up to kNearWidth workgroups where two share a compute unit,
   // up to kXcdCus otherwise; a single pair that needs more runs on every XCD.
   // So does one whose sequence is too short to make up for what its slices cost
-  // one XCD to load: about 2 us more per MB past 2.4 than over the device, where
-  // a timestep takes 1 us longer (driving shape, K = 512, 6 MB: near 23.4 + 2.7 T
-  // us, spread 13.3 + 3.8 T; K = 256, 3 MB: 14.9 + 2.0 T, 13.3 + 3.1 T).
-  const double mb = pairs == 1 ? 1e-6 * a.lv[0].K * (6.0 * a.G * hcap[0] + 16.0 * a.H) : 0.0;
-  const bool quick = a.T < 2.0 * (mb - 2.4);
+  // one XCD to load, in timesteps 1.4 per MB of U rows and 1.8 per MB of h parts;
+  // the wider exchange costs wide layers more (us, near / spread; H = 512, 75%
+  // pruning: K = 256, T = 1 15.5 / 15.1, T = 2 17.5 / 18.3, K = 512, T = 1 22.5 /
+  // 15.7, 6 35.1 / 33.6, 8 40.2 / 40.9; 50%: K = 512, T = 8 46.1 / 44.2, 11 54.9 / 56.6;
+  // H = 2048, 90%: K = 128, T = 1 15.4 / 15.9, K = 256, T = 1 21.8 / 15.7, 6 36.1 /
+  // 35.3, 8 41.7 / 43.3).
+  const double mu = 16e-6 * a.H * a.lv[0].K, mv = 6e-6 * a.G * a.lv[0].K * hcap[0];
+  const bool quick = pairs == 1 && a.T < 1.4 * mu + 1.8 * mv - 1.4 - 3.6 * a.H / 1024.0;
   const int caps[2][3] = {{kNearWidth, kXcdCus, num_cu}, {num_cu, kNearWidth, kXcdCus}};
   for (int optcap : {4, 2, 1}) {
     for (int cap : caps[quick]) {
       if (cap == num_cu && (pairs > 1 || num_cu > kSpreadWords)) continue;
-      const int P = plan_levels(a, hcap, std::min(cap, std::max(1, num_cu)), want, optcap);
+      const int P = plan_levels(a, hcap, std::min(cap, std::max(1, num_cu)), want, optcap, quick && cap == num_cu);
       if (!P) continue;
       const bool two = a.opt == 1 && a.apass == 1 && a.hpl <= kTwoHmax;
       const bool near = xcds && P <= (two ? kNearWidth : kXcdCus) && !(quick && cap == num_cu);
