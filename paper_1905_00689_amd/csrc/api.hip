@@ -1622,29 +1622,30 @@ approx_lstm_status approx_lstm_exact_run_rows(approx_lstm_exact* m, const float*
     return fail(APPROX_LSTM_ERR_UNSUPPORTED, "LDS need %zu bytes exceeds 160 KiB (H=%d, B=%d)", lds, m->H, B);
   approx_lstm_status st = grow(m->d_px, m->px_cap, (size_t)T * B * 4 * m->H, stream, "hipMalloc(px)");
   if (st != APPROX_LSTM_OK) return st;
-  if ((size_t)B * m->H > m->hx_cap) {
-    st = grow(m->d_hx, m->hx_cap, (size_t)B * m->H, stream, "hipMalloc(hx)");
-    if (st != APPROX_LSTM_OK) return st;
-    HIP_TRY(alstm::launch_clear_u64(m->d_hx, m->hx_cap, stream), "clear(hx)");
-    m->seq = 0;
-  }
-  // launch sequence numbers: one, or one per launch of the wide kernel
+  st = grow(m->d_hx, m->hx_cap, (size_t)2 * B * m->H, stream, "hipMalloc(hx)");
+  if (st != APPROX_LSTM_OK) return st;
+  // launch sequence numbers: one, or one per launch of the wide kernel (the words
+  // that carry them are cleared before every run)
   const unsigned turns = ex_floats && m->H > alstm::kNearH ? (unsigned)((B + alstm::kWideSeq - 1) / alstm::kWideSeq) : 1;
   m->seq += 1;
-  if (m->seq + turns - 1 > 0xFFFFu) {
-    HIP_TRY(alstm::launch_clear_u64(m->d_hx, m->hx_cap, stream), "clear(hx)");
-    m->seq = 1;
-  }
+  if (m->seq + turns - 1 > 0xFFFFu) m->seq = 1;
   a.tag_base = m->seq << 16;
   m->seq += turns - 1;
   if (ex_floats) {
     st = grow(m->d_ex, m->ex_cap, ex_floats, stream, "hipMalloc(h slots)");
     if (st != APPROX_LSTM_OK) return st;
     a.ex = m->d_ex;
-    if (a.P > 1) a.ctl = m->d_ctl;
+    if (a.P > 1) {
+      a.ctl = m->d_ctl;
+      a.ctl_words = alstm::kXcds * alstm::kCtlWords;
+    }
     const int side = m->H <= alstm::kNearH ? std::min<int>(B, alstm::kXcds) : 1;   // groups side by side
     a.wait_ticks = start_wait(m->start_wait_us, 16.0 * m->H * m->H * T * std::min<int>(B, side == 1 ? alstm::kWideSeq : B) / side);
     a.first_xcd = (int)(g_next_xcd.fetch_add((unsigned)B, std::memory_order_relaxed) % alstm::kXcds);
+  }
+  if (!ex_floats && P > 1) {
+    a.ctl = m->d_hx;
+    a.ctl_words = 2 * B * m->H;
   }
   a.px = m->d_px; a.hx = m->d_hx; a.err = m->d_err;
   HIP_TRY(alstm::launch_exact(a, P, stream), "launch exact_lstm_kernel");

@@ -3,13 +3,15 @@
 // with the full weight matrices (Sec. II, Fig. 1; the augmented matrix of
 // Sec. III without any factorisation), then the same cell update.
 //
-// Two launches per run.  exact_xproj_*_kernel computes the x part of every
-// gate row for every timestep at once (it does not depend on h).  The
-// persistent exact_lstm_kernel then runs the recurrence: workgroup j owns a
-// slice of hidden units and the four W_h rows of each, held in registers for
-// the whole sequence, so one timestep needs a single exchange between
-// workgroups (the h all-gather), where the progressive scheme needs two
-// (z, then h).
+// Two steps per run.  exact_xproj_*_kernel computes the x part of every gate row
+// for every timestep at once (it does not depend on h).  Then the recurrence:
+// every workgroup owns hidden units and the four W_h rows of each, so one
+// timestep needs a single exchange between workgroups (the h all-gather), where
+// the progressive scheme needs two (z, then h).  exact_near_kernel (up to 768
+// units, a sequence per XCD) and exact_wide_kernel (up to 2048, eight sequences
+// at a time over the device) hold W_h in registers; exact_lstm_kernel takes the
+// rest: longer sequences than their x parts fit LDS, a few timesteps, more
+// units, part of a device, and widths given by the caller.
 //
 // A row budget (a.rows < H) gives the paper's anytime baseline (Sec. VI-B):
 // the dense products stopped after that many rows of every gate, the rows
@@ -92,7 +94,7 @@ template <bool WV, bool XV, int U>
 __global__ void __launch_bounds__(kThreads) exact_xproj_skinny_kernel(ExactArgs a, int nrow) {
   constexpr int kXUnits = U < 8 ? U : 8;   // units of x at a time
   __shared__ float part[kWaves][4][16][17];
-  if (clear_start_words(a.ctl, kXcds * kCtlWords)) return;
+  if (clear_start_words(a.ctl, a.ctl_words)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int TB = a.T * a.B, D = a.D, R = 4 * a.H;
@@ -165,7 +167,7 @@ template <bool WV, bool XV>
 __global__ void __launch_bounds__(kThreads) exact_xproj_tile_kernel(ExactArgs a, int nrow) {
   __shared__ __align__(16) float As[2][kTile * kTileLd];
   __shared__ __align__(16) float Bs[2][kTile * kTileLd];
-  if (clear_start_words(a.ctl, kXcds * kCtlWords)) return;
+  if (clear_start_words(a.ctl, a.ctl_words)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = 4 * (lane >> 4);
   const int wm = (wave & 1) * 64, wn = (wave >> 1) * 32;
@@ -708,6 +710,9 @@ __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
   };
   for (int t = 0; t < T; ++t) {
     const unsigned tag = a.tag_base | (unsigned)(t + 1);
+    // two halves by parity: the words of t are overwritten at t+2, when everyone's
+    // h_{t+1} is here, which each published after it had read all of h_t
+    unsigned long long* hx = a.hx + (size_t)(t & 1) * B * H;
     if (wreg) {
       // pass 0's entries are in registers; later passes read their rows
       for (int b = 0; b < B; ++b) {
@@ -814,10 +819,10 @@ __global__ void __launch_bounds__(kThreads) exact_lstm_kernel(ExactArgs a) {
         const int b = i / rc, rr = i - b * rc;
         const float hv = hown[b * RP + rr];
         a.h_out[((size_t)t * B + b) * H + r0 + rr] = hv;
-        if (!local) publish(a.hx + (size_t)b * H + r0 + rr, hv, tag);
+        if (!local) publish(hx + (size_t)b * H + r0 + rr, hv, tag);
       }
     }
-    if (!local && !publisher) gather_tagged<2>(hs, nullptr, a.hx, B * H, tag, a.err, threadIdx.x, gthr);
+    if (!local && !publisher) gather_tagged<2>(hs, nullptr, hx, B * H, tag, a.err, threadIdx.x, gthr);
     lds_barrier();
   }
   if (a.c_out)
@@ -944,7 +949,7 @@ hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else if (a.ctl) {
-    const hipError_t e = launch_clear_u64(a.ctl, kXcds * kCtlWords, stream);
+    const hipError_t e = launch_clear_u64(a.ctl, a.ctl_words, stream);
     if (e != hipSuccess) return e;
   }
   if (a.P > 0) {
@@ -975,6 +980,9 @@ hipError_t launch_exact(const ExactArgs& a, int blocks, hipStream_t stream) {
   ExactArgs c = a;
   const size_t lds = plan_exact(c, blocks);
   if (lds > kLdsCap) return hipErrorInvalidValue;
+  // only workgroups that own units: nobody waits for one without, whose h would be
+  // overwritten under it
+  blocks = std::min(blocks, (a.H + c.rows_per - 1) / c.rows_per);
   exact_lstm_kernel<<<dim3(blocks), dim3(kThreads), lds, stream>>>(c);
   return hipGetLastError();
 }

@@ -326,7 +326,7 @@ int plan_batched_persistent(const BatchedArgs& a, int K, int* W, int* slots);
 
 // Exact (dense) LSTM: x [T][B][D], h0, c0 [B][H] or null, h_out [T][B][H],
 // c_out [B][H] or null; Wx [4H][D], Wh [4H][H], bias [4H] (gate rows i, f,
-// g, o); px [T*B][4H] (x part plus bias, workspace); hx [B][H] tagged words.
+// g, o); px [T*B][4H] (x part plus bias, workspace); hx [2][B][H] tagged words.
 struct ExactArgs {
   const float* x;
   const float* h0;
@@ -356,7 +356,10 @@ struct ExactArgs {
   int nb;          // sequences of this launch (the wide kernel: at most kWideSeq of the B)
   unsigned wait_ticks;        // as PairArgs::wait_ticks
   float* ex;                  // [B][3][slots], or [3][sequences up to 8][slots] over the device
-  unsigned long long* ctl;    // as PairArgs::ctl
+  // words that the x projection clears for the recurrence (null: none): start
+  // words as PairArgs::ctl, or for exact_lstm_kernel hx
+  unsigned long long* ctl;
+  int ctl_words;
 };
 
 constexpr int kWideSeq = 8;       // sequences of a launch whose W_h is spread over the device

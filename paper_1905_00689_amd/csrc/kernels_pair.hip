@@ -21,7 +21,7 @@
 //            h into its exchange slot and to h_out;
 //   h        every thread polls its share of the units' h into LDS.
 // With one workgroup (P = 1) nothing is exchanged: z and h go through LDS
-// (H = 64, K = 16, T = 100: 1.08 -> 0.78 us per timestep, once the rows applied
+// (H = 64, K = 16, T = 100: 1.08 -> 0.76 us per timestep, once the rows applied
 // their own gates' nonlinearities and no wait for LDS was one for h_out).
 //
 // What bounds a timestep is the latency of its two exchanges.  Two things
@@ -41,28 +41,29 @@
 //   words and a quarter of the loads.
 // Driving shape (D = 2048, H = 512, 75% pruning, T = 16, one sequence), whole
 // run, us, with tagged words across XCDs / near groups with tagged words /
-// near groups with slots: K = 32 75.2 / 60.3 / 38.8, K = 128 76.9 / 63.2 /
-// 41.3, K = 512 87.5 / 92.3 / 66.5; phases at K = 64 (A, z, B, h) 0.25, 1.31,
-// 0.70, 1.69 -> 0.35, 0.43, 0.37, 0.48 us.  Several pairs, against the general
-// kernel's one launch for all of them: eight sequences at K = 128 389 -> 54,
-// levels 16, 64, 128, 192 202 -> 49; H = 2048, K = 64, T = 64, eight sequences
-// 1505 -> 155; K = 256, T = 32 943 -> 142.
+// near groups with slots: K = 32 75.2 / 60.3 / 36.5, K = 128 76.9 / 63.2 /
+// 39.4, K = 512 87.5 / 92.3 / 63.4; phases at K = 64 (A, z, B, h) 0.25, 1.31,
+// 0.70, 1.69 -> 0.35, 0.38, 0.38, 0.48 us.  Several pairs, against the general
+// kernel's one launch for all of them: eight sequences at K = 128 389 -> 51,
+// levels 16, 64, 128, 192 202 -> 46; H = 2048, K = 64, T = 64, eight sequences
+// 1505 -> 144; K = 256, T = 32 943 -> 140.
 // * Spread groups (SPREAD; a single pair whose slices one XCD cannot hold).
 //   Across XCDs a store's acknowledgement takes as long as the exchange, and a
 //   wave's loads and stores retire in order, so a wave that polls after storing
 //   waits for its own stores first.  There the last wave alone publishes, from
 //   LDS, and the others only poll.  H = 1024, K = 512, 75% pruning, T = 32, on
 //   128 workgroups: 175 us with tagged words and 185 with slots published by
-//   every wave, 152 so; the driving shape without pruning, K = 512: 97, 105, 97.
+//   every wave, 146 so; the driving shape without pruning, K = 512: 97, 105, 94.
+//   Short sequences of one pair go there too (plan_pair).
 //
 // Residency.  A group's workgroups wait for each other, so all of them must
 // be resident.  When another stream's kernels hold part of an XCD that may
 // take time, and two such launches holding parts of one XCD would wait for
-// each other.  The start of a group is therefore a bounded decision: once all
-// have arrived they go ahead (one compare-and-swap on the group's decision
-// word); a workgroup whose wait runs out first decides otherwise, takes the
-// group's pairs alone (every slice read from memory, nothing exchanged) and
-// the rest of the group leaves.  Both ways compute every sum in one order.
+// each other.  The start of a group is therefore a bounded decision (group_start):
+// once all have arrived they go ahead; a workgroup whose wait runs out first
+// decides otherwise, takes the group's pairs alone (every slice read from memory,
+// nothing exchanged) and the rest of the group leaves.  Both ways compute every
+// sum in one order.
 //
 // The order of every sum is that of progressive_lstm_kernel (phase A: entry
 // sla + 16k of the term's h part at lane sla, k ascending, then the 16-lane

@@ -54,6 +54,35 @@ def test_replays_equal_eager_runs(D, H, T, Bn, rank, p):
         check()
 
 
+@pytest.mark.parametrize("H,T,blocks", [(512, 2, 0), (512, 2, 64), (700, 3, 0), (203, 6, 128), (203, 1, 7)])
+def test_replays_of_the_exact_kernel_on_any_width(H, T, blocks):
+    """exact_lstm_kernel's tagged words: two halves by parity, cleared by the projection before it; more
+    workgroups than units to deal out."""
+    w = synth.make(40, H, T, 2, index=79)
+    m = B.approx_lstm_exact_prepare(w.W[:, :40], w.W[:, 40:], w.b, 40, H)
+    B.approx_lstm_exact_set_launch(m, blocks)
+    xs = [torch.from_numpy(np.ascontiguousarray(np.roll(w.x, i, axis=2)[:, :1])).cuda() for i in range(3)]
+    say("exact replays H", H, "T", T, "blocks", blocks)
+    x, h, want = xs[0].clone(), torch.empty(T, 1, H, device="cuda"), []
+    for v in xs:
+        B.approx_lstm_exact_run(m, v, h)
+        want.append(h.clone())
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.approx_lstm_exact_run(m, x, h)
+    for i in (0, 1, 2, 1, 1, 0):
+        x.copy_(xs[i])
+        h.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(h, want[i]), i
+        other = torch.empty_like(h)
+        B.approx_lstm_exact_run(m, xs[2], other)
+        assert torch.equal(other, want[2])
+    B.approx_lstm_exact_check(m)
+
+
 def test_one_timestep_again_and_again():
     w, runs = calls(40, 512, 1, 20, 20, 0.5)
     x = torch.from_numpy(w.x).cuda()
