@@ -9,6 +9,9 @@ per gate (Sec. III).  The expected values below are those sums worked out by
 hand for the workloads the bench times.
 """
 
+import os
+import re
+
 import bench
 
 
@@ -42,3 +45,13 @@ def test_batched_mfma_flops():
     assert bench.mfma_flops_batched(4, 2048, 512, 16, 256, 512) == 51_539_607_552
     # budgets and sizes are padded to the 32-wide contraction: K = 20 runs as 32
     assert bench.mfma_flops_batched(4, 2048, 512, 16, 256, 20) == bench.mfma_flops_batched(4, 2048, 512, 16, 256, 32)
+
+
+def test_traffic_summaries_hold_what_the_bench_reads():
+    """The committed counter summaries state the traffic of a step and the sources it was taken on, in the
+    lines that the bench's roofline looks for."""
+    for name, sources in bench.TRAFFIC_PROFILES.values():
+        text = open(os.path.join(os.path.dirname(bench.__file__), "profiles", name)).read()
+        assert len(re.findall(r"^traffic_bytes_per_step: \d+$", text, re.M)) == 1, name
+        assert len(re.findall(r"^kernel_sources_sha256: [0-9a-f]{64}$", text, re.M)) == 1, name
+        assert len(bench.kernel_sources_sha256(sources)) == 64
